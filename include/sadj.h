@@ -241,7 +241,8 @@ sadj_status sadj_adjoint_star3d(sadj_dtype dtype, int radius, long nx, long ny, 
  *
  * sadj_primal_burgers1d_steps: `states` holds nsteps+1 rows of n elements, row t = u^t.
  *   Row 0 is the initial state; for t = 0 .. nsteps-1 the call assigns row t+1 on I = [1, n-2]
- *   from row t.  Elements 0 and n-1 of every row are inputs (boundary data), never written.
+ *   from row t.  Elements 0 and n-1 of every row are inputs (boundary data), never written.  A kernel
+ *   takes up to 16 steps (option "burgers1d.fuse").
  *
  * sadj_adjoint_burgers1d_steps: reverse sweep over the steps last-1, last-2, ..., last-nsteps
  *   (step t maps row t to row t+1; rows last-nsteps .. last-1 of `states` are read).  On entry
@@ -252,8 +253,8 @@ sadj_status sadj_adjoint_star3d(sadj_dtype dtype, int radius, long nx, long ny, 
  *   consumed; adjoints of earlier states start from zero).  As in every adjoint call, values
  *   of lam[s%2] outside I are never used.  After the call lam[nsteps%2] holds the adjoint of
  *   u^{last-nsteps}.  nsteps = 0 does nothing; nsteps > last -> SADJ_ERR_SIZE.  lam0, lam1 and
- *   the rows read must not overlap.  One kernel per step is enqueued (fewer where steps are fused, see
- *   option "burgers1d.fuse").
+ *   the rows read must not overlap.  The first reverse step is one kernel, the others share kernels of up
+ *   to 15 steps (option "burgers1d.fuse").
  */
 sadj_status sadj_primal_burgers1d_steps(sadj_dtype dtype, long n, long nsteps, double C, double D,
                                         void *states, void *stream);
@@ -264,22 +265,23 @@ sadj_status sadj_adjoint_burgers1d_steps(sadj_dtype dtype, long n, long last, lo
  * At the size of the paper's own Burgers experiment (10^9 cells, Section 4.2) one state is 8 GB,
  * so a long time loop cannot keep every state; the standard remedy stores every `every`-th state
  * (a checkpoint) and recomputes the states in between, one segment at a time, while sweeping
- * backwards.  Both calls run the kernels of the single-step calls; the reverse sweep's result
+ * backwards.  Both calls round every cell like the single-step calls; the reverse sweep's result
  * equals that of sadj_adjoint_burgers1d_steps over a full history bit for bit.
  * Boundary data: elements 0 and n-1 of every state equal those of u^0 (held fixed in time).
  *
  * sadj_primal_burgers1d_ckpt: `ckpt` holds nsteps/every + 1 rows of n elements; row 0 = u^0 on
  *   entry; on return row j = u^{j*every}.  `work`: 2 rows of scratch.  u_final (nullable, n
- *   elements) receives u^{nsteps}.  nsteps+1 kernels (and one copy) are enqueued.
+ *   elements) receives u^{nsteps}.  A kernel takes up to 16 steps, checkpoints among them.
  *
  * sadj_adjoint_burgers1d_ckpt: reverse sweep over the steps nsteps-1 .. 0.  On entry lam0 =
  *   adjoint of u^{nsteps}, lam1 = what the objective contributes directly to the adjoint of
  *   u^{nsteps-1} (often zero); rotation and assign/accumulate rules as in
  *   sadj_adjoint_burgers1d_steps; after the call lam[nsteps%2] holds the adjoint of u^0.  `work`:
  *   scratch of at least (every-1)*n elements (work_bytes states its size; may be NULL when
- *   every == 1) that receives the recomputed states of one segment at a time.
+ *   every == 1) for states recomputed between checkpoints; its contents after the call are undefined.
  *   Errors: every < 1, work_bytes too small -> SADJ_ERR_SIZE; ckpt, lam0, lam1, work overlapping
- *   -> SADJ_ERR_ALIAS.  Roughly (2 - 1/every) kernels per step are enqueued.
+ *   -> SADJ_ERR_ALIAS.  A kernel takes up to 8 reverse steps, whose states it recomputes from the last
+ *   one in memory; where every > 8 another kernel first recomputes the states at which they start.
  */
 sadj_status sadj_primal_burgers1d_ckpt(sadj_dtype dtype, long n, long nsteps, long every, double C, double D,
                                        void *ckpt, void *work, void *u_final /* nullable */, void *stream);
@@ -369,11 +371,10 @@ sadj_status sadj_describe_wave3d_plan(sadj_dtype dtype, int radius, long nx, lon
  *   "star3d.functor" 1: radius-1 calls of sadj_*_star3d run through the generic functor kernels of
  *                    sadj_stencil_star.hpp where nx and the arrays' alignment allow 16-byte
  *                    accesses (default 0: their own kernel).
- *   "burgers1d.fuse" 0 (default): the reverse sweeps of the Burgers time loop
- *                    (sadj_adjoint_burgers1d_steps, sadj_adjoint_burgers1d_ckpt*) apply runs of five
- *                    assigned steps in one pass over the data (lam read and written once per
- *                    five states read, instead of once per state) where all arrays are 16-byte
- *                    aligned; 1: one kernel per step.  Same result bit for bit.
+ *   "burgers1d.fuse" 0 (default): the time loops of the Burgers step (sadj_*_burgers1d_steps,
+ *                    sadj_*_burgers1d_ckpt*) take several steps in one pass over the data (states and
+ *                    adjoints stay in registers between them); 1: one kernel per step.  Same result
+ *                    bit for bit; contents of `work` and of the consumed lam buffer differ.
  *   "wave3d.fuse"    0 (default): sadj_adjoint_wave3d_steps_fused fuses pairs of steps where it can;
  *                    1: it runs single steps only.
  *   "wave3d.order"   order in which sadj_adjoint_wave3d adds the terms of one u_bar[j]

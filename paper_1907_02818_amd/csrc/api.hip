@@ -127,30 +127,17 @@ void clear_stale_hip_error() { (void)hipGetLastError(); }
 namespace {
 
 // Reverse steps s0, s0+1, ... of a sweep over the states state(0), state(1), ... (in the order
-// they are applied).  Step s reads lam[s%2] and updates lam[(s+1)%2]: accumulated for s = 0,
-// assigned from then on.  Runs of assigned steps are fused, several steps per pass over the
-// data, unless option "burgers1d.fuse" is 1 or the arrays' alignment rules it out; the result is
-// the same bit for bit.  Returns the number of steps done in `s0`.
+// they are applied), one launch each (option "burgers1d.fuse" 1).  Step s reads lam[s%2] and updates
+// lam[(s+1)%2]: accumulated for s = 0, assigned from then on.  Adds the number of steps done to `s0`.
 template <class StateOf>
 sadj_status burgers_reverse_steps(sadj_dtype dtype, long n, double C, double D, long count, StateOf state, void *const (&lam)[2],
                                   long &s0, hipStream_t st)
 {
     const int f64 = dtype == SADJ_F64;
-    const int M = sadj::burgers_fused_steps();
-    const bool fuse = g_burgers_fuse.load() == 0;
-    long k = 0;
-    while (k < count) {
+    for (long k = 0; k < count; ++k) {
         const long s = s0 + k;
-        if (fuse && s > 0 && count - k >= M) {
-            const void *u[16];
-            for (int i = 0; i < M; ++i) u[i] = state(k + i);
-            const hipError_t e = sadj::launch_adjoint_burgers1d_fused(f64, n, C, D, u, lam[s % 2], lam[(s + M) % 2], st);
-            if (e == hipSuccess) { k += M; continue; }
-            if (e != hipErrorNotSupported) return from_hip(e);
-        }
         const hipError_t e = sadj::launch_adjoint_burgers1d(f64, n, C, D, state(k), lam[s % 2], lam[(s + 1) % 2], s > 0 ? 1 : 0, st);
         if (e != hipSuccess) return from_hip(e);
-        ++k;
     }
     s0 += count;
     return SADJ_OK;
@@ -163,6 +150,8 @@ sadj_status burgers_ckpt_reverse(sadj_dtype dtype, long n, long nsteps, long eve
     const size_t row = (size_t)n * elem(dtype);
     const int f64 = dtype == SADJ_F64;
     void *const lam[2] = {lam0, lam1};
+    if (g_burgers_fuse.load() == 0)
+        return from_hip(sadj::launch_burgers_ckpt_reverse(f64, n, nsteps, every, C, D, ckpt, work, lam, st));
     const char *cb = static_cast<const char *>(ckpt);
     char *wb = static_cast<char *>(work);
     long s = 0;                                             // reverse steps done
@@ -790,6 +779,8 @@ sadj_status sadj_primal_burgers1d_steps(sadj_dtype dtype, long n, long nsteps, d
     if (g_check_pointers.load() == 1)
         if (sadj_status m = check_span_memory({states, (size_t)(nsteps + 1) * row}); m != SADJ_OK) return m;
     clear_stale_hip_error();
+    if (g_burgers_fuse.load() == 0)
+        return from_hip(sadj::launch_burgers_history_forward(dtype == SADJ_F64, n, nsteps, C, D, states, static_cast<hipStream_t>(stream)));
     char *base = static_cast<char *>(states);
     for (long t = 0; t < nsteps; ++t) {
         hipError_t e = sadj::launch_primal_burgers1d(dtype == SADJ_F64, n, C, D, base + (size_t)t * row,
@@ -813,6 +804,9 @@ sadj_status sadj_adjoint_burgers1d_steps(sadj_dtype dtype, long n, long last, lo
     clear_stale_hip_error();
     void *const lam[2] = {lam0, lam1};
     const char *base = static_cast<const char *>(states);
+    if (g_burgers_fuse.load() == 0)
+        return from_hip(sadj::launch_burgers_history_reverse(dtype == SADJ_F64, n, nsteps, C, D, base + (size_t)(last - nsteps) * row, lam,
+                                                             static_cast<hipStream_t>(stream)));
     // reverse step s undoes the primal step u^t -> u^{t+1}, t = last-1-s; lam[(s+1)%2] receives
     // lam^t; from s = 1 on it is the consumed buffer and is assigned
     auto applied = [&](long s) -> const void * { return base + (size_t)(last - 1 - s) * row; };
@@ -836,6 +830,8 @@ sadj_status sadj_primal_burgers1d_ckpt(sadj_dtype dtype, long n, long nsteps, lo
     clear_stale_hip_error();
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int f64 = dtype == SADJ_F64;
+    if (g_burgers_fuse.load() == 0 && nsteps > 0)
+        return from_hip(sadj::launch_burgers_ckpt_forward(f64, n, nsteps, every, C, D, ckpt, work, u_final, st));
     char *cb = static_cast<char *>(ckpt), *wb = static_cast<char *>(work);
     const char *cur = cb;                                   // u^0
     for (long t = 0; t < nsteps; ++t) {

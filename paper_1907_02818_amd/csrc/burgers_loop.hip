@@ -1,0 +1,401 @@
+// Time loops of the Burgers step: several steps per pass over the data, forward and reverse
+// (paper Sections 3.1 and 4.2: the nonlinear stencil's adjoint reads the primal states).
+//
+// A wave holds a window of 64*PXL consecutive cells in registers, PXL per lane, and applies m steps to
+// it.  A cell's value after k steps depends on k cells to either side, so H cells at either end of
+// the window are recomputed by the neighbouring windows and only the V = 64*PXL - 2H between
+// them are stored.  No LDS, no barrier: neighbours travel by whole-wave lane shifts (DPP).
+//
+// Windows that lie in I = [1, n-2] run without guards; the others clamp their loads into the array
+// and mask with selects.  A window belongs to one wave, so the branch between the two is uniform.
+//
+// What bounds it (fp64; one launch per step before).  Forward with every state stored: memory, 8 + 8/m bytes
+// per cell and step instead of 16; 10^7 cells, 16 steps: 245 us, 5.5 TB/s.  Reverse over stored states:
+// memory, 8 + 16/m bytes instead of 24; 15 steps of 10^7 cells 241 us, 5.6 TB/s.  Reverse from a
+// checkpoint: 24/m bytes, the m states are recomputed in registers and the vector ALUs are the bound
+// (43 instructions per four cells of a forward step, 103 of a reverse one); so is the forward sweep
+// that stores checkpoints only, 16 steps of 10^7 cells in 60 us.
+#include "burgers.hpp"
+#include "burgers_plan.hpp"
+#include "launch.hpp"
+
+namespace sadj {
+
+struct BurgersForwardArgs {
+    const void *src;        // the state the pass starts from
+    void *rows;             // receives the states after steps first, first+every, ... in consecutive rows of n cells
+    void *last;             // receives the state after step m (nullable)
+    long first, every;
+    long n;
+    double C, D;
+    int m;
+    int hold;               // 1: the end cells keep their values; 0: every state is stored (first = every = 1) and
+                            // the end cells of every row are given, never written
+};
+
+struct BurgersReverseArgs {
+    const void *src;        // state t
+    const void *rows;       // states t+first, t+first+every, ... (the others are recomputed)
+    const void *lam_in;
+    void *lam_out;
+    long n;
+    double C, D;
+    int m, first, every;
+};
+
+constexpr int kLoopWaves = 4;         // windows per workgroup
+constexpr int kLoopH = 16;            // cells recomputed on either side of a window
+static_assert(kLoopH >= kForwardSteps && kLoopH >= kReverseSteps && kLoopH >= 2 * kRecomputeSteps - 1, "halo of a pass");
+
+// Whole-wave lane shifts (DPP).  shift: the value of the lane to the left (right), `edge` in lane 0
+// (63); rotate: the same with lanes 0 and 63 taken as neighbours.
+template <bool RIGHT> __device__ __forceinline__ int lane_shift(int v, int edge)
+{
+    return __builtin_amdgcn_update_dpp(edge, v, RIGHT ? 0x130 : 0x138, 0xf, 0xf, false);
+}
+template <bool RIGHT> __device__ __forceinline__ int lane_rotate(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, RIGHT ? 0x134 : 0x13c, 0xf, 0xf, true);
+}
+template <bool RIGHT> __device__ __forceinline__ float lane_shift(float v, float edge)
+{
+    return __int_as_float(lane_shift<RIGHT>(__float_as_int(v), __float_as_int(edge)));
+}
+template <bool RIGHT> __device__ __forceinline__ float lane_rotate(float v) { return __int_as_float(lane_rotate<RIGHT>(__float_as_int(v))); }
+template <bool RIGHT> __device__ __forceinline__ double lane_shift(double v, double edge)
+{
+    return __hiloint2double(lane_shift<RIGHT>(__double2hiint(v), __double2hiint(edge)),
+                            lane_shift<RIGHT>(__double2loint(v), __double2loint(edge)));
+}
+template <bool RIGHT> __device__ __forceinline__ double lane_rotate(double v)
+{
+    return __hiloint2double(lane_rotate<RIGHT>(__double2hiint(v)), lane_rotate<RIGHT>(__double2loint(v)));
+}
+
+// A lane's PXL cells of one row, in runs of RUN consecutive cells.  SPREAD: a run is one 16-byte access
+// and the lanes' runs lie side by side, so that every access of a wave is one piece of memory; else the
+// lane's cells are one run, which needs half the lane shifts.  Rows of an odd length start at
+// addresses that are multiples of the element size only, and the vector type says so.
+template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
+    static constexpr int W = 64 * PXL, V = W - 2 * kLoopH;
+    static constexpr int PXV = PXL * sizeof(T) < 16 ? PXL : 16 / (int)sizeof(T);
+    static constexpr int RUN = SPREAD ? PXV : PXL, RUNS = PXL / RUN;
+    typedef T VT __attribute__((ext_vector_type(PXV), aligned(sizeof(T))));
+    long x0, lo, hi;                  // first cell of the lane's first run; cells lo .. hi-1 are the window's own
+    long n;
+    int lane;
+    bool in[PXL];
+
+    __device__ __forceinline__ Lane(long w, int lane_, long n_) : n(n_), lane(lane_)
+    {
+        x0 = w * V - kLoopH + (long)lane * RUN;
+        lo = w * V;
+        hi = (w + 1) * V < n ? (w + 1) * V : n;
+#pragma unroll
+        for (int e = 0; e < PXL; ++e) in[e] = GUARD ? (cell(e) >= 1 && cell(e) <= n - 2) : true;
+    }
+    __device__ __forceinline__ long cell(int e) const { return x0 + e / RUN * (64 * RUN) + e % RUN; }
+
+    template <bool STREAM = false> __device__ __forceinline__ void load(const T *p, T (&v)[PXL]) const
+    {
+        if (!GUARD) {
+#pragma unroll
+            for (int h = 0; h < PXL; h += PXV) {
+                const VT *q = reinterpret_cast<const VT *>(p + cell(h));
+                const VT t = STREAM ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+                for (int e = 0; e < PXV; ++e) v[h + e] = t[e];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < PXL; ++e) {
+                long i = cell(e);
+                i = i < 0 ? 0 : (i > n - 1 ? n - 1 : i);
+                v[e] = p[i];
+            }
+        }
+    }
+    // ends: the end cells of the array are stored as well
+    __device__ __forceinline__ void store(T *p, const T (&v)[PXL], bool ends) const
+    {
+        if (!GUARD) {
+            // whole runs are the window's own or not
+#pragma unroll
+            for (int h = 0; h < PXL; h += PXV) {
+                const int r = h / RUN;
+                VT t;
+#pragma unroll
+                for (int e = 0; e < PXV; ++e) t[e] = v[h + e];
+                if ((r > 0 || lane >= kLoopH / RUN) && (r < RUNS - 1 || lane < 64 - kLoopH / RUN))
+                    __builtin_nontemporal_store(t, reinterpret_cast<VT *>(p + cell(h)));
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < PXL; ++e)
+                if (cell(e) >= lo && cell(e) < hi && (ends || in[e])) p[cell(e)] = v[e];
+        }
+    }
+    // The cells before (after) each run; any value beyond the window, which only reaches cells that are discarded.
+    __device__ __forceinline__ void beside(const T (&v)[PXL], T (&left)[RUNS], T (&right)[RUNS]) const
+    {
+#pragma unroll
+        for (int r = 0; r < RUNS; ++r) {
+            const T end = v[r * RUN + RUN - 1], first = v[r * RUN];
+            left[r] = r > 0 ? lane_shift<false>(end, lane_rotate<false>(v[r > 0 ? r * RUN - 1 : 0])) : lane_rotate<false>(end);
+            right[r] = r < RUNS - 1 ? lane_shift<true>(first, lane_rotate<true>(v[r < RUNS - 1 ? (r + 1) * RUN : 0])) : lane_rotate<true>(first);
+        }
+    }
+    __device__ __forceinline__ void primal_step(T (&u)[PXL], T C, T D) const
+    {
+        T ul[RUNS], ur[RUNS], next[PXL];
+        beside(u, ul, ur);
+#pragma unroll
+        for (int e = 0; e < PXL; ++e) {
+            const T val = burgers_primal_cell(e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1], C, D);
+            next[e] = in[e] ? val : u[e];
+        }
+#pragma unroll
+        for (int e = 0; e < PXL; ++e) u[e] = next[e];
+    }
+    __device__ __forceinline__ void reverse_step(const T (&u)[PXL], T (&lam)[PXL], T C, T D) const
+    {
+#pragma unroll
+        for (int e = 0; e < PXL; ++e) lam[e] = in[e] ? lam[e] : T(0);      // lam outside I is never used
+        T ul[RUNS], ur[RUNS], ll[RUNS], lr[RUNS], next[PXL];
+        beside(u, ul, ur);
+        beside(lam, ll, lr);
+#pragma unroll
+        for (int e = 0; e < PXL; ++e) {
+            const bool first = e % RUN == 0, end = e % RUN == RUN - 1;
+            next[e] = burgers_adjoint_terms(first ? ul[e / RUN] : u[e - 1], u[e], end ? ur[e / RUN] : u[e + 1],
+                                            first ? ll[e / RUN] : lam[e - 1], lam[e], end ? lr[e / RUN] : lam[e + 1], C, D, in[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < PXL; ++e) lam[e] = next[e];
+    }
+};
+
+// The value that lane `from` (uniform) holds, in all lanes.
+__device__ __forceinline__ float lane_value(float v, int from) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), from)); }
+__device__ __forceinline__ double lane_value(double v, int from)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), from), __builtin_amdgcn_readlane(__double2loint(v), from));
+}
+
+template <class T, int PXL, bool GUARD, bool SPREAD>
+__device__ __forceinline__ void burgers_forward_window(const BurgersForwardArgs &a, long w, int lane)
+{
+    const Lane<T, PXL, GUARD, SPREAD> L(w, lane, a.n);
+    const T C = (T)a.C, D = (T)a.D;
+    T u[PXL];
+    L.load(static_cast<const T *>(a.src), u);
+    T *row = static_cast<T *>(a.rows);
+    long next = a.first;
+    // Given end cells of the m rows: lanes 0 .. 15 fetch cell 0, lanes 16 .. 31 cell n-1 of row 0 .. 15 before the
+    // loop.  Fetched where they are needed, each step of an end window would wait for memory
+    // (16 stored steps of 10^6 fp32 cells: 29 us instead of 13).
+    T ends = T(0);
+    if (GUARD && !a.hold && lane < 32) ends = row[(long)min(lane & 15, a.m - 1) * a.n + (lane < 16 ? 0 : a.n - 1)];
+    static_assert(kForwardSteps <= 16, "a lane per given end cell");
+    for (int s = 0; s < a.m;) {
+        const int stop = next < a.m ? (int)next : a.m;
+        for (; s + 2 <= stop; s += 2) {           // by twos: the cells need no moves between registers
+            L.primal_step(u, C, D);
+            L.primal_step(u, C, D);
+        }
+        if (s < stop) {
+            L.primal_step(u, C, D);
+            ++s;
+        }
+        if (s != next) continue;
+        if (GUARD && !a.hold) {
+#pragma unroll
+            for (int e = 0; e < PXL; ++e) {
+                const T left = lane_value(ends, s - 1), right = lane_value(ends, s + 15);
+                u[e] = L.cell(e) == 0 ? left : L.cell(e) == a.n - 1 ? right : u[e];
+            }
+        }
+        L.store(row, u, a.hold);
+        row += a.n;
+        next += a.every;
+    }
+    if (a.last) L.store(static_cast<T *>(a.last), u, true);
+}
+
+template <class T, int PXL, bool SPREAD> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_forward_kernel(BurgersForwardArgs a)
+{
+    using L = Lane<T, PXL, false, false>;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * L::V - kLoopH;
+    if (w * L::V >= a.n) return;
+    if (x0 >= 1 && x0 + L::W - 1 <= a.n - 2) burgers_forward_window<T, PXL, false, SPREAD>(a, w, lane);
+    else burgers_forward_window<T, PXL, true, SPREAD>(a, w, lane);
+}
+
+// Reverse steps over m states that are all in memory (rows follows src, first = every = 1).  AHEAD states are
+// in flight; requests for steps that the pass does not have re-read its last state, so that no load
+// is behind a branch and the wait before a step leaves the later ones outstanding.
+template <class T, int PXL, bool GUARD, int AHEAD>
+__device__ __forceinline__ void burgers_reverse_stored(const BurgersReverseArgs &a, long w, int lane)
+{
+    const Lane<T, PXL, GUARD, true> L(w, lane, a.n);
+    const T C = (T)a.C, D = (T)a.D;
+    const T *src = static_cast<const T *>(a.src);
+    T lam[PXL], u[AHEAD][PXL];
+    L.load(static_cast<const T *>(a.lam_in), lam);
+    auto request = [&](int s) {
+        if (s >= 0) L.template load<true>(src + (long)min(s, a.m - 1) * a.n, u[s % AHEAD]);
+    };
+#pragma unroll
+    for (int s = kReverseSteps - 1; s > kReverseSteps - 1 - AHEAD; --s) request(s);
+#pragma unroll
+    for (int s = kReverseSteps - 1; s >= 0; --s) {
+        if (s < a.m) L.reverse_step(u[s % AHEAD], lam, C, D);
+        request(s - AHEAD);
+    }
+    L.store(static_cast<T *>(a.lam_out), lam, true);
+}
+
+// Reverse steps from a checkpoint: the states are recomputed forward from state t into registers, except
+// where a further checkpoint is met.
+template <class T, int PXL, bool GUARD>
+__device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseArgs &a, long w, int lane)
+{
+    constexpr int M = kRecomputeSteps;
+    const Lane<T, PXL, GUARD, false> L(w, lane, a.n);
+    const T C = (T)a.C, D = (T)a.D;
+    T lam[PXL], u[M][PXL];
+    L.load(static_cast<const T *>(a.src), u[0]);
+    L.load(static_cast<const T *>(a.lam_in), lam);
+    const T *row = static_cast<const T *>(a.rows);
+    int next = a.first;
+#pragma unroll
+    for (int s = 1; s < M; ++s) {
+        if (s >= a.m) continue;
+        if (s == next) {
+            L.load(row, u[s]);
+            row += a.n;
+            next += a.every;
+        } else {
+#pragma unroll
+            for (int e = 0; e < PXL; ++e) u[s][e] = u[s - 1][e];
+            L.primal_step(u[s], C, D);
+        }
+    }
+#pragma unroll
+    for (int s = M - 1; s >= 0; --s)
+        if (s < a.m) L.reverse_step(u[s], lam, C, D);
+    L.store(static_cast<T *>(a.lam_out), lam, true);
+}
+
+constexpr int kAhead = 4;
+
+template <class T, int PXL, bool STORED> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_reverse_kernel(BurgersReverseArgs a)
+{
+    using L = Lane<T, PXL, false, false>;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * L::V - kLoopH;
+    if (w * L::V >= a.n) return;
+    if (x0 >= 1 && x0 + L::W - 1 <= a.n - 2) {
+        if (STORED) burgers_reverse_stored<T, PXL, false, kAhead>(a, w, lane);
+        else burgers_reverse_recompute<T, PXL, false>(a, w, lane);
+    } else {
+        if (STORED) burgers_reverse_stored<T, PXL, true, kAhead>(a, w, lane);
+        else burgers_reverse_recompute<T, PXL, true>(a, w, lane);
+    }
+}
+
+// Cells per lane: wide windows (224 own cells of 256 in fp64, 480 of 512 in fp32) recompute the least and
+// are taken where every SIMD of the chip gets one; shorter arrays are spread over more SIMDs in narrow
+// windows (96 of 128): 400 000 cells, 16 stored steps, fp64: narrow 11.8, wide 10.0 us; a checkpointed
+// reverse pass of 10^6 cells 38 and 35 us, in fp32 30 and 29 us, of 4 10^6 cells in fp32 79 and 61 us.
+template <class T> static bool wide_windows(long n)
+{
+    using L = Lane<T, 32 / (int)sizeof(T), false, false>;
+    return n >= 1024L * L::V;
+}
+
+template <class T, int PXL> static dim3 loop_grid(long n)
+{
+    const long windows = ceil_div(n, Lane<T, PXL, false, false>::V);
+    return dim3((unsigned)ceil_div(windows, kLoopWaves));
+}
+
+template <class T, bool SPREAD> static hipError_t forward_T(const BurgersForwardArgs &a, hipStream_t stream)
+{
+    constexpr int WIDE = 32 / (int)sizeof(T), NARROW = 2;
+    const dim3 block(64 * kLoopWaves);
+    if (wide_windows<T>(a.n)) hipLaunchKernelGGL((burgers_forward_kernel<T, WIDE, SPREAD>), (loop_grid<T, WIDE>(a.n)), block, 0, stream, a);
+    else hipLaunchKernelGGL((burgers_forward_kernel<T, NARROW, SPREAD>), (loop_grid<T, NARROW>(a.n)), block, 0, stream, a);
+    return hipGetLastError();
+}
+
+template <class T, bool STORED> static hipError_t reverse_T(const BurgersReverseArgs &a, hipStream_t stream)
+{
+    constexpr int WIDE = 32 / (int)sizeof(T), NARROW = 2;
+    const dim3 block(64 * kLoopWaves);
+    if (wide_windows<T>(a.n))
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, STORED>), (loop_grid<T, WIDE>(a.n)), block, 0, stream, a);
+    else
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, NARROW, STORED>), (loop_grid<T, NARROW>(a.n)), block, 0, stream, a);
+    return hipGetLastError();
+}
+
+namespace {
+
+struct LoopOps {
+    int is_f64;
+    long n;
+    double C, D;
+    hipStream_t stream;
+
+    int forward(const char *src, char *rows, long first, long every, int m, char *last, bool hold) const
+    {
+        const BurgersForwardArgs a{src, rows, last, first, every, n, C, D, m, hold ? 1 : 0};
+        if (every == 1) return is_f64 ? forward_T<double, true>(a, stream) : forward_T<float, true>(a, stream);
+        return is_f64 ? forward_T<double, false>(a, stream) : forward_T<float, false>(a, stream);
+    }
+    int reverse(const char *src, const char *rows, int first, int every, int m, const char *lam_in, char *lam_out) const
+    {
+        const BurgersReverseArgs a{src, rows, lam_in, lam_out, n, C, D, m, first, every};
+        if (every == 1) return is_f64 ? reverse_T<double, true>(a, stream) : reverse_T<float, true>(a, stream);
+        return is_f64 ? reverse_T<double, false>(a, stream) : reverse_T<float, false>(a, stream);
+    }
+    int reverse_first(const char *u, const char *lam_in, char *lam_out) const
+    {
+        return launch_adjoint_burgers1d(is_f64, n, C, D, u, lam_in, lam_out, 0, stream);
+    }
+};
+
+}  // namespace
+
+hipError_t launch_burgers_history_forward(int is_f64, long n, long nsteps, double C, double D, void *states, hipStream_t stream)
+{
+    LoopOps ops{is_f64, n, C, D, stream};
+    return (hipError_t)plan_burgers_history_forward(ops, static_cast<char *>(states), (size_t)n * (is_f64 ? 8 : 4), nsteps);
+}
+hipError_t launch_burgers_history_reverse(int is_f64, long n, long nsteps, double C, double D, const void *states, void *const (&lam)[2],
+                                          hipStream_t stream)
+{
+    LoopOps ops{is_f64, n, C, D, stream};
+    char *const l[2] = {static_cast<char *>(lam[0]), static_cast<char *>(lam[1])};
+    return (hipError_t)plan_burgers_history_reverse(ops, static_cast<const char *>(states), (size_t)n * (is_f64 ? 8 : 4), nsteps, l);
+}
+hipError_t launch_burgers_ckpt_forward(int is_f64, long n, long nsteps, long every, double C, double D, void *ckpt, void *work,
+                                       void *u_final, hipStream_t stream)
+{
+    LoopOps ops{is_f64, n, C, D, stream};
+    return (hipError_t)plan_burgers_ckpt_forward(ops, static_cast<char *>(ckpt), static_cast<char *>(work), static_cast<char *>(u_final),
+                                                 (size_t)n * (is_f64 ? 8 : 4), nsteps, every);
+}
+hipError_t launch_burgers_ckpt_reverse(int is_f64, long n, long nsteps, long every, double C, double D, const void *ckpt, void *work,
+                                       void *const (&lam)[2], hipStream_t stream)
+{
+    if (every == 1) return launch_burgers_history_reverse(is_f64, n, nsteps, C, D, ckpt, lam, stream);
+    LoopOps ops{is_f64, n, C, D, stream};
+    char *const l[2] = {static_cast<char *>(lam[0]), static_cast<char *>(lam[1])};
+    BurgersCkptReverse<LoopOps> plan{ops, static_cast<const char *>(ckpt), static_cast<char *>(work), (size_t)n * (is_f64 ? 8 : 4), every};
+    return (hipError_t)plan.run(nsteps, l);
+}
+
+}  // namespace sadj

@@ -51,13 +51,16 @@ hipError_t launch_primal_wave1d(int is_f64, long n, const void *u, const void *u
 // assign != 0: u_bar = J^T r_bar (u_bar is not read) instead of u_bar += J^T r_bar
 hipError_t launch_adjoint_burgers1d(int is_f64, long n, double C, double D, const void *u,
                                     const void *r_bar, void *u_bar, int assign, hipStream_t stream);
-// burgers_fused_steps() consecutive reverse steps of a time loop in one pass, all in assign mode:
-// lam_out = J(u[M-1])^T ... J(u[0])^T lam_in (u[0] is the state of the step applied first).
-// lam_in and lam_out must differ.  hipErrorNotSupported (nothing enqueued) if an array is not
-// 16-byte aligned.
-int burgers_fused_steps();
-hipError_t launch_adjoint_burgers1d_fused(int is_f64, long n, double C, double D, const void *const *u,
-                                          const void *lam_in, void *lam_out, hipStream_t stream);
+// Time loops with several steps per pass over the data (burgers_loop.hip); same results bit for bit
+// as one launch per step.  Arguments are those of the C entry points.
+hipError_t launch_burgers_history_forward(int is_f64, long n, long nsteps, double C, double D, void *states, hipStream_t stream);
+// states: the nsteps rows the sweep reads, oldest first
+hipError_t launch_burgers_history_reverse(int is_f64, long n, long nsteps, double C, double D, const void *states, void *const (&lam)[2],
+                                          hipStream_t stream);
+hipError_t launch_burgers_ckpt_forward(int is_f64, long n, long nsteps, long every, double C, double D, void *ckpt, void *work,
+                                       void *u_final, hipStream_t stream);
+hipError_t launch_burgers_ckpt_reverse(int is_f64, long n, long nsteps, long every, double C, double D, const void *ckpt, void *work,
+                                       void *const (&lam)[2], hipStream_t stream);
 
 // keep_ends != 0: r[0] = u[0] and r[n-1] = u[n-1] as well (boundary data carried to the next state)
 hipError_t launch_primal_burgers1d(int is_f64, long n, double C, double D, const void *u, void *r,
