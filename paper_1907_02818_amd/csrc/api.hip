@@ -554,15 +554,19 @@ static sadj_status wave_steps_args(sadj_dtype dtype, int radius, long nx, long n
     return check_arrays(in, out);
 }
 
-// Single steps k0 .. nsteps-1 rotating three buffers.
-static sadj_status wave_steps_plain(int f64, int radius, long nx, long ny, long nz, long k0, long nsteps, const void *c,
+// All nsteps single steps rotating three buffers: step k reads a = lam[k%3] and updates b = lam[(k+1)%3]; the
+// third buffer held the a of step k-1, which is dead.  From step 1 on the b of the next step would be
+// -a on I: instead of writing that, step k leaves it to step k+1, which finds this a in its own third
+// buffer (the last step writes it, because the caller gets it).
+static sadj_status wave_steps_plain(int f64, int radius, long nx, long ny, long nz, long nsteps, const void *c,
                                     void *const (&lam)[3], const sadj::LaunchOptions &opt, hipStream_t st)
 {
-    for (long k = k0; k < nsteps; ++k) {
+    for (long k = 0; k < nsteps; ++k) {
         void *a = lam[k % 3], *b = lam[(k + 1) % 3], *p = lam[(k + 2) % 3];
-        // the buffer that receives -a was the r_bar of the previous step: it is dead and is assigned
-        hipError_t e = sadj::launch_adjoint_wave3d(f64, radius, (int)nx, (int)ny, (int)nz, c, a, b, p, k > 0 ? 1 : 0,
-                                                   opt, st);
+        const bool last = k == nsteps - 1;
+        hipError_t e;
+        if (k >= 2) e = sadj::launch_adjoint_wave3d_middle(f64, radius, (int)nx, (int)ny, (int)nz, c, a, p, b, last, opt, st);
+        else e = sadj::launch_adjoint_wave3d(f64, radius, (int)nx, (int)ny, (int)nz, c, a, b, k == 0 || last ? p : nullptr, k > 0 ? 1 : 0, opt, st);
         if (e != hipSuccess) return from_hip(e);
     }
     return SADJ_OK;
@@ -576,7 +580,7 @@ sadj_status sadj_adjoint_wave3d_steps(sadj_dtype dtype, int radius, long nx, lon
     clear_stale_hip_error();
     sadj::LaunchOptions opt = current_options();
     opt.remainder = 0;   // the strategy variants exist for the single-step call only
-    return wave_steps_plain(dtype == SADJ_F64, radius, nx, ny, nz, 0, nsteps, c, lam, opt, static_cast<hipStream_t>(stream));
+    return wave_steps_plain(dtype == SADJ_F64, radius, nx, ny, nz, nsteps, c, lam, opt, static_cast<hipStream_t>(stream));
 }
 
 // The same sweep with a fourth array to work in: pairs of steps run fused where the kernel exists.
@@ -595,9 +599,9 @@ sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long n
     const bool fusable = radius == 1 && g_wave_fuse.load() == 0 &&
                          sadj::adjoint_wave3d_pair_supported(f64, (int)nx, c, lam0, lam1, lam2, work);
     const WaveSweepPlan plan = fusable ? plan_wave_sweep(nsteps) : WaveSweepPlan{};
-    if (plan.plain) return wave_steps_plain(f64, radius, nx, ny, nz, 0, nsteps, c, lam, opt, st);
+    if (plan.plain) return wave_steps_plain(f64, radius, nx, ny, nz, nsteps, c, lam, opt, st);
     // step 0 accumulates into lam2, which may hold the objective's own contribution
-    if (sadj_status s = wave_steps_plain(f64, radius, nx, ny, nz, 0, 1, c, lam, opt, st); s != SADJ_OK) return s;
+    if (sadj_status s = wave_steps_plain(f64, radius, nx, ny, nz, 1, c, lam, opt, st); s != SADJ_OK) return s;
     auto run = [&](const WaveStepLaunch &l) {
         return l.pair ? sadj::launch_adjoint_wave3d_pair(f64, (int)nx, (int)ny, (int)nz, c, buf[l.a], buf[l.b], buf[l.o0],
                                                          buf[l.o1], opt, st)

@@ -19,6 +19,11 @@ struct LaunchOptions {
 hipError_t launch_adjoint_wave3d(int is_f64, int radius, int nx, int ny, int nz, const void *c,
                                  const void *r_bar, void *u_bar, void *u_prev_bar, int u_prev_bar_assign,
                                  const LaunchOptions &opt, hipStream_t stream);
+// A middle step of a time loop: u_bar is assigned what launch_adjoint_wave3d would leave there if it
+// held -before on I and 0 elsewhere, `before` being the r_bar of the step before.  last != 0: `before`
+// is then assigned -r_bar on I, 0 elsewhere.
+hipError_t launch_adjoint_wave3d_middle(int is_f64, int radius, int nx, int ny, int nz, const void *c, const void *r_bar,
+                                        void *before, void *u_bar, int last, const LaunchOptions &opt, hipStream_t stream);
 // Same result up to rounding; terms added in the order and rounding of the sequential scatter.
 hipError_t launch_adjoint_wave3d_ordered(int is_f64, int radius, int nx, int ny, int nz, const void *c,
                                          const void *r_bar, void *u_bar, void *u_prev_bar,

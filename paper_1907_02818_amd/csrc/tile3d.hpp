@@ -100,7 +100,7 @@ struct TileMap {
 };
 
 struct March3dArgs {
-    const void *in0, *in1, *in2;   // adjoint: c, r_bar, -      primal: u, u_prev, c
+    const void *in0, *in1, *in2;   // adjoint: c, r_bar, r_bar of the step before (middle steps of a loop)   primal: u, u_prev, c
     void *out0, *out1;             // adjoint: u_bar, u_prev_bar (nullable)   primal: r, -
     int out1_assign;               // adjoint: 1 = u_prev_bar is assigned (-r_bar on I, 0 elsewhere), 0 = accumulated
     int nx, ny, nz;

@@ -9,6 +9,12 @@
 // u_prev_bar[j] -= r_bar[j] for j in I (accumulate mode), or u_prev_bar[j] = -r_bar[j]
 // for j in I and 0 elsewhere (assign mode, used when a time loop recycles a buffer).
 //
+// Template parameter UPREV: 0 u_bar only, 1 u_prev_bar accumulated, 2 u_prev_bar assigned, and for the
+// middle steps of a time loop, whose u_bar starts as -s[j] on I (0 elsewhere) with s the r_bar of the
+// step before, still in memory: 3 reads s in place of that start value and assigns u_bar, so the
+// start value is neither written by the step before nor read back (four words a cell instead of
+// five); 4 the same, and afterwards assigns s[j] = -r_bar[j] on I, 0 elsewhere (last step of a loop).
+//
 // Mapping to CDNA4.  The x-y plane is cut into tiles of TX x TY outputs; a workgroup
 // owns one tile and marches along z.  Each arriving plane of q is staged in LDS
 // (tile + halo of width R, no corners: a star never reads them) and contributes
@@ -50,24 +56,33 @@
 
 namespace sadj {
 
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// The arithmetic of a cell, contraction off and every multiply-add written out: all instantiations of
+// the kernel round alike, so that no bit depends on where the z-chunks are cut, on whether a tile is
+// guarded, or on which kernels a time loop's steps are made of (a loop of n+1 steps passes through
+// the states of a loop of n steps).
 template <class T> __device__ __forceinline__ T mul_rounded(T a, T b)
 {
 #pragma clang fp contract(off)
     return a * b;
 }
-
-// acc + (2 r + (3 w_0 q + sum_k w_k xs_k + sum_k w_k ys_k)) with every multiply-add explicit
-// and contraction of the remaining operations off.
-template <class T, int R>
-__device__ __forceinline__ T pinned_centre(T q, T r, const T (&xs)[R], const T (&ys)[R], T acc)
+template <class T> __device__ __forceinline__ T add_rounded(T a, T b)
+{
+#pragma clang fp contract(off)
+    return a + b;
+}
+// acc + (2 r + (3 w_0 q + sum_k w_k xs_k + sum_k w_k ys_k))
+template <class T, int R> __device__ __forceinline__ T centre_terms(T q, T r, const T (&xs)[R], const T (&ys)[R], T acc)
 {
 #pragma clang fp contract(off)
     T s = T(3.0 * star_w<R>(0)) * q;
 #pragma unroll
-    for (int k = 1; k <= R; ++k) s = __builtin_fmaf(T(star_w<R>(k)), xs[k - 1], s);
+    for (int k = 1; k <= R; ++k) s = fma_t(T(star_w<R>(k)), xs[k - 1], s);
 #pragma unroll
-    for (int k = 1; k <= R; ++k) s = __builtin_fmaf(T(star_w<R>(k)), ys[k - 1], s);
-    return acc + __builtin_fmaf(T(2), r, s);
+    for (int k = 1; k <= R; ++k) s = fma_t(T(star_w<R>(k)), ys[k - 1], s);
+    return acc + fma_t(T(2), r, s);
 }
 
 template <class T, int R, int BX, int BY, int PY, int PX, int D, bool NTU, bool GUARD, int UPREV>
@@ -84,11 +99,9 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
     // loaded values; without the branch two stores stay in flight across the loop end.
     // Measured at 512^3 .. 1000^3: fp32 with u_bar only gains 1-6 points; fp64 loses 1-8 (the
     // wait keeps waves and workgroups closer together, which is worth more there) and the
-    // u_prev_bar variants lose more, so only the fp32 u_bar-only kernels have it.  Their
-    // arithmetic is written with explicit fused multiply-adds (PINNED), so that the two
-    // instantiations of a step round alike and no bit depends on where the z-chunks are cut.
-    constexpr bool STEADY_PHASE = D == 1 && sizeof(T) == 4 && UPREV == 0;
-    constexpr bool PINNED = STEADY_PHASE;
+    // u_prev_bar variants lose more, so only the fp32 kernels with the streams of the u_bar-only call
+    // (three read, one written) have it.
+    constexpr bool STEADY_PHASE = D == 1 && sizeof(T) == 4 && (UPREV == 0 || UPREV == 3);
     const int tid = threadIdx.x;
     const int tx = tid % BX, ty = tid / BX;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -98,7 +111,8 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
     const T *__restrict__ cg = static_cast<const T *>(a.in0);
     const T *__restrict__ rg = static_cast<const T *>(a.in1);
     T *__restrict__ ug = static_cast<T *>(a.out0);
-    T *__restrict__ upg = static_cast<T *>(a.out1);
+    T *upg = static_cast<T *>(a.out1);              // UPREV 4: the array in2
+    const T *startg = UPREV >= 3 ? static_cast<const T *>(a.in2) : static_cast<const T *>(a.out0);
 
     // owned cells x = x0 + tx*PX + e, y = y0 + ty*PY + p and halo slots (tile3d.hpp); c and r_bar are
     // used on I only, and not fetched at all where none of a vector's cells lies in I
@@ -136,7 +150,7 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
             for (int k = 0; k < NACC; ++k) acc[p][e][k] = T(0);
 
     // D stages of values in flight
-    V sc[D][PY], sr[D][PY], su[D][PY], sp[D][PY];
+    V sc[D][PY], sr[D][PY], su[D][PY], sp[D][PY];       // sp: u_prev_bar of plane z (1), r_bar of plane z-R (4)
     T shc[D][HS], shr[D][HS];
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -176,9 +190,14 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
         }
         const int zo = z - R;
         if (ST || zo >= zs) {                      // zo <= ze-1 because z <= zi1
-            const T *up = ug + (size_t)zo * plane;
+            const T *up = startg + (size_t)zo * plane;
 #pragma unroll
             for (int p = 0; p < PY; ++p) su[d][p] = ld_vec_off<T, PX, NTU>(up, ooff[p]);
+            if (UPREV == 4) {
+                const T *rp = rg + (size_t)zo * plane;
+#pragma unroll
+                for (int p = 0; p < PY; ++p) sp[d][p] = ld_vec_off<T, PX, NTU>(rp, ooff[p]);
+            }
         }
     };
 
@@ -189,9 +208,9 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
         const int zo = zi - R;
         T *sb = sq + buf * (LY * LX);
         T qo[PY][PX], ro[PY][PX];
-        V cu[PY];
+        V cu[PY], cp[PY];
 #pragma unroll
-        for (int p = 0; p < PY; ++p) cu[p] = su[d][p];
+        for (int p = 0; p < PY; ++p) { cu[p] = su[d][p]; cp[p] = sp[d][p]; }
         if (zin) {
 #pragma unroll
             for (int p = 0; p < PY; ++p)
@@ -199,9 +218,7 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
                 for (int e = 0; e < PX; ++e) {
                     const T cc = sc[d][p].v[e], rv = sr[d][p].v[e];
                     ro[p][e] = GUARD ? (ouse[p][e] ? rv : T(0)) : rv;
-                    // PINNED: a product rounded on its own, never fused into a later addition
-                    // (for radius 1 the z-terms are acc + 1.0 * q, which would otherwise invite it)
-                    const T cr = PINNED ? mul_rounded(cc, rv) : cc * rv;
+                    const T cr = mul_rounded(cc, rv);
                     qo[p][e] = GUARD ? (ouse[p][e] ? cr : T(0)) : cr;
                     sb[(R + ty * PY + p) * LX + R + tx * PX + e] = qo[p][e];
                 }
@@ -210,7 +227,7 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
                 const T qq = GUARD ? (huse[s] ? shc[d][s] * shr[d][s] : T(0)) : shc[d][s] * shr[d][s];
                 sb[hlds[s]] = qq;
             }
-            if (UPREV) {
+            if (UPREV == 1 || UPREV == 2) {
                 if (ST || (zi >= zs && zi < ze)) {
                     T *pp = upg + (size_t)zi * plane;
 #pragma unroll
@@ -243,30 +260,17 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
 #pragma unroll
                 for (int p = 0; p < PY; ++p) {
                     const T *row = sb + (R + ty * PY + p) * LX + R + tx * PX + e;
-                    if constexpr (PINNED) {
-                        // every multiply-add written out, so that the generic and the branch-free
-                        // instantiation of this step round alike
-                        T xs[R], ys[R];
+                    T xs[R], ys[R];
 #pragma unroll
-                        for (int k = 1; k <= R; ++k) { xs[k - 1] = row[-k] + row[k]; ys[k - 1] = col[R + p - k] + col[R + p + k]; }
-                        acc[p][e][R] = pinned_centre<T, R>(qo[p][e], ro[p][e], xs, ys, acc[p][e][R]);
+                    for (int k = 1; k <= R; ++k) {
+                        xs[k - 1] = add_rounded(row[-k], row[k]);
+                        ys[k - 1] = add_rounded(col[R + p - k], col[R + p + k]);
+                    }
+                    acc[p][e][R] = centre_terms<T, R>(qo[p][e], ro[p][e], xs, ys, acc[p][e][R]);
 #pragma unroll
-                        for (int k = 1; k <= R; ++k) {
-                            acc[p][e][R - k] = __builtin_fmaf(T(star_w<R>(k)), qo[p][e], acc[p][e][R - k]);
-                            acc[p][e][R + k] = __builtin_fmaf(T(star_w<R>(k)), qo[p][e], acc[p][e][R + k]);
-                        }
-                    } else {
-                        T s = T(3.0 * star_w<R>(0)) * qo[p][e];
-#pragma unroll
-                        for (int k = 1; k <= R; ++k) s += T(star_w<R>(k)) * (row[-k] + row[k]);
-#pragma unroll
-                        for (int k = 1; k <= R; ++k) s += T(star_w<R>(k)) * (col[R + p - k] + col[R + p + k]);
-                        acc[p][e][R] += s + T(2) * ro[p][e];
-#pragma unroll
-                        for (int k = 1; k <= R; ++k) {
-                            acc[p][e][R - k] += T(star_w<R>(k)) * qo[p][e];
-                            acc[p][e][R + k] += T(star_w<R>(k)) * qo[p][e];
-                        }
+                    for (int k = 1; k <= R; ++k) {
+                        acc[p][e][R - k] = fma_t(T(star_w<R>(k)), qo[p][e], acc[p][e][R - k]);
+                        acc[p][e][R + k] = fma_t(T(star_w<R>(k)), qo[p][e], acc[p][e][R + k]);
                     }
                 }
             }
@@ -278,8 +282,17 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
             for (int p = 0; p < PY; ++p) {
                 V o;
 #pragma unroll
-                for (int e = 0; e < PX; ++e) o.v[e] = cu[p].v[e] + acc[p][e][0];
+                for (int e = 0; e < PX; ++e) {
+                    const bool in = plane_in_I(zo) && (!GUARD || ouse[p][e]);
+                    const T start = UPREV >= 3 ? (in ? T(0) - cu[p].v[e] : T(0)) : cu[p].v[e];
+                    o.v[e] = start + acc[p][e][0];
+                }
                 if (!GUARD || ostore[p]) st_vec_off<T, PX, NTU>(up, ooff[p], o);
+                if (UPREV == 4) {
+#pragma unroll
+                    for (int e = 0; e < PX; ++e) o.v[e] = plane_in_I(zo) && (!GUARD || ouse[p][e]) ? T(0) - cp[p].v[e] : T(0);
+                    if (!GUARD || ostore[p]) st_vec_off<T, PX, NTU>(upg + (size_t)zo * plane, ooff[p], o);
+                }
             }
         }
 #pragma unroll
@@ -358,7 +371,7 @@ static hipError_t launch_cfg(March3dArgs a, const LaunchOptions &opt, hipStream_
         // PX and every array aligned to the vector size; otherwise use a PX = 1 shape
         const size_t al = PX * sizeof(T);
         const bool ok = a.nx % PX == 0 && aligned_to(a.in0, al) && aligned_to(a.in1, al) &&
-                        aligned_to(a.out0, al) && aligned_to(a.out1, al);
+                        aligned_to(a.in2, al) && aligned_to(a.out0, al) && aligned_to(a.out1, al);
         if (!ok) return launch_cfg<T, R, 64, 8, 4, 1, 1, true>(a, opt, stream);
     }
     plan_march(a.map, a.nx, a.ny, a.nz, G::TX, G::TY, R, opt);
@@ -379,7 +392,9 @@ static hipError_t launch_cfg(March3dArgs a, const LaunchOptions &opt, hipStream_
             return hipErrorNotSupported;
         }
     }
-    if (!a.out1)                hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, PY, PX, D, NTU, 0, 0>), grid, block, pad, stream, a);
+    if (a.in2 && !a.out1)       hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, PY, PX, D, NTU, 3, 0>), grid, block, pad, stream, a);
+    else if (a.in2)             hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, PY, PX, D, NTU, 4, 0>), grid, block, pad, stream, a);
+    else if (!a.out1)           hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, PY, PX, D, NTU, 0, 0>), grid, block, pad, stream, a);
     else if (a.out1_assign == 0) hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, PY, PX, D, NTU, 1, 0>), grid, block, pad, stream, a);
     else                        hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, PY, PX, D, NTU, 2, 0>), grid, block, pad, stream, a);
     return hipGetLastError();
@@ -485,14 +500,8 @@ void describe_march_plan(int is_f64, int radius, int nx, int ny, int nz, int wit
     }
 }
 
-hipError_t launch_adjoint_wave3d(int is_f64, int radius, int nx, int ny, int nz, const void *c,
-                                 const void *r_bar, void *u_bar, void *u_prev_bar, int u_prev_bar_assign,
-                                 const LaunchOptions &opt, hipStream_t stream)
+static hipError_t launch_march(int is_f64, int radius, const March3dArgs &a, const LaunchOptions &opt, hipStream_t stream)
 {
-    March3dArgs a{};
-    a.in0 = c; a.in1 = r_bar; a.out0 = u_bar; a.out1 = u_prev_bar;
-    a.out1_assign = u_prev_bar_assign;
-    a.nx = nx; a.ny = ny; a.nz = nz;
     if (is_f64) {
         switch (radius) {
         case 1: return launch_T<double, 1>(a, opt, stream);
@@ -507,6 +516,27 @@ hipError_t launch_adjoint_wave3d(int is_f64, int radius, int nx, int ny, int nz,
     case 3: return launch_T<float, 3>(a, opt, stream);
     default: return launch_T<float, 4>(a, opt, stream);
     }
+}
+
+hipError_t launch_adjoint_wave3d(int is_f64, int radius, int nx, int ny, int nz, const void *c,
+                                 const void *r_bar, void *u_bar, void *u_prev_bar, int u_prev_bar_assign,
+                                 const LaunchOptions &opt, hipStream_t stream)
+{
+    March3dArgs a{};
+    a.in0 = c; a.in1 = r_bar; a.out0 = u_bar; a.out1 = u_prev_bar;
+    a.out1_assign = u_prev_bar_assign;
+    a.nx = nx; a.ny = ny; a.nz = nz;
+    return launch_march(is_f64, radius, a, opt, stream);
+}
+
+hipError_t launch_adjoint_wave3d_middle(int is_f64, int radius, int nx, int ny, int nz, const void *c, const void *r_bar,
+                                        void *before, void *u_bar, int last, const LaunchOptions &opt, hipStream_t stream)
+{
+    March3dArgs a{};
+    a.in0 = c; a.in1 = r_bar; a.in2 = before; a.out0 = u_bar; a.out1 = last ? before : nullptr;
+    a.out1_assign = 1;
+    a.nx = nx; a.ny = ny; a.nz = nz;
+    return launch_march(is_f64, radius, a, opt, stream);
 }
 
 }  // namespace sadj
