@@ -173,18 +173,19 @@ sadj_status burgers_ckpt_reverse(sadj_dtype dtype, long n, long nsteps, long eve
 // Order of launches of a reverse sweep of wave steps that may use a fourth array.
 // Buffers 0..2 are the caller's lam arrays, 3 is the work array.  A state is the pair (A, B) of
 // buffers that hold lam^{k+1} and lam^k.  A single step updates B in place and assigns -A m to
-// a buffer F outside {A, B}: (A, B) -> (B, F).  A fused pair of steps writes both results to the
+// a buffer F outside {A, B}: (A, B) -> (B, F).  A pass over two or three steps writes both results to the
 // two buffers outside {A, B}: (A, B) -> (F, G).  After the first step (which accumulates into
 // lam2 and is always single) the state is (1, 2); the sweep must end in (n%3, (n+1)%3).  The
-// body alternates pairs (1,2) -> (0,3) -> (1,2) ...; the last few steps are chosen by exhaustive
-// dynamic programming so that the end state is met with as many pairs as possible.
-struct WaveStepLaunch { int pair, a, b, o0, o1; };   // single: o0 = F;  pair: o0 <- a'', o1 <- b''
+// body alternates passes of `most` steps (1,2) -> (0,3) -> (1,2) ...; the last few steps are chosen by
+// exhaustive dynamic programming so that the end state is met with as few launches as possible
+// (every launch moves five words per cell, however many steps it takes).
+struct WaveStepLaunch { int steps, a, b, o0, o1; };   // single: o0 = F;  pass: o0 <- lam^{k+1-steps}, o1 <- lam^{k-steps}
 
 constexpr int kTailMax = 12;
 
 struct WaveSweepPlan {
     bool plain = true;                 // single steps rotating the caller's three buffers, work unused
-    long body_pairs = 0;               // else: pairs alternating (1,2) -> (0,3) -> (1,2) ..., then the tail
+    long body = 0;                     // else: passes alternating (1,2) -> (0,3) -> (1,2) ..., then the tail
     int tail_len = 0;
     WaveStepLaunch tail[kTailMax];
 };
@@ -192,17 +193,18 @@ struct WaveSweepPlan {
 inline int state_id(int a, int b) { return a * 4 + b; }
 
 // Launches for steps 1 .. nsteps-1 (step 0 is not part of the plan).
-WaveSweepPlan plan_wave_sweep(long nsteps)
+WaveSweepPlan plan_wave_sweep(long nsteps, int most)
 {
     WaveSweepPlan plan;
     const long m = nsteps - 1;
     if (m < 2) return plan;
     const int ta = (int)(nsteps % 3), tb = (int)((nsteps + 1) % 3);
     const int tmax = (int)(m < kTailMax ? m : kTailMax);
-    // best[t][state]: most pairs on a way from state to the target in exactly t steps, -1 if none
+    // best[t][state]: fewest launches on a way from state to the target in exactly t steps, none: kNone
+    constexpr int kNone = 1000;
     int best[kTailMax + 1][16], choice[kTailMax + 1][16][3];
     for (int t = 0; t <= tmax; ++t)
-        for (int s = 0; s < 16; ++s) best[t][s] = -1;
+        for (int s = 0; s < 16; ++s) best[t][s] = kNone;
     best[0][state_id(ta, tb)] = 0;
     for (int t = 1; t <= tmax; ++t)
         for (int a = 0; a < 4; ++a)
@@ -214,31 +216,32 @@ WaveSweepPlan plan_wave_sweep(long nsteps)
                 int &bst = best[t][state_id(a, b)];
                 int *ch = choice[t][state_id(a, b)];
                 for (int i = 0; i < 2; ++i) {
-                    const int v = best[t - 1][state_id(b, fr[i])];
-                    if (v >= 0 && v > bst) { bst = v; ch[0] = 0; ch[1] = fr[i]; ch[2] = -1; }
-                    if (t >= 2) {
-                        const int w = best[t - 2][state_id(fr[i], fr[1 - i])];
-                        if (w >= 0 && w + 1 > bst) { bst = w + 1; ch[0] = 1; ch[1] = fr[i]; ch[2] = fr[1 - i]; }
+                    const int v = best[t - 1][state_id(b, fr[i])] + 1;
+                    if (v < bst) { bst = v; ch[0] = 1; ch[1] = fr[i]; ch[2] = -1; }
+                    for (int k = 2; k <= most && k <= t; ++k) {
+                        const int w = best[t - k][state_id(fr[i], fr[1 - i])] + 1;
+                        if (w < bst) { bst = w; ch[0] = k; ch[1] = fr[i]; ch[2] = fr[1 - i]; }
                     }
                 }
             }
-    auto body_state = [](long pairs, int &a, int &b) { if (pairs % 2 == 0) { a = 1; b = 2; } else { a = 0; b = 3; } };
-    long q = m / 2;
+    auto body_state = [](long passes, int &a, int &b) { if (passes % 2 == 0) { a = 1; b = 2; } else { a = 0; b = 3; } };
+    long total = -1;
     int t = 0, a = 1, b = 2;
-    bool found = false;
-    for (; q >= 0 && m - 2 * q <= tmax; --q) {
-        t = (int)(m - 2 * q);
+    for (long q = m / most; q >= 0 && m - most * q <= tmax; --q) {
         body_state(q, a, b);
-        if (best[t][state_id(a, b)] >= 0) { found = true; break; }
+        const int launches = best[m - most * q][state_id(a, b)];
+        if (launches < kNone && (total < 0 || q + launches < total)) { total = q + launches; plan.body = q; }
     }
-    if (!found) return plan;           // plain stays set: single steps over three buffers
+    if (total < 0) return plan;        // plain stays set: single steps over three buffers
     plan.plain = false;
-    plan.body_pairs = q;
+    t = (int)(m - most * plan.body);
+    body_state(plan.body, a, b);
     while (t > 0) {
         const int *ch = choice[t][state_id(a, b)];
-        WaveStepLaunch &l = plan.tail[plan.tail_len++];
-        if (ch[0] == 0) { l = {0, a, b, ch[1], -1}; const int nb = ch[1]; a = b; b = nb; t -= 1; }
-        else            { l = {1, a, b, ch[1], ch[2]}; a = ch[1]; b = ch[2]; t -= 2; }
+        plan.tail[plan.tail_len++] = {ch[0], a, b, ch[1], ch[2]};
+        if (ch[0] == 1) { a = b; b = ch[1]; }
+        else            { a = ch[1]; b = ch[2]; }
+        t -= ch[0];
     }
     return plan;
 }
@@ -598,18 +601,19 @@ sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long n
     opt.remainder = 0;
     const bool fusable = radius == 1 && g_wave_fuse.load() == 0 &&
                          sadj::adjoint_wave3d_pair_supported(f64, (int)nx, c, lam0, lam1, lam2, work);
-    const WaveSweepPlan plan = fusable ? plan_wave_sweep(nsteps) : WaveSweepPlan{};
+    const int most = sadj::adjoint_wave3d_steps_per_pass(f64, (int)nx, (int)ny, (int)nz, opt);
+    const WaveSweepPlan plan = fusable ? plan_wave_sweep(nsteps, most) : WaveSweepPlan{};
     if (plan.plain) return wave_steps_plain(f64, radius, nx, ny, nz, nsteps, c, lam, opt, st);
     // step 0 accumulates into lam2, which may hold the objective's own contribution
     if (sadj_status s = wave_steps_plain(f64, radius, nx, ny, nz, 1, c, lam, opt, st); s != SADJ_OK) return s;
     auto run = [&](const WaveStepLaunch &l) {
-        return l.pair ? sadj::launch_adjoint_wave3d_pair(f64, (int)nx, (int)ny, (int)nz, c, buf[l.a], buf[l.b], buf[l.o0],
-                                                         buf[l.o1], opt, st)
-                      : sadj::launch_adjoint_wave3d(f64, radius, (int)nx, (int)ny, (int)nz, c, buf[l.a], buf[l.b], buf[l.o0], 1,
-                                                    opt, st);
+        if (l.steps == 1)
+            return sadj::launch_adjoint_wave3d(f64, radius, (int)nx, (int)ny, (int)nz, c, buf[l.a], buf[l.b], buf[l.o0], 1, opt, st);
+        const auto launch = l.steps == 2 ? sadj::launch_adjoint_wave3d_pair : sadj::launch_adjoint_wave3d_triple;
+        return launch(f64, (int)nx, (int)ny, (int)nz, c, buf[l.a], buf[l.b], buf[l.o0], buf[l.o1], opt, st);
     };
-    for (long i = 0; i < plan.body_pairs; ++i) {
-        const WaveStepLaunch l = i % 2 == 0 ? WaveStepLaunch{1, 1, 2, 0, 3} : WaveStepLaunch{1, 0, 3, 1, 2};
+    for (long i = 0; i < plan.body; ++i) {
+        const WaveStepLaunch l = i % 2 == 0 ? WaveStepLaunch{most, 1, 2, 0, 3} : WaveStepLaunch{most, 0, 3, 1, 2};
         if (hipError_t e = run(l); e != hipSuccess) return from_hip(e);
     }
     for (int i = 0; i < plan.tail_len; ++i)
@@ -622,12 +626,12 @@ sadj_status sadj_describe_wave3d_sweep(long nsteps, long *body_pairs, int *tail_
 {
     if (!body_pairs || !tail_len || !tail) return SADJ_ERR_NULL;
     if (nsteps < 0) return SADJ_ERR_SIZE;
-    const WaveSweepPlan plan = plan_wave_sweep(nsteps);
-    *body_pairs = plan.plain ? -1 : plan.body_pairs;
+    const WaveSweepPlan plan = plan_wave_sweep(nsteps, 2);
+    *body_pairs = plan.plain ? -1 : plan.body;
     *tail_len = plan.tail_len;
     for (int i = 0; i < plan.tail_len; ++i) {
         const WaveStepLaunch &l = plan.tail[i];
-        const int v[5] = {l.pair, l.a, l.b, l.o0, l.o1};
+        const int v[5] = {l.steps == 2, l.a, l.b, l.o0, l.o1};
         for (int k = 0; k < 5; ++k) tail[5 * i + k] = v[k];
     }
     return SADJ_OK;

@@ -39,6 +39,11 @@ bool adjoint_wave3d_pair_supported(int is_f64, int nx, const void *c, const void
                                    const void *p3);
 hipError_t launch_adjoint_wave3d_pair(int is_f64, int nx, int ny, int nz, const void *c, const void *a, const void *b,
                                       void *out_a, void *out_b, const LaunchOptions &opt, hipStream_t stream);
+// The same with three steps: out_a = lam^{k-2}, out_b = -(lam^{k-1}) on I, 0 elsewhere.
+hipError_t launch_adjoint_wave3d_triple(int is_f64, int nx, int ny, int nz, const void *c, const void *a, const void *b,
+                                        void *out_a, void *out_b, const LaunchOptions &opt, hipStream_t stream);
+// How many steps (2 or 3) a pass of a long sweep takes on a grid of this size.
+int adjoint_wave3d_steps_per_pass(int is_f64, int nx, int ny, int nz, const LaunchOptions &opt);
 hipError_t launch_primal_wave3d(int is_f64, int radius, int nx, int ny, int nz, const void *u,
                                 const void *u_prev, const void *c, void *r,
                                 const LaunchOptions &opt, hipStream_t stream);

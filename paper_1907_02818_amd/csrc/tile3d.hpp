@@ -246,6 +246,14 @@ static inline void plan_march(TileMap &m, int nx, int ny, int nz, int TX, int TY
     m.total_blocks = m.blocks_a + (int)(tiles - m.tiles_a) * m.ntz;
 }
 
+// The planner's model of a march's run time: planes marched, summed over the rounds, where a chunk marches
+// `beyond` planes more than its own.
+static inline long march_planes(const TileMap &m, int beyond)
+{
+    const int blocks_b = m.total_blocks - m.blocks_a;
+    return (long)cdiv_i(m.blocks_a, m.round_blocks) * (m.zchunk_a + beyond) + (long)cdiv_i(blocks_b, m.round_blocks) * (m.zchunk + beyond);
+}
+
 // Rows whose length in bytes is not a multiple of the 128-byte cache line (nx = 1000 in fp64:
 // every other row starts in the middle of a line).  Tile rows then begin and end inside a line
 // on most rows, and tiles with long rows (fewer row ends per byte) measured faster than the

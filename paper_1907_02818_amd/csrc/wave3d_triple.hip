@@ -1,0 +1,412 @@
+// Three reverse steps of a time loop of radius-1 wave steps in one pass over the data: the two-step march of
+// wave3d_pair.hip with one more stage.  With a = lam^{k+1}, b = lam^k, m the indicator of I and S the
+// 7-point star,
+//     a1 = b + 2 a m + S(c a m),   a2 = -a m + 2 a1 m + S(c a1 m),   a3 = -a1 m + 2 a2 m + S(c a2 m)
+// and the pass reads a, b, c and writes a3 and -a2 m: 40 bytes per cell (fp64) for three steps.
+//
+// In step zi of the march stage 1 reads plane zi of q0 = c a m and completes a1 of plane zi-1, stage 2 reads
+// q1 = c a1 m of plane zi-2 and completes a2 of plane zi-3, stage 3 reads q2 = c a2 m of plane zi-4 and
+// completes a3 of plane zi-5.  A tile needs a2 on itself and the cells next to it (D1), a1 also two cells
+// out (D2) and q0 three cells out (D3); distances are counted in cells along x plus along y, so
+// the frames have cut corners.  The first threads own one frame cell each (fp32: two): D1 cells run stages 1
+// and 2, D2 cells stage 1.  All three LDS planes are double-buffered and one barrier per step serves
+// all.  Values outside I are replaced by zero with selects, never by a multiplication.
+//
+// What bounds it: registers first.  A spill costs more than its own traffic, because a reload waits for
+// all loads in flight.  512 threads with 256 registers hold three sums per stage and owned cell because
+// q1 and q2 go to LDS as soon as they are formed, c of older planes waits in LDS (all but 320 bytes of the
+// 160 KB are used in fp64), and all LDS planes share one geometry.  Then memory: 512^3 fp64, a pass
+// takes 1.09 ms = 4.9 TB/s on its 40 bytes per cell (a two-step pass 0.95 ms), 0.36 ms per step against 0.48.
+#include "launch.hpp"
+#include "tile3d.hpp"
+
+#include <type_traits>
+
+namespace sadj {
+
+struct TripleArgs {
+    const void *c, *a, *b;
+    void *out_a, *out_b;
+    int nx, ny, nz;
+    TileMap map;
+};
+
+template <class T, int BX, int BY, int PY, int PX> struct TripleTile {
+    static constexpr int TX = BX * PX, TY = BY * PY, NT = BX * BY;
+    // all LDS planes have the geometry of the widest, origin (x0-3, y0-3), so that a cell has one address in
+    // all of them (three geometries need more address registers than the kernel has)
+    static constexpr int LX = TX + 6, PLANE = LX * (TY + 6);
+    static constexpr int SIDE = 2 * TX + 2 * TY;
+    static constexpr int N1 = SIDE, N2 = SIDE + 4, N3 = SIDE + 8;           // cells of D1, D2, D3
+    static constexpr int NFRAME = N1 + N2 + N3;
+    static constexpr int HS = (NFRAME + NT - 1) / NT;
+    static constexpr int RS = (N1 + N2 + NT - 1) / NT;                      // slots whose cells run stage 1
+    static_assert(N1 <= NT, "one cell that runs stage 2 per thread");
+
+    // Frame slot s of thread tid -> coordinates in the q0 plane; false if the slot is unused.
+    __device__ static __forceinline__ bool frame_cell(int tid, int s, int &lx, int &ly)
+    {
+        int h = tid + s * NT;
+        const bool used = h < NFRAME;
+        const int d = h < N1 ? 1 : h < N1 + N2 ? 2 : 3;
+        h -= d == 1 ? 0 : d == 2 ? N1 : N1 + N2;
+        int x, y;
+        if (h < 2 * TX) {                       // rows d above and below
+            x = h % TX;
+            y = h < TX ? -d : TY - 1 + d;
+        } else if (h < SIDE) {                  // columns d left and right
+            h -= 2 * TX;
+            x = (h & 1) ? TX - 1 + d : -d;
+            y = h / 2;
+        } else {                                // corners: d-1 cells each, i+1 out in x and d-1-i in y
+            h -= SIDE;
+            const int i = h >> 2;
+            x = (h & 1) ? TX + i : -1 - i;
+            y = (h & 2) ? TY + d - 2 - i : 1 - d + i;
+        }
+        lx = x + 3;
+        ly = y + 3;
+        return used;
+    }
+};
+
+template <class T, int BX, int BY, int PY, int PX, bool GUARD>
+__device__ __forceinline__ void triple_march(const TripleArgs &a, int tix, int tiy, int zs, int ze, T *__restrict__ sq0,
+                                             T *__restrict__ sq1, T *__restrict__ sq2, Vec<T, PX> *__restrict__ cold, T *__restrict__ coldr)
+{
+    using G = TripleTile<T, BX, BY, PY, PX>;
+    using V = Vec<T, PX>;
+    constexpr int TX = G::TX, TY = G::TY, LX = G::LX, HS = G::HS, RS = G::RS;
+    constexpr T W0 = T(3.0 * star_w<1>(0)), W1 = T(star_w<1>(1));
+    const int tid = threadIdx.x;
+    const int tx = tid % BX, ty = tid / BX;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const size_t plane = (size_t)nx * ny;
+    const int x0 = tix * TX, y0 = tiy * TY;
+
+    const T *__restrict__ cg = static_cast<const T *>(a.c);
+    const T *__restrict__ ag = static_cast<const T *>(a.a);
+    const T *__restrict__ bg = static_cast<const T *>(a.b);
+    T *__restrict__ oag = static_cast<T *>(a.out_a);
+    T *__restrict__ obg = static_cast<T *>(a.out_b);
+
+    TileAddr<PX, PY, HS, GUARD> ad;
+    ad.init(tx, ty, x0, y0, nx, ny, 1, 3, LX, 0 /* plane corner, never read */, (uint32_t)sizeof(T),
+            [&](int s, int &lx, int &ly) { return G::frame_cell(tid, s, lx, ly); });
+    const uint32_t dummy = ad.dummy;
+    uint32_t ooff[PY];
+    bool ouse[PY][PX], ostore[PY];
+#pragma unroll
+    for (int p = 0; p < PY; ++p) {
+        ostore[p] = ad.own_grid[p];
+        ooff[p] = ad.own_off[p];             // inside the grid, so that loads need no guard of their own
+#pragma unroll
+        for (int e = 0; e < PX; ++e) ouse[p][e] = ad.own_I[p][e];
+    }
+    // the thread's vector of row p in a plane: core tiles need the offset of the first row only
+    auto row = [&](auto *base, int p) { return base + (GUARD ? 0 : (size_t)p * nx); };
+    auto off = [&](int p) { return ooff[GUARD ? p : 0]; };
+    uint32_t hoff[HS];
+    uint32_t hpack = 0;
+    bool huse[HS];
+#pragma unroll
+    for (int s = 0; s < HS; ++s) {
+        huse[s] = ad.halo_I[s];
+        hoff[s] = huse[s] ? ad.halo_off[s] : dummy;
+        hpack |= (uint32_t)ad.halo_lds[s] << (16 * s);
+    }
+    static_assert(HS <= 2 && G::PLANE <= 65536, "two LDS indexes share a register");
+    auto hlds = [&](int s) { return s == 0 ? hpack & 0xffffu : hpack >> 16; };
+    // the frame cells of this thread that run stage 1 (D1, D2) and stage 2 (D1: slot 0, whole waves)
+    bool ring1[RS], ruse[RS];
+    const bool ring2 = tid < G::N1;
+#pragma unroll
+    for (int s = 0; s < RS; ++s) {
+        ring1[s] = tid + s * G::NT < G::N1 + G::N2;
+        ruse[s] = ring1[s] && huse[s];
+    }
+    const int own = (3 + ty * PY) * LX + 3 + tx * PX;
+
+    // running sums of the three stages: index 0 = the plane that completes in this step
+    T acc1[PY][PX][3], acc2[PY][PX][3], acc3[PY][PX][3], acc1r[RS][3], acc2r[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        acc2r[k] = T(0);
+#pragma unroll
+        for (int s = 0; s < RS; ++s) acc1r[s][k] = T(0);
+#pragma unroll
+        for (int p = 0; p < PY; ++p)
+#pragma unroll
+            for (int e = 0; e < PX; ++e) acc1[p][e][k] = acc2[p][e][k] = acc3[p][e][k] = T(0);
+    }
+    // c and a1 m of the plane before (c of the two planes before that waits in LDS, where only its own thread
+    // touches it)
+    T c1[PY][PX], a1m[PY][PX], c1r[RS], sbr[RS];
+#pragma unroll
+    for (int i = 0; i < 2 * PY; ++i) cold[i * G::NT + tid] = V{};
+    if (ring2) coldr[tid] = coldr[G::N1 + tid] = T(0);
+#pragma unroll
+    for (int s = 0; s < RS; ++s) c1r[s] = sbr[s] = T(0);
+#pragma unroll
+    for (int p = 0; p < PY; ++p)
+#pragma unroll
+        for (int e = 0; e < PX; ++e) c1[p][e] = a1m[p][e] = T(0);
+    bool q1_valid = false, q2_valid = false;     // the planes of q1 and q2 that this step reads were staged by the last one
+
+    V sa[PY], sc[PY], sb[PY];
+    T sha[HS], shc[HS];
+#pragma unroll
+    for (int p = 0; p < PY; ++p) { sa[p] = V{}; sc[p] = V{}; sb[p] = V{}; }
+#pragma unroll
+    for (int s = 0; s < HS; ++s) sha[s] = shc[s] = T(0);
+
+    auto plane_in_I = [&](int z) { return z >= 1 && z < nz - 1; };
+    const int zi0 = zs - 3, zi1 = ze + 2;        // q0 planes that reach the outputs [zs, ze)
+    auto a1_wanted = [&](int z) { return z >= zs - 2 && z <= ze + 1 && plane_in_I(z); };
+    auto a2_wanted = [&](int z) { return z >= zs - 1 && z <= ze && plane_in_I(z); };
+
+    // request what step z consumes: a and c of plane z (tile and frame), and, once the values of the step
+    // before are used up, b of plane z-1 (tile, D1 and D2); `steady`: every condition on the plane
+    // index holds
+    auto issue = [&](int z, auto steady) {
+        constexpr bool ST = decltype(steady)::value;
+        if (ST || (z <= zi1 && plane_in_I(z))) {
+            const T *cp = cg + (size_t)z * plane;
+            const T *ap = ag + (size_t)z * plane;
+#pragma unroll
+            for (int p = 0; p < PY; ++p) {
+                sc[p] = ld_vec_off<T, PX, false>(row(cp, p), off(p));
+                sa[p] = ld_vec_off<T, PX, false>(row(ap, p), off(p));
+            }
+#pragma unroll
+            for (int s = 0; s < HS; ++s) { shc[s] = ld_off(cp, hoff[s]); sha[s] = ld_off(ap, hoff[s]); }
+        }
+    };
+    auto issue_b = [&](int z, auto steady) {
+        constexpr bool ST = decltype(steady)::value;
+        if (ST || a1_wanted(z)) {
+            const T *bp = bg + (size_t)z * plane;
+#pragma unroll
+            for (int p = 0; p < PY; ++p) sb[p] = ld_vec_off<T, PX, false>(row(bp, p), off(p));
+#pragma unroll
+            for (int s = 0; s < RS; ++s) sbr[s] = ld_off(bp, hoff[s]);
+        }
+    };
+    // the star of one staged plane at a thread's tile cells and its sums: planes before, at and after
+    // (the thread's own values of q are read back: kept in registers from staging to here they cost spills)
+    auto star = [&](const T *sp, T (&acc)[PY][PX][3]) {
+        T q[PY][PX];
+#pragma unroll
+        for (int p = 0; p < PY; ++p)
+#pragma unroll
+            for (int e = 0; e < PX; ++e) q[p][e] = sp[own + p * LX + e];
+#pragma unroll
+        for (int p = 0; p < PY; ++p)
+#pragma unroll
+            for (int e = 0; e < PX; ++e) {
+                const T *at = sp + own + p * LX + e;
+                const T left = e > 0 ? q[p][e - 1] : at[-1];
+                const T right = e < PX - 1 ? q[p][e + 1] : at[1];
+                const T up = p > 0 ? q[p - 1][e] : at[-LX];
+                const T down = p < PY - 1 ? q[p + 1][e] : at[LX];
+                acc[p][e][1] += W0 * q[p][e] + W1 * (left + right) + W1 * (up + down);
+                acc[p][e][0] += W1 * q[p][e];
+                acc[p][e][2] += W1 * q[p][e];
+            }
+    };
+    auto star_ring = [&](const T *at, T (&acc)[3]) {
+        const T q = at[0];
+        acc[1] += W0 * q + W1 * (at[-1] + at[1]) + W1 * (at[-LX] + at[LX]);
+        acc[0] += W1 * q;
+        acc[2] += W1 * q;
+    };
+
+    issue(zi0, std::false_type{});
+    issue_b(zi0 - 1, std::false_type{});
+    int buf = 0;
+    auto step = [&](int zi, auto steady) {
+        constexpr bool ST = decltype(steady)::value;
+        const bool zin = ST || (zi <= zi1 && plane_in_I(zi));
+        // what this step reads (s0 is staged now), and where it leaves q1 and q2 for the next step: the buffers
+        // that the step before last wrote and the last one read, which every thread has left at the barrier
+        T *s0 = sq0 + buf * G::PLANE;
+        const T *s1 = sq1 + buf * G::PLANE, *s2 = sq2 + buf * G::PLANE;
+        T *n1 = sq1 + (buf ^ 1) * G::PLANE, *n2 = sq2 + (buf ^ 1) * G::PLANE;
+        T am[PY][PX], cc[PY][PX], amr[RS], ccr[RS];
+#pragma unroll
+        for (int s = 0; s < RS; ++s) amr[s] = ccr[s] = T(0);
+        if (zin) {
+#pragma unroll
+            for (int p = 0; p < PY; ++p)
+#pragma unroll
+                for (int e = 0; e < PX; ++e) {
+                    const T cv = sc[p].v[e], av = sa[p].v[e];
+                    cc[p][e] = cv;
+                    am[p][e] = GUARD ? (ouse[p][e] ? av : T(0)) : av;
+                    s0[own + p * LX + e] = GUARD ? (ouse[p][e] ? cv * av : T(0)) : cv * av;
+                }
+#pragma unroll
+            for (int s = 0; s < HS; ++s) {
+                const T qq = GUARD ? (huse[s] ? shc[s] * sha[s] : T(0)) : shc[s] * sha[s];
+                s0[hlds(s)] = qq;
+                if (s < RS) { ccr[s] = shc[s]; amr[s] = GUARD ? (huse[s] ? sha[s] : T(0)) : sha[s]; }
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < PY; ++p)
+#pragma unroll
+                for (int e = 0; e < PX; ++e) cc[p][e] = am[p][e] = T(0);
+        }
+        issue(zi + 1, steady);
+        __syncthreads();
+
+        // ---- stage 3: q2 of plane zi-4; a3 of plane zi-5 is complete
+        if (ST || q2_valid) star(s2, acc3);
+        const int zo3 = zi - 5;
+        if (ST || (zo3 >= zs && zo3 < ze)) {
+            T *op = oag + (size_t)zo3 * plane;
+#pragma unroll
+            for (int p = 0; p < PY; ++p) {
+                V o;
+#pragma unroll
+                for (int e = 0; e < PX; ++e) o.v[e] = acc3[p][e][0];
+                if (!GUARD || ostore[p]) st_vec_off<T, PX, true>(row(op, p), off(p), o);
+            }
+        }
+
+        // ---- stage 2: q1 of plane zi-2; a2 of plane zi-3 is complete
+        if (ST || q1_valid) {
+            star(s1, acc2);
+            if (ring2) star_ring(s1 + hlds(0), acc2r);
+        }
+        const int zo2 = zi - 3;
+        q2_valid = ST || a2_wanted(zo2);
+#pragma unroll
+        for (int p = 0; p < PY; ++p) {
+            const V c3 = cold[(buf * PY + p) * G::NT + tid];
+            V o, keep;
+#pragma unroll
+            for (int e = 0; e < PX; ++e) {
+                const T a2m = q2_valid && (!GUARD || ouse[p][e]) ? acc2[p][e][0] : T(0);
+                if (q2_valid) n2[own + p * LX + e] = !GUARD || ouse[p][e] ? c3.v[e] * a2m : T(0);
+                acc3[p][e][0] = acc3[p][e][1];
+                acc3[p][e][1] = acc3[p][e][2] + T(2) * a2m;
+                acc3[p][e][2] = -a1m[p][e];                                   // of plane zi-2
+                acc2[p][e][0] = acc2[p][e][1];
+                acc2[p][e][1] = acc2[p][e][2];
+                acc2[p][e][2] = -am[p][e];                                    // of plane zi
+                keep.v[e] = c1[p][e];
+                o.v[e] = -a2m;
+            }
+            cold[(buf * PY + p) * G::NT + tid] = keep;
+            if (ST || (zo2 >= zs && zo2 < ze))       // zero on planes outside I
+                if (!GUARD || ostore[p]) st_vec_off<T, PX, true>(row(obg + (size_t)zo2 * plane, p), off(p), o);
+        }
+        if (ring2) {
+            T *cr = coldr + buf * G::N1 + tid;
+            if (q2_valid) n2[hlds(0)] = ruse[0] ? *cr * acc2r[0] : T(0);
+            *cr = c1r[0];
+        }
+        acc2r[0] = acc2r[1]; acc2r[1] = acc2r[2]; acc2r[2] = -amr[0];
+
+        // ---- stage 1: q0 of plane zi; a1 of plane zi-1 is complete
+        if (zin) {
+            star(s0, acc1);
+#pragma unroll
+            for (int s = 0; s < RS; ++s)
+                if (ring1[s]) star_ring(s0 + hlds(s), acc1r[s]);
+        }
+        q1_valid = ST || a1_wanted(zi - 1);
+#pragma unroll
+        for (int p = 0; p < PY; ++p)
+#pragma unroll
+            for (int e = 0; e < PX; ++e) {
+                const T v = acc1[p][e][0] + sb[p].v[e];
+                a1m[p][e] = q1_valid && (!GUARD || ouse[p][e]) ? v : T(0);
+                if (q1_valid) n1[own + p * LX + e] = !GUARD || ouse[p][e] ? c1[p][e] * v : T(0);
+                acc2[p][e][1] += T(2) * a1m[p][e];
+                acc1[p][e][0] = acc1[p][e][1] + T(2) * am[p][e];
+                acc1[p][e][1] = acc1[p][e][2];
+                acc1[p][e][2] = T(0);
+                c1[p][e] = cc[p][e];
+            }
+#pragma unroll
+        for (int s = 0; s < RS; ++s) {
+            const T v = acc1r[s][0] + sbr[s];
+            const T a1 = q1_valid && ruse[s] ? v : T(0);
+            if (q1_valid && ring1[s]) n1[hlds(s)] = ruse[s] ? c1r[s] * v : T(0);
+            if (s == 0) acc2r[1] += T(2) * a1;
+            acc1r[s][0] = acc1r[s][1] + T(2) * amr[s];
+            acc1r[s][1] = acc1r[s][2];
+            acc1r[s][2] = T(0);
+            c1r[s] = ccr[s];
+        }
+        issue_b(zi, steady);
+        buf ^= 1;
+    };
+    // steady steps: planes zi-4 .. zi+1 lie in I, the output planes zi-5 and zi-3 in this chunk
+    const int lo = zs + 5, hi = min(ze + 1, nz - 3);
+    int zi = zi0;
+    for (; zi <= ze + 4 && zi < lo; ++zi) step(zi, std::false_type{});
+    // (guarded fp64 tiles have no register left for a second copy of the step: it would spill, and a reload
+    // waits for every load in flight)
+    if constexpr (!GUARD || sizeof(T) == 4) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // enter the steady loop with nothing outstanding (vmcnt(0))
+        for (; zi <= hi; ++zi) step(zi, std::true_type{});
+    }
+    for (; zi <= ze + 4; ++zi) step(zi, std::false_type{});
+}
+
+template <class T, int BX, int BY, int PY, int PX>
+__global__ __launch_bounds__(BX *BY) void adj_wave3d_triple_kernel(TripleArgs a)
+{
+    using G = TripleTile<T, BX, BY, PY, PX>;
+    __shared__ T sq0[2 * G::PLANE];
+    __shared__ T sq1[2 * G::PLANE];
+    __shared__ T sq2[2 * G::PLANE];
+    __shared__ Vec<T, PX> cold[2 * PY * G::NT];
+    __shared__ T coldr[2 * G::N1];
+    int tix, tiy, zs, ze;
+    block_to_tile(a.map, blockIdx.x, tix, tiy, zs, ze);
+    // core tile: the tile and its frame lie in I in x and y
+    const int x0 = tix * G::TX, y0 = tiy * G::TY;
+    const bool core = x0 >= 4 && x0 + G::TX + 4 <= a.nx && y0 >= 4 && y0 + G::TY + 4 <= a.ny;
+    if (core) triple_march<T, BX, BY, PY, PX, false>(a, tix, tiy, zs, ze, sq0, sq1, sq2, cold, coldr);
+    else      triple_march<T, BX, BY, PY, PX, true>(a, tix, tiy, zs, ze, sq0, sq1, sq2, cold, coldr);
+}
+
+template <class T, int PX>
+static hipError_t launch_triple(TripleArgs a, const LaunchOptions &opt, hipStream_t stream)
+{
+    constexpr int BX = 32, BY = 16, PY = 2;
+    using G = TripleTile<T, BX, BY, PY, PX>;
+    // each chunk marches 8 planes beyond its own: plan as a march of radius 4
+    plan_march(a.map, a.nx, a.ny, a.nz, G::TX, G::TY, 4, opt);
+    hipLaunchKernelGGL((adj_wave3d_triple_kernel<T, BX, BY, PY, PX>), dim3(a.map.total_blocks), dim3(G::NT), 0, stream, a);
+    return hipGetLastError();
+}
+
+// A chunk marches 5 planes beyond its own for two steps and 8 for three, and a plane of the three-step march
+// takes about 1.1 (fp64) or 1.2 (fp32) times as long.  Short marches on small grids therefore take two
+// steps per pass: 25 steps, two / three per pass, fp64 33 x 40 x 72 71 / 83 us, 128^3 309 / 265, 512^3
+// 12.9 / 9.4 ms; fp32 128^3 192 / 221 us, 96 x 130 x 164 262 / 279, 160 x 180 x 200 451 / 406, 512^3 6.6 / 5.0 ms.
+int adjoint_wave3d_steps_per_pass(int is_f64, int nx, int ny, int nz, const LaunchOptions &opt)
+{
+    const int TX = is_f64 ? 64 : 128, TY = 32;
+    TileMap two, three;
+    plan_march(two, nx, ny, nz, TX, TY, 2, opt);
+    plan_march(three, nx, ny, nz, TX, TY, 4, opt);
+    return 20 * march_planes(three, 8) * (is_f64 ? 11 : 12) < 300 * march_planes(two, 5) ? 3 : 2;
+}
+
+hipError_t launch_adjoint_wave3d_triple(int is_f64, int nx, int ny, int nz, const void *c, const void *a, const void *b,
+                                        void *out_a, void *out_b, const LaunchOptions &opt, hipStream_t stream)
+{
+    if (!adjoint_wave3d_pair_supported(is_f64, nx, c, a, b, out_a, out_b)) return hipErrorNotSupported;
+    TripleArgs p{};
+    p.c = c; p.a = a; p.b = b; p.out_a = out_a; p.out_b = out_b;
+    p.nx = nx; p.ny = ny; p.nz = nz;
+    return is_f64 ? launch_triple<double, 2>(p, opt, stream) : launch_triple<float, 4>(p, opt, stream);
+}
+
+}  // namespace sadj
