@@ -224,7 +224,7 @@ struct BoxTile {
 // Tile form of the 2-D kernels (the default; see wave2d.hip for the measurements that made it
 // so): one workgroup per tile of TX x TY outputs, no march.  The staged field S (u, or q) on the
 // tile and the full ring around it goes to LDS once; a thread owns PX cells of one row.
-template <class T, int PX, int TY, bool ADJ, bool GUARD>
+template <class T, int PX, int TY, bool ADJ, bool GUARD, bool RAGGED>
 __device__ __forceinline__ void box2d_tile(const BoxArgs &a, int tix, int tiy, T *__restrict__ sq)
 {
     using G = BoxTile<T, 32, TY, 1, PX>;
@@ -250,8 +250,9 @@ __device__ __forceinline__ void box2d_tile(const BoxArgs &a, int tix, int tiy, T
     const uint32_t ooff = ad.own_off[0];
     // adjoint: c and r_bar are used on I only; primal: u is read on the whole grid, c on I
     const uint32_t ioff = (!GUARD || any) ? ooff : ad.dummy;
-    const V v0 = ld_vec_off<T, PX, false>(g0, ADJ ? ioff : ooff);
-    const V v1 = ld_vec_off<T, PX, !ADJ>(g1, ioff);
+    const int cells = cells_in_row(ad.own_grid[0], x0 + tx * PX, a.nx, PX);
+    const V v0 = ld_cells_off<T, PX, false, RAGGED, GUARD>(g0, ADJ ? ioff : ooff, cells);
+    const V v1 = ld_cells_off<T, PX, !ADJ, RAGGED, GUARD>(g1, ioff, cells);
     T h0[HS], h1[HS];
 #pragma unroll
     for (int s = 0; s < HS; ++s) {
@@ -261,7 +262,7 @@ __device__ __forceinline__ void box2d_tile(const BoxArgs &a, int tix, int tiy, T
         h1[s] = ADJ ? ld_off(g1, off) : T(0);
     }
     V vo{};
-    if (ADJ) vo = ld_vec_off<T, PX, true>(og, ooff);
+    if (ADJ) vo = ld_cells_off<T, PX, true, RAGGED, GUARD>(og, ooff, cells);
     T sv[PX];
 #pragma unroll
     for (int e = 0; e < PX; ++e) {
@@ -286,9 +287,9 @@ __device__ __forceinline__ void box2d_tile(const BoxArgs &a, int tix, int tiy, T
         o.v[e] = ADJ ? vo.v[e] + s : v1.v[e] * s;
     }
     if (ADJ) {
-        if (!GUARD || ad.own_grid[0]) st_vec_off<T, PX, true>(og, ooff, o);
+        if (!GUARD || ad.own_grid[0]) st_cells_off<T, PX, true, RAGGED, GUARD>(og, ooff, cells, o);
     } else if (!GUARD || all) {
-        st_vec_off<T, PX, true>(og, ooff, o);
+        st_cells_off<T, PX, true, RAGGED, GUARD>(og, ooff, cells, o);
     } else {                                               // r outside I stays untouched
         T *rp = reinterpret_cast<T *>(reinterpret_cast<char *>(og) + ooff);
 #pragma unroll
@@ -297,7 +298,7 @@ __device__ __forceinline__ void box2d_tile(const BoxArgs &a, int tix, int tiy, T
     }
 }
 
-template <class T, int PX, int TY, bool ADJ>
+template <class T, int PX, int TY, bool ADJ, bool RAGGED>
 __global__ __launch_bounds__(32 * TY) void box2d_tile_kernel(BoxArgs a, int ntx, int total)
 {
     using G = BoxTile<T, 32, TY, 1, PX>;
@@ -306,18 +307,19 @@ __global__ __launch_bounds__(32 * TY) void box2d_tile_kernel(BoxArgs a, int ntx,
     const int tiy = L / ntx, tix = L - tiy * ntx;
     const int x0 = tix * G::TX, y0 = tiy * TY;
     const bool core = x0 >= 2 && x0 + G::TX + 2 <= a.nx && y0 >= 2 && y0 + TY + 2 <= a.ny;
-    if (core) box2d_tile<T, PX, TY, ADJ, false>(a, tix, tiy, sq);
-    else      box2d_tile<T, PX, TY, ADJ, true>(a, tix, tiy, sq);
+    if (core) box2d_tile<T, PX, TY, ADJ, false, RAGGED>(a, tix, tiy, sq);
+    else      box2d_tile<T, PX, TY, ADJ, true, RAGGED>(a, tix, tiy, sq);
 }
 
-template <class T, int PX, bool ADJ>
+// RAGGED: nx or an array is not aligned to whole 16-byte vectors (see wave2d.hip).
+template <class T, bool RAGGED, bool ADJ>
 static hipError_t launch_box2d_tile(const BoxArgs &a, hipStream_t stream)
 {
-    constexpr int TY = 8, TX = 32 * PX;
+    constexpr int PX = 16 / sizeof(T), TY = 8, TX = 32 * PX;
     const long ntx = cdiv_i(a.nx, TX), nty = cdiv_i(a.ny, TY);
     if (ntx * nty > 0x3fffffffL) return hipErrorNotSupported;
     const int total = (int)(ntx * nty);
-    hipLaunchKernelGGL((box2d_tile_kernel<T, PX, TY, ADJ>), dim3(total), dim3(32 * TY), 0, stream, a, (int)ntx, total);
+    hipLaunchKernelGGL((box2d_tile_kernel<T, PX, TY, ADJ, RAGGED>), dim3(total), dim3(32 * TY), 0, stream, a, (int)ntx, total);
     return hipGetLastError();
 }
 
@@ -555,8 +557,8 @@ static hipError_t launch_box_nd(int is_f64, int ndim, const BoxArgs &a, const La
         if (is_f64) return (al && a.nx % 2 == 0) ? launch_box2d<double, 2, ADJ>(a, stream) : launch_box2d<double, 1, ADJ>(a, stream);
         return (al && a.nx % 4 == 0) ? launch_box2d<float, 4, ADJ>(a, stream) : launch_box2d<float, 1, ADJ>(a, stream);
     }
-    if (is_f64) return (al && a.nx % 2 == 0) ? launch_box2d_tile<double, 2, ADJ>(a, stream) : launch_box2d_tile<double, 1, ADJ>(a, stream);
-    return (al && a.nx % 4 == 0) ? launch_box2d_tile<float, 4, ADJ>(a, stream) : launch_box2d_tile<float, 1, ADJ>(a, stream);
+    if (is_f64) return (al && a.nx % 2 == 0) ? launch_box2d_tile<double, false, ADJ>(a, stream) : launch_box2d_tile<double, true, ADJ>(a, stream);
+    return (al && a.nx % 4 == 0) ? launch_box2d_tile<float, false, ADJ>(a, stream) : launch_box2d_tile<float, true, ADJ>(a, stream);
 }
 
 // w: 27 gather weights indexed (ox+1) + 3(oy+1) + 9(oz+1) (already mirrored for the adjoint)

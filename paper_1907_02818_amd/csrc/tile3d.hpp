@@ -320,4 +320,55 @@ template <class T, int N, bool NT> __device__ __forceinline__ void st_vec_off(T 
     else st_vec<T, N>(p, v);
 }
 
+// A lane's N cells of one row where rows or arrays are not aligned to whole vectors (RAGGED; else the plain vector
+// accesses above).  Tiles inside the grid move them with one instruction all the same (the type says that only
+// the elements are aligned, which the memory system takes); guarded tiles move `cells` of them one by
+// one, the rest reading the first.
+template <class T, int N> struct AnyVec { typedef T type __attribute__((ext_vector_type(N), aligned(sizeof(T)))); };
+
+template <class T, int N, bool NT, bool RAGGED, bool GUARD>
+__device__ __forceinline__ Vec<T, N> ld_cells_off(const T *base, uint32_t byte_off, int cells)
+{
+    if constexpr (!RAGGED) {
+        return ld_vec_off<T, N, NT>(base, byte_off);
+    } else {
+        const T *p = reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + byte_off);
+        Vec<T, N> r;
+        if constexpr (!GUARD) {
+            typedef typename AnyVec<T, N>::type VT;
+            const VT *q = reinterpret_cast<const VT *>(p);
+            const VT t = NT ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+            for (int e = 0; e < N; ++e) r.v[e] = t[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < N; ++e) r.v[e] = p[e < cells ? e : 0];
+        }
+        return r;
+    }
+}
+template <class T, int N, bool NT, bool RAGGED, bool GUARD>
+__device__ __forceinline__ void st_cells_off(T *base, uint32_t byte_off, int cells, const Vec<T, N> &v)
+{
+    if constexpr (!RAGGED) {
+        st_vec_off<T, N, NT>(base, byte_off, v);
+    } else {
+        T *p = reinterpret_cast<T *>(reinterpret_cast<char *>(base) + byte_off);
+        if constexpr (!GUARD) {
+            typedef typename AnyVec<T, N>::type VT;
+            VT t;
+#pragma unroll
+            for (int e = 0; e < N; ++e) t[e] = v.v[e];
+            if (NT) __builtin_nontemporal_store(t, reinterpret_cast<VT *>(p));
+            else *reinterpret_cast<VT *>(p) = t;
+        } else {
+#pragma unroll
+            for (int e = 0; e < N; ++e)
+                if (e < cells) p[e] = v.v[e];
+        }
+    }
+}
+// Cells of a lane's vector at column x that lie in the grid; `inside`: the first of them does.
+__device__ __forceinline__ int cells_in_row(bool inside, int x, int nx, int n) { return !inside ? 1 : nx - x < n ? nx - x : n; }
+
 }  // namespace sadj

@@ -346,7 +346,7 @@ __global__ __launch_bounds__(64 * WAVES) void primal_wave2d_kernel(Wave2dArgs a)
 // c and r_bar (found in L2 where the neighbour runs on the same XCD).  Measured a few points
 // slower than the strip march where that is at its best and a little faster where it is not
 // (see launch_adj2d).
-template <class T, int PX, int TY, bool GUARD, bool UPREV>
+template <class T, int PX, int TY, bool GUARD, bool UPREV, bool RAGGED, bool NT>
 __device__ __forceinline__ void adj2d_tile(const Wave2dArgs &a, int tix, int tiy, T *__restrict__ sq)
 {
     using G = Tile3d<T, 1, 32, TY, 1, PX>;
@@ -366,7 +366,9 @@ __device__ __forceinline__ void adj2d_tile(const Wave2dArgs &a, int tix, int tiy
 #pragma unroll
     for (int e = 0; e < PX; ++e) any = any || ad.own_I[0][e];
     const uint32_t ooff = ad.own_off[0], coff = (!GUARD || any) ? ooff : ad.dummy;
-    const V vc = ld_vec_off<T, PX, false>(cg, coff), vr = ld_vec_off<T, PX, false>(rg, coff);
+    const int cells = cells_in_row(ad.own_grid[0], x0 + tx * PX, a.nx, PX);
+    auto load = [&](const T *g, uint32_t off, auto nt) { return ld_cells_off<T, PX, decltype(nt)::value, RAGGED, GUARD>(g, off, cells); };
+    const V vc = load(cg, coff, std::false_type{}), vr = load(rg, coff, std::false_type{});
     T hc[HS], hr[HS];
 #pragma unroll
     for (int s = 0; s < HS; ++s) {
@@ -374,9 +376,9 @@ __device__ __forceinline__ void adj2d_tile(const Wave2dArgs &a, int tix, int tiy
         hc[s] = ld_off(cg, off);
         hr[s] = ld_off(rg, off);
     }
-    const V vu = ld_vec_off<T, PX, true>(ug, ooff);
+    const V vu = load(ug, ooff, std::bool_constant<NT>{});
     V vp{};
-    if (UPREV) vp = ld_vec_off<T, PX, true>(pg, ooff);
+    if (UPREV) vp = load(pg, ooff, std::bool_constant<NT>{});
     T q[PX], rm[PX];
 #pragma unroll
     for (int e = 0; e < PX; ++e) {
@@ -398,12 +400,12 @@ __device__ __forceinline__ void adj2d_tile(const Wave2dArgs &a, int tix, int tiy
         op.v[e] = vp.v[e] - rm[e];
     }
     if (!GUARD || ad.own_grid[0]) {
-        st_vec_off<T, PX, true>(ug, ooff, o);
-        if (UPREV) st_vec_off<T, PX, true>(pg, ooff, op);
+        st_cells_off<T, PX, NT, RAGGED, GUARD>(ug, ooff, cells, o);
+        if (UPREV) st_cells_off<T, PX, NT, RAGGED, GUARD>(pg, ooff, cells, op);
     }
 }
 
-template <class T, int PX, int TY, bool UPREV>
+template <class T, int PX, int TY, bool UPREV, bool RAGGED, bool NT>
 __global__ __launch_bounds__(32 * TY) void adj_wave2d_tile_kernel(Wave2dArgs a, int ntx, int total)
 {
     using G = Tile3d<T, 1, 32, TY, 1, PX>;
@@ -412,11 +414,11 @@ __global__ __launch_bounds__(32 * TY) void adj_wave2d_tile_kernel(Wave2dArgs a, 
     const int tiy = L / ntx, tix = L - tiy * ntx;
     const int x0 = tix * G::TX, y0 = tiy * TY;
     const bool core = x0 >= 2 && x0 + G::TX + 2 <= a.nx && y0 >= 2 && y0 + TY + 2 <= a.ny;
-    if (core) adj2d_tile<T, PX, TY, false, UPREV>(a, tix, tiy, sq);
-    else      adj2d_tile<T, PX, TY, true, UPREV>(a, tix, tiy, sq);
+    if (core) adj2d_tile<T, PX, TY, false, UPREV, RAGGED, NT>(a, tix, tiy, sq);
+    else      adj2d_tile<T, PX, TY, true, UPREV, RAGGED, NT>(a, tix, tiy, sq);
 }
 
-template <class T, int PX, int TY>
+template <class T, int PX, int TY, bool RAGGED>
 static hipError_t launch_adj2d_tile(const Wave2dArgs &a, hipStream_t stream)
 {
     constexpr int TX = 32 * PX;
@@ -424,14 +426,26 @@ static hipError_t launch_adj2d_tile(const Wave2dArgs &a, hipStream_t stream)
     if (ntx * nty > 0x3fffffffL) return hipErrorNotSupported;
     const int total = (int)(ntx * nty);
     dim3 grid(total), block(32 * TY);
-    if (a.u_prev_bar) hipLaunchKernelGGL((adj_wave2d_tile_kernel<T, PX, TY, true>), grid, block, 0, stream, a, (int)ntx, total);
-    else              hipLaunchKernelGGL((adj_wave2d_tile_kernel<T, PX, TY, false>), grid, block, 0, stream, a, (int)ntx, total);
+    // Streaming accesses for u_bar and u_prev_bar, except where both are read and written in ragged rows and the four
+    // arrays exceed the 256 MB of the last-level cache: there most tile rows end inside a cache line,
+    // the line is streamed out before the neighbouring tile touches it, and with two such arrays regular
+    // accesses are faster (fp64 4099^2 165 -> 148 us, 6001^2 385 -> 333, 8191^2 713 -> 594; fp32 6001^2 185 -> 167).
+    // With one such array, with aligned rows or in the cache they are up to 15 % slower.
+    const bool regular = RAGGED && 4 * sizeof(T) * (size_t)a.nx * a.ny >= ((size_t)256 << 20);
+    if (!a.u_prev_bar) {
+        hipLaunchKernelGGL((adj_wave2d_tile_kernel<T, PX, TY, false, RAGGED, true>), grid, block, 0, stream, a, (int)ntx, total);
+    } else if constexpr (RAGGED) {
+        if (regular) hipLaunchKernelGGL((adj_wave2d_tile_kernel<T, PX, TY, true, RAGGED, false>), grid, block, 0, stream, a, (int)ntx, total);
+        else         hipLaunchKernelGGL((adj_wave2d_tile_kernel<T, PX, TY, true, RAGGED, true>), grid, block, 0, stream, a, (int)ntx, total);
+    } else {
+        hipLaunchKernelGGL((adj_wave2d_tile_kernel<T, PX, TY, true, RAGGED, true>), grid, block, 0, stream, a, (int)ntx, total);
+    }
     return hipGetLastError();
 }
 
 
 // Tile form of the primal: u on the tile and its ring staged in LDS, one workgroup per tile.
-template <class T, int PX, int TY, bool GUARD>
+template <class T, int PX, int TY, bool GUARD, bool RAGGED>
 __device__ __forceinline__ void primal2d_tile(const Wave2dArgs &a, int tix, int tiy, T *__restrict__ sq)
 {
     using G = Tile3d<T, 1, 32, TY, 1, PX>;
@@ -451,11 +465,13 @@ __device__ __forceinline__ void primal2d_tile(const Wave2dArgs &a, int tix, int 
 #pragma unroll
     for (int e = 0; e < PX; ++e) { any = any || ad.own_I[0][e]; all = all && ad.own_I[0][e]; }
     const uint32_t ooff = ad.own_off[0], coff = (!GUARD || any) ? ooff : ad.dummy;
-    const V vu = ld_vec_off<T, PX, false>(ug, ooff);       // u is read on the whole grid
+    const int cells = cells_in_row(ad.own_grid[0], x0 + tx * PX, a.nx, PX);
+    auto load = [&](const T *g, uint32_t off, auto nt) { return ld_cells_off<T, PX, decltype(nt)::value, RAGGED, GUARD>(g, off, cells); };
+    const V vu = load(ug, ooff, std::false_type{});        // u is read on the whole grid
     T hu[HS];
 #pragma unroll
     for (int s = 0; s < HS; ++s) hu[s] = ld_off(ug, ad.halo_off[s]);
-    const V vc = ld_vec_off<T, PX, true>(cg, coff), vp = ld_vec_off<T, PX, true>(pg, coff);
+    const V vc = load(cg, coff, std::true_type{}), vp = load(pg, coff, std::true_type{});
 #pragma unroll
     for (int e = 0; e < PX; ++e) sq[(1 + ty) * LX + 1 + tx * PX + e] = vu.v[e];
 #pragma unroll
@@ -471,7 +487,7 @@ __device__ __forceinline__ void primal2d_tile(const Wave2dArgs &a, int tix, int 
         o.v[e] = T(2) * vu.v[e] - vp.v[e] + vc.v[e] * lap;
     }
     if (!GUARD || all) {
-        st_vec_off<T, PX, true>(rg, ooff, o);
+        st_cells_off<T, PX, true, RAGGED, GUARD>(rg, ooff, cells, o);
     } else {                                               // r outside I stays untouched
         T *rp = reinterpret_cast<T *>(reinterpret_cast<char *>(rg) + ooff);
 #pragma unroll
@@ -480,7 +496,7 @@ __device__ __forceinline__ void primal2d_tile(const Wave2dArgs &a, int tix, int 
     }
 }
 
-template <class T, int PX, int TY>
+template <class T, int PX, int TY, bool RAGGED>
 __global__ __launch_bounds__(32 * TY) void primal_wave2d_tile_kernel(Wave2dArgs a, int ntx, int total)
 {
     using G = Tile3d<T, 1, 32, TY, 1, PX>;
@@ -489,18 +505,18 @@ __global__ __launch_bounds__(32 * TY) void primal_wave2d_tile_kernel(Wave2dArgs 
     const int tiy = L / ntx, tix = L - tiy * ntx;
     const int x0 = tix * G::TX, y0 = tiy * TY;
     const bool core = x0 >= 1 && x0 + G::TX + 1 <= a.nx && y0 >= 1 && y0 + TY + 1 <= a.ny;
-    if (core) primal2d_tile<T, PX, TY, false>(a, tix, tiy, sq);
-    else      primal2d_tile<T, PX, TY, true>(a, tix, tiy, sq);
+    if (core) primal2d_tile<T, PX, TY, false, RAGGED>(a, tix, tiy, sq);
+    else      primal2d_tile<T, PX, TY, true, RAGGED>(a, tix, tiy, sq);
 }
 
-template <class T, int PX, int TY>
+template <class T, int PX, int TY, bool RAGGED>
 static hipError_t launch_pri2d_tile(const Wave2dArgs &a, hipStream_t stream)
 {
     constexpr int TX = 32 * PX;
     const long ntx = (a.nx + TX - 1) / TX, nty = (a.ny + TY - 1) / TY;
     if (ntx * nty > 0x3fffffffL) return hipErrorNotSupported;
     const int total = (int)(ntx * nty);
-    hipLaunchKernelGGL((primal_wave2d_tile_kernel<T, PX, TY>), dim3(total), dim3(32 * TY), 0, stream, a, (int)ntx, total);
+    hipLaunchKernelGGL((primal_wave2d_tile_kernel<T, PX, TY, RAGGED>), dim3(total), dim3(32 * TY), 0, stream, a, (int)ntx, total);
     return hipGetLastError();
 }
 
@@ -550,23 +566,29 @@ static hipError_t launch_adj2d_cfg(Wave2dArgs a, const LaunchOptions &opt, hipSt
 // picture (8192^2 72.8 / 73.4, 7000^2 63.6 / 75.4); tiles of 16 rows within 2 points of 8 rows,
 // tiles of 4 and of 32 rows 1-3 points lower.  Other strip-march shapes that were tried (one or
 // four rows in flight, four or sixteen waves per workgroup) were never better than the one kept.
-template <class T, int PX>
+//
+// RAGGED: nx or an array is not aligned to whole 16-byte vectors.  The tile form moves 16 bytes per lane all
+// the same (ld_cells_off), where one cell per lane was 10-20 % (fp64) and 20-40 % (fp32) slower: 2050 x 4099
+// adjoint fp64 58 -> 52 us, with u_prev_bar 90 -> 76, fp32 29 -> 22, primal 45 -> 41 and 31 -> 22 us.  The strip
+// march, whose lanes all take the same path, takes one cell per lane there.
+template <class T, bool RAGGED>
 static hipError_t launch_adj2d(const Wave2dArgs &a, const LaunchOptions &opt, hipStream_t stream)
 {
+    constexpr int PX = 16 / sizeof(T);
     switch (opt.variant2d) {
     default:
-    case 0: return launch_adj2d_tile<T, PX, 8>(a, stream);
-    case 1: return launch_adj2d_cfg<T, PX, 2, 8>(a, opt, stream);
-    case 2: return launch_adj2d_tile<T, PX, 16>(a, stream);
+    case 0: return launch_adj2d_tile<T, PX, 8, RAGGED>(a, stream);
+    case 1: return launch_adj2d_cfg<T, RAGGED ? 1 : PX, 2, 8>(a, opt, stream);
+    case 2: return launch_adj2d_tile<T, PX, 16, RAGGED>(a, stream);
     }
 }
 
-template <class T, int PX>
+template <class T, bool RAGGED>
 static hipError_t launch_pri2d(const Wave2dArgs &a0, const LaunchOptions &opt, hipStream_t stream)
 {
-    if (opt.variant2d == 2) return launch_pri2d_tile<T, PX, 16>(a0, stream);
-    if (opt.variant2d != 1) return launch_pri2d_tile<T, PX, 8>(a0, stream);
-    constexpr int WAVES = 8, D = 2;
+    if (opt.variant2d == 2) return launch_pri2d_tile<T, 16 / sizeof(T), 16, RAGGED>(a0, stream);
+    if (opt.variant2d != 1) return launch_pri2d_tile<T, 16 / sizeof(T), 8, RAGGED>(a0, stream);
+    constexpr int WAVES = 8, D = 2, PX = RAGGED ? 1 : 16 / sizeof(T);
     Wave2dArgs a = a0;
     constexpr int W = 64 * PX;
     const int nstrips = (a.nx + W - 1) / W;
@@ -587,11 +609,11 @@ hipError_t launch_adjoint_wave2d(int is_f64, int nx, int ny, const void *c, cons
     a.nx = nx; a.ny = ny;
     const bool al = aligned16(c) && aligned16(r_bar) && aligned16(u_bar) && aligned16(u_prev_bar);
     if (is_f64) {
-        if (al && nx % 2 == 0) return launch_adj2d<double, 2>(a, opt, stream);
-        return launch_adj2d<double, 1>(a, opt, stream);
+        if (al && nx % 2 == 0) return launch_adj2d<double, false>(a, opt, stream);
+        return launch_adj2d<double, true>(a, opt, stream);
     }
-    if (al && nx % 4 == 0) return launch_adj2d<float, 4>(a, opt, stream);
-    return launch_adj2d<float, 1>(a, opt, stream);
+    if (al && nx % 4 == 0) return launch_adj2d<float, false>(a, opt, stream);
+    return launch_adj2d<float, true>(a, opt, stream);
 }
 
 hipError_t launch_primal_wave2d(int is_f64, int nx, int ny, const void *u, const void *u_prev,
@@ -602,11 +624,11 @@ hipError_t launch_primal_wave2d(int is_f64, int nx, int ny, const void *u, const
     a.nx = nx; a.ny = ny;
     const bool al = aligned16(u) && aligned16(u_prev) && aligned16(c) && aligned16(r);
     if (is_f64) {
-        if (al && nx % 2 == 0) return launch_pri2d<double, 2>(a, opt, stream);
-        return launch_pri2d<double, 1>(a, opt, stream);
+        if (al && nx % 2 == 0) return launch_pri2d<double, false>(a, opt, stream);
+        return launch_pri2d<double, true>(a, opt, stream);
     }
-    if (al && nx % 4 == 0) return launch_pri2d<float, 4>(a, opt, stream);
-    return launch_pri2d<float, 1>(a, opt, stream);
+    if (al && nx % 4 == 0) return launch_pri2d<float, false>(a, opt, stream);
+    return launch_pri2d<float, true>(a, opt, stream);
 }
 
 }  // namespace sadj
