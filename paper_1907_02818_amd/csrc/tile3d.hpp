@@ -260,7 +260,7 @@ static inline long march_planes(const TileMap &m, int beyond)
 // default shapes, while for line-aligned rows they measured equal or slower.
 //
 // Radius 1 keeps three running sums per cell, so eight cells per lane fit the register file:
-// tiles of 256 (fp32 adjoint: 512) cells x 16 rows measured 4-10 points faster (500^3, 1000^3,
+// tiles of 256 (fp32 wave kernels: 512) cells x 16 rows measured 4-10 points faster (500^3, 1000^3,
 // 200 x 700 x 1500, both dtypes, adjoint and primal).  Larger radii stay at four fp64 (eight
 // fp32) cells per lane and trade tile rows for width: 1 KB x 16 rows instead of 512 B x 32
 // (radius 4 fp64 at 500^3, 1000^3, 250 x 900 x 1100, 300 x 300 x 1250: adjoint +2 to +5
