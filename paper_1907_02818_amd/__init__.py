@@ -126,36 +126,56 @@ def get_option(name: str) -> int:
     return v.value
 
 
-def _marshal(tensors, ndim, optional=()):
-    """Common checks: same device/dtype/shape, contiguous, on the GPU.  Returns
-    (dtype code, shape, pointers, stream handle)."""
+_dtype_code = None     # torch dtype -> SADJ_F32 / SADJ_F64, filled by the first call
+_raw_stream = None     # device index -> handle of its current stream
+
+
+def _bind_torch():
+    global _dtype_code, _raw_stream
     import torch
 
+    # the handle itself where this torch offers it: building the Stream object that holds it takes
+    # 1.9 us of an 8 us call
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda index: torch.cuda.current_stream(index).cuda_stream)
+    _dtype_code = {torch.float64: SADJ_F64, torch.float32: SADJ_F32}
+
+
+def _refuse(t, ref) -> None:
+    """Raise what is wrong with tensor t of a call whose first tensor is ref."""
+    if not t.is_cuda:
+        raise ValueError("libsadj works on GPU memory only (no CPU path)")
+    if t.dtype != ref.dtype or t.shape != ref.shape or t.device != ref.device:
+        raise ValueError("all tensors of a call share dtype, shape and device")
+    raise ValueError("tensors must be C-contiguous (x fastest)")
+
+
+def _marshal(tensors, ndim, optional=()):
+    """Common checks: same device/dtype/shape, contiguous, on the GPU.  Returns
+    (dtype code, shape, addresses, stream handle).  A small grid's kernel is shorter than the host's
+    part of the call, so every tensor is checked in one expression and named only when refused
+    (n = 4096: the call 8.2 -> 4.6 us, 3 of them in the library)."""
+    if _dtype_code is None:
+        _bind_torch()
     ref = next(t for t in tensors if t is not None)
     if ref.dim() != ndim:
         raise ValueError("expected %d-D tensors" % ndim)
-    if ref.dtype == torch.float64:
-        code = SADJ_F64
-    elif ref.dtype == torch.float32:
-        code = SADJ_F32
-    else:
+    dtype = ref.dtype
+    code = _dtype_code.get(dtype)
+    if code is None:
         raise TypeError("float32 or float64 tensors only")
+    shape, index = ref.shape, ref.get_device()
     ptrs = []
     for i, t in enumerate(tensors):
         if t is None:
             if i not in optional:
                 raise ValueError("tensor %d is required" % i)
             ptrs.append(None)
-            continue
-        if not t.is_cuda:
-            raise ValueError("libsadj works on GPU memory only (no CPU path)")
-        if t.dtype != ref.dtype or t.shape != ref.shape or t.device != ref.device:
-            raise ValueError("all tensors of a call share dtype, shape and device")
-        if not t.is_contiguous():
-            raise ValueError("tensors must be C-contiguous (x fastest)")
-        ptrs.append(ctypes.c_void_p(t.data_ptr()))
-    stream = ctypes.c_void_p(torch.cuda.current_stream(ref.device).cuda_stream)
-    return code, tuple(ref.shape), ptrs, stream
+        elif t.is_cuda and t.dtype is dtype and t.shape == shape and t.get_device() == index and t.is_contiguous():
+            ptrs.append(t.data_ptr())
+        else:
+            _refuse(t, ref)
+    return code, tuple(shape), ptrs, _raw_stream(index)
 
 
 def sadj_primal_wave1d(u, u_prev, c, r) -> None:
@@ -268,11 +288,20 @@ def sadj_adjoint_star3d(radius: int, weights, c, r_bar, u_bar) -> None:
 
 
 def _flatten(w):
+    """The numbers of a nested sequence or array in order."""
+    if hasattr(w, "tolist"):
+        w = w.tolist()
     try:
-        for x in w:
-            yield from _flatten(x)
+        items = iter(w)
     except TypeError:
-        yield w
+        return [w]
+    out = []
+    for x in items:
+        if type(x) is float:
+            out.append(x)
+        else:
+            out.extend(_flatten(x))
+    return out
 
 
 def sadj_primal_box(weights, u, c, r) -> None:
