@@ -216,8 +216,14 @@ static inline void plan_march(TileMap &m, int nx, int ny, int nz, int TX, int TY
                 best_cost = cost; best_blocks = blocks; best_a = (int)tiles_a; best_ca = ca; best_cb = cb;
             }
         };
-        for (int c = 1; c <= max_chunks; ++c) consider(0, 1, c);
-        for (int c = max_chunks + 1; c <= nz && tiles * c <= ncu; ++c) consider(0, 1, c);
+        // Within one round the run time falls with the number of chunks, so of the counts that fit only the
+        // largest matters, or the smallest that cuts as short (small grids are planned in a call's own time).
+        auto same_cut = [nz](long c) { return cdiv_i(nz, cdiv_i(nz, (int)c)); };
+        const long one_round = ncu / tiles;
+        const int c1 = (int)(one_round < max_chunks ? one_round : max_chunks);
+        if (c1 >= 1) consider(0, 1, same_cut(c1));
+        for (int c = c1 + 1; c <= max_chunks; ++c) consider(0, 1, c);
+        if (one_round > max_chunks) consider(0, 1, same_cut(one_round < nz ? one_round : nz));
         if (opt.split == 0 && tiles < 0x3fffffffL / 64) {
             for (int ca = 1; ca <= max_chunks && ca <= 8; ++ca) {
                 // the largest number of tiles whose ca chunks fill whole rounds
@@ -248,10 +254,10 @@ static inline void plan_march(TileMap &m, int nx, int ny, int nz, int TX, int TY
 
 // The planner's model of a march's run time: planes marched, summed over the rounds, where a chunk marches
 // `beyond` planes more than its own.
-static inline long march_planes(const TileMap &m, int beyond)
+static inline long march_planes(const TileMap &m, int beyond, int wg_per_cu = 1)
 {
-    const int blocks_b = m.total_blocks - m.blocks_a;
-    return (long)cdiv_i(m.blocks_a, m.round_blocks) * (m.zchunk_a + beyond) + (long)cdiv_i(blocks_b, m.round_blocks) * (m.zchunk + beyond);
+    const int blocks_b = m.total_blocks - m.blocks_a, round = m.round_blocks * wg_per_cu;
+    return (long)cdiv_i(m.blocks_a, round) * (m.zchunk_a + beyond) + (long)cdiv_i(blocks_b, round) * (m.zchunk + beyond);
 }
 
 // Rows whose length in bytes is not a multiple of the 128-byte cache line (nx = 1000 in fp64:

@@ -362,6 +362,40 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_kernel(March3dArgs a)
 
 static inline bool aligned_to(const void *p, size_t n) { return (reinterpret_cast<uintptr_t>(p) % n) == 0; }
 
+// Small grids.  Where the z-chunks of the default shapes are shorter than 4R planes the chip waits for one
+// plane-step after the other, and a 32 x 16 tile with one cell per thread, two workgroups per CU, has the
+// shorter steps: measured per plane 0.74-0.88 of the 64 x 32 fp64 tile's time and 0.58-0.65 of the 128 x 32
+// fp32 tile's (more arithmetic per cell at larger radii, hence the table), against more planes per
+// workgroup.  20 steps of a sweep, default / small tiles, fp64: radius 4 40^3 305 / 171 us, 101 x 99 x 97
+// 526 / 382, 128^3 478 / 440, 150^3 732 / 750; radius 1 40^3 108 / 86, 80 x 96 x 112 146 / 192; fp32 radius 4 40^3
+// 289 / 139, 128^3 341 / 318, 150^3 518 / 533.  (Tiles of 32 x 8 and one workgroup per CU were slower from 80^3 on.)
+constexpr int kSmallBX = 32, kSmallBY = 16, kSmallPerCu = 2;
+
+// Whether a grid takes them, and the plan if so; TX x TY: the default shape.
+static bool small_tiles(TileMap &small, bool is_f64, int radius, int nx, int ny, int nz, int TX, int TY, const LaunchOptions &opt)
+{
+    if (opt.variant != 0 || opt.remainder != 0 || opt.zchunk != 0 || opt.lds_pad != 0) return false;
+    if (wide_tile_for_unaligned_rows(nx, is_f64 ? 8 : 4, radius, !is_f64)) return false;
+    TileMap big;
+    plan_march(big, nx, ny, nz, TX, TY, radius, opt);
+    if (big.tiles_a != 0 || big.zchunk >= 4 * radius || big.zchunk >= nz) return false;
+    plan_march(small, nx, ny, nz, kSmallBX, kSmallBY, radius, opt, kSmallPerCu);
+    constexpr int percent[2][4] = {{65, 63, 58, 62}, {88, 79, 70, 74}};
+    return percent[is_f64][radius - 1] * march_planes(small, 2 * radius, kSmallPerCu) < 100 * march_planes(big, 2 * radius);
+}
+
+template <class T, int R> static hipError_t launch_small(const March3dArgs &a, hipStream_t stream)
+{
+    constexpr int BX = kSmallBX, BY = kSmallBY;
+    const dim3 grid(a.map.total_blocks), block(BX * BY);
+    if (a.in2 && !a.out1)        hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 3, 0>), grid, block, 0, stream, a);
+    else if (a.in2)              hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 4, 0>), grid, block, 0, stream, a);
+    else if (!a.out1)            hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 0, 0>), grid, block, 0, stream, a);
+    else if (a.out1_assign == 0) hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 1, 0>), grid, block, 0, stream, a);
+    else                         hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 2, 0>), grid, block, 0, stream, a);
+    return hipGetLastError();
+}
+
 template <class T, int R, int BX, int BY, int PY, int PX, int D, bool NTU>
 static hipError_t launch_cfg(March3dArgs a, const LaunchOptions &opt, hipStream_t stream)
 {
@@ -447,6 +481,10 @@ template <class T, int R>
 static hipError_t launch_T(const March3dArgs &a, const LaunchOptions &opt, hipStream_t stream)
 {
     const long v = choose_adjoint_shape(sizeof(T) == 8, R, a.nx, a.out1 && !a.out1_assign, opt);
+    int TX, TY, PX;
+    shape_extents(v, sizeof(T) == 8, R, TX, TY, PX);
+    March3dArgs as = a;
+    if (small_tiles(as.map, sizeof(T) == 8, R, a.nx, a.ny, a.nz, TX, TY, opt)) return launch_small<T, R>(as, stream);
     if constexpr (R == 2 || R == 3) {            // the default shapes of the dtype only
         if constexpr (sizeof(T) == 8) {
             return v == 3 ? launch_cfg<T, R, 64, 8, 4, 1, 1, true>(a, opt, stream)
@@ -485,11 +523,14 @@ void describe_march_plan(int is_f64, int radius, int nx, int ny, int nz, int wit
     long v = choose_adjoint_shape(is_f64 != 0, radius, nx, with_u_prev_bar != 0, opt);
     int TX, TY, PX;
     shape_extents(v, is_f64 != 0, radius, TX, TY, PX);
-    if (nx % PX != 0) shape_extents(3, is_f64 != 0, radius, TX, TY, PX);
-    March3dArgs a{};
-    a.nx = nx; a.ny = ny; a.nz = nz;
-    TileMap &m = a.map;
-    plan_march(m, nx, ny, nz, TX, TY, radius, opt);
+    TileMap m;
+    if (small_tiles(m, is_f64 != 0, radius, nx, ny, nz, TX, TY, opt)) {
+        TX = kSmallBX;
+        TY = kSmallBY;
+    } else {
+        if (nx % PX != 0) shape_extents(3, is_f64 != 0, radius, TX, TY, PX);
+        plan_march(m, nx, ny, nz, TX, TY, radius, opt);
+    }
     plan[0] = m.ntx; plan[1] = m.nty; plan[2] = TX; plan[3] = TY; plan[4] = m.total_blocks;
     plan[5] = m.tiles_a; plan[6] = m.ntz_a; plan[7] = m.ntz;
     if (!tiles) return;

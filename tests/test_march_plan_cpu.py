@@ -1,5 +1,6 @@
 """Host-only test of the z cut of small grids: a grid whose tiles do not fill the chip is cut into chunks
-shorter than 4R planes, as many as there are compute units for and no more."""
+shorter than 4R planes, as many as there are workgroups resident and no more, and takes 32 x 16 tiles,
+two per compute unit, where those march for a shorter time."""
 import pytest
 
 # without a GPU the planner assumes this many compute units
@@ -22,10 +23,11 @@ def test_small_grids_fill_the_chip_in_one_round(dtype_code, radius, shape):
     info, tiles = _plan(dtype_code, radius, shape)
     nz = shape[0]
     n_tiles = info["ntx"] * info["nty"]
-    assert info["workgroups"] <= CUS
+    resident = 2 * CUS if (info["tile_w"], info["tile_h"]) == (32, 16) else CUS
+    assert info["workgroups"] <= resident
     longest = max(ze - zs for _, _, zs, ze in tiles)
-    # the longest chunk is as short as the compute units allow
-    assert longest <= max(-(-nz // max(1, CUS // n_tiles)), 1)
+    # the longest chunk is as short as the resident workgroups allow
+    assert longest <= max(-(-nz // max(1, resident // n_tiles)), 1)
     seen = {}
     for tx, ty, zs, ze in tiles:
         seen.setdefault((tx, ty), []).append((zs, ze))
@@ -41,3 +43,14 @@ def test_larger_grids_keep_chunks_of_at_least_four_radii():
     assert min(ze - zs for _, _, zs, ze in tiles) >= 16 or info["workgroups"] <= CUS
     info, tiles = _plan(1, 4, (200, 1000, 1000))
     assert min(ze - zs for _, _, zs, ze in tiles) >= 16
+
+
+@pytest.mark.parametrize("dtype_code,radius,shape,small", [(1, 4, (40, 40, 40), True), (1, 4, (80, 96, 112), True), (1, 1, (80, 96, 112), False),
+                                                           (0, 4, (128, 128, 128), True), (1, 4, (160, 180, 200), False),
+                                                           (1, 4, (256, 256, 256), False), (1, 4, (20, 37, 250), False)])
+def test_which_grids_take_small_tiles(dtype_code, radius, shape, small):
+    torch = pytest.importorskip("torch")
+    if torch.cuda.is_available():
+        pytest.skip("plans depend on the device's compute units; this test counts on the default")
+    info, _ = _plan(dtype_code, radius, shape)
+    assert ((info["tile_w"], info["tile_h"]) == (32, 16)) == small
