@@ -356,6 +356,37 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_kernel(PairArgs a)
     else      pair_march<T, BX, BY, PY, PX, true>(a, tix, tiy, zs, ze, sq1, sq2);
 }
 
+// Tiles of 64 x 32 (fp32: 128 x 32) cells, one workgroup per CU; on small grids, whose chunks the 5 planes that a
+// workgroup marches beyond its own dominate, 64 x 16 cells (fp32: two workgroups per CU), whose march
+// step takes 0.72 (fp32: 0.79) of the time.  25 steps, default / small tiles: fp64 24^3 125 / 101 us, 64^3
+// 134 / 110, 128^3 309 / 307; fp32 24^3 146 / 91, 64^3 152 / 96, 96 x 130 x 164 262 / 242, 128^3 191 / 194.
+struct PairPlan {
+    TileMap map;
+    bool small;
+    long cost;             // planes marched in default tiles, times 100
+};
+
+static PairPlan plan_pair(int is_f64, int nx, int ny, int nz, const LaunchOptions &opt)
+{
+    // each chunk marches 5 planes beyond its own: planned as a march of radius 2
+    PairPlan p{};
+    plan_march(p.map, nx, ny, nz, is_f64 ? 64 : 128, 32, 2, opt);
+    p.cost = 100 * march_planes(p.map, 5);
+    if (opt.zchunk == 0 && opt.lds_pad == 0 && p.map.zchunk < 8) {
+        const int per_cu = is_f64 ? 1 : 2;
+        TileMap m;
+        plan_march(m, nx, ny, nz, 64, 16, 2, opt, per_cu);
+        const long cost = (is_f64 ? 72 : 79) * march_planes(m, 5, per_cu);
+        if (cost < p.cost) p = {m, true, cost};
+    }
+    return p;
+}
+
+long adjoint_wave3d_pair_cost(int is_f64, int nx, int ny, int nz, const LaunchOptions &opt)
+{
+    return plan_pair(is_f64, nx, ny, nz, opt).cost;
+}
+
 template <class T, int PX>
 static hipError_t launch_pair(PairArgs a, const LaunchOptions &opt, hipStream_t stream)
 {
@@ -366,8 +397,14 @@ static hipError_t launch_pair(PairArgs a, const LaunchOptions &opt, hipStream_t 
     for (const void *p : arrays)
         if (reinterpret_cast<uintptr_t>(p) % al != 0) return hipErrorNotSupported;
     if (a.nx % PX != 0) return hipErrorNotSupported;
-    // each chunk marches 4 planes beyond its own: plan as a march of radius 2
-    plan_march(a.map, a.nx, a.ny, a.nz, G::TX, G::TY, 2, opt);
+    const PairPlan plan = plan_pair(sizeof(T) == 8, a.nx, a.ny, a.nz, opt);
+    a.map = plan.map;
+    if (plan.small) {
+        using S = PairTile<T, BX, BY, 1, 2>;
+        const unsigned spad = sizeof(T) == 8 ? one_workgroup_per_cu_pad(sizeof(T) * 2 * (S::PLANE1 + S::PLANE2), opt.lds_pad) : 0;
+        hipLaunchKernelGGL((adj_wave3d_pair_kernel<T, BX, BY, 1, 2>), dim3(a.map.total_blocks), dim3(S::NT), spad, stream, a);
+        return hipGetLastError();
+    }
     const size_t lds = sizeof(T) * 2 * (G::PLANE1 + G::PLANE2);
     const unsigned pad = one_workgroup_per_cu_pad(lds, opt.lds_pad);
     hipLaunchKernelGGL((adj_wave3d_pair_kernel<T, BX, BY, PY, PX>), dim3(a.map.total_blocks), dim3(G::NT), pad, stream, a);
