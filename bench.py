@@ -345,7 +345,7 @@ def main():
     def burgers_steps_leg():
         # Reverse sweep over stored Burgers states.  Step by step: per step read u^t and lam, write
         # lam (24 B/pt; the first step accumulates: 32).  The same 24 B/pt are the yardstick for the
-        # fused sweep (runs of five assigned steps per pass: lam read and written once per five
+        # fused sweep (up to 15 assigned steps per pass: lam read and written once per 15
         # states), whose fraction may therefore exceed what one pass per step could reach.
         ks = 16
         states = torch.rand(ks + 1, nb, device=dev, dtype=torch.float64) - 0.5
@@ -358,10 +358,10 @@ def main():
         o = add("burgers1d_f64_adjoint_steps_fused_per_step",
                 lambda: sadj.sadj_adjoint_burgers1d_steps(0.1, 0.05, ks, ks, states, la, lb), nb * ks, per_step_bytes, "f64", per=ks)
         o["note"] = ("fraction is against the step-by-step compulsory bytes (24 B/pt/step); the fused passes themselves move "
-                     "(16 + 8*5)/5 = 11.2 B/pt/step plus 6.7 % recomputed window overlap")
+                     "(16 + 8*15)/15 = 9.1 B/pt/step plus the overlap of the windows")
 
-    # reverse sweep of a time loop of 7-point wave steps, 25 steps per call: one kernel per step, or with
-    # pairs of steps fused (step 0 alone, then 12 pairs); both priced at the step-by-step bytes
+    # reverse sweep of a time loop of 7-point wave steps, 25 steps per call: one kernel per step, or step 0
+    # alone and then passes of three steps (two on grids of about a million cells or fewer); both priced at the step-by-step bytes
     wave_ks = 25
     wave_step_bytes = 16 * I1 + 24 * N
 
@@ -375,10 +375,10 @@ def main():
                 lambda: sadj.sadj_adjoint_wave3d_steps_fused(1, wave_ks, c, rb, ub, upb(), work), N * wave_ks,
                 wave_ks * wave_step_bytes, "f64", per=wave_ks)
         o["kernel_algorithmic_bytes"] = 24 * I1 + 16 * N
-        if "traffic" in o:                       # the recorded counters are those of one launch of the pair kernel
+        if "traffic" in o:                       # the recorded counters are those of one pass
             o["kernel_traffic"] = o.pop("traffic")
-        o["note"] = ("fraction is against the step-by-step compulsory bytes (40 B/pt/step); a call is one single step and 12 "
-                     "launches of the pair kernel, each of which moves kernel_algorithmic_bytes for two steps "
+        o["note"] = ("fraction is against the step-by-step compulsory bytes (40 B/pt/step); a call is one single step and then "
+                     "passes of three steps (two on small grids), each of which moves kernel_algorithmic_bytes "
                      "(a, b, c read on I, two results written)")
 
     def functor_leg():
@@ -555,7 +555,7 @@ def main():
                   {"seconds_best": 0.897188, "hardware": "Xeon E5-2650 v4, 12 threads",
                    "seconds_best_other": 0.843320, "hardware_other": "Xeon Phi 7210, 32 threads"})
         # reverse sweep of a time loop of such steps (the paper notes that solvers take many, Section 4): 25 steps per
-        # call, one kernel per step, then with pairs of steps fused (step 0 alone, then 12 pairs)
+        # call, one kernel per step, then three steps per pass after step 0
         a4 = torch.empty_like(a1)
         ks3, step3 = 25, 16 * interior_points(s3, 1) + 24 * N3
         add("paper_wave3d_7pt_1000^3_f64_adjoint_steps_per_step", lambda: sadj.sadj_adjoint_wave3d_steps(1, ks3, cw, a1, a2, a3),

@@ -586,7 +586,7 @@ sadj_status sadj_adjoint_wave3d_steps(sadj_dtype dtype, int radius, long nx, lon
     return wave_steps_plain(dtype == SADJ_F64, radius, nx, ny, nz, nsteps, c, lam, opt, static_cast<hipStream_t>(stream));
 }
 
-// The same sweep with a fourth array to work in: pairs of steps run fused where the kernel exists.
+// The same sweep with a fourth array to work in: two or three steps per pass where the kernels exist.
 sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long nx, long ny, long nz, long nsteps,
                                             const void *c, void *lam0, void *lam1, void *lam2, void *work, void *stream)
 {
@@ -621,7 +621,7 @@ sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long n
     return SADJ_OK;
 }
 
-// Diagnostic: the launches sadj_adjoint_wave3d_steps_fused makes after step 0 when pairs can be fused.
+// Diagnostic: the launches sadj_adjoint_wave3d_steps_fused makes after step 0 where its passes take two steps.
 sadj_status sadj_describe_wave3d_sweep(long nsteps, long *body_pairs, int *tail_len, int *tail /* 5 ints per launch, 12 launches */)
 {
     if (!body_pairs || !tail_len || !tail) return SADJ_ERR_NULL;
