@@ -2,16 +2,16 @@
 // (paper Sections 3.1 and 4.2: the nonlinear stencil's adjoint reads the primal states).
 //
 // A wave holds a window of 64*PXL consecutive cells in registers, PXL per lane, and applies m steps to
-// it.  A cell's value after k steps depends on k cells to either side, so H cells at either end of
-// the window are recomputed by the neighbouring windows and only the V = 64*PXL - 2H between
-// them are stored.  No LDS, no barrier: neighbours travel by whole-wave lane shifts (DPP).
+// it.  A cell's value after k steps depends on k cells to either side, so `halo` cells at either end of
+// the window are recomputed by the neighbouring windows and only the 64*PXL - 2 halo between
+// them are stored: halo 16, or 8 in passes of up to 8 steps over stored states.  No LDS, no barrier: neighbours travel by whole-wave lane shifts (DPP).
 //
 // Windows that lie in I = [1, n-2] run without guards; the others clamp their loads into the array
 // and mask with selects.  A window belongs to one wave, so the branch between the two is uniform.
 //
 // What bounds it (fp64; one launch per step before).  Forward with every state stored: memory, 8 + 8/m bytes
 // per cell and step instead of 16; 10^7 cells, 16 steps: 245 us, 5.5 TB/s.  Reverse over stored states:
-// memory, 8 + 16/m bytes instead of 24; 15 steps of 10^7 cells 241 us, 5.6 TB/s.  Reverse from a
+// memory, 8 + 16/m bytes instead of 24; a sweep of 16 steps of 10^7 cells 284 us.  Reverse from a
 // checkpoint: 24/m bytes, the m states are recomputed in registers and the vector ALUs are the bound
 // (43 instructions per four cells of a forward step, 103 of a reverse one); so is the forward sweep
 // that stores checkpoints only, 16 steps of 10^7 cells in 60 us.
@@ -41,11 +41,17 @@ struct BurgersReverseArgs {
     long n;
     double C, D;
     int m, first, every;
+    int halo;               // cells recomputed on either side of a window, states all in memory
 };
 
 constexpr int kLoopWaves = 4;         // windows per workgroup
+constexpr int kAhead = 4;             // states in flight in a pass over stored states
 constexpr int kLoopH = 16;            // cells recomputed on either side of a window
-static_assert(kLoopH >= kForwardSteps && kLoopH >= kReverseSteps && kLoopH >= 2 * kRecomputeSteps - 1, "halo of a pass");
+constexpr int kShortH = 8;            // the same in short passes over stored states
+static_assert(kLoopH >= kForwardSteps && kLoopH >= kReverseSteps && kLoopH >= 2 * kRecomputeSteps - 1 && kShortH >= kShortSteps, "halo of a pass");
+
+// Cells that a window stores, of the 64 * PXL that it holds.
+__host__ __device__ constexpr int own_cells(int PXL, int halo) { return 64 * PXL - 2 * halo; }
 
 // Whole-wave lane shifts (DPP).  shift: the value of the lane to the left (right), `edge` in lane 0
 // (63); rotate: the same with lanes 0 and 63 taken as neighbours.
@@ -77,18 +83,19 @@ template <bool RIGHT> __device__ __forceinline__ double lane_rotate(double v)
 // lane's cells are one run, which needs half the lane shifts.  Rows of an odd length start at
 // addresses that are multiples of the element size only, and the vector type says so.
 template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
-    static constexpr int W = 64 * PXL, V = W - 2 * kLoopH;
+    static constexpr int W = 64 * PXL;
     static constexpr int PXV = PXL * sizeof(T) < 16 ? PXL : 16 / (int)sizeof(T);
     static constexpr int RUN = SPREAD ? PXV : PXL, RUNS = PXL / RUN;
     typedef T VT __attribute__((ext_vector_type(PXV), aligned(sizeof(T))));
     long x0, lo, hi;                  // first cell of the lane's first run; cells lo .. hi-1 are the window's own
     long n;
-    int lane;
+    int lane, halo;                   // cells recomputed on either side, a multiple of RUN
     bool in[PXL];
 
-    __device__ __forceinline__ Lane(long w, int lane_, long n_) : n(n_), lane(lane_)
+    __device__ __forceinline__ Lane(long w, int lane_, long n_, int halo_) : n(n_), lane(lane_), halo(halo_)
     {
-        x0 = w * V - kLoopH + (long)lane * RUN;
+        const int V = own_cells(PXL, halo);
+        x0 = w * V - halo + (long)lane * RUN;
         lo = w * V;
         hi = (w + 1) * V < n ? (w + 1) * V : n;
 #pragma unroll
@@ -126,7 +133,7 @@ template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
                 VT t;
 #pragma unroll
                 for (int e = 0; e < PXV; ++e) t[e] = v[h + e];
-                if ((r > 0 || lane >= kLoopH / RUN) && (r < RUNS - 1 || lane < 64 - kLoopH / RUN))
+                if ((r > 0 || lane >= halo / RUN) && (r < RUNS - 1 || lane < 64 - halo / RUN))
                     __builtin_nontemporal_store(t, reinterpret_cast<VT *>(p + cell(h)));
             }
         } else {
@@ -185,7 +192,7 @@ __device__ __forceinline__ double lane_value(double v, int from)
 template <class T, int PXL, bool GUARD, bool SPREAD>
 __device__ __forceinline__ void burgers_forward_window(const BurgersForwardArgs &a, long w, int lane)
 {
-    const Lane<T, PXL, GUARD, SPREAD> L(w, lane, a.n);
+    const Lane<T, PXL, GUARD, SPREAD> L(w, lane, a.n, kLoopH);
     const T C = (T)a.C, D = (T)a.D;
     T u[PXL];
     L.load(static_cast<const T *>(a.src), u);
@@ -224,35 +231,32 @@ __device__ __forceinline__ void burgers_forward_window(const BurgersForwardArgs 
 
 template <class T, int PXL, bool SPREAD> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_forward_kernel(BurgersForwardArgs a)
 {
-    using L = Lane<T, PXL, false, false>;
+    constexpr int W = 64 * PXL, V = own_cells(PXL, kLoopH);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * L::V - kLoopH;
-    if (w * L::V >= a.n) return;
-    if (x0 >= 1 && x0 + L::W - 1 <= a.n - 2) burgers_forward_window<T, PXL, false, SPREAD>(a, w, lane);
+    const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * V - kLoopH;
+    if (w * V >= a.n) return;
+    if (x0 >= 1 && x0 + W - 1 <= a.n - 2) burgers_forward_window<T, PXL, false, SPREAD>(a, w, lane);
     else burgers_forward_window<T, PXL, true, SPREAD>(a, w, lane);
 }
 
-// Reverse steps over m states that are all in memory (rows follows src, first = every = 1).  AHEAD states are
-// in flight; requests for steps that the pass does not have re-read its last state, so that no load
-// is behind a branch and the wait before a step leaves the later ones outstanding.
-template <class T, int PXL, bool GUARD, int AHEAD>
+// Reverse steps over m states that are all in memory (rows follows src, first = every = 1), m % kAhead == REM.
+// The requests follow the length of the pass: an earlier form issued those of 15 steps always, re-reading the
+// last state for the missing ones, and a sweep of 5 steps over 4 10^6 fp32 cells took 60 us instead of 38, of 3 steps
+// over 10^6 fp64 cells 29 instead of 17.
+template <class T, int PXL, bool GUARD, int REM>
 __device__ __forceinline__ void burgers_reverse_stored(const BurgersReverseArgs &a, long w, int lane)
 {
-    const Lane<T, PXL, GUARD, true> L(w, lane, a.n);
+    const Lane<T, PXL, GUARD, true> L(w, lane, a.n, a.halo);
     const T C = (T)a.C, D = (T)a.D;
     const T *src = static_cast<const T *>(a.src);
-    T lam[PXL], u[AHEAD][PXL];
+    T lam[PXL], u[kAhead][PXL];
     L.load(static_cast<const T *>(a.lam_in), lam);
-    auto request = [&](int s) {
-        if (s >= 0) L.template load<true>(src + (long)min(s, a.m - 1) * a.n, u[s % AHEAD]);
-    };
-#pragma unroll
-    for (int s = kReverseSteps - 1; s > kReverseSteps - 1 - AHEAD; --s) request(s);
-#pragma unroll
-    for (int s = kReverseSteps - 1; s >= 0; --s) {
-        if (s < a.m) L.reverse_step(u[s % AHEAD], lam, C, D);
-        request(s - AHEAD);
-    }
+    stored_reverse_schedule<kAhead, REM>(
+        a.m, [&](int t, int slot) { L.template load<true>(src + (long)t * a.n, u[slot]); },
+        [&](int slot) {
+            L.reverse_step(u[slot], lam, C, D);
+            __builtin_amdgcn_sched_barrier(0);       // steps interleaved with each other need half as many registers again
+        });
     L.store(static_cast<T *>(a.lam_out), lam, true);
 }
 
@@ -262,7 +266,7 @@ template <class T, int PXL, bool GUARD>
 __device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseArgs &a, long w, int lane)
 {
     constexpr int M = kRecomputeSteps;
-    const Lane<T, PXL, GUARD, false> L(w, lane, a.n);
+    const Lane<T, PXL, GUARD, false> L(w, lane, a.n, kLoopH);
     const T C = (T)a.C, D = (T)a.D;
     T lam[PXL], u[M][PXL];
     L.load(static_cast<const T *>(a.src), u[0]);
@@ -288,36 +292,34 @@ __device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseAr
     L.store(static_cast<T *>(a.lam_out), lam, true);
 }
 
-constexpr int kAhead = 4;
-
-template <class T, int PXL, bool STORED> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_reverse_kernel(BurgersReverseArgs a)
+// REM: number of steps modulo kAhead of a pass over stored states, -1: the states are recomputed
+template <class T, int PXL, int REM> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_reverse_kernel(BurgersReverseArgs a)
 {
-    using L = Lane<T, PXL, false, false>;
+    const int halo = REM >= 0 ? a.halo : kLoopH, W = 64 * PXL, V = own_cells(PXL, halo);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * L::V - kLoopH;
-    if (w * L::V >= a.n) return;
-    if (x0 >= 1 && x0 + L::W - 1 <= a.n - 2) {
-        if (STORED) burgers_reverse_stored<T, PXL, false, kAhead>(a, w, lane);
+    const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * V - halo;
+    if (w * V >= a.n) return;
+    if (x0 >= 1 && x0 + W - 1 <= a.n - 2) {
+        if constexpr (REM >= 0) burgers_reverse_stored<T, PXL, false, REM>(a, w, lane);
         else burgers_reverse_recompute<T, PXL, false>(a, w, lane);
     } else {
-        if (STORED) burgers_reverse_stored<T, PXL, true, kAhead>(a, w, lane);
+        if constexpr (REM >= 0) burgers_reverse_stored<T, PXL, true, REM>(a, w, lane);
         else burgers_reverse_recompute<T, PXL, true>(a, w, lane);
     }
 }
 
 // Cells per lane: wide windows (224 own cells of 256 in fp64, 480 of 512 in fp32) recompute the least and
 // are taken where every SIMD of the chip gets one; shorter arrays are spread over more SIMDs in narrow
-// windows (96 of 128): 400 000 cells, 16 stored steps, fp64: narrow 11.8, wide 10.0 us; a checkpointed
+// windows (96 of 128): 400 000 cells, 16 stored forward steps, fp64: narrow 11.8, wide 10.0 us; a checkpointed
 // reverse pass of 10^6 cells 38 and 35 us, in fp32 30 and 29 us, of 4 10^6 cells in fp32 79 and 61 us.
 template <class T> static bool wide_windows(long n)
 {
-    using L = Lane<T, 32 / (int)sizeof(T), false, false>;
-    return n >= 1024L * L::V;
+    return n >= 1024L * own_cells(32 / (int)sizeof(T), kLoopH);
 }
 
-template <class T, int PXL> static dim3 loop_grid(long n)
+static dim3 loop_grid(int PXL, int halo, long n)
 {
-    const long windows = ceil_div(n, Lane<T, PXL, false, false>::V);
+    const long windows = ceil_div(n, own_cells(PXL, halo));
     return dim3((unsigned)ceil_div(windows, kLoopWaves));
 }
 
@@ -325,20 +327,31 @@ template <class T, bool SPREAD> static hipError_t forward_T(const BurgersForward
 {
     constexpr int WIDE = 32 / (int)sizeof(T), NARROW = 2;
     const dim3 block(64 * kLoopWaves);
-    if (wide_windows<T>(a.n)) hipLaunchKernelGGL((burgers_forward_kernel<T, WIDE, SPREAD>), (loop_grid<T, WIDE>(a.n)), block, 0, stream, a);
-    else hipLaunchKernelGGL((burgers_forward_kernel<T, NARROW, SPREAD>), (loop_grid<T, NARROW>(a.n)), block, 0, stream, a);
+    if (wide_windows<T>(a.n)) hipLaunchKernelGGL((burgers_forward_kernel<T, WIDE, SPREAD>), loop_grid(WIDE, kLoopH, a.n), block, 0, stream, a);
+    else hipLaunchKernelGGL((burgers_forward_kernel<T, NARROW, SPREAD>), loop_grid(NARROW, kLoopH, a.n), block, 0, stream, a);
     return hipGetLastError();
 }
 
-template <class T, bool STORED> static hipError_t reverse_T(const BurgersReverseArgs &a, hipStream_t stream)
+template <class T, int REM> static hipError_t reverse_T(const BurgersReverseArgs &a, hipStream_t stream)
 {
     constexpr int WIDE = 32 / (int)sizeof(T), NARROW = 2;
     const dim3 block(64 * kLoopWaves);
     if (wide_windows<T>(a.n))
-        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, STORED>), (loop_grid<T, WIDE>(a.n)), block, 0, stream, a);
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, REM>), loop_grid(WIDE, REM >= 0 ? a.halo : kLoopH, a.n), block, 0, stream, a);
     else
-        hipLaunchKernelGGL((burgers_reverse_kernel<T, NARROW, STORED>), (loop_grid<T, NARROW>(a.n)), block, 0, stream, a);
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, NARROW, REM>), loop_grid(NARROW, REM >= 0 ? a.halo : kLoopH, a.n), block, 0, stream, a);
     return hipGetLastError();
+}
+
+template <class T> static hipError_t reverse_stored_T(const BurgersReverseArgs &a, hipStream_t stream)
+{
+    static_assert(kAhead == 4, "a case per remainder");
+    switch (a.m % kAhead) {
+    case 0: return reverse_T<T, 0>(a, stream);
+    case 1: return reverse_T<T, 1>(a, stream);
+    case 2: return reverse_T<T, 2>(a, stream);
+    default: return reverse_T<T, 3>(a, stream);
+    }
 }
 
 namespace {
@@ -357,9 +370,13 @@ struct LoopOps {
     }
     int reverse(const char *src, const char *rows, int first, int every, int m, const char *lam_in, char *lam_out) const
     {
-        const BurgersReverseArgs a{src, rows, lam_in, lam_out, n, C, D, m, first, every};
-        if (every == 1) return is_f64 ? reverse_T<double, true>(a, stream) : reverse_T<float, true>(a, stream);
-        return is_f64 ? reverse_T<double, false>(a, stream) : reverse_T<float, false>(a, stream);
+        // Nothing to keep between steps: the single-step kernel computes no cell twice.  It moves one cell per lane
+        // where an array is not 16-byte aligned, which costs more (16 10^6 cells fp64 80 us, the window 63).
+        const uintptr_t at = reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(lam_in) | reinterpret_cast<uintptr_t>(lam_out);
+        if (m == 1 && at % 16 == 0) return launch_adjoint_burgers1d(is_f64, n, C, D, src, lam_in, lam_out, 1, stream);
+        const BurgersReverseArgs a{src, rows, lam_in, lam_out, n, C, D, m, first, every, m <= kShortSteps ? kShortH : kLoopH};
+        if (every == 1) return is_f64 ? reverse_stored_T<double>(a, stream) : reverse_stored_T<float>(a, stream);
+        return is_f64 ? reverse_T<double, -1>(a, stream) : reverse_T<float, -1>(a, stream);
     }
     int reverse_first(const char *u, const char *lam_in, char *lam_out) const
     {
