@@ -429,7 +429,10 @@ static hipError_t launch_adj2d_tile(const Wave2dArgs &a, hipStream_t stream)
     // Streaming accesses for u_bar and u_prev_bar, except where both are read and written in ragged rows and the four
     // arrays exceed the 256 MB of the last-level cache: there most tile rows end inside a cache line,
     // the line is streamed out before the neighbouring tile touches it, and with two such arrays regular
-    // accesses are faster (fp64 4099^2 165 -> 148 us, 6001^2 385 -> 333, 8191^2 713 -> 594; fp32 6001^2 185 -> 167).
+    // accesses are faster.  Three sets of arrays in turn, streaming / regular: fp64 2893 x 2895 (just below the
+    // line) 82 / 80 us, 2897^2 (just above) 80 / 79, 4093 x 4095 170 / 151, 6001^2 385 / 341; fp32 2897^2 34 / 40, 4093 x 4095
+    // (just below) 85 / 79, 4097^2 (just above) 80 / 78, 6001^2 188 / 170.  One set over and over, which the cache then holds
+    // in part, moves the line by up to a factor of two either way.
     // With one such array, with aligned rows or in the cache they are up to 15 % slower.
     const bool regular = RAGGED && 4 * sizeof(T) * (size_t)a.nx * a.ny >= ((size_t)256 << 20);
     if (!a.u_prev_bar) {
@@ -569,7 +572,7 @@ static hipError_t launch_adj2d_cfg(Wave2dArgs a, const LaunchOptions &opt, hipSt
 //
 // RAGGED: nx or an array is not aligned to whole 16-byte vectors.  The tile form moves 16 bytes per lane all
 // the same (ld_cells_off), where one cell per lane was 10-20 % (fp64) and 20-40 % (fp32) slower: 2050 x 4099
-// adjoint fp64 58 -> 52 us, with u_prev_bar 90 -> 76, fp32 29 -> 22, primal 45 -> 41 and 31 -> 22 us.  The strip
+// adjoint fp64 45 -> 40 us, with u_prev_bar 84 -> 57, fp32 29 -> 21, primal 47 -> 41 and 31 -> 21 us (the same arrays each call).  The strip
 // march, whose lanes all take the same path, takes one cell per lane there.
 template <class T, bool RAGGED>
 static hipError_t launch_adj2d(const Wave2dArgs &a, const LaunchOptions &opt, hipStream_t stream)
