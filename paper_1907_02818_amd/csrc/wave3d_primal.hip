@@ -208,11 +208,8 @@ static hipError_t launch_primal_T(const March3dArgs &a, const LaunchOptions &opt
 {
     long v = opt.variant;
     if (v == 0) {
-        v = sizeof(T) == 8 ? 3 : 8;              // measured best per dtype
-        const int wide = wide_tile_for_unaligned_rows(a.nx, sizeof(T), R, sizeof(T) == 4 && R == 1);
-        if (R == 1 && wide == 512) v = 11;
-        else if (R == 1 && wide == 256) v = 10;
-        else if (R > 1 && wide) v = 5;
+        const auto at = [](const void *p) { return reinterpret_cast<uintptr_t>(p); };
+        v = primal_shape(sizeof(T), R, a.nx, at(a.in0) | at(a.in1) | at(a.in2) | at(a.out0));
     }
     if constexpr (R == 2 || R == 3) {            // the default shapes only
         if constexpr (sizeof(T) == 8) {
@@ -235,7 +232,7 @@ static hipError_t launch_primal_T(const March3dArgs &a, const LaunchOptions &opt
         case 10:                                 // radius 1: 256 x 16 tile (see wide_tile_for_unaligned_rows)
             if constexpr (R == 1) return launch_primal_cfg<T, R, 128, 4, 4, 2>(a, opt, stream);
             else return launch_primal_cfg<T, R, 64, 8, 4, 1>(a, opt, stream);
-        case 11:                                 // radius 1, fp32: 512 x 16 tile, 16 bytes per lane (500^3: 398 -> 389 us)
+        case 11:                                 // radius 1, fp32: 512 x 16 tile, 16 bytes per lane
             if constexpr (R == 1 && sizeof(T) == 4) return launch_primal_cfg<T, R, 128, 4, 4, 4>(a, opt, stream);
             else return launch_primal_cfg<T, R, 32, 16, 2, 2>(a, opt, stream);
         }
