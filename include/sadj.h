@@ -159,8 +159,8 @@ sadj_status sadj_adjoint_wave3d_steps(sadj_dtype dtype, int radius, long nx, lon
  * the others (NULL -> SADJ_ERR_NULL), whose contents on entry are ignored and on exit undefined,
  * as are those of lam[(nsteps+2)%3].  Step 0 accumulates into lam2 and runs alone; from then on
  * steps are fused, three per pass or, on small grids, two, and the last few launches are chosen
- * such that the results land in the documented buffers (sadj_describe_wave3d_sweep shows the
- * choice for two steps per pass).  Fused passes exist for radius 1 where nx is a multiple of 16 bytes' worth
+ * such that the results land in the documented buffers (sadj_describe_wave3d_sweep_launches shows
+ * them).  Fused passes exist for radius 1 where nx is a multiple of 16 bytes' worth
  * of elements and all five arrays are 16-byte aligned; otherwise, with nsteps < 3, or with
  * option "wave3d.fuse" 1, the call is sadj_adjoint_wave3d_steps and `work` is not touched.
  * Fused and single steps add the same terms in a different order: results agree to rounding,
@@ -170,13 +170,21 @@ sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long n
                                             long nsteps, const void *c,
                                             void *lam0, void *lam1, void *lam2, void *work, void *stream);
 
-/* Diagnostic (host only, no device access): the launches of sadj_adjoint_wave3d_steps_fused
- * after step 0 when steps can be fused and a pass takes two of them.  Buffers are numbered 0..2 =
- * lam0..lam2, 3 = work.
- * *body_pairs fused pairs alternate (a, b) = (1, 2) -> results in (0, 3) -> results in (1, 2)
- * ...; then *tail_len launches follow, five ints each in `tail` (room for 12 launches):
- * fused (1 or 0), a, b, and the output buffers (fused: a'', b''; single: the buffer that
- * receives -a m, then -1).  *body_pairs = -1: single steps over lam0..lam2 only (nsteps < 3).
+/* Diagnostic (host only, no device access beyond reading the CU count): the launches that
+ * sadj_adjoint_wave3d_steps_fused makes after step 0 on a grid of this size with 16-byte aligned arrays under
+ * the options in force.  Buffers are numbered 0..2 = lam0..lam2, 3 = work.
+ * *body passes of *body_steps steps (2 or 3) alternate (a, b) = (1, 2) -> results in (0, 3) ->
+ * results in (1, 2) ...; then *tail_len launches follow, five ints each in `tail` (room for 12 launches):
+ * the number of steps, a, b, and the output buffers (several steps: lam^{k+1-steps}, lam^{k-steps};
+ * one step: the buffer that receives -a m, then -1).  *body = -1: single steps over lam0..lam2 only.
+ * Errors as sadj_adjoint_wave3d_steps_fused.
+ */
+sadj_status sadj_describe_wave3d_sweep_launches(sadj_dtype dtype, int radius, long nx, long ny, long nz, long nsteps,
+                                                long *body, int *body_steps, int *tail_len, int *tail);
+
+/* Diagnostic (host only, no device access): the same for any grid whose passes take two steps.
+ * *body_pairs passes, then *tail_len launches whose first int is 1 for a pass of two steps and 0 for a
+ * single step.  *body_pairs = -1: single steps over lam0..lam2 only (nsteps < 3).
  */
 sadj_status sadj_describe_wave3d_sweep(long nsteps, long *body_pairs, int *tail_len, int *tail);
 

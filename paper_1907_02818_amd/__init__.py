@@ -22,7 +22,7 @@ __all__ = [
     "sadj_adjoint_wave3d_atomic_scatter", "sadj_describe_wave3d_plan", "sadj_check_array",
     "sadj_stream_probe", "sadj_primal_burgers1d_ckpt", "sadj_adjoint_burgers1d_ckpt",
     "sadj_adjoint_burgers1d_ckpt_static", "sadj_static_scratch_bytes",
-    "sadj_adjoint_wave3d_steps_fused", "sadj_describe_wave3d_sweep",
+    "sadj_adjoint_wave3d_steps_fused", "sadj_describe_wave3d_sweep", "sadj_describe_wave3d_sweep_launches",
 ]
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -88,6 +88,8 @@ def load() -> ctypes.CDLL:
     lib.sadj_adjoint_burgers1d_ckpt_static.argtypes = [I, L, L, L, D, D, P, P, P, P]
     lib.sadj_adjoint_wave3d_steps_fused.argtypes = [I, I, L, L, L, L, P, P, P, P, P, P]
     lib.sadj_describe_wave3d_sweep.argtypes = [L, ctypes.POINTER(L), ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
+    lib.sadj_describe_wave3d_sweep_launches.argtypes = [I, I, L, L, L, L, ctypes.POINTER(L), ctypes.POINTER(ctypes.c_int),
+                                                        ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
     lib.sadj_static_scratch_bytes.argtypes = []
     lib.sadj_static_scratch_bytes.restype = ctypes.c_size_t
     for name in ("sadj_set_option", "sadj_get_option", "sadj_primal_wave1d", "sadj_adjoint_wave1d",
@@ -98,7 +100,7 @@ def load() -> ctypes.CDLL:
                  "sadj_primal_burgers1d_steps", "sadj_adjoint_burgers1d_steps", "sadj_check_array",
                  "sadj_stream_probe", "sadj_primal_burgers1d_ckpt", "sadj_adjoint_burgers1d_ckpt",
                  "sadj_adjoint_burgers1d_ckpt_static", "sadj_adjoint_wave3d_steps_fused",
-                 "sadj_describe_wave3d_sweep"):
+                 "sadj_describe_wave3d_sweep", "sadj_describe_wave3d_sweep_launches"):
         getattr(lib, name).restype = I
     _lib = lib
     return lib
@@ -249,8 +251,18 @@ def sadj_adjoint_wave3d_steps_fused(radius: int, nsteps: int, c, lam0, lam1, lam
     _check(load().sadj_adjoint_wave3d_steps_fused(code, int(radius), nx, ny, nz, int(nsteps), *p, s))
 
 
+def sadj_describe_wave3d_sweep_launches(dtype_code: int, radius: int, nx: int, ny: int, nz: int, nsteps: int):
+    """(body, body_steps, [(steps, a, b, o0, o1), ...]) of the launches after step 0 on this grid; body = -1:
+    single steps over the caller's three buffers only."""
+    body, steps, n = ctypes.c_long(0), ctypes.c_int(0), ctypes.c_int(0)
+    tail = (ctypes.c_int * 60)()
+    _check(load().sadj_describe_wave3d_sweep_launches(dtype_code, int(radius), nx, ny, nz, int(nsteps), ctypes.byref(body),
+                                                      ctypes.byref(steps), ctypes.byref(n), tail))
+    return body.value, steps.value, [tuple(tail[5 * i:5 * i + 5]) for i in range(n.value)]
+
+
 def sadj_describe_wave3d_sweep(nsteps: int):
-    """(body_pairs, [(pair, a, b, o0, o1), ...]) of the launches after step 0; body_pairs = -1: single
+    """For a grid whose passes take two steps: (body_pairs, [(pair, a, b, o0, o1), ...]) of the launches after step 0; body_pairs = -1: single
     steps over the caller's three buffers only."""
     body = ctypes.c_long(0)
     n = ctypes.c_int(0)

@@ -2,6 +2,7 @@
 // contract of every entry point.
 #include "../../include/sadj.h"
 #include "launch.hpp"
+#include "wave_sweep_plan.hpp"
 
 #include <atomic>
 #include <cstdint>
@@ -168,82 +169,6 @@ sadj_status burgers_ckpt_reverse(sadj_dtype dtype, long n, long nsteps, long eve
         if (sadj_status rs = burgers_reverse_steps(dtype, n, C, D, t1 - t0, applied, lam, s, st); rs != SADJ_OK) return rs;
     }
     return SADJ_OK;
-}
-
-// Order of launches of a reverse sweep of wave steps that may use a fourth array.
-// Buffers 0..2 are the caller's lam arrays, 3 is the work array.  A state is the pair (A, B) of
-// buffers that hold lam^{k+1} and lam^k.  A single step updates B in place and assigns -A m to
-// a buffer F outside {A, B}: (A, B) -> (B, F).  A pass over two or three steps writes both results to the
-// two buffers outside {A, B}: (A, B) -> (F, G).  After the first step (which accumulates into
-// lam2 and is always single) the state is (1, 2); the sweep must end in (n%3, (n+1)%3).  The
-// body alternates passes of `most` steps (1,2) -> (0,3) -> (1,2) ...; the last few steps are chosen by
-// exhaustive dynamic programming so that the end state is met with as few launches as possible
-// (every launch moves five words per cell, however many steps it takes).
-struct WaveStepLaunch { int steps, a, b, o0, o1; };   // single: o0 = F;  pass: o0 <- lam^{k+1-steps}, o1 <- lam^{k-steps}
-
-constexpr int kTailMax = 12;
-
-struct WaveSweepPlan {
-    bool plain = true;                 // single steps rotating the caller's three buffers, work unused
-    long body = 0;                     // else: passes alternating (1,2) -> (0,3) -> (1,2) ..., then the tail
-    int tail_len = 0;
-    WaveStepLaunch tail[kTailMax];
-};
-
-inline int state_id(int a, int b) { return a * 4 + b; }
-
-// Launches for steps 1 .. nsteps-1 (step 0 is not part of the plan).
-WaveSweepPlan plan_wave_sweep(long nsteps, int most)
-{
-    WaveSweepPlan plan;
-    const long m = nsteps - 1;
-    if (m < 2) return plan;
-    const int ta = (int)(nsteps % 3), tb = (int)((nsteps + 1) % 3);
-    const int tmax = (int)(m < kTailMax ? m : kTailMax);
-    // best[t][state]: fewest launches on a way from state to the target in exactly t steps, none: kNone
-    constexpr int kNone = 1000;
-    int best[kTailMax + 1][16], choice[kTailMax + 1][16][3];
-    for (int t = 0; t <= tmax; ++t)
-        for (int s = 0; s < 16; ++s) best[t][s] = kNone;
-    best[0][state_id(ta, tb)] = 0;
-    for (int t = 1; t <= tmax; ++t)
-        for (int a = 0; a < 4; ++a)
-            for (int b = 0; b < 4; ++b) {
-                if (a == b) continue;
-                int fr[2], nf = 0;
-                for (int f = 0; f < 4; ++f)
-                    if (f != a && f != b) fr[nf++] = f;
-                int &bst = best[t][state_id(a, b)];
-                int *ch = choice[t][state_id(a, b)];
-                for (int i = 0; i < 2; ++i) {
-                    const int v = best[t - 1][state_id(b, fr[i])] + 1;
-                    if (v < bst) { bst = v; ch[0] = 1; ch[1] = fr[i]; ch[2] = -1; }
-                    for (int k = 2; k <= most && k <= t; ++k) {
-                        const int w = best[t - k][state_id(fr[i], fr[1 - i])] + 1;
-                        if (w < bst) { bst = w; ch[0] = k; ch[1] = fr[i]; ch[2] = fr[1 - i]; }
-                    }
-                }
-            }
-    auto body_state = [](long passes, int &a, int &b) { if (passes % 2 == 0) { a = 1; b = 2; } else { a = 0; b = 3; } };
-    long total = -1;
-    int t = 0, a = 1, b = 2;
-    for (long q = m / most; q >= 0 && m - most * q <= tmax; --q) {
-        body_state(q, a, b);
-        const int launches = best[m - most * q][state_id(a, b)];
-        if (launches < kNone && (total < 0 || q + launches < total)) { total = q + launches; plan.body = q; }
-    }
-    if (total < 0) return plan;        // plain stays set: single steps over three buffers
-    plan.plain = false;
-    t = (int)(m - most * plan.body);
-    body_state(plan.body, a, b);
-    while (t > 0) {
-        const int *ch = choice[t][state_id(a, b)];
-        plan.tail[plan.tail_len++] = {ch[0], a, b, ch[1], ch[2]};
-        if (ch[0] == 1) { a = b; b = ch[1]; }
-        else            { a = ch[1]; b = ch[2]; }
-        t -= ch[0];
-    }
-    return plan;
 }
 
 // Scratch memory of the entry point that must not allocate: a fixed array in device memory,
@@ -586,6 +511,21 @@ sadj_status sadj_adjoint_wave3d_steps(sadj_dtype dtype, int radius, long nx, lon
     return wave_steps_plain(dtype == SADJ_F64, radius, nx, ny, nz, nsteps, c, lam, opt, static_cast<hipStream_t>(stream));
 }
 
+// How the sweep with a fourth array runs: passes of `most` steps, or single steps over three buffers (plain).
+// whole_vectors: nx and every array allow 16-byte accesses.
+struct FusedSweep {
+    int most = 0;
+    sadj::WaveSweepPlan plan;
+};
+static FusedSweep fused_sweep(int f64, int radius, long nx, long ny, long nz, long nsteps, bool whole_vectors, const sadj::LaunchOptions &opt)
+{
+    FusedSweep s;
+    if (radius != 1 || nsteps < 3 || !whole_vectors || g_wave_fuse.load() != 0) return s;
+    s.most = sadj::adjoint_wave3d_steps_per_pass(f64, (int)nx, (int)ny, (int)nz, opt);
+    s.plan = sadj::plan_wave_sweep(nsteps, s.most);
+    return s;
+}
+
 // The same sweep with a fourth array to work in: two or three steps per pass where the kernels exist.
 sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long nx, long ny, long nz, long nsteps,
                                             const void *c, void *lam0, void *lam1, void *lam2, void *work, void *stream)
@@ -599,21 +539,20 @@ sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long n
     clear_stale_hip_error();
     sadj::LaunchOptions opt = current_options();
     opt.remainder = 0;
-    const bool fusable = radius == 1 && g_wave_fuse.load() == 0 &&
-                         sadj::adjoint_wave3d_pair_supported(f64, (int)nx, c, lam0, lam1, lam2, work);
-    const int most = sadj::adjoint_wave3d_steps_per_pass(f64, (int)nx, (int)ny, (int)nz, opt);
-    const WaveSweepPlan plan = fusable ? plan_wave_sweep(nsteps, most) : WaveSweepPlan{};
+    const bool whole_vectors = sadj::adjoint_wave3d_pair_supported(f64, (int)nx, c, lam0, lam1, lam2, work);
+    const FusedSweep sweep = fused_sweep(f64, radius, nx, ny, nz, nsteps, whole_vectors, opt);
+    const sadj::WaveSweepPlan &plan = sweep.plan;
     if (plan.plain) return wave_steps_plain(f64, radius, nx, ny, nz, nsteps, c, lam, opt, st);
     // step 0 accumulates into lam2, which may hold the objective's own contribution
     if (sadj_status s = wave_steps_plain(f64, radius, nx, ny, nz, 1, c, lam, opt, st); s != SADJ_OK) return s;
-    auto run = [&](const WaveStepLaunch &l) {
+    auto run = [&](const sadj::WaveStepLaunch &l) {
         if (l.steps == 1)
             return sadj::launch_adjoint_wave3d(f64, radius, (int)nx, (int)ny, (int)nz, c, buf[l.a], buf[l.b], buf[l.o0], 1, opt, st);
         const auto launch = l.steps == 2 ? sadj::launch_adjoint_wave3d_pair : sadj::launch_adjoint_wave3d_triple;
         return launch(f64, (int)nx, (int)ny, (int)nz, c, buf[l.a], buf[l.b], buf[l.o0], buf[l.o1], opt, st);
     };
     for (long i = 0; i < plan.body; ++i) {
-        const WaveStepLaunch l = i % 2 == 0 ? WaveStepLaunch{most, 1, 2, 0, 3} : WaveStepLaunch{most, 0, 3, 1, 2};
+        const sadj::WaveStepLaunch l = i % 2 == 0 ? sadj::WaveStepLaunch{sweep.most, 1, 2, 0, 3} : sadj::WaveStepLaunch{sweep.most, 0, 3, 1, 2};
         if (hipError_t e = run(l); e != hipSuccess) return from_hip(e);
     }
     for (int i = 0; i < plan.tail_len; ++i)
@@ -621,16 +560,39 @@ sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long n
     return SADJ_OK;
 }
 
-// Diagnostic: the launches sadj_adjoint_wave3d_steps_fused makes after step 0 where its passes take two steps.
+// Diagnostic: the launches of the call above.
+sadj_status sadj_describe_wave3d_sweep_launches(sadj_dtype dtype, int radius, long nx, long ny, long nz, long nsteps, long *body,
+                                                int *body_steps, int *tail_len, int *tail /* 5 ints per launch, 12 launches */)
+{
+    if (radius < 1 || radius > 4 || !dtype_ok(dtype)) return SADJ_ERR_UNSUPPORTED;
+    if (!body || !body_steps || !tail_len || !tail) return SADJ_ERR_NULL;
+    if (nsteps < 0) return SADJ_ERR_SIZE;
+    if (sadj_status s = check_extents(radius, nx, ny, nz, 3); s != SADJ_OK) return s;
+    const int f64 = dtype == SADJ_F64;
+    const bool whole_vectors = sadj::adjoint_wave3d_pair_supported(f64, (int)nx, nullptr, nullptr, nullptr, nullptr, nullptr);
+    const FusedSweep sweep = fused_sweep(f64, radius, nx, ny, nz, nsteps, whole_vectors, current_options());
+    (void)hipGetLastError();       // a machine without a GPU leaves an error code behind; it is not ours to keep
+    *body = sweep.plan.plain ? -1 : sweep.plan.body;
+    *body_steps = sweep.plan.plain ? 1 : sweep.most;
+    *tail_len = sweep.plan.tail_len;
+    for (int i = 0; i < sweep.plan.tail_len; ++i) {
+        const sadj::WaveStepLaunch &l = sweep.plan.tail[i];
+        const int v[5] = {l.steps, l.a, l.b, l.o0, l.o1};
+        for (int k = 0; k < 5; ++k) tail[5 * i + k] = v[k];
+    }
+    return SADJ_OK;
+}
+
+// Diagnostic: the same for a grid where a pass takes two steps.
 sadj_status sadj_describe_wave3d_sweep(long nsteps, long *body_pairs, int *tail_len, int *tail /* 5 ints per launch, 12 launches */)
 {
     if (!body_pairs || !tail_len || !tail) return SADJ_ERR_NULL;
     if (nsteps < 0) return SADJ_ERR_SIZE;
-    const WaveSweepPlan plan = plan_wave_sweep(nsteps, 2);
+    const sadj::WaveSweepPlan plan = sadj::plan_wave_sweep(nsteps, 2);
     *body_pairs = plan.plain ? -1 : plan.body;
     *tail_len = plan.tail_len;
     for (int i = 0; i < plan.tail_len; ++i) {
-        const WaveStepLaunch &l = plan.tail[i];
+        const sadj::WaveStepLaunch &l = plan.tail[i];
         const int v[5] = {l.steps == 2, l.a, l.b, l.o0, l.o1};
         for (int k = 0; k < 5; ++k) tail[5 * i + k] = v[k];
     }
