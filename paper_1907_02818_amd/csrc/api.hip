@@ -517,11 +517,11 @@ struct FusedSweep {
     int most = 0;
     sadj::WaveSweepPlan plan;
 };
-static FusedSweep fused_sweep(int f64, int radius, long nx, long ny, long nz, long nsteps, bool whole_vectors, const sadj::LaunchOptions &opt)
+static FusedSweep fused_sweep(int f64, int radius, long nx, long ny, long nz, long nsteps, bool whole_vectors)
 {
     FusedSweep s;
     if (radius != 1 || nsteps < 3 || !whole_vectors || g_wave_fuse.load() != 0) return s;
-    s.most = sadj::adjoint_wave3d_steps_per_pass(f64, (int)nx, (int)ny, (int)nz, opt);
+    s.most = sadj::adjoint_wave3d_steps_per_pass(f64, (int)nx, (int)ny, (int)nz);
     s.plan = sadj::plan_wave_sweep(nsteps, s.most);
     return s;
 }
@@ -540,7 +540,7 @@ sadj_status sadj_adjoint_wave3d_steps_fused(sadj_dtype dtype, int radius, long n
     sadj::LaunchOptions opt = current_options();
     opt.remainder = 0;
     const bool whole_vectors = sadj::adjoint_wave3d_pair_supported(f64, (int)nx, c, lam0, lam1, lam2, work);
-    const FusedSweep sweep = fused_sweep(f64, radius, nx, ny, nz, nsteps, whole_vectors, opt);
+    const FusedSweep sweep = fused_sweep(f64, radius, nx, ny, nz, nsteps, whole_vectors);
     const sadj::WaveSweepPlan &plan = sweep.plan;
     if (plan.plain) return wave_steps_plain(f64, radius, nx, ny, nz, nsteps, c, lam, opt, st);
     // step 0 accumulates into lam2, which may hold the objective's own contribution
@@ -570,7 +570,7 @@ sadj_status sadj_describe_wave3d_sweep_launches(sadj_dtype dtype, int radius, lo
     if (sadj_status s = check_extents(radius, nx, ny, nz, 3); s != SADJ_OK) return s;
     const int f64 = dtype == SADJ_F64;
     const bool whole_vectors = sadj::adjoint_wave3d_pair_supported(f64, (int)nx, nullptr, nullptr, nullptr, nullptr, nullptr);
-    const FusedSweep sweep = fused_sweep(f64, radius, nx, ny, nz, nsteps, whole_vectors, current_options());
+    const FusedSweep sweep = fused_sweep(f64, radius, nx, ny, nz, nsteps, whole_vectors);
     (void)hipGetLastError();       // a machine without a GPU leaves an error code behind; it is not ours to keep
     *body = sweep.plan.plain ? -1 : sweep.plan.body;
     *body_steps = sweep.plan.plain ? 1 : sweep.most;

@@ -43,9 +43,9 @@ hipError_t launch_adjoint_wave3d_pair(int is_f64, int nx, int ny, int nz, const 
 hipError_t launch_adjoint_wave3d_triple(int is_f64, int nx, int ny, int nz, const void *c, const void *a, const void *b,
                                         void *out_a, void *out_b, const LaunchOptions &opt, hipStream_t stream);
 // How many steps (2 or 3) a pass of a long sweep takes on a grid of this size, and the modelled time of a pass of
-// two (planes marched in the default tiles, times 100).
-long adjoint_wave3d_pair_cost(int is_f64, int nx, int ny, int nz, const LaunchOptions &opt);
-int adjoint_wave3d_steps_per_pass(int is_f64, int nx, int ny, int nz, const LaunchOptions &opt);
+// two (planes marched in the default tiles, times 100), both without regard to options.
+long adjoint_wave3d_pair_cost(int is_f64, int nx, int ny, int nz);
+int adjoint_wave3d_steps_per_pass(int is_f64, int nx, int ny, int nz);
 hipError_t launch_primal_wave3d(int is_f64, int radius, int nx, int ny, int nz, const void *u,
                                 const void *u_prev, const void *c, void *r,
                                 const LaunchOptions &opt, hipStream_t stream);

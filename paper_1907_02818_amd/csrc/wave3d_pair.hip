@@ -382,9 +382,9 @@ static PairPlan plan_pair(int is_f64, int nx, int ny, int nz, const LaunchOption
     return p;
 }
 
-long adjoint_wave3d_pair_cost(int is_f64, int nx, int ny, int nz, const LaunchOptions &opt)
+long adjoint_wave3d_pair_cost(int is_f64, int nx, int ny, int nz)
 {
-    return plan_pair(is_f64, nx, ny, nz, opt).cost;
+    return plan_pair(is_f64, nx, ny, nz, LaunchOptions{}).cost;
 }
 
 template <class T, int PX>

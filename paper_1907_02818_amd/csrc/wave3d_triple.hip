@@ -390,12 +390,13 @@ static hipError_t launch_triple(TripleArgs a, const LaunchOptions &opt, hipStrea
 // takes about 1.1 (fp64) or 1.2 (fp32) times as long.  Short marches on small grids therefore take two
 // steps per pass: 25 steps, two (in 64 x 32 tiles, fp32 128 x 32) / three per pass, fp64 33 x 40 x 72 71 / 83 us,
 // 128^3 309 / 265, 512^3 12.9 / 9.4 ms; fp32 128^3 192 / 221 us, 96 x 130 x 164 262 / 279, 160 x 180 x 200 451 / 406,
-// 512^3 6.6 / 5.0 ms.
-int adjoint_wave3d_steps_per_pass(int is_f64, int nx, int ny, int nz, const LaunchOptions &opt)
+// 512^3 6.6 / 5.0 ms.  Two and three steps group the sums differently, so grid and type alone decide: options that
+// cut the march another way must not change a bit.
+int adjoint_wave3d_steps_per_pass(int is_f64, int nx, int ny, int nz)
 {
     TileMap three;
-    plan_march(three, nx, ny, nz, is_f64 ? 64 : 128, 32, 4, opt);
-    return 20 * march_planes(three, 8) * (is_f64 ? 11 : 12) < 3 * adjoint_wave3d_pair_cost(is_f64, nx, ny, nz, opt) ? 3 : 2;
+    plan_march(three, nx, ny, nz, is_f64 ? 64 : 128, 32, 4, LaunchOptions{});
+    return 20 * march_planes(three, 8) * (is_f64 ? 11 : 12) < 3 * adjoint_wave3d_pair_cost(is_f64, nx, ny, nz) ? 3 : 2;
 }
 
 hipError_t launch_adjoint_wave3d_triple(int is_f64, int nx, int ny, int nz, const void *c, const void *a, const void *b,

@@ -80,3 +80,20 @@ def test_the_diagnostic_shows_where_single_steps_run():
     for bad in ((1, 5, 64, 64, 64, 4), (1, 1, 2, 64, 64, 4), (1, 1, 64, 64, 64, -1), (2, 1, 64, 64, 64, 4)):
         with pytest.raises(lib.SadjError):
             lib.sadj_describe_wave3d_sweep_launches(*bad)
+
+
+def test_options_that_move_work_do_not_change_the_steps_of_a_pass():
+    """Two and three steps per pass round differently, and the header promises that these options change no bit."""
+    import paper_1907_02818_amd as lib
+    grids = [(1, s) for s in ((207, 35, 136), (136, 35, 208), (81, 68, 260), (96, 100, 128), (64, 64, 64), (150, 150, 150), (512, 512, 512))]
+    grids += [(0, s) for s in ((96, 130, 164), (197, 68, 260), (160, 180, 200), (64, 64, 64), (512, 512, 512))]
+    ask = lambda d, s: lib.sadj_describe_wave3d_sweep_launches(d, 1, s[2], s[1], s[0], 25)   # noqa: E731
+    want = [ask(d, s) for d, s in grids]
+    for name, values in (("wave3d.zchunk", (1, 5, 9, 100)), ("wave3d.split", (1,)), ("wave3d.ldspad", (-1, 4096)), ("wave3d.xcdmap", (2, 3)),
+                         ("wave3d.band", (1, 8))):
+        for v in values:
+            lib.set_option(name, v)
+            try:
+                assert [ask(d, s) for d, s in grids] == want, (name, v)
+            finally:
+                lib.set_option(name, 0)
