@@ -213,12 +213,14 @@ __global__ __launch_bounds__(BX *BY) void star3d_kernel(StarArgs a)
 // small tiles, fp64 40^3 14.2 / 8.9 us, 101 x 99 x 96 20.0 / 16.2, 128^3 23.0 / 21.6; fp32 40^3 15.1 / 8.8, 128^3 17.6 / 15.7;
 // fp64 150^3 would be 34.0 / 34.7, 60 x 200 x 180 24.4 / 24.8, fp32 primal 150^3 21.3 / 22.6.
 // Radius 1 and 2 gain nothing up to 64^3 and lose up to 40 % from there on.
-static bool star_small_tiles(TileMap &small, const TileMap &big, int percent, int nx, int ny, int nz, const LaunchOptions &opt)
+// The two shapes contract their sums into fused multiply-adds differently, so grid and type alone decide: options that
+// move work between workgroups must not change a bit.  big: the plan of the default tiles without options.
+static bool star_small_tiles(const TileMap &big, int percent, int nx, int ny, int nz)
 {
     constexpr int R = 4;
-    if (opt.variant != 0 || opt.zchunk != 0 || opt.lds_pad != 0) return false;
     if (big.tiles_a != 0 || big.zchunk >= 4 * R || big.zchunk >= nz) return false;
-    plan_march(small, nx, ny, nz, 32, 16, R, opt, 2);
+    TileMap small;
+    plan_march(small, nx, ny, nz, 32, 16, R, LaunchOptions{}, 2);
     return percent * march_planes(small, 2 * R, 2) < 100 * march_planes(big, 2 * R);
 }
 
@@ -228,10 +230,12 @@ static hipError_t launch_star_shape(StarArgs a, const LaunchOptions &opt, hipStr
     using G = Tile3d<T, R, BX, BY, PY, PX>;
     plan_march(a.map, a.nx, a.ny, a.nz, G::TX, G::TY, R, opt);
     if constexpr (R == 4) {
-        TileMap small;
-        if (star_small_tiles(small, a.map, PX * PY == 8 ? 60 : G::TX == 128 ? 79 : 74, a.nx, a.ny, a.nz, opt)) {
-            a.map = small;
-            hipLaunchKernelGGL((star3d_kernel<T, R, 32, 16, 1, 1, ADJ>), dim3(a.map.total_blocks), dim3(32 * 16), 0, stream, a);
+        TileMap big = a.map;
+        if (opt.zchunk != 0 || opt.split != 0) plan_march(big, a.nx, a.ny, a.nz, G::TX, G::TY, R, LaunchOptions{});
+        if (opt.variant == 0 && star_small_tiles(big, PX * PY == 8 ? 60 : G::TX == 128 ? 79 : 74, a.nx, a.ny, a.nz)) {
+            plan_march(a.map, a.nx, a.ny, a.nz, 32, 16, R, opt, 2);
+            const unsigned small_pad = opt.lds_pad > 0 ? (unsigned)opt.lds_pad : 0;
+            hipLaunchKernelGGL((star3d_kernel<T, R, 32, 16, 1, 1, ADJ>), dim3(a.map.total_blocks), dim3(32 * 16), small_pad, stream, a);
             return hipGetLastError();
         }
     }

@@ -11,6 +11,15 @@ from parity import to_gpu, to_host
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture
+def sadj_options():
+    """Leaves the options as they are by default, whatever happens in between."""
+    import paper_1907_02818_amd as lib
+    yield
+    for name in ("zchunk", "split", "xcdmap", "band", "ldspad"):
+        lib.set_option("wave3d." + name, 0)
+
+
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("shape", [(9, 9, 9), (24, 16, 32), (25, 17, 33), (40, 25, 41), (64, 33, 64), (70, 48, 97), (101, 34, 96)])
 def test_small_tiles_are_exact_on_dyadic_data(shape, dtype):
@@ -28,3 +37,23 @@ def test_small_tiles_are_exact_on_dyadic_data(shape, dtype):
     sadj.sadj_primal_star3d(4, w, to_gpu(u.astype(dtype)), to_gpu(np.where(m, c, np.nan).astype(dtype)), r)
     assert np.array_equal(to_host(r).astype(np.float64)[m], oracle.star3d_primal(w, u, c, 4)[m])
     assert (to_host(r)[~m] == 7).all()
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("shape", [(9, 21, 40), (16, 35, 80), (63, 81, 96), (98, 34, 52), (40, 40, 41)])
+def test_options_that_move_work_change_no_bit(sadj_options, shape, dtype):
+    """wave3d.zchunk, split, xcdmap, band and ldspad only move work between workgroups."""
+    import torch
+    import paper_1907_02818_amd as sadj
+    w = list(inputs.uniform(2, "aux", (25,), -1, 1))
+    c, x, ub = (to_gpu(inputs.uniform(5, k, shape, -1, 1).astype(dtype)) for k in ("c", "r_bar", "u_bar"))
+    want = None
+    for name, value in [("wave3d.split", 0), ("wave3d.split", 1), ("wave3d.ldspad", -1), ("wave3d.ldspad", 2048), ("wave3d.xcdmap", 3),
+                        ("wave3d.band", 2), ("wave3d.zchunk", 1), ("wave3d.zchunk", 3), ("wave3d.zchunk", 50)]:
+        got = [ub.clone(), ub.clone()]
+        sadj.set_option(name, value)
+        sadj.sadj_adjoint_star3d(4, w, c, x, got[0])
+        sadj.sadj_primal_star3d(4, w, x, c, got[1])
+        sadj.set_option(name, 0)
+        want = want or got
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), (name, value)
