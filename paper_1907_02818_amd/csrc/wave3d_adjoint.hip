@@ -112,7 +112,7 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
     const T *__restrict__ rg = static_cast<const T *>(a.in1);
     T *__restrict__ ug = static_cast<T *>(a.out0);
     T *upg = static_cast<T *>(a.out1);              // UPREV 4: the array in2
-    const T *startg = UPREV >= 3 ? static_cast<const T *>(a.in2) : static_cast<const T *>(a.out0);
+    const T *startg = UPREV >= 3 ? static_cast<const T *>(a.in2) : ug;      // u_bar is written through ug, so it is read through it
 
     // owned cells x = x0 + tx*PX + e, y = y0 + ty*PY + p and halo slots (tile3d.hpp); c and r_bar are
     // used on I only, and not fetched at all where none of a vector's cells lies in I
