@@ -362,26 +362,39 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_kernel(March3dArgs a)
 
 static inline bool aligned_to(const void *p, size_t n) { return (reinterpret_cast<uintptr_t>(p) % n) == 0; }
 
+// PX cells per lane and memory instruction need whole vectors: nx a multiple of PX and every array aligned to the
+// vector size.
+template <class T> static bool whole_vectors(const March3dArgs &a, int PX)
+{
+    const size_t al = PX * sizeof(T);
+    return a.nx % PX == 0 && aligned_to(a.in0, al) && aligned_to(a.in1, al) && aligned_to(a.in2, al) && aligned_to(a.out0, al) &&
+           aligned_to(a.out1, al);
+}
+
 // Small grids.  Where the z-chunks of the default shapes are shorter than 4R planes the chip waits for one
 // plane-step after the other, and a 32 x 16 tile with one cell per thread, two workgroups per CU, has the
-// shorter steps: measured per plane 0.74-0.88 of the 64 x 32 fp64 tile's time and 0.58-0.65 of the 128 x 32
-// fp32 tile's (more arithmetic per cell at larger radii, hence the table), against more planes per
-// workgroup.  20 steps of a sweep, default / small tiles, fp64: radius 4 40^3 305 / 171 us, 101 x 99 x 97
+// shorter steps, against more planes per workgroup: measured per plane 0.70-0.88 of the time of the 64 x 32 fp64 tile,
+// 0.58-0.65 of the 128 x 32 fp32 tile with four cells per lane, and 0.66-1.0 of the 64 x 32 fp32 tile with one, which runs where
+// rows or arrays are not whole vectors (more arithmetic per cell at larger radii, hence the table).  20 steps of a sweep,
+// default / small tiles, fp64: radius 4 40^3 305 / 171 us, 101 x 99 x 97
 // 526 / 382, 128^3 478 / 440, 150^3 732 / 750; radius 1 40^3 108 / 86, 80 x 96 x 112 146 / 192; fp32 radius 4 40^3
-// 289 / 139, 128^3 341 / 318, 150^3 518 / 533.  (Tiles of 32 x 8 and one workgroup per CU were slower from 80^3 on.)
+// 289 / 139, 128^3 341 / 318, 150^3 518 / 533.  One step, fp32, odd rows, 64 x 32 / small tiles: radius 1 73 x 174 x 61 6.1 / 7.2, radius 2
+// with u_prev_bar 117 x 161 x 49 10.5 / 13.0, radius 4 37 x 178 x 39 12.1 / 9.5.
+// (Tiles of 32 x 8 and one workgroup per CU were slower from 80^3 on.)
 constexpr int kSmallBX = 32, kSmallBY = 16, kSmallPerCu = 2;
 
-// Whether a grid takes them, and the plan if so; TX x TY: the default shape.
-static bool small_tiles(TileMap &small, bool is_f64, int radius, int nx, int ny, int nz, int TX, int TY, const LaunchOptions &opt)
+// Whether a grid takes them, and the plan if so; TX x TY: the default shape; whole: rows and arrays allow its vectors
+// (launch_cfg falls back to 64 x 32 tiles with one cell per lane otherwise).
+static bool small_tiles(TileMap &small, bool is_f64, int radius, int nx, int ny, int nz, int TX, int TY, bool whole, const LaunchOptions &opt)
 {
     if (opt.variant != 0 || opt.remainder != 0 || opt.zchunk != 0 || opt.lds_pad != 0) return false;
     if (wide_tile_for_unaligned_rows(nx, is_f64 ? 8 : 4, radius, !is_f64)) return false;
     TileMap big;
-    plan_march(big, nx, ny, nz, TX, TY, radius, opt);
+    plan_march(big, nx, ny, nz, whole ? TX : 64, whole ? TY : 32, radius, opt);
     if (big.tiles_a != 0 || big.zchunk >= 4 * radius || big.zchunk >= nz) return false;
     plan_march(small, nx, ny, nz, kSmallBX, kSmallBY, radius, opt, kSmallPerCu);
-    constexpr int percent[2][4] = {{65, 63, 58, 62}, {88, 79, 70, 74}};
-    return percent[is_f64][radius - 1] * march_planes(small, 2 * radius, kSmallPerCu) < 100 * march_planes(big, 2 * radius);
+    constexpr int percent[3][4] = {{65, 63, 58, 62}, {100, 77, 70, 70}, {88, 79, 70, 74}};
+    return percent[is_f64 ? 2 : whole ? 0 : 1][radius - 1] * march_planes(small, 2 * radius, kSmallPerCu) < 100 * march_planes(big, 2 * radius);
 }
 
 template <class T, int R> static hipError_t launch_small(const March3dArgs &a, hipStream_t stream)
@@ -400,14 +413,7 @@ template <class T, int R, int BX, int BY, int PY, int PX, int D, bool NTU>
 static hipError_t launch_cfg(March3dArgs a, const LaunchOptions &opt, hipStream_t stream)
 {
     using G = Tile3d<T, R, BX, BY, PY, PX>;
-    if (PX > 1) {
-        // PX cells per lane and memory instruction need whole vectors: nx a multiple of
-        // PX and every array aligned to the vector size; otherwise use a PX = 1 shape
-        const size_t al = PX * sizeof(T);
-        const bool ok = a.nx % PX == 0 && aligned_to(a.in0, al) && aligned_to(a.in1, al) &&
-                        aligned_to(a.in2, al) && aligned_to(a.out0, al) && aligned_to(a.out1, al);
-        if (!ok) return launch_cfg<T, R, 64, 8, 4, 1, 1, true>(a, opt, stream);
-    }
+    if (PX > 1 && !whole_vectors<T>(a, PX)) return launch_cfg<T, R, 64, 8, 4, 1, 1, true>(a, opt, stream);
     plan_march(a.map, a.nx, a.ny, a.nz, G::TX, G::TY, R, opt);
     dim3 grid(a.map.total_blocks), block(G::NT);
     const unsigned pad = one_workgroup_per_cu_pad(sizeof(T) * 2 * G::PLANE, opt.lds_pad);
@@ -483,8 +489,9 @@ static hipError_t launch_T(const March3dArgs &a, const LaunchOptions &opt, hipSt
     const long v = choose_adjoint_shape(sizeof(T) == 8, R, a.nx, a.out1 && !a.out1_assign, opt);
     int TX, TY, PX;
     shape_extents(v, sizeof(T) == 8, R, TX, TY, PX);
+    const bool whole = whole_vectors<T>(a, PX);
     March3dArgs as = a;
-    if (small_tiles(as.map, sizeof(T) == 8, R, a.nx, a.ny, a.nz, TX, TY, opt)) return launch_small<T, R>(as, stream);
+    if (small_tiles(as.map, sizeof(T) == 8, R, a.nx, a.ny, a.nz, TX, TY, whole, opt)) return launch_small<T, R>(as, stream);
     if constexpr (R == 2 || R == 3) {            // the default shapes of the dtype only
         if constexpr (sizeof(T) == 8) {
             return v == 3 ? launch_cfg<T, R, 64, 8, 4, 1, 1, true>(a, opt, stream)
@@ -524,7 +531,7 @@ void describe_march_plan(int is_f64, int radius, int nx, int ny, int nz, int wit
     int TX, TY, PX;
     shape_extents(v, is_f64 != 0, radius, TX, TY, PX);
     TileMap m;
-    if (small_tiles(m, is_f64 != 0, radius, nx, ny, nz, TX, TY, opt)) {
+    if (small_tiles(m, is_f64 != 0, radius, nx, ny, nz, TX, TY, nx % PX == 0, opt)) {
         TX = kSmallBX;
         TY = kSmallBY;
     } else {
