@@ -260,13 +260,26 @@ __device__ __forceinline__ void adj3d_march(const March3dArgs &a, int tix, int t
 #pragma unroll
                 for (int p = 0; p < PY; ++p) {
                     const T *row = sb + (R + ty * PY + p) * LX + R + tx * PX + e;
-                    T xs[R], ys[R];
+                    // The same sum, x pairs before y pairs, with the LDS reads in two orders: the compiler schedules by it.  Pairs
+                    // of both axes read together: fp32 radius 4, one cell per lane, 200 x 200 x 201 with u_prev_bar 62 us
+                    // against 76, fp64 500^3 741 against 749; read axis after axis: fp64 with one cell per lane, radius 4,
+                    // 200 x 200 x 201 79 us against 81.
+                    if constexpr (sizeof(T) == 8 && PX == 1) {
+                        T s = mul_rounded(T(3.0 * star_w<R>(0)), qo[p][e]);
 #pragma unroll
-                    for (int k = 1; k <= R; ++k) {
-                        xs[k - 1] = add_rounded(row[-k], row[k]);
-                        ys[k - 1] = add_rounded(col[R + p - k], col[R + p + k]);
+                        for (int k = 1; k <= R; ++k) s = fma_t(T(star_w<R>(k)), add_rounded(row[-k], row[k]), s);
+#pragma unroll
+                        for (int k = 1; k <= R; ++k) s = fma_t(T(star_w<R>(k)), add_rounded(col[R + p - k], col[R + p + k]), s);
+                        acc[p][e][R] = add_rounded(acc[p][e][R], fma_t(T(2), ro[p][e], s));
+                    } else {
+                        T xs[R], ys[R];
+#pragma unroll
+                        for (int k = 1; k <= R; ++k) {
+                            xs[k - 1] = add_rounded(row[-k], row[k]);
+                            ys[k - 1] = add_rounded(col[R + p - k], col[R + p + k]);
+                        }
+                        acc[p][e][R] = centre_terms<T, R>(qo[p][e], ro[p][e], xs, ys, acc[p][e][R]);
                     }
-                    acc[p][e][R] = centre_terms<T, R>(qo[p][e], ro[p][e], xs, ys, acc[p][e][R]);
 #pragma unroll
                     for (int k = 1; k <= R; ++k) {
                         acc[p][e][R - k] = fma_t(T(star_w<R>(k)), qo[p][e], acc[p][e][R - k]);
