@@ -108,3 +108,27 @@ def test_large_ragged_arrays_with_u_prev_bar(sadj):
     # seven terms of magnitude below 2: rounding below 7 * 2 * 2^-53 each
     assert (u - wu).abs().max().item() <= 7 * 2 * 2.0 ** -52
     assert torch.equal(p, wp)
+
+
+def test_large_ragged_fp32_arrays_with_u_prev_bar(sadj):
+    """The same in fp32, where the four arrays exceed 256 MB from 4097 x 4097 cells on; reference in float64."""
+    import torch
+    ny, nx = 4097, 4099
+    g = torch.Generator(device="cuda").manual_seed(1)
+    rnd = lambda: torch.rand((ny, nx), generator=g, dtype=torch.float32, device="cuda") - 0.5   # noqa: E731
+    c, r, u, p = rnd(), rnd(), rnd(), rnd()
+    q = torch.zeros((ny, nx), dtype=torch.float64, device="cuda")
+    q[1:-1, 1:-1] = c[1:-1, 1:-1].double() * r[1:-1, 1:-1].double()
+    wu = u.double() - 4 * q
+    wu[:, 1:] += q[:, :-1]
+    wu[:, :-1] += q[:, 1:]
+    wu[1:] += q[:-1]
+    wu[:-1] += q[1:]
+    wu[1:-1, 1:-1] += 2 * r[1:-1, 1:-1].double()
+    wp = p.double()
+    wp[1:-1, 1:-1] -= r[1:-1, 1:-1].double()
+    sadj.sadj_adjoint_wave2d(c, r, u, p)
+    # as above, with the products rounded to fp32 first: eight terms of magnitude below 2, rounding below 2 * 2^-24 each; one
+    # subtraction of numbers below 1 in u_prev_bar
+    assert (u.double() - wu).abs().max().item() <= 8 * 2 * 2.0 ** -23
+    assert (p.double() - wp).abs().max().item() <= 2.0 ** -24

@@ -142,9 +142,10 @@ def test_burgers_forward_and_reverse_sweeps(sadj, n, nsteps, dtype):
 @pytest.mark.parametrize("n", [3, 17, 64, 239, 240, 241, 257, 495, 496, 497, 1000, 4099, 100003])
 @pytest.mark.parametrize("nsteps", [6, 11, 17])
 def test_fused_reverse_steps_equal_single_steps_bit_for_bit(sadj, n, nsteps, dtype):
-    """Runs of five assigned steps go through one kernel that keeps a window of cells in
+    """Runs of up to 15 assigned steps go through one kernel that keeps a window of cells in
     registers (option burgers1d.fuse = 0, the default); the step-by-step sweep is the reference.
-    Sizes around the window widths (240 / 496 finished cells per wave) and the clamped ends."""
+    Sizes around the window widths (96 or 112 finished cells per wave, in long arrays up to 240 / 496) and the
+    clamped ends."""
     import torch
     st = to_gpu(_burgers_states(n, nsteps, 3 * n + nsteps, dtype))
     lam0 = inputs.uniform(n, "r_bar", (n,), -1, 1).astype(dtype)
@@ -162,9 +163,9 @@ def test_fused_reverse_steps_equal_single_steps_bit_for_bit(sadj, n, nsteps, dty
     assert np.array_equal(out[0], out[1])
 
 
-def test_fused_reverse_steps_with_unaligned_rows_fall_back(sadj):
-    """Rows of an odd length start at addresses that are not 16-byte aligned: those steps run
-    one by one; the result is unchanged."""
+def test_fused_reverse_steps_with_unaligned_rows(sadj):
+    """Rows of an odd length start at addresses that are not 16-byte aligned: they share passes like others, and the
+    result is that of one launch per step, bit for bit."""
     import torch
     n, nsteps = 1001, 12
     st = to_gpu(_burgers_states(n, nsteps, 5, np.float64))

@@ -47,3 +47,27 @@ def test_middle_steps_equal_single_calls_bitwise(sadj, radius, shape, dtype):
                 assert np.isfinite(want).all()
                 assert np.array_equal(to_host(g[k]), want), (zchunk, nsteps, k)
     sadj.set_option("wave3d.zchunk", 0)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("radius,shape", [(1, (30, 36, 140)), (2, (40, 37, 132)), (2, (31, 70, 260)), (3, (45, 40, 136)), (3, (33, 71, 259)),
+                                          (4, (50, 44, 140)), (4, (40, 75, 264))])
+def test_middle_steps_of_long_marches(sadj, radius, shape, dtype):
+    """Chunks much longer than R + 2 planes, where the fp32 kernels run their phase without conditions on the plane, in
+    tiles inside the grid and at its edge; the same bits as single calls, and as any other cut."""
+    import torch
+    c = to_gpu(inputs.uniform(1, "c", shape, 0.01, 0.1).astype(dtype))
+    lams = [to_gpu(inputs.uniform(7, k, shape, -1, 1).astype(dtype)) for k in ("r_bar", "u_bar", "u_prev_bar")]
+    nsteps, want = 5, [x.clone() for x in lams]
+    for s in range(nsteps):
+        a, b, p = want[s % 3], want[(s + 1) % 3], want[(s + 2) % 3]
+        if s > 0:
+            p.zero_()
+        sadj.sadj_adjoint_wave3d(radius, c, a, b, p)
+    for zchunk in (0, 17, 1000):
+        sadj.set_option("wave3d.zchunk", zchunk)
+        g = [x.clone() for x in lams]
+        sadj.sadj_adjoint_wave3d_steps(radius, nsteps, c, *g)
+        sadj.set_option("wave3d.zchunk", 0)
+        for k in (nsteps % 3, (nsteps + 1) % 3):
+            assert torch.isfinite(want[k]).all() and torch.equal(g[k], want[k]), (zchunk, k)
