@@ -360,6 +360,28 @@ def main():
         o["note"] = ("fraction is against the step-by-step compulsory bytes (24 B/pt/step); the fused passes themselves move "
                      "(16 + 8*15)/15 = 9.1 B/pt/step plus the overlap of the windows")
 
+    def burgers_ckpt_leg(which):
+        # The Burgers time loop with every 16th of 64 states kept.  Forward: a pass reads one state and writes one
+        # (16 B/pt for 16 steps).  Reverse: a pass recomputes 8 steps from a state in memory and reverses them (reads the
+        # state and lam, writes lam: 24 B/pt for 8 steps).  Both are priced at one launch per step, forward 16 B/pt,
+        # reverse 16 B/pt for the 15 of 16 steps that are recomputed and 24 B/pt.
+        ks, every = 64, 16
+        rows = get("ckpt", lambda: torch.rand(ks // every + 1, nb, device=dev, dtype=torch.float64) - 0.5)
+        work = get("ckpt_work", lambda: torch.empty(every - 1, nb, device=dev, dtype=torch.float64))
+        if which == "burgers1d_f64_ckpt_forward_per_step":
+            o = add(which, lambda: sadj.sadj_primal_burgers1d_ckpt(0.1, 0.05, ks, every, rows, work, None), nb * ks, 16 * nb * ks,
+                    "f64", per=ks)
+            o["kernel_algorithmic_bytes"] = 16 * nb
+        else:
+            la, lb = torch.rand(nb, device=dev, dtype=torch.float64), torch.zeros(nb, device=dev, dtype=torch.float64)
+            o = add(which, lambda: sadj.sadj_adjoint_burgers1d_ckpt(0.1, 0.05, ks, every, rows, work, la, lb), nb * ks,
+                    24 * nb * ks + 16 * nb * (ks - ks // every), "f64", per=ks)
+            o["kernel_algorithmic_bytes"] = 24 * nb
+        if "traffic" in o:                       # the recorded counters are those of one pass
+            o["kernel_traffic"] = o.pop("traffic")
+        o["note"] = ("fraction is against the bytes of one launch per step; a pass takes 16 forward or 8 reverse steps in registers, moves "
+                     "kernel_algorithmic_bytes and is bound by the vector ALUs")
+
     # reverse sweep of a time loop of 7-point wave steps, 25 steps per call: one kernel per step, or step 0
     # alone and then passes of three steps (two on grids of about a million cells or fewer); both priced at the step-by-step bytes
     wave_ks = 25
@@ -422,6 +444,9 @@ def main():
     if args.all or args.only in ("burgers1d_f64_adjoint_steps_per_step", "burgers1d_f64_adjoint_steps_fused_per_step"):
         table["burgers1d_f64_adjoint_steps_per_step"] = burgers_steps_leg
         table["burgers1d_f64_adjoint_steps_fused_per_step"] = burgers_steps_leg
+    for name in ("burgers1d_f64_ckpt_forward_per_step", "burgers1d_f64_ckpt_adjoint_per_step"):
+        if args.all or args.only == name:
+            table[name] = lambda name=name: burgers_ckpt_leg(name)
     table["wave3d_r1_f64_adjoint_steps_per_step"] = wave_steps_leg
     table["wave3d_r1_f64_adjoint_steps_fused_per_step"] = wave_steps_fused_leg
     default_names += ["wave3d_r1_f64_adjoint_steps_per_step", "wave3d_r1_f64_adjoint_steps_fused_per_step"]

@@ -366,7 +366,8 @@ sadj_status sadj_describe_wave3d_plan(sadj_dtype dtype, int radius, long nx, lon
  *                    and the plane at least 8 tile rows.
  *   "wave3d.ldspad"  dynamic LDS bytes requested per workgroup of the 3-D marching kernels,
  *                    which limits how many workgroups share a CU: 0 (default) as much as
- *                    keeps it at one workgroup per CU, -1 none, n > 0 exactly n (<= 65536).
+ *                    keeps it at one workgroup per CU (none for the 32 x 16 and fp32 64 x 16 tiles that
+ *                    small grids take, which two share), -1 none, n > 0 exactly n (<= 65536).
  *   "wave3d.remainder" treatment of the boundary / remainder regions (Section 3.3.4) by
  *                    sadj_adjoint_wave3d:  0 (default) one dispatch, tiles that touch the
  *                    remainder run guarded statements, core tiles unguarded ones;

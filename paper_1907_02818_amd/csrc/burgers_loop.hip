@@ -14,7 +14,8 @@
 // memory, 8 + 16/m bytes instead of 24; a sweep of 16 steps of 10^7 cells 284 us.  Reverse from a
 // checkpoint: 24/m bytes, the m states are recomputed in registers and the vector ALUs are the bound
 // (43 instructions per four cells of a forward step, 103 of a reverse one); so is the forward sweep
-// that stores checkpoints only, 16 steps of 10^7 cells in 60 us.
+// that stores checkpoints only.  Counted over 2^24 cells: a reverse pass of 8 steps issues 8.5 10^7 instructions, which the
+// chip's 1024 SIMDs take 139 us for at 2.4 GHz, and runs 162 us; a forward pass of 16 steps 5.1 10^7, 83 us, and 101 us.
 #include "burgers.hpp"
 #include "burgers_plan.hpp"
 #include "launch.hpp"

@@ -49,7 +49,9 @@ struct Tile3d {
 // grid).  GUARD = false (core tiles: everything lies in I) folds all predicates to constants.
 template <int PX, int PY, int HS, bool GUARD> struct TileAddr {
     uint32_t dummy;
-    uint32_t own_off[PY];     // owned vector of row p (nx is a multiple of PX: inside or outside the grid as a whole)
+    // Owned vector of row p, and whether its first cell lies in the grid.  Where nx is a multiple of PX the others then do
+    // too; callers that take other rows (the ragged 2-D tiles) limit their accesses with cells_in_row.
+    uint32_t own_off[PY];
     bool own_grid[PY];
     bool own_I[PY][PX];
     uint32_t halo_off[HS];
@@ -198,9 +200,9 @@ static inline void plan_march(TileMap &m, int nx, int ny, int nz, int TX, int TY
     // Chunks of at least 4R planes; at most 64 of them, or what fills the chip where the grid has few tiles.
     // Shorter chunks, down to one plane, only where all of them are resident at a time: there the chip
     // waits for one plane after the other, not for memory, so re-reading 2R planes per chunk costs
-    // nothing and every CU that gets a workgroup shortens the march (fp64 adjoint radius 4: 40^3 36 -> 14.5 us,
-    // 80 x 96 x 112 41 -> 17, 128^3 41 -> 23; radius 1 80 x 96 x 112 12 -> 9; tiles of 32 x 16 or 64 x 8 cells
-    // with several workgroups per CU measured within 10 % of that except below 64^3).
+    // nothing and every CU that gets a workgroup shortens the march (fp64 adjoint, u_bar only, default tiles: radius 4
+    // 40^3 36 -> 14.5 us, 80 x 96 x 112 41 -> 17, 128^3 41 -> 23; radius 1 80 x 96 x 112 12 -> 9).  Such grids may take smaller
+    // tiles as well, see the kernels.
     const long chunk_cap = tiles * 64 >= ncu ? 64 : (ncu + tiles - 1) / tiles;
     const int max_chunks = nz / (4 * R) > 0 ? (int)(nz / (4 * R) < chunk_cap ? nz / (4 * R) : chunk_cap) : 1;
     int zchunk = (int)opt.zchunk;

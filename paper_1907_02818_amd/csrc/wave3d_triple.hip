@@ -16,7 +16,7 @@
 // all loads in flight.  512 threads with 256 registers hold three sums per stage and owned cell because
 // q1 and q2 go to LDS as soon as they are formed, c of older planes waits in LDS (all but 320 bytes of the
 // 160 KB are used in fp64), and all LDS planes share one geometry.  Then memory: 512^3 fp64, a pass
-// takes 1.09 ms = 4.9 TB/s on its 40 bytes per cell (a two-step pass 0.95 ms), 0.36 ms per step against 0.48.
+// takes 1.02 ms = 5.2 TB/s on its 40 bytes per cell (a two-step pass 0.95 ms), 0.34 ms per step against 0.48.
 #include "launch.hpp"
 #include "tile3d.hpp"
 

@@ -180,6 +180,9 @@ def summarise(workload, d):
                       "  rocprofv3 --pmc " + " ".join(sorted(m)) + " --kernel-trace -d DIR/sq -o p --output-format csv -- python3 bench.py "
                       + only + "--steps 5 --warmup 2 --settle-cap 0 --no-cpu-baseline",
                       "  " + ", ".join("%s %.4g" % (k, v) for k, v in sorted(m.items()))]
+            if m.get("SQ_INSTS_VALU"):
+                lines.append("  vector ALU issue: %.1f us per launch (4 cycles an instruction, 1024 SIMDs, 2.4 GHz)"
+                             % (m["SQ_INSTS_VALU"] * 4 / 1024 / 2400))
             if m.get("SQ_WAVE_CYCLES") and "SQ_WAIT_INST_ANY" in m:
                 lines.append("  wave-cycles spent waiting for an instruction to complete: %.0f %%"
                              % (100 * m["SQ_WAIT_INST_ANY"] / m["SQ_WAVE_CYCLES"]))
