@@ -1,0 +1,409 @@
+// Star stencils on grids that do not fill the chip: a z-march whose requests run ahead of the arithmetic.
+//
+// The kernels of wave3d_adjoint.hip, wave3d_primal.hip and star3d.hip are built for grids of several 10^8 bytes, where memory
+// is the bound and one plane in flight per workgroup keeps it busy.  On smaller grids a workgroup marches a few planes only
+// and waits for each of them; what counts there is the time from a plane's request to the next plane's.  This march differs in
+// three things:
+//   - No condition on the plane index around any memory access: arrays are addressed through buffer resources, a plane that is
+//     not wanted has a resource of zero bytes (loads return zero, stores are dropped by the hardware's bounds check), and cells
+//     outside the grid or outside I have an offset beyond any plane.  The wait counters therefore know exactly what is
+//     outstanding, and D planes are really in flight; with a branch around a load or store the compiler waits for everything.
+//     (All slots of the ring of requests are filled and emptied in one order, hence the scheduling barriers.)
+//   - The R planes before and after a chunk add to the chunk's sums by their own cell only (a star has no corners): they
+//     are read without halo, are not staged in LDS and need no barrier, and the R planes before the chunk are requested together.
+//     A chunk of n planes costs n full steps and R cheap ones where the other kernels take n + 2R.
+//   - Halo cells move as vectors, 16 bytes (fp32, small tiles: 8) per lane.
+// Adjoint, u_bar only, GPU time in us, the kernels named above with the shapes they took before / this: fp64 radius 4
+// 40^3 8.7 / 4.3, 80 x 96 x 112 16.6 / 8.5, 128^3 22.9 / 15.7, 200^3 64.9 / 43.3, 256^3 93.3 / 84.0; fp32 radius 4 40^3 6.5 / 4.1,
+// 128^3 15.4 / 9.1, 256^3 53.2 / 43.6; fp64 radius 1 128^3 14.8 / 12.1, 200^3 54.1 / 40.4.
+// Two planes in flight: one measured 0 to 10 % slower; four, in fp64, up to six times as long.
+#pragma once
+#include "ahead.hpp"
+
+namespace sadj {
+
+// 3 w_0 s + sum_k w_k xs_k + sum_k w_k ys_k
+template <class T, int R> __device__ __forceinline__ T wave_in_plane(T s, const T (&xs)[R], const T (&ys)[R])
+{
+    T t = mul_rounded(T(3.0 * star_w<R>(0)), s);
+#pragma unroll
+    for (int k = 1; k <= R; ++k) t = fma_t(T(star_w<R>(k)), xs[k - 1], t);
+#pragma unroll
+    for (int k = 1; k <= R; ++k) t = fma_t(T(star_w<R>(k)), ys[k - 1], t);
+    return t;
+}
+
+// A value the compiler must have computed by now (it would otherwise compute it from a slot's registers after the slot's next
+// request was issued, and copy the slot to keep both).
+template <class T> __device__ __forceinline__ void computed(T &v) { asm volatile("" : "+v"(v)); }
+
+// ---- buffer access
+typedef unsigned Dwords2 __attribute__((ext_vector_type(2)));
+typedef unsigned Dwords4 __attribute__((ext_vector_type(4)));
+constexpr unsigned kNowhere = 0x80000000u;          // an offset beyond every plane that takes this path (below 2^31 bytes)
+constexpr int kCached = 0, kStreaming = 2;          // cache policy operand: none, non-temporal
+
+// N cells at a byte offset; dwords at or beyond the resource's size read as zero.  Dword alignment is enough.
+template <class T, int N, int POLICY> __device__ __forceinline__ Vec<T, N> buffer_load(__amdgpu_buffer_rsrc_t r, unsigned off)
+{
+    Vec<T, N> v;
+    if constexpr (sizeof(v) == 4) { const unsigned t = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, POLICY); __builtin_memcpy(&v, &t, 4); }
+    else if constexpr (sizeof(v) == 8) { const Dwords2 t = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, POLICY); __builtin_memcpy(&v, &t, 8); }
+    else { const Dwords4 t = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, POLICY); __builtin_memcpy(&v, &t, 16); }
+    return v;
+}
+template <class T, int N, int POLICY> __device__ __forceinline__ void buffer_store(__amdgpu_buffer_rsrc_t r, unsigned off, const Vec<T, N> &v)
+{
+    if constexpr (sizeof(v) == 4) { unsigned t; __builtin_memcpy(&t, &v, 4); __builtin_amdgcn_raw_buffer_store_b32(t, r, off, 0, POLICY); }
+    else if constexpr (sizeof(v) == 8) { Dwords2 t; __builtin_memcpy(&t, &v, 8); __builtin_amdgcn_raw_buffer_store_b64(t, r, off, 0, POLICY); }
+    else { Dwords4 t; __builtin_memcpy(&t, &v, 16); __builtin_amdgcn_raw_buffer_store_b128(t, r, off, 0, POLICY); }
+}
+
+enum class StarOp { WaveAdjoint, WavePrimal, StarAdjoint, StarPrimal };
+
+template <class T, int R, int BX, int BY, int PX> struct AheadTile {
+    static constexpr int TX = BX * PX, TY = BY, NT = BX * BY;
+    static constexpr int HV = (R + PX - 1) / PX, HX = HV * PX;           // halo columns on a side, in vectors and in cells
+    static constexpr int LX = TX + 2 * HX, LY = TY + 2 * R, PLANE = LX * LY;
+    static constexpr int NH = 2 * R * BX + 2 * HV * TY, HS = (NH + NT - 1) / NT;     // halo vectors; slots per thread
+    // LDS coordinates of the first cell of halo vector tid + s * NT: rows above and below the tile, then columns beside it
+    __device__ static __forceinline__ bool halo_vector(int tid, int s, int &lx, int &ly)
+    {
+        const int h = tid + s * NT;
+        if (h < 2 * R * BX) {
+            const int row = h / BX;
+            lx = HX + h % BX * PX;
+            ly = row < R ? row : row + TY;
+        } else {
+            const int h2 = h - 2 * R * BX, k = h2 % (2 * HV);
+            lx = (k < HV ? k : k + BX) * PX;
+            ly = R + h2 / (2 * HV);
+        }
+        return h < NH;
+    }
+};
+
+// One thread: PX consecutive cells of one row.  RAGGED: rows or arrays are not whole vectors, so a row's last vector may reach
+// into the next row: its cells there are masked on loading and it is stored cell by cell.
+// UPREV (wave adjoint): see wave3d_adjoint.hip.  D: planes in flight.  POLICY: of the arrays without reuse.
+template <StarOp OP, class T, int R, int BX, int BY, int PX, int D, int UPREV, int POLICY, bool RAGGED>
+__global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
+{
+    using G = AheadTile<T, R, BX, BY, PX>;
+    using V = Vec<T, PX>;
+    constexpr int LX = G::LX, HS = G::HS, HX = G::HX;
+    constexpr bool ADJ = OP == StarOp::WaveAdjoint || OP == StarOp::StarAdjoint;
+    constexpr bool WAVE = OP == StarOp::WaveAdjoint || OP == StarOp::WavePrimal;
+    constexpr bool UPRIMAL = OP == StarOp::WavePrimal;
+    constexpr bool MASK = ADJ && (RAGGED || R % PX != 0);           // vectors that straddle the edge of I
+    constexpr bool PARTIAL = RAGGED || (!ADJ && R % PX != 0);       // vectors that are stored in part
+    __shared__ __attribute__((aligned(16))) T sq[2 * G::PLANE];
+    const March3dArgs &a = args.m;
+    int tix, tiy, zs, ze;
+    block_to_tile(a.map, blockIdx.x, tix, tiy, zs, ze);
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    if (!ADJ) {                                     // a primal's outputs are the planes of I
+        zs = max(zs, R);
+        ze = min(ze, nz - R);
+        if (zs >= ze) return;
+    }
+    const int tid = threadIdx.x, tx = tid % BX, ty = tid / BX;
+    const unsigned bytes = (unsigned)nx * (unsigned)ny * (unsigned)sizeof(T);
+    const int x0 = tix * G::TX, y0 = tiy * G::TY;
+    const int x = x0 + tx * PX, y = y0 + ty;
+    auto in_I = [&](int xx, int yy) { return xx >= R && xx < nx - R && yy >= R && yy < ny - R; };
+    auto in_grid = [&](int xx, int yy) { return xx >= 0 && xx < nx && yy >= 0 && yy < ny; };
+    auto offset = [&](int xx, int yy) { return ((unsigned)yy * (unsigned)nx + (unsigned)xx) * (unsigned)sizeof(T); };
+    // goff: the vector if any cell lies in the grid, ioff: if any lies in I; woff / poff: the vector if all cells that receive
+    // output are there / its single cells if only some are
+    bool in[PX], out[PX], any_I = false, all_out = true, any_out = false;
+#pragma unroll
+    for (int e = 0; e < PX; ++e) {
+        in[e] = in_I(x + e, y);
+        out[e] = ADJ ? in_grid(x + e, y) : in[e];
+        any_I = any_I || in[e];
+        all_out = all_out && out[e];
+        any_out = any_out || out[e];
+    }
+    const unsigned goff = in_grid(x, y) ? offset(x, y) : kNowhere, ioff = any_I ? offset(x, y) : kNowhere;
+    const unsigned woff = all_out ? offset(x, y) : kNowhere;
+    unsigned poff[PX];
+#pragma unroll
+    for (int e = 0; e < PX; ++e) poff[e] = out[e] && !all_out ? offset(x + e, y) : kNowhere;
+    const bool parts = PARTIAL && __any(any_out && !all_out);       // the same in all lanes of a wave
+    const unsigned soff = ADJ ? ioff : goff;                         // source field: q on I, u on the grid
+    unsigned hoff[HS];
+    bool hin[HS][PX];
+    int hl[HS];
+#pragma unroll
+    for (int s = 0; s < HS; ++s) {
+        int lx, ly;
+        const bool slot = G::halo_vector(tid, s, lx, ly);
+        const int hx = x0 - HX + lx, hy = y0 - R + ly;
+        bool any = false;
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            hin[s][e] = slot && (ADJ ? in_I(hx + e, hy) : in_grid(hx + e, hy));
+            any = any || hin[s][e];
+        }
+        hoff[s] = any ? offset(hx, hy) : kNowhere;
+        hl[s] = slot ? ly * LX + lx : 0;            // (0, 0) is a corner nobody reads
+    }
+    const T w0 = (T)args.w0;
+    T wx[2 * R], wy[2 * R], wz[2 * R];
+#pragma unroll
+    for (int i = 0; i < 2 * R; ++i) { wx[i] = (T)args.w[0][i]; wy[i] = (T)args.w[1][i]; wz[i] = (T)args.w[2][i]; }
+    // weight with which plane z adds to plane z + k (before) / z - k (after)
+    auto z_weight_up = [&](int k) { return WAVE ? T(star_w<R>(k)) : wz[R - k]; };
+    auto z_weight_down = [&](int k) { return WAVE ? T(star_w<R>(k)) : wz[R + k - 1]; };
+
+    // source planes that exist: of I (adjoint: q is zero elsewhere), of the grid (primal)
+    auto plane_used = [&](int z) { return ADJ ? z >= R && z < nz - R : true; };
+    auto plane_of = [&](const void *base, int z, bool wanted) {
+        char *p = static_cast<char *>(const_cast<void *>(base)) + (long long)z * (long long)bytes;
+        return __builtin_amdgcn_make_buffer_rsrc(p, 0, wanted ? bytes : 0u, 0x00020000);
+    };
+    const void *startg = OP == StarOp::WaveAdjoint && UPREV >= 3 ? a.in2 : a.out0;
+
+    // values in flight; s0 (, s1): the source field's factors; o0 (, o1): what the completing output plane is combined with
+    // (wave adjoint: start value, UPREV 4: r_bar; star adjoint: u_bar; wave primal: c, u_prev; star primal: c);
+    // pv: u_prev_bar of the arriving plane (UPREV 1)
+    V s0[D], s1[D], o0[D], o1[D], pv[D], h0[D][HS], h1[D][HS];
+    const int zlast = ze - 1 + R;
+    auto issue = [&](int z, int d) {
+        const bool used = z <= zlast && plane_used(z);
+        const auto r0 = plane_of(a.in0, z, used);
+        s0[d] = buffer_load<T, PX, kCached>(r0, soff);
+        const auto q0 = plane_of(a.in0, z, used && z < ze);
+        if (ADJ) {
+            s1[d] = buffer_load<T, PX, kCached>(plane_of(a.in1, z, used), soff);
+            if (UPREV == 1) pv[d] = buffer_load<T, PX, POLICY>(plane_of(a.out1, z, used && z < ze), goff);
+            const auto q1 = plane_of(a.in1, z, used && z < ze);
+#pragma unroll
+            for (int s = 0; s < HS; ++s) {
+                h0[d][s] = buffer_load<T, PX, kCached>(q0, hoff[s]);
+                h1[d][s] = buffer_load<T, PX, kCached>(q1, hoff[s]);
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < HS; ++s) h0[d][s] = buffer_load<T, PX, kCached>(q0, hoff[s]);
+        }
+    };
+    auto issue_out = [&](int z, int d) {
+        const int zo = z - R;
+        const bool wanted = zo >= zs && zo < ze;
+        if (OP == StarOp::WaveAdjoint) {
+            o0[d] = buffer_load<T, PX, POLICY>(plane_of(startg, zo, wanted), goff);
+            if (UPREV == 4) o1[d] = buffer_load<T, PX, POLICY>(plane_of(a.in1, zo, wanted), goff);
+        } else if (OP == StarOp::StarAdjoint) {
+            o0[d] = buffer_load<T, PX, POLICY>(plane_of(a.out0, zo, wanted), goff);
+        } else if (OP == StarOp::WavePrimal) {
+            o0[d] = buffer_load<T, PX, POLICY>(plane_of(a.in2, zo, wanted), ioff);
+            o1[d] = buffer_load<T, PX, POLICY>(plane_of(a.in1, zo, wanted), ioff);
+        } else {
+            o0[d] = buffer_load<T, PX, POLICY>(plane_of(a.in1, zo, wanted), ioff);
+        }
+    };
+    auto store_out = [&](__amdgpu_buffer_rsrc_t r, const V &o) {
+        buffer_store<T, PX, POLICY>(r, woff, o);
+        if (PARTIAL && parts) {
+#pragma unroll
+            for (int e = 0; e < PX; ++e) buffer_store<T, 1, POLICY>(r, poff[e], Vec<T, 1>{{o.v[e]}});
+        }
+    };
+    auto source = [&](T f0, T f1, bool inside) {
+        if (!ADJ) return f0;
+        const T q = mul_rounded(f0, f1);
+        return MASK ? (inside ? q : T(0)) : q;
+    };
+
+    // acc[k]: running sum of output plane z - R + k, z the arriving plane; the last one, z + R, starts at zero.
+    // hist[k] (wave primal): u of plane z - 1 - k
+    T acc[PX][2 * R + 1], hist[PX][R];
+#pragma unroll
+    for (int e = 0; e < PX; ++e) {
+#pragma unroll
+        for (int k = 0; k <= 2 * R; ++k) acc[e][k] = T(0);
+#pragma unroll
+        for (int k = 0; k < R; ++k) hist[e][k] = T(0);
+    }
+
+    auto step = [&](int z, int d) {
+        const int zo = z - R;
+        T *sb = sq + ((z - zs) & 1) * G::PLANE;
+        T own[PX], rr[PX], r2[PX];
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            own[e] = source(s0[d].v[e], s1[d].v[e], in[e]);
+            if (OP == StarOp::WaveAdjoint) {
+                rr[e] = MASK ? (in[e] ? s1[d].v[e] : T(0)) : s1[d].v[e];
+                r2[e] = rr[e] + rr[e];
+            }
+        }
+        if (z < ze) {
+            V v;
+#pragma unroll
+            for (int e = 0; e < PX; ++e) v.v[e] = own[e];
+            st_vec<T, PX>(sb + (R + ty) * LX + HX + tx * PX, v);
+#pragma unroll
+            for (int s = 0; s < HS; ++s) {
+#pragma unroll
+                for (int e = 0; e < PX; ++e) v.v[e] = source(h0[d][s].v[e], h1[d][s].v[e], hin[s][e]);
+                st_vec<T, PX>(sb + hl[s], v);
+            }
+        }
+        if (OP == StarOp::WaveAdjoint && (UPREV == 1 || UPREV == 2)) {
+            V o;
+#pragma unroll
+            for (int e = 0; e < PX; ++e) o.v[e] = (UPREV == 1 ? pv[d].v[e] : T(0)) - rr[e];
+            store_out(plane_of(a.out1, z, z < ze && (UPREV == 2 || plane_used(z))), o);
+        }
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            computed(own[e]);
+            if (OP == StarOp::WaveAdjoint) computed(r2[e]);
+        }
+        issue(z + D, d);
+        if (z < ze) {
+            __syncthreads();
+            T row[PX + 2 * HX];
+            V col[2 * R + 1];
+            const T *at = sb + (R + ty) * LX + tx * PX;
+#pragma unroll
+            for (int i = 0; i < PX + 2 * HX; i += PX) {
+                const V t = ld_vec<T, PX>(at + i);
+#pragma unroll
+                for (int e = 0; e < PX; ++e) row[i + e] = t.v[e];
+            }
+#pragma unroll
+            for (int k = -R; k <= R; ++k)
+                if (k != 0) col[R + k] = ld_vec<T, PX>(at + HX + k * LX);
+#pragma unroll
+            for (int e = 0; e < PX; ++e) {
+                if (WAVE) {
+                    T xs[R], ys[R];
+#pragma unroll
+                    for (int k = 1; k <= R; ++k) {
+                        xs[k - 1] = add_rounded(row[HX + e - k], row[HX + e + k]);
+                        ys[k - 1] = add_rounded(col[R - k].v[e], col[R + k].v[e]);
+                    }
+                    const T t = wave_in_plane<T, R>(own[e], xs, ys);
+                    acc[e][R] = add_rounded(acc[e][R], OP == StarOp::WaveAdjoint ? add_rounded(r2[e], t) : t);
+                } else {
+                    T t = mul_rounded(w0, own[e]);
+#pragma unroll
+                    for (int k = 1; k <= R; ++k) t = fma_t(wx[R + k - 1], row[HX + e + k], fma_t(wx[R - k], row[HX + e - k], t));
+#pragma unroll
+                    for (int k = 1; k <= R; ++k) t = fma_t(wy[R + k - 1], col[R + k].v[e], fma_t(wy[R - k], col[R - k].v[e], t));
+                    acc[e][R] = add_rounded(acc[e][R], t);
+                }
+#pragma unroll
+                for (int k = 1; k <= R; ++k) acc[e][R + k] = fma_t(z_weight_up(k), own[e], acc[e][R + k]);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < PX; ++e)
+#pragma unroll
+            for (int k = 1; k <= R; ++k) acc[e][R - k] = fma_t(z_weight_down(k), own[e], acc[e][R - k]);
+        const auto ro = plane_of(a.out0, zo, zo >= zs);
+        const bool zin = zo >= R && zo < nz - R;
+        V o;
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            if (OP == StarOp::WaveAdjoint) {
+                const T start = UPREV >= 3 ? (zin && in[e] ? T(0) - o0[d].v[e] : T(0)) : o0[d].v[e];
+                o.v[e] = add_rounded(start, acc[e][0]);
+            } else if (OP == StarOp::StarAdjoint) {
+                o.v[e] = add_rounded(o0[d].v[e], acc[e][0]);
+            } else if (OP == StarOp::WavePrimal) {
+                o.v[e] = fma_t(o0[d].v[e], acc[e][0], fma_t(T(2), hist[e][R - 1], T(0) - o1[d].v[e]));
+            } else {
+                o.v[e] = mul_rounded(o0[d].v[e], acc[e][0]);
+            }
+        }
+        store_out(ro, o);
+        if (OP == StarOp::WaveAdjoint && UPREV == 4) {
+#pragma unroll
+            for (int e = 0; e < PX; ++e) o.v[e] = zin && in[e] ? T(0) - o1[d].v[e] : T(0);
+            store_out(plane_of(a.out1, zo, zo >= zs), o);
+        }
+        issue_out(z + D, d);
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+#pragma unroll
+            for (int k = 0; k < 2 * R; ++k) { acc[e][k] = acc[e][k + 1]; computed(acc[e][k]); }
+            acc[e][2 * R] = T(0);
+            if (UPRIMAL) {
+#pragma unroll
+                for (int k = R - 1; k > 0; --k) { hist[e][k] = hist[e][k - 1]; computed(hist[e][k]); }
+                hist[e][0] = own[e];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // the R planes before the chunk, together
+    V f0[R], f1[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int z = zs - R + j;
+        f0[j] = buffer_load<T, PX, kCached>(plane_of(a.in0, z, plane_used(z)), soff);
+        if (ADJ) f1[j] = buffer_load<T, PX, kCached>(plane_of(a.in1, z, plane_used(z)), soff);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        issue(zs + d, d);
+        issue_out(zs + d, d);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            const T q = source(f0[j].v[e], f1[j].v[e], in[e]);
+            // plane zs - R + j adds to planes zs .. zs + j
+#pragma unroll
+            for (int i = 0; i <= j; ++i) acc[e][R + i] = fma_t(z_weight_up(R - j + i), q, acc[e][R + i]);
+            if (UPRIMAL) hist[e][R - 1 - j] = q;
+        }
+    int z = zs;
+    for (; z + D - 1 <= zlast; z += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) step(z + d, d);
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) {
+        if (z + d > zlast) return;
+        step(z + d, d);
+    }
+}
+
+template <StarOp OP, class T, int R, int UPREV, int BX, int BY, int PX, int POLICY, bool RAGGED>
+static hipError_t launch_ahead_kernel(const AheadArgs &a, unsigned pad, hipStream_t stream)
+{
+    hipLaunchKernelGGL((star_ahead_kernel<OP, T, R, BX, BY, PX, 2, UPREV, POLICY, RAGGED>), dim3(a.m.map.total_blocks), dim3(BX * BY), pad, stream, a);
+    return hipGetLastError();
+}
+
+// Rows that are not whole vectors take the RAGGED instantiations; an array need only be aligned to its elements.
+template <StarOp OP, class T, int R, int UPREV> static hipError_t launch_ahead(AheadShape shape, const AheadArgs &a, unsigned pad, hipStream_t stream)
+{
+    constexpr int PXV = 16 / sizeof(T);
+    constexpr int RX = sizeof(T) == 8 ? 32 : 16, RY = sizeof(T) == 8 ? 16 : 32;      // threads of the ragged wide tile
+    const bool whole = a.m.nx % (shape == AheadShape::Small ? 2 : PXV) == 0;
+    switch (shape) {
+    case AheadShape::Small:
+        return whole ? launch_ahead_kernel<OP, T, R, UPREV, 16, 16, 2, kCached, false>(a, pad, stream)
+                     : launch_ahead_kernel<OP, T, R, UPREV, 16, 16, 2, kCached, true>(a, pad, stream);
+    case AheadShape::Wide:
+        return whole ? launch_ahead_kernel<OP, T, R, UPREV, 32, 16, PXV, kCached, false>(a, pad, stream)
+                     : launch_ahead_kernel<OP, T, R, UPREV, RX, RY, PXV, kCached, true>(a, pad, stream);
+    case AheadShape::WideStream:
+        return whole ? launch_ahead_kernel<OP, T, R, UPREV, 32, 16, PXV, kStreaming, false>(a, pad, stream)
+                     : launch_ahead_kernel<OP, T, R, UPREV, RX, RY, PXV, kStreaming, true>(a, pad, stream);
+    default: return hipErrorNotSupported;
+    }
+}
+
+}  // namespace sadj

@@ -27,6 +27,20 @@ template <> __host__ __device__ constexpr double star_w<4>(int k)
                   : -1.0 / 560.0;
 }
 
+// Arithmetic with contraction off and every multiply-add written out, for kernels whose instantiations must round alike.
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <class T> __device__ __forceinline__ T mul_rounded(T a, T b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
+template <class T> __device__ __forceinline__ T add_rounded(T a, T b)
+{
+#pragma clang fp contract(off)
+    return a + b;
+}
+
 // Workgroups are dealt to the 8 XCDs round-robin by their linear id, and each XCD
 // has its own L2.  Map the hardware id to a logical id such that every XCD works
 // on one contiguous range of logical ids (so that neighbouring tiles, which share

@@ -49,30 +49,16 @@
 // I cannot leak.  Along z the same rule is applied per plane with a wave-uniform
 // (scalar) test in both instantiations: planes outside I are skipped.  The regions
 // are disjoint and need no ordering, so they share one dispatch.
-#include "launch.hpp"
-#include "tile3d.hpp"
+#include "ahead.hpp"
 
 #include <type_traits>
 
 namespace sadj {
 
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-
 // The arithmetic of a cell, contraction off and every multiply-add written out: all instantiations of
-// the kernel round alike, so that no bit depends on where the z-chunks are cut, on whether a tile is
-// guarded, or on which kernels a time loop's steps are made of (a loop of n+1 steps passes through
+// this kernel and of the march of ahead3d.hpp round alike, so that no bit depends on where the z-chunks are cut, on whether a
+// tile is guarded, or on which kernels a time loop's steps are made of (a loop of n+1 steps passes through
 // the states of a loop of n steps).
-template <class T> __device__ __forceinline__ T mul_rounded(T a, T b)
-{
-#pragma clang fp contract(off)
-    return a * b;
-}
-template <class T> __device__ __forceinline__ T add_rounded(T a, T b)
-{
-#pragma clang fp contract(off)
-    return a + b;
-}
 // acc + (2 r + (3 w_0 q + sum_k w_k xs_k + sum_k w_k ys_k))
 template <class T, int R> __device__ __forceinline__ T centre_terms(T q, T r, const T (&xs)[R], const T (&ys)[R], T acc)
 {
@@ -384,44 +370,6 @@ template <class T> static bool whole_vectors(const March3dArgs &a, int PX)
            aligned_to(a.out1, al);
 }
 
-// Small grids.  Where the z-chunks of the default shapes are shorter than 4R planes the chip waits for one
-// plane-step after the other, and a 32 x 16 tile with one cell per thread, two workgroups per CU, has the
-// shorter steps, against more planes per workgroup: measured per plane 0.70-0.88 of the time of the 64 x 32 fp64 tile,
-// 0.58-0.65 of the 128 x 32 fp32 tile with four cells per lane, and 0.66-1.0 of the 64 x 32 fp32 tile with one, which runs where
-// rows or arrays are not whole vectors (more arithmetic per cell at larger radii, hence the table).  20 steps of a sweep,
-// default / small tiles, fp64: radius 4 40^3 305 / 171 us, 101 x 99 x 97
-// 526 / 382, 128^3 478 / 440, 150^3 732 / 750; radius 1 40^3 108 / 86, 80 x 96 x 112 146 / 192; fp32 radius 4 40^3
-// 289 / 139, 128^3 341 / 318, 150^3 518 / 533.  One step, fp32, odd rows, 64 x 32 / small tiles: radius 1 73 x 174 x 61 6.1 / 7.2, radius 2
-// with u_prev_bar 117 x 161 x 49 10.5 / 13.0, radius 4 37 x 178 x 39 12.1 / 9.5.
-// (Tiles of 32 x 8 and one workgroup per CU were slower from 80^3 on.)
-constexpr int kSmallBX = 32, kSmallBY = 16, kSmallPerCu = 2;
-
-// Whether a grid takes them, and the plan if so; TX x TY: the default shape; whole: rows and arrays allow its vectors
-// (launch_cfg falls back to 64 x 32 tiles with one cell per lane otherwise).
-static bool small_tiles(TileMap &small, bool is_f64, int radius, int nx, int ny, int nz, int TX, int TY, bool whole, const LaunchOptions &opt)
-{
-    if (opt.variant != 0 || opt.remainder != 0 || opt.zchunk != 0 || opt.lds_pad != 0) return false;
-    if (wide_tile_for_unaligned_rows(nx, is_f64 ? 8 : 4, radius, !is_f64)) return false;
-    TileMap big;
-    plan_march(big, nx, ny, nz, whole ? TX : 64, whole ? TY : 32, radius, opt);
-    if (big.tiles_a != 0 || big.zchunk >= 4 * radius || big.zchunk >= nz) return false;
-    plan_march(small, nx, ny, nz, kSmallBX, kSmallBY, radius, opt, kSmallPerCu);
-    constexpr int percent[3][4] = {{65, 63, 58, 62}, {100, 77, 70, 70}, {88, 79, 70, 74}};
-    return percent[is_f64 ? 2 : whole ? 0 : 1][radius - 1] * march_planes(small, 2 * radius, kSmallPerCu) < 100 * march_planes(big, 2 * radius);
-}
-
-template <class T, int R> static hipError_t launch_small(const March3dArgs &a, hipStream_t stream)
-{
-    constexpr int BX = kSmallBX, BY = kSmallBY;
-    const dim3 grid(a.map.total_blocks), block(BX * BY);
-    if (a.in2 && !a.out1)        hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 3, 0>), grid, block, 0, stream, a);
-    else if (a.in2)              hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 4, 0>), grid, block, 0, stream, a);
-    else if (!a.out1)            hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 0, 0>), grid, block, 0, stream, a);
-    else if (a.out1_assign == 0) hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 1, 0>), grid, block, 0, stream, a);
-    else                         hipLaunchKernelGGL((adj_wave3d_kernel<T, R, BX, BY, 1, 1, 1, true, 2, 0>), grid, block, 0, stream, a);
-    return hipGetLastError();
-}
-
 template <class T, int R, int BX, int BY, int PY, int PX, int D, bool NTU>
 static hipError_t launch_cfg(March3dArgs a, const LaunchOptions &opt, hipStream_t stream)
 {
@@ -499,12 +447,14 @@ static inline void shape_extents(long v, bool is_f64, int radius, int &TX, int &
 template <class T, int R>
 static hipError_t launch_T(const March3dArgs &a, const LaunchOptions &opt, hipStream_t stream)
 {
+    const AheadPlan ahead = plan_adjoint_ahead(sizeof(T) == 8, R, a.nx, a.ny, a.nz, a.out1 && !a.in2 && !a.out1_assign, a.out1 != nullptr, opt);
+    if (ahead.shape != AheadShape::None) {
+        AheadArgs h{};
+        h.m = a;
+        h.m.map = ahead.map;
+        return launch_adjoint_wave3d_ahead(sizeof(T) == 8, R, h, ahead.shape, opt.lds_pad > 0 ? (unsigned)opt.lds_pad : 0u, stream);
+    }
     const long v = choose_adjoint_shape(sizeof(T) == 8, R, a.nx, a.out1 && !a.out1_assign, opt);
-    int TX, TY, PX;
-    shape_extents(v, sizeof(T) == 8, R, TX, TY, PX);
-    const bool whole = whole_vectors<T>(a, PX);
-    March3dArgs as = a;
-    if (small_tiles(as.map, sizeof(T) == 8, R, a.nx, a.ny, a.nz, TX, TY, whole, opt)) return launch_small<T, R>(as, stream);
     if constexpr (R == 2 || R == 3) {            // the default shapes of the dtype only
         if constexpr (sizeof(T) == 8) {
             return v == 3 ? launch_cfg<T, R, 64, 8, 4, 1, 1, true>(a, opt, stream)
@@ -540,13 +490,15 @@ void describe_march_plan(int is_f64, int radius, int nx, int ny, int nz, int wit
 {
     // the shape launch_T takes for 16-byte aligned arrays and an nx that allows whole vectors;
     // otherwise the one-cell shape
+    const AheadPlan ahead = plan_adjoint_ahead(is_f64 != 0, radius, nx, ny, nz, with_u_prev_bar != 0, with_u_prev_bar != 0, opt);
     long v = choose_adjoint_shape(is_f64 != 0, radius, nx, with_u_prev_bar != 0, opt);
     int TX, TY, PX;
     shape_extents(v, is_f64 != 0, radius, TX, TY, PX);
     TileMap m;
-    if (small_tiles(m, is_f64 != 0, radius, nx, ny, nz, TX, TY, nx % PX == 0, opt)) {
-        TX = kSmallBX;
-        TY = kSmallBY;
+    if (ahead.shape != AheadShape::None) {
+        m = ahead.map;
+        TX = ahead.TX;
+        TY = ahead.TY;
     } else {
         if (nx % PX != 0) shape_extents(3, is_f64 != 0, radius, TX, TY, PX);
         plan_march(m, nx, ny, nz, TX, TY, radius, opt);
