@@ -11,7 +11,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsadj.so")
-SOURCES = ["api.hip", "wave3d_adjoint.hip", "wave3d_ahead.hip", "wave3d_ordered.hip", "wave3d_scatter_atomic.hip", "wave3d_primal.hip", "wave2d.hip", "stencil1d.hip", "burgers_loop.hip", "functor1d.hip", "functor_star.hip", "box.hip", "star3d.hip", "probe.hip", "wave3d_pair.hip", "wave3d_triple.hip"]
+SOURCES = ["api.hip", "wave3d_adjoint.hip", "wave3d_ahead.hip", "wave3d_ordered.hip", "wave3d_scatter_atomic.hip", "wave3d_primal.hip", "wave3d_primal_ahead.hip", "wave2d.hip", "stencil1d.hip", "burgers_loop.hip", "functor1d.hip", "functor_star.hip", "box.hip", "star3d.hip", "star3d_ahead.hip", "probe.hip", "wave3d_pair.hip", "wave3d_triple.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -21,39 +21,45 @@ struct AheadArgs {
     double w0, w[3][8];         // free-weight star: gather table (see StarArgs in star3d.hip)
 };
 
-// Grids whose arrays, `words` of them moved per call, take at most this many bytes.  Above, the kernels that keep the
-// neighbours of a plane in L2 and stream the rest are as fast or faster: adjoint, this / those, fp64 384^3 (1.8 GB) radius 2
-// 333 / 336 us, with u_prev_bar 519 / 492; 512^3 radius 4 742 / 703; 300 x 350 x 404 (1.4 GB) 274 / 292, radius 1 290 / 275.  Of 120
-// drawn grids of 0.6 to 3 GB 45 lose, by up to 12 %; of 820 below the line 4, by up to 2.2 %.
-constexpr double kAheadBytes = 560e6;
-// Above this the 256 MB last-level cache does not serve enough of the repeated accesses, and streaming the others leaves it to
-// c and r_bar: 0.82 to 0.95 of the time above 450 MB, 1.10 to 1.15 below 330 MB, equal within 2 % from 360 to 400.
-constexpr double kAheadStreamBytes = 380e6;
+// When this march is taken, by the bytes a call moves (what it moves per cell, times the cells).  All figures: 1300 drawn grids
+// of 3 10^4 to 1.2 10^8 cells, three sets of arrays in turn, time of the other kernels over time of this march; geometric mean
+// (smallest).
+//   limit    largest call.  Beyond it the kernels that keep the neighbours of a plane in L2 and stream the rest are as fast: wave
+//            adjoint fp64 radius 4 560 .. 1400 MB 1.11 (1.06), radius 3 560 .. 800 MB 1.08, radius 1 560 .. 800 MB 0.97 (0.93); wave
+//            primal radius 1 fp64 120 .. 250 MB 1.10 (0.98), 560 .. 800 MB 0.95, fp32 120 .. 250 MB 1.02 (0.93), 250 .. 560 MB 0.89
+//            (0.70); star adjoint radius 2 to 4 560 .. 800 MB 1.05 to 1.13.
+//   stream   largest call whose arrays without reuse go through the caches.  Arrays that the same loop touches in every step are
+//            found in the 256 MB last-level cache up to 380 MB (fp64 200^3: 42 us cached, 56 streaming; 256^3: 96 and 84); a single
+//            call finds less (wave adjoint fp64, three sets: 90 .. 120 MB 1.42 cached and 1.29 streaming, 130 .. 200 MB 1.13 and 1.24).
+struct AheadRule {
+    int words;                  // moved per cell
+    double limit, stream;
+    int percent;                // cost of Small's step against Wide's
+    int percent_short;          // the same where Small's chunks are 2R planes or shorter and the chip is hardly filled
+    bool long_rows_stay;        // rows that wide_tile_for_unaligned_rows gives tiles of 1 KB and more, in whole vectors, keep them
+};
+constexpr double kAheadLoopStream = 380e6, kAheadCallStream = 125e6;
+constexpr int kPercentStream = 150;     // streaming, Wide against Small, which has no streaming form (12 of 455 such grids take Small)
 
-// Small or Wide: the planes marched, times the relative cost of a step.  `beyond`: cheap planes of a chunk, counted as 2R full
-// ones, which is what the z cut is planned with.  percent: cost of Small's step against Wide's.  Over 820 drawn grids this
-// choice is 1.7 % (fp64) and 2.5 % (fp32) behind the better of the two; the grids are 1.43 and 1.40 times as fast as in the
-// shapes of the other kernels.  Where Small's chunks are short (2R planes or less) the chip is hardly filled and its
-// smaller workgroups win except at radius 1 in ragged fp32 rows (40^3 fp64 radius 4 4.3 us, Wide 5.3).
-static inline AheadPlan plan_ahead(bool is_f64, int radius, int nx, int ny, int nz, int words, int percent, const int (&percent_short)[4],
-                                   const LaunchOptions &opt)
+// Small or Wide: the planes marched, times the relative cost of a step.  The cheap planes of a chunk count as 2R full ones, which
+// is also what the z cut is planned with (other weights moved no grid's time by more than 3 %).
+static inline AheadPlan plan_ahead(bool is_f64, int radius, int nx, int ny, int nz, const AheadRule &rule, const LaunchOptions &opt)
 {
     AheadPlan p;
-    const double bytes = (double)nx * ny * nz * words * (is_f64 ? 8 : 4);
-    if (opt.variant != 0 || opt.remainder != 0 || bytes > kAheadBytes) return p;
-    // Rows that are no multiple of a cache line and fill tiles of 1 KB and more: where they are whole vectors such tiles run
-    // (wide_tile_for_unaligned_rows); where not, those would fall back to one cell per lane, and the wide tile here is taken.
-    const bool long_rows = wide_tile_for_unaligned_rows(nx, is_f64 ? 8 : 4, radius, !is_f64) != 0;
-    if (long_rows && nx % (is_f64 ? 2 : 4) == 0) return p;
-    const int wide_x = is_f64 ? 64 : nx % 4 == 0 ? 128 : 64, wide_y = !is_f64 && nx % 4 != 0 ? 32 : 16;
+    const double bytes = (double)nx * ny * nz * rule.words * (is_f64 ? 8 : 4);
+    if (opt.variant != 0 || opt.remainder != 0 || bytes > rule.limit) return p;
+    const bool whole = nx % (is_f64 ? 2 : 4) == 0;
+    const bool long_rows = rule.long_rows_stay && wide_tile_for_unaligned_rows(nx, is_f64 ? 8 : 4, radius, !is_f64) != 0;
+    if (long_rows && whole) return p;
+    const int wide_x = is_f64 ? 64 : whole ? 128 : 64, wide_y = !is_f64 && !whole ? 32 : 16;
     // grid and type alone decide, so that options that move work between workgroups change nothing else
     TileMap small, wide;
     plan_march(small, nx, ny, nz, 32, 16, radius, LaunchOptions{}, 2);
     plan_march(wide, nx, ny, nz, wide_x, wide_y, radius, LaunchOptions{});
-    if (small.tiles_a == 0 && small.zchunk <= 2 * radius)
-        percent = percent_short[radius - 1];
+    const bool stream = bytes > rule.stream;
+    const int percent = small.tiles_a == 0 && small.zchunk <= 2 * radius ? rule.percent_short : stream ? kPercentStream : rule.percent;
     const bool is_small = !long_rows && percent * march_planes(small, 2 * radius, 2) < 100 * march_planes(wide, 2 * radius);
-    p.shape = is_small ? AheadShape::Small : bytes > kAheadStreamBytes ? AheadShape::WideStream : AheadShape::Wide;
+    p.shape = is_small ? AheadShape::Small : stream ? AheadShape::WideStream : AheadShape::Wide;
     p.TX = is_small ? 32 : wide_x;
     p.TY = is_small ? 16 : wide_y;
     p.map = is_small ? small : wide;
@@ -62,17 +68,36 @@ static inline AheadPlan plan_ahead(bool is_f64, int radius, int nx, int ny, int 
     return p;
 }
 
-// The wave adjoint; accumulates: u_prev_bar is read and written, writes_prev: written (or the array it replaces is).
-static inline AheadPlan plan_adjoint_ahead(bool is_f64, int radius, int nx, int ny, int nz, bool accumulates, bool writes_prev,
+// The wave adjoint; accumulates: u_prev_bar is read and written, writes_prev: written (or the array it replaces is), loop: a step
+// of a time loop after its first.  Below 120 MB 1.42 to 1.45 (fp64) and 1.40 (fp32) times as fast as in the tiles of
+// wave3d_adjoint.hip, 1 % behind the better of the two shapes.  40^3 fp64 radius 4, Small / Wide: 4.3 / 5.3 us; 80 x 96 x 112 with
+// u_prev_bar 11.7 / 10.2.
+static inline AheadPlan plan_adjoint_ahead(bool is_f64, int radius, int nx, int ny, int nz, bool accumulates, bool writes_prev, bool loop,
                                            const LaunchOptions &opt)
 {
-    constexpr int short_f64[4] = {100, 99, 99, 99}, short_f32[4] = {74, 74, 74, 74}, short_ragged[4] = {100, 74, 74, 74}, both_f64[4] = {105, 105, 105, 105};
     const int words = accumulates ? 6 : writes_prev ? 5 : 4;
-    if (is_f64) return plan_ahead(true, radius, nx, ny, nz, words, accumulates ? 105 : 115, accumulates ? both_f64 : short_f64, opt);
-    return plan_ahead(false, radius, nx, ny, nz, words, 85, nx % 4 == 0 ? short_f32 : short_ragged, opt);
+    const double limit = radius == 4 ? 1400e6 : radius == 3 ? 800e6 : 560e6, stream = loop ? kAheadLoopStream : kAheadCallStream;
+    AheadRule rule{words, limit, stream, 85, 74, true};
+    if (is_f64) rule = {words, limit, stream, accumulates ? 105 : 115, accumulates ? 105 : radius == 1 ? 100 : 99, true};
+    else if (radius == 1 && nx % 4 != 0) rule.percent_short = 100;
+    return plan_ahead(is_f64, radius, nx, ny, nz, rule, opt);
 }
 
-// opt.lds_pad > 0: dynamic LDS to request.
+// The free-weight star, both directions, and the wave primal.  Below 120 MB star adjoint 1.46 (fp64) and 1.51 (fp32) times as
+// fast as before, star primal 1.63 and 1.56, wave primal 1.59 and 1.82.
+static inline AheadPlan plan_star_ahead(bool is_f64, int radius, int nx, int ny, int nz, bool adjoint, bool wave, LaunchOptions opt)
+{
+    opt.remainder = 0;                               // an option of the wave adjoint
+    const int percent = is_f64 ? (wave ? 115 : 110) : adjoint ? 80 : 70;
+    const double limit = radius == 4 ? 1400e6 : radius > 1 ? (adjoint ? 800e6 : 560e6) : adjoint ? 560e6 : is_f64 ? 250e6 : kAheadCallStream;
+    const AheadRule rule{adjoint || wave ? 4 : 3, limit, kAheadCallStream, percent, percent, false};
+    return plan_ahead(is_f64, radius, nx, ny, nz, rule, opt);
+}
+
+// pad: dynamic LDS to request.
+static inline unsigned ahead_pad(const LaunchOptions &opt) { return opt.lds_pad > 0 ? (unsigned)opt.lds_pad : 0u; }
 hipError_t launch_adjoint_wave3d_ahead(int is_f64, int radius, const AheadArgs &a, AheadShape shape, unsigned pad, hipStream_t stream);
+hipError_t launch_primal_wave3d_ahead(int is_f64, int radius, const AheadArgs &a, AheadShape shape, unsigned pad, hipStream_t stream);
+hipError_t launch_star3d_ahead(int adjoint, int is_f64, int radius, const AheadArgs &a, AheadShape shape, unsigned pad, hipStream_t stream);
 
 }  // namespace sadj

@@ -15,7 +15,8 @@
 //   - Halo cells move as vectors, 16 bytes (fp32, small tiles: 8) per lane.
 // Adjoint, u_bar only, GPU time in us, the kernels named above with the shapes they took before / this: fp64 radius 4
 // 40^3 8.7 / 4.3, 80 x 96 x 112 16.6 / 8.5, 128^3 22.9 / 15.7, 200^3 64.9 / 43.3, 256^3 93.3 / 84.0; fp32 radius 4 40^3 6.5 / 4.1,
-// 128^3 15.4 / 9.1, 256^3 53.2 / 43.6; fp64 radius 1 128^3 14.8 / 12.1, 200^3 54.1 / 40.4.
+// 128^3 15.4 / 9.1, 256^3 53.2 / 43.6; fp64 radius 1 128^3 14.8 / 12.1, 200^3 54.1 / 40.4.  128^3 fp64 radius 4: star adjoint 26.6 /
+// 16.3, star primal 22.8 / 12.4, wave primal 22.3 / 14.3 (the first of each in the kernels' shapes of larger grids).
 // Two planes in flight: one measured 0 to 10 % slower; four, in fp64, up to six times as long.
 #pragma once
 #include "ahead.hpp"

@@ -15,8 +15,7 @@
 // Mapping: the z-march of the wave kernels (a workgroup owns a 64 x 32 x-y tile, the arriving
 // plane of S is staged in LDS with a halo of width R without corners, 2R+1 running sums per
 // owned cell in registers), with the weights as kernel arguments.
-#include "launch.hpp"
-#include "tile3d.hpp"
+#include "ahead.hpp"
 
 namespace sadj {
 
@@ -206,39 +205,11 @@ __global__ __launch_bounds__(BX *BY) void star3d_kernel(StarArgs a)
     else      star3d_march<T, R, BX, BY, PY, PX, ADJ, true>(a, tix, tiy, zs, ze, sq);
 }
 
-// Small grids at radius 4.  Where the z-chunks are shorter than 4R planes each workgroup waits for one plane-step
-// after the other, and 32 x 16 tiles with one cell per thread, two workgroups per CU, step in 0.74 of the time
-// (0.6 of that of tiles with eight cells per thread, 0.79 of 128 x 16 tiles with four), against more planes per
-// workgroup.  Adjoint, default /
-// small tiles, fp64 40^3 14.2 / 8.9 us, 101 x 99 x 96 20.0 / 16.2, 128^3 23.0 / 21.6; fp32 40^3 15.1 / 8.8, 128^3 17.6 / 15.7;
-// fp64 150^3 would be 34.0 / 34.7, 60 x 200 x 180 24.4 / 24.8, fp32 primal 150^3 21.3 / 22.6.
-// Radius 1 and 2 gain nothing up to 64^3 and lose up to 40 % from there on.
-// The two shapes contract their sums into fused multiply-adds differently, so grid and type alone decide: options that
-// move work between workgroups must not change a bit.  big: the plan of the default tiles without options.
-static bool star_small_tiles(const TileMap &big, int percent, int nx, int ny, int nz)
-{
-    constexpr int R = 4;
-    if (big.tiles_a != 0 || big.zchunk >= 4 * R || big.zchunk >= nz) return false;
-    TileMap small;
-    plan_march(small, nx, ny, nz, 32, 16, R, LaunchOptions{}, 2);
-    return percent * march_planes(small, 2 * R, 2) < 100 * march_planes(big, 2 * R);
-}
-
 template <class T, int R, bool ADJ, int BX, int BY, int PY, int PX>
 static hipError_t launch_star_shape(StarArgs a, const LaunchOptions &opt, hipStream_t stream)
 {
     using G = Tile3d<T, R, BX, BY, PY, PX>;
     plan_march(a.map, a.nx, a.ny, a.nz, G::TX, G::TY, R, opt);
-    if constexpr (R == 4) {
-        TileMap big = a.map;
-        if (opt.zchunk != 0 || opt.split != 0) plan_march(big, a.nx, a.ny, a.nz, G::TX, G::TY, R, LaunchOptions{});
-        if (opt.variant == 0 && star_small_tiles(big, PX * PY == 8 ? 60 : G::TX == 128 ? 79 : 74, a.nx, a.ny, a.nz)) {
-            plan_march(a.map, a.nx, a.ny, a.nz, 32, 16, R, opt, 2);
-            const unsigned small_pad = opt.lds_pad > 0 ? (unsigned)opt.lds_pad : 0;
-            hipLaunchKernelGGL((star3d_kernel<T, R, 32, 16, 1, 1, ADJ>), dim3(a.map.total_blocks), dim3(32 * 16), small_pad, stream, a);
-            return hipGetLastError();
-        }
-    }
     const unsigned pad = one_workgroup_per_cu_pad(sizeof(T) * 2 * G::PLANE, opt.lds_pad);
     hipLaunchKernelGGL((star3d_kernel<T, R, BX, BY, PY, PX, ADJ>), dim3(a.map.total_blocks), dim3(G::NT), pad, stream, a);
     return hipGetLastError();
@@ -254,6 +225,17 @@ static inline bool star_aligned(const void *p, size_t n) { return (reinterpret_c
 template <class T, int R, bool ADJ>
 static hipError_t launch_star_TR(const StarArgs &a, const LaunchOptions &opt, hipStream_t stream)
 {
+    const AheadPlan ahead = plan_star_ahead(sizeof(T) == 8, R, a.nx, a.ny, a.nz, ADJ, false, opt);
+    if (ahead.shape != AheadShape::None) {
+        AheadArgs h{};
+        h.m.in0 = a.in0; h.m.in1 = a.in1; h.m.out0 = a.out;
+        h.m.nx = a.nx; h.m.ny = a.ny; h.m.nz = a.nz;
+        h.m.map = ahead.map;
+        h.w0 = a.w0;
+        for (int d = 0; d < 3; ++d)
+            for (int i = 0; i < 8; ++i) h.w[d][i] = a.w[d][i];
+        return launch_star3d_ahead(ADJ, sizeof(T) == 8, R, h, ahead.shape, ahead_pad(opt), stream);
+    }
     constexpr int PXV = 16 / sizeof(T);
     const bool ok = a.nx % PXV == 0 && star_aligned(a.in0, 16) && star_aligned(a.in1, 16) && star_aligned(a.out, 16);
     // the primal measured 2-6 points faster with the one-cell shape for radius 1 and 2, and for

@@ -447,12 +447,13 @@ static inline void shape_extents(long v, bool is_f64, int radius, int &TX, int &
 template <class T, int R>
 static hipError_t launch_T(const March3dArgs &a, const LaunchOptions &opt, hipStream_t stream)
 {
-    const AheadPlan ahead = plan_adjoint_ahead(sizeof(T) == 8, R, a.nx, a.ny, a.nz, a.out1 && !a.in2 && !a.out1_assign, a.out1 != nullptr, opt);
+    const AheadPlan ahead = plan_adjoint_ahead(sizeof(T) == 8, R, a.nx, a.ny, a.nz, a.out1 && !a.in2 && !a.out1_assign, a.out1 != nullptr,
+                                               a.in2 != nullptr, opt);
     if (ahead.shape != AheadShape::None) {
         AheadArgs h{};
         h.m = a;
         h.m.map = ahead.map;
-        return launch_adjoint_wave3d_ahead(sizeof(T) == 8, R, h, ahead.shape, opt.lds_pad > 0 ? (unsigned)opt.lds_pad : 0u, stream);
+        return launch_adjoint_wave3d_ahead(sizeof(T) == 8, R, h, ahead.shape, ahead_pad(opt), stream);
     }
     const long v = choose_adjoint_shape(sizeof(T) == 8, R, a.nx, a.out1 && !a.out1_assign, opt);
     if constexpr (R == 2 || R == 3) {            // the default shapes of the dtype only
@@ -490,7 +491,7 @@ void describe_march_plan(int is_f64, int radius, int nx, int ny, int nz, int wit
 {
     // the shape launch_T takes for 16-byte aligned arrays and an nx that allows whole vectors;
     // otherwise the one-cell shape
-    const AheadPlan ahead = plan_adjoint_ahead(is_f64 != 0, radius, nx, ny, nz, with_u_prev_bar != 0, with_u_prev_bar != 0, opt);
+    const AheadPlan ahead = plan_adjoint_ahead(is_f64 != 0, radius, nx, ny, nz, with_u_prev_bar != 0, with_u_prev_bar != 0, false, opt);
     long v = choose_adjoint_shape(is_f64 != 0, radius, nx, with_u_prev_bar != 0, opt);
     int TX, TY, PX;
     shape_extents(v, is_f64 != 0, radius, TX, TY, PX);

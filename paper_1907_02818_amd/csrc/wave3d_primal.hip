@@ -18,8 +18,7 @@
 // from L2.  Workgroups are mapped to XCD patches and sized to one resident wave, as
 // in the adjoint kernel.  Reads of u never leave the grid for outputs in I, so the only
 // guards are address clamps for tiles that stick out of the grid and the store mask.
-#include "launch.hpp"
-#include "tile3d.hpp"
+#include "ahead.hpp"
 
 namespace sadj {
 
@@ -206,6 +205,13 @@ static hipError_t launch_primal_cfg(March3dArgs a, const LaunchOptions &opt, hip
 template <class T, int R>
 static hipError_t launch_primal_T(const March3dArgs &a, const LaunchOptions &opt, hipStream_t stream)
 {
+    const AheadPlan ahead = plan_star_ahead(sizeof(T) == 8, R, a.nx, a.ny, a.nz, false, true, opt);
+    if (ahead.shape != AheadShape::None) {
+        AheadArgs h{};
+        h.m = a;
+        h.m.map = ahead.map;
+        return launch_primal_wave3d_ahead(sizeof(T) == 8, R, h, ahead.shape, ahead_pad(opt), stream);
+    }
     long v = opt.variant;
     if (v == 0) {
         const auto at = [](const void *p) { return reinterpret_cast<uintptr_t>(p); };

@@ -84,3 +84,48 @@ def test_against_the_oracle_with_nan_outside_the_iteration_space(sadj, radius, s
     bound = 2 * (6 * radius + 4) * np.finfo(np.float64).eps * (scale + np.abs(d["u_bar"]))
     assert np.all(np.abs(to_host(ub) - want) <= bound)
     assert np.array_equal(to_host(pb), want_p)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("radius", [1, 2, 3, 4])
+def test_star_is_exact_on_dyadic_data(sadj, radius, dtype):
+    """Weights and c multiples of 1/4 below 2, fields whole numbers up to 4: every product is a multiple of 1/16 and the at most
+    25 terms stay below 512, 13 bits in all, so fp32 is exact as well.  NaN where values must not be read."""
+    import torch
+    for k, shape in enumerate(SHAPES):
+        shape = _shape(shape, radius)
+        w = np.round(inputs.uniform(2, "aux", (1 + 6 * radius,), -2, 2) * 4) / 4
+        c = np.round(inputs.uniform(3, "c", shape, 0, 1) * 4) / 4
+        u, rb, ub = (np.round(4 * inputs.uniform(5, n, shape, -1, 1)) for n in ("u", "r_bar", "u_bar"))
+        m = np.zeros(shape, bool)
+        m[tuple(slice(radius, n - radius) for n in shape)] = True
+        put = lambda x: _placed(torch, to_gpu(x.astype(dtype)), k % 2)   # noqa: E731
+        got = put(ub)
+        sadj.sadj_adjoint_star3d(radius, w, put(np.where(m, c, np.nan)), put(np.where(m, rb, np.nan)), got)
+        assert np.array_equal(to_host(got).astype(np.float64), oracle.star3d_adjoint(w, c, rb, ub, radius)[0]), shape
+        r = put(np.full(shape, 7.0))
+        sadj.sadj_primal_star3d(radius, w, put(u), put(np.where(m, c, np.nan)), r)
+        assert np.array_equal(to_host(r).astype(np.float64)[m], oracle.star3d_primal(w, u, c, radius)[m]), shape
+        assert (to_host(r)[~m] == 7).all(), shape
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("radius", [1, 2, 3, 4])
+def test_wave_primal_against_the_oracle(sadj, radius, dtype):
+    import torch
+    from parity import wave_primal_scale
+    for k, shape in enumerate(SHAPES):
+        shape = _shape(shape, radius)
+        d = inputs.wave_inputs(shape, 0.01, 0.1, seed=k, dtype=dtype, c_mode="iid")
+        m = np.zeros(shape, bool)
+        m[tuple(slice(radius, n - radius) for n in shape)] = True
+        put = lambda x: _placed(torch, to_gpu(x.astype(dtype)), k % 2)   # noqa: E731
+        r = put(np.full(shape, 7.0))
+        sadj.sadj_primal_wave3d(radius, put(d["u"]), put(np.where(m, d["u_prev"], np.nan)), put(np.where(m, d["c"], np.nan)), r)
+        want = oracle.wave_primal(d["u"], d["u_prev"], d["c"], radius)
+        scale = wave_primal_scale(d["u"], d["u_prev"], d["c"], radius)
+        # as many roundings as terms, of the sum of their magnitudes
+        bound = (6 * radius + 6) * np.finfo(dtype).eps * scale
+        got = to_host(r).astype(np.float64)
+        assert np.all(np.abs(got - want)[m] <= bound[m]), shape
+        assert (got[~m] == 7).all(), shape
