@@ -14,33 +14,51 @@ __device__ __forceinline__ double neg_part(double v) { double r; asm("v_min_f64 
 __device__ __forceinline__ float pos_part(float v) { float r; asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(v)); return r; }
 __device__ __forceinline__ float neg_part(float v) { float r; asm("v_min_f32 %0, 0, %1" : "=v"(r) : "v"(v)); return r; }
 
-__device__ __forceinline__ double fused_mul_add(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fused_mul_add(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+// What a cell gives its neighbours: g_-(i) = C max(u_i,0) + D to the cell on its left, g_+(i) = -C min(u_i,0) + D to the one on its
+// right.  The forward step is written with the same two: with d_l = u_i - u_{i-1}, d_r = u_{i+1} - u_i
+//   r_i = u_i - C (max(u_i,0) d_l + min(u_i,0) d_r) + D (d_r - d_l) = u_i - g_- d_l + g_+ d_r,
+// 8 operations a cell (d_l is its neighbour's d_r) where the formula as it stands takes 10.
+template <class T> __device__ __forceinline__ T burgers_to_left(T u, T C, T D) { return fma_t(C, pos_part(u), D); }
+template <class T> __device__ __forceinline__ T burgers_to_right(T u, T C, T D) { return fma_t(-C, neg_part(u), D); }
 
 // r_i from (um, u0, up) = u[i-1], u[i], u[i+1].
 template <class T> __device__ __forceinline__ T burgers_primal_cell(T um, T u0, T up, T C, T D)
 {
 #pragma clang fp contract(off)
-    const T conv = fused_mul_add(pos_part(u0), u0 - um, neg_part(u0) * (up - u0));
-    const T lap = fused_mul_add(T(-2), u0, um) + up;
-    return fused_mul_add(D, lap, fused_mul_add(-C, conv, u0));
+    return u0 + fma_t(burgers_to_right(u0, C, D), up - u0, -(burgers_to_left(u0, C, D) * (u0 - um)));
 }
 
-// The three terms of one u_bar[j]; (um, u0, up) = u[j-1], u[j], u[j+1], (rm, r0, rp) = r_bar at
-// the same cells with zeros where the iteration does not exist:
-//   g_-(i) = C max(u_i,0) + D,  g_+(i) = -C min(u_i,0) + D,
-//   g_0(i) = 1 - 2D - C( [u_i>=0](u_i-u_{i-1}) + max(u_i,0) + [-u_i>=0](u_{i+1}-u_i) - min(u_i,0) )
-template <class T> __device__ __forceinline__ T burgers_adjoint_terms(T um, T u0, T up, T rm, T r0, T rp, T C, T D, bool in0)
+// The upwind slope without the second term that u = 0 has: |u| + (u >= 0 ? d_l : d_r).  max(u,0) - min(u,0) is |u|.
+template <class T> __device__ __forceinline__ T burgers_slope(T um, T u0, T up)
 {
 #pragma clang fp contract(off)
-    const T dpos = u0 >= T(0) ? T(1) : T(0);
-    const T dneg = -u0 >= T(0) ? T(1) : T(0);
-    // dpos and dneg are 0 or 1: their products are exact, and fusing them changes no bit
-    const T slope = fused_mul_add(dneg, up - u0, fused_mul_add(dpos, u0 - um, pos_part(u0))) - neg_part(u0);
-    const T g0 = T(1) - C * slope - T(2) * D;
-    const T from_right = (C * pos_part(up) + D) * rp;      // iteration j+1 read u[j] as its left cell
-    const T from_left = (-C * neg_part(um) + D) * rm;      // iteration j-1 read u[j] as its right cell
-    return from_right + (in0 ? g0 * r0 : T(0)) + from_left;
+    const T dl = u0 - um, dr = up - u0;
+    return __builtin_elementwise_abs(u0) + (u0 >= T(0) ? dl : dr);
+}
+// Both one-sided differences count where u = 0 (of either sign).
+template <class T> __device__ __forceinline__ T burgers_slope_at_zero(T slope, T u0, T up)
+{
+#pragma clang fp contract(off)
+    return u0 == T(0) ? slope + (up - u0) : slope;
+}
+
+// One u_bar[j] of its three terms: iteration j+1 read u[j] as its left cell, j-1 as its right cell:
+//   g_-(j+1) r_bar[j+1] + g_+(j-1) r_bar[j-1] + g_0(j) r_bar[j],
+//   g_0(i) = 1 - 2D - C( |u_i| + [u_i>=0](u_i-u_{i-1}) + [u_i<=0](u_{i+1}-u_i) )
+// from_left = g_+(j-1) r_bar[j-1]; r_bar zero where the iteration does not exist; in0: iteration j exists.
+template <class T> __device__ __forceinline__ T burgers_adjoint_cell(T slope, T up, T from_left, T r0, T rp, T C, T D, bool in0)
+{
+#pragma clang fp contract(off)
+    const T sides = fma_t(burgers_to_left(up, C, D), rp, from_left);
+    const T g0 = fma_t(-C, slope, T(1)) - T(2) * D;
+    return in0 ? fma_t(g0, r0, sides) : sides;
+}
+
+// The same from the values at j-1, j, j+1.
+template <class T> __device__ __forceinline__ T burgers_adjoint_terms(T um, T u0, T up, T rm, T r0, T rp, T C, T D, bool in0)
+{
+    const T slope = burgers_slope_at_zero(burgers_slope(um, u0, up), u0, up);
+    return burgers_adjoint_cell(slope, up, mul_rounded(burgers_to_right(um, C, D), rm), r0, rp, C, D, in0);
 }
 
 }  // namespace sadj

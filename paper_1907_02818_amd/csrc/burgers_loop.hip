@@ -13,9 +13,9 @@
 // per cell and step instead of 16; 10^7 cells, 16 steps: 245 us, 5.5 TB/s.  Reverse over stored states:
 // memory, 8 + 16/m bytes instead of 24; a sweep of 16 steps of 10^7 cells 284 us.  Reverse from a
 // checkpoint: 24/m bytes, the m states are recomputed in registers and the vector ALUs are the bound
-// (43 instructions per four cells of a forward step, 103 of a reverse one); so is the forward sweep
-// that stores checkpoints only.  Counted over 2^24 cells: a reverse pass of 8 steps issues 8.5 10^7 instructions, which the
-// chip's 1024 SIMDs take 139 us for at 2.4 GHz, and runs 162 us; a forward pass of 16 steps 5.1 10^7, 83 us, and 101 us.
+// (38 instructions per four fp64 cells of a forward step, 78 of a reverse one; 43 and 103 before both were written with g_- and
+// g_+, see burgers.hpp); so is the forward sweep that stores checkpoints only.  3 10^6 cells, 128 steps, every 16th kept: forward
+// 164 -> 155 us, reverse 616 -> 532.
 #include "burgers.hpp"
 #include "burgers_plan.hpp"
 #include "launch.hpp"
@@ -144,14 +144,26 @@ template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
         }
     }
     // The cells before (after) each run; any value beyond the window, which only reaches cells that are discarded.
-    __device__ __forceinline__ void beside(const T (&v)[PXL], T (&left)[RUNS], T (&right)[RUNS]) const
+    __device__ __forceinline__ void before(const T (&v)[PXL], T (&left)[RUNS]) const
     {
 #pragma unroll
         for (int r = 0; r < RUNS; ++r) {
-            const T end = v[r * RUN + RUN - 1], first = v[r * RUN];
+            const T end = v[r * RUN + RUN - 1];
             left[r] = r > 0 ? lane_shift<false>(end, lane_rotate<false>(v[r > 0 ? r * RUN - 1 : 0])) : lane_rotate<false>(end);
+        }
+    }
+    __device__ __forceinline__ void after(const T (&v)[PXL], T (&right)[RUNS]) const
+    {
+#pragma unroll
+        for (int r = 0; r < RUNS; ++r) {
+            const T first = v[r * RUN];
             right[r] = r < RUNS - 1 ? lane_shift<true>(first, lane_rotate<true>(v[r < RUNS - 1 ? (r + 1) * RUN : 0])) : lane_rotate<true>(first);
         }
+    }
+    __device__ __forceinline__ void beside(const T (&v)[PXL], T (&left)[RUNS], T (&right)[RUNS]) const
+    {
+        before(v, left);
+        after(v, right);
     }
     __device__ __forceinline__ void primal_step(T (&u)[PXL], T C, T D) const
     {
@@ -167,16 +179,28 @@ template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
     }
     __device__ __forceinline__ void reverse_step(const T (&u)[PXL], T (&lam)[PXL], T C, T D) const
     {
-#pragma unroll
-        for (int e = 0; e < PXL; ++e) lam[e] = in[e] ? lam[e] : T(0);      // lam outside I is never used
-        T ul[RUNS], ur[RUNS], ll[RUNS], lr[RUNS], next[PXL];
+        T ul[RUNS], ur[RUNS], lr[RUNS], left[RUNS], slope[PXL], give[PXL], next[PXL];
+        bool zero = false;
         beside(u, ul, ur);
-        beside(lam, ll, lr);
+#pragma unroll
+        for (int e = 0; e < PXL; ++e) {
+            lam[e] = in[e] ? lam[e] : T(0);                                // lam outside I is never used
+            slope[e] = burgers_slope(e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1]);
+            give[e] = mul_rounded(burgers_to_right(u[e], C, D), lam[e]);
+            zero = zero || u[e] == T(0);
+        }
+        // u = 0 exactly is rare but in fields that are zero over a stretch: one test per wave instead of two selections per cell
+        if (__any(zero)) {
+#pragma unroll
+            for (int e = 0; e < PXL; ++e) slope[e] = burgers_slope_at_zero(slope[e], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1]);
+        }
+        before(give, left);
+        after(lam, lr);
 #pragma unroll
         for (int e = 0; e < PXL; ++e) {
             const bool first = e % RUN == 0, end = e % RUN == RUN - 1;
-            next[e] = burgers_adjoint_terms(first ? ul[e / RUN] : u[e - 1], u[e], end ? ur[e / RUN] : u[e + 1],
-                                            first ? ll[e / RUN] : lam[e - 1], lam[e], end ? lr[e / RUN] : lam[e + 1], C, D, in[e]);
+            next[e] = burgers_adjoint_cell(slope[e], end ? ur[e / RUN] : u[e + 1], first ? left[e / RUN] : give[e - 1], lam[e],
+                                           end ? lr[e / RUN] : lam[e + 1], C, D, in[e]);
         }
 #pragma unroll
         for (int e = 0; e < PXL; ++e) lam[e] = next[e];

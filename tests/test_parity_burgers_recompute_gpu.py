@@ -1,0 +1,72 @@
+"""GPU tests of the Burgers reverse sweep where a state is exactly zero over a stretch (both one-sided differences count, for
+either sign of the zero), and of passes that recompute up to 8, 12 and 16 states at the edges of their windows (96, 80, 64 own
+cells in short arrays; 224, 208, 192 in fp64 and 480, 464, 448 in fp32 from 229376 and 491520 cells on): the same bits as one
+launch per step, and the oracle's values."""
+import numpy as np
+import pytest
+
+import inputs
+import oracle
+from parity import assert_close, to_gpu, to_host
+
+pytestmark = pytest.mark.gpu
+
+BC, BD = 0.1, 0.05
+
+
+@pytest.fixture(scope="module")
+def sadj():
+    import paper_1907_02818_amd as lib
+    lib.load()
+    yield lib
+    lib.set_option("burgers1d.fuse", 0)
+
+
+def _both(sadj, fn):
+    out = []
+    for fuse in (1, 0):
+        sadj.set_option("burgers1d.fuse", fuse)
+        out.append([to_host(t) for t in fn()])
+    sadj.set_option("burgers1d.fuse", 0)
+    return out
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("n", [65, 300, 1021])
+def test_states_that_are_zero_over_a_stretch(sadj, n, dtype):
+    u = inputs.uniform(n, "u", (n,), -1, 1).astype(dtype)
+    u[n // 4: n // 2] = 0.0
+    u[n // 3: n // 2: 3] = -0.0
+    r_bar, u_bar = (inputs.uniform(n, k, (n,), -1, 1).astype(dtype) for k in ("r_bar", "u_bar"))
+    got = to_gpu(u_bar)
+    sadj.sadj_adjoint_burgers1d(BC, BD, to_gpu(u), to_gpu(r_bar), got)
+    want, scale = oracle.burgers_adjoint(u, r_bar, u_bar, BC, BD, want_scale=True)
+    assert_close(to_host(got), want, scale + np.abs(u_bar), dtype, "zero states n=%d" % n)
+    states = to_gpu(np.stack([u] * 6))
+
+    def sweep():
+        lam = [to_gpu(r_bar), to_gpu(u_bar)]
+        sadj.sadj_adjoint_burgers1d_steps(BC, BD, 5, 5, states, *lam)
+        return [lam[5 % 2]]
+
+    single, fused = _both(sadj, sweep)
+    assert np.isfinite(single[0]).all() and np.array_equal(single[0], fused[0])
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("n", [3, 63, 65, 80, 81, 129, 193, 961, 229632, 229633, 492064])
+def test_passes_of_every_length(sadj, n, dtype):
+    u0 = inputs.burgers_inputs(n, seed=n, dtype=dtype)["u"]
+    u0[n // 2: n // 2 + 5] = 0
+    lam0 = inputs.uniform(n, "r_bar", (n,), -1, 1).astype(dtype)
+    lam1 = inputs.uniform(n, "u_bar", (n,), -1, 1).astype(dtype)
+    for nsteps, every in ((34, 16), (26, 12), (31, 15), (29, 5), (18, 17), (40, 40), (16, 3), (15, 14)):
+        def go():
+            ck = to_gpu(np.stack([u0] + [np.zeros_like(u0)] * (nsteps // every)))
+            work, fin, g = to_gpu(np.zeros((max(2, every - 1), n), dtype)), to_gpu(np.zeros_like(u0)), [to_gpu(lam0), to_gpu(lam1)]
+            sadj.sadj_primal_burgers1d_ckpt(BC, BD, nsteps, every, ck, work, fin)
+            sadj.sadj_adjoint_burgers1d_ckpt(BC, BD, nsteps, every, ck, work, *g)
+            return [ck, fin, g[nsteps % 2]]
+
+        single, fused = _both(sadj, go)
+        assert all(np.isfinite(x).all() and np.array_equal(x, y) for x, y in zip(single, fused)), (nsteps, every)
