@@ -12,10 +12,10 @@
 // What bounds it (fp64; one launch per step before).  Forward with every state stored: memory, 8 + 8/m bytes
 // per cell and step instead of 16; 10^7 cells, 16 steps: 245 us, 5.5 TB/s.  Reverse over stored states:
 // memory, 8 + 16/m bytes instead of 24; a sweep of 16 steps of 10^7 cells 284 us.  Reverse from a
-// checkpoint: 24/m bytes, the m states are recomputed in registers and the vector ALUs are the bound
-// (38 instructions per four fp64 cells of a forward step, 78 of a reverse one; 43 and 103 before both were written with g_- and
-// g_+, see burgers.hpp); so is the forward sweep that stores checkpoints only.  3 10^6 cells, 128 steps, every 16th kept: forward
-// 164 -> 155 us, reverse 616 -> 532.
+// checkpoint: 24/m bytes, the m states are recomputed in registers and the vector ALUs are the bound; so is the forward sweep
+// that stores checkpoints only.  Per four fp64 cells a forward step takes 38 instructions and a reverse one 78 (43 and 103 before
+// both were written with g_- and g_+, see burgers.hpp): 3 10^6 cells, 128 steps, every 16th kept, forward 164 -> 155 us, reverse
+// 616 -> 532, and -> 486 with passes of 16 steps.
 #include "burgers.hpp"
 #include "burgers_plan.hpp"
 #include "launch.hpp"
@@ -49,7 +49,7 @@ constexpr int kLoopWaves = 4;         // windows per workgroup
 constexpr int kAhead = 4;             // states in flight in a pass over stored states
 constexpr int kLoopH = 16;            // cells recomputed on either side of a window
 constexpr int kShortH = 8;            // the same in short passes over stored states
-static_assert(kLoopH >= kForwardSteps && kLoopH >= kReverseSteps && kLoopH >= 2 * kRecomputeSteps - 1 && kShortH >= kShortSteps, "halo of a pass");
+static_assert(kLoopH >= kForwardSteps && kLoopH >= kReverseSteps && kShortH >= kShortSteps, "halo of a pass");
 
 // Cells that a window stores, of the 64 * PXL that it holds.
 __host__ __device__ constexpr int own_cells(int PXL, int halo) { return 64 * PXL - 2 * halo; }
@@ -287,11 +287,10 @@ __device__ __forceinline__ void burgers_reverse_stored(const BurgersReverseArgs 
 
 // Reverse steps from a checkpoint: the states are recomputed forward from state t into registers, except
 // where a further checkpoint is met.
-template <class T, int PXL, bool GUARD>
+template <class T, int PXL, bool GUARD, int M>
 __device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseArgs &a, long w, int lane)
 {
-    constexpr int M = kRecomputeSteps;
-    const Lane<T, PXL, GUARD, false> L(w, lane, a.n, kLoopH);
+    const Lane<T, PXL, GUARD, false> L(w, lane, a.n, 2 * M);
     const T C = (T)a.C, D = (T)a.D;
     T lam[PXL], u[M][PXL];
     L.load(static_cast<const T *>(a.src), u[0]);
@@ -317,19 +316,19 @@ __device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseAr
     L.store(static_cast<T *>(a.lam_out), lam, true);
 }
 
-// REM: number of steps modulo kAhead of a pass over stored states, -1: the states are recomputed
+// REM: number of steps modulo kAhead of a pass over stored states; -M: up to M states are recomputed
 template <class T, int PXL, int REM> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_reverse_kernel(BurgersReverseArgs a)
 {
-    const int halo = REM >= 0 ? a.halo : kLoopH, W = 64 * PXL, V = own_cells(PXL, halo);
+    const int halo = REM >= 0 ? a.halo : -2 * REM, W = 64 * PXL, V = own_cells(PXL, halo);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * V - halo;
     if (w * V >= a.n) return;
     if (x0 >= 1 && x0 + W - 1 <= a.n - 2) {
         if constexpr (REM >= 0) burgers_reverse_stored<T, PXL, false, REM>(a, w, lane);
-        else burgers_reverse_recompute<T, PXL, false>(a, w, lane);
+        else burgers_reverse_recompute<T, PXL, false, -REM>(a, w, lane);
     } else {
         if constexpr (REM >= 0) burgers_reverse_stored<T, PXL, true, REM>(a, w, lane);
-        else burgers_reverse_recompute<T, PXL, true>(a, w, lane);
+        else burgers_reverse_recompute<T, PXL, true, -REM>(a, w, lane);
     }
 }
 
@@ -362,9 +361,9 @@ template <class T, int REM> static hipError_t reverse_T(const BurgersReverseArgs
     constexpr int WIDE = 32 / (int)sizeof(T), NARROW = 2;
     const dim3 block(64 * kLoopWaves);
     if (wide_windows<T>(a.n))
-        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, REM>), loop_grid(WIDE, REM >= 0 ? a.halo : kLoopH, a.n), block, 0, stream, a);
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, REM>), loop_grid(WIDE, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
     else
-        hipLaunchKernelGGL((burgers_reverse_kernel<T, NARROW, REM>), loop_grid(NARROW, REM >= 0 ? a.halo : kLoopH, a.n), block, 0, stream, a);
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, NARROW, REM>), loop_grid(NARROW, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
     return hipGetLastError();
 }
 
@@ -376,6 +375,15 @@ template <class T> static hipError_t reverse_stored_T(const BurgersReverseArgs &
     case 1: return reverse_T<T, 1>(a, stream);
     case 2: return reverse_T<T, 2>(a, stream);
     default: return reverse_T<T, 3>(a, stream);
+    }
+}
+
+template <class T> static hipError_t reverse_recompute_T(const BurgersReverseArgs &a, hipStream_t stream)
+{
+    switch (recompute_kernel(a.m)) {
+    case 8: return reverse_T<T, -8>(a, stream);
+    case 12: return reverse_T<T, -12>(a, stream);
+    default: return reverse_T<T, -16>(a, stream);
     }
 }
 
@@ -401,7 +409,7 @@ struct LoopOps {
         if (m == 1 && at % 16 == 0) return launch_adjoint_burgers1d(is_f64, n, C, D, src, lam_in, lam_out, 1, stream);
         const BurgersReverseArgs a{src, rows, lam_in, lam_out, n, C, D, m, first, every, m <= kShortSteps ? kShortH : kLoopH};
         if (every == 1) return is_f64 ? reverse_stored_T<double>(a, stream) : reverse_stored_T<float>(a, stream);
-        return is_f64 ? reverse_T<double, -1>(a, stream) : reverse_T<float, -1>(a, stream);
+        return is_f64 ? reverse_recompute_T<double>(a, stream) : reverse_recompute_T<float>(a, stream);
     }
     int reverse_first(const char *u, const char *lam_in, char *lam_out) const
     {
@@ -437,6 +445,8 @@ hipError_t launch_burgers_ckpt_reverse(int is_f64, long n, long nsteps, long eve
     LoopOps ops{is_f64, n, C, D, stream};
     char *const l[2] = {static_cast<char *>(lam[0]), static_cast<char *>(lam[1])};
     BurgersCkptReverse<LoopOps> plan{ops, static_cast<const char *>(ckpt), static_cast<char *>(work), (size_t)n * (is_f64 ? 8 : 4), every};
+    const bool wide = is_f64 ? wide_windows<double>(n) : wide_windows<float>(n);
+    plan.most = recompute_steps(n, wide ? (is_f64 ? 256 : 512) : 128, every);
     return (hipError_t)plan.run(nsteps, l);
 }
 

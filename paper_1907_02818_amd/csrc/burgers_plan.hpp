@@ -20,7 +20,7 @@ constexpr int kForwardSteps = 16;     // forward: one cell per step and side
 constexpr int kReverseSteps = 15;     // reverse, all states in memory: one cell per step and side
 constexpr int kShortSteps = 8;        // longest of the passes over states in memory that recompute half as many cells
 constexpr size_t kUnevenRow = (size_t)96 << 20;
-constexpr int kRecomputeSteps = 8;    // reverse from a checkpoint: two cells per step and side
+constexpr int kRecomputeSteps = 16;   // reverse from a checkpoint: two cells per step and side
 
 inline long ceil_div(long a, long b) { return (a + b - 1) / b; }
 
@@ -54,6 +54,44 @@ __attribute__((always_inline)) constexpr void stored_reverse_schedule(int m, con
         }
 #pragma unroll
     for (int j = 0; j < AHEAD; ++j) step((REM + j) % AHEAD);
+}
+
+// The kernel that takes a pass of m recomputed steps: it holds 8, 12 or 16 states in registers (109, 141, 173 of them in fp64: 4, 3
+// and 2 waves per SIMD) and recomputes two cells per state and side.
+inline int recompute_kernel(int m) { return m <= 8 ? 8 : m <= 12 ? 12 : 16; }
+
+// Longest pass of a checkpointed reverse sweep (8, 12 or 16 steps) on n cells in windows of `window`: the one whose passes cost
+// least per step.  A pass costs its launch, about 60 instructions in each of 10^6 cells, and per cell 20 instructions' time for
+// its loads and stores, 9 instructions for each state that it recomputes and 17 for each reverse step, times window / own cells;
+// fewer waves per SIMD cost 3 and 5 %.  Long passes spare launches and, where they cover a checkpoint interval, the launches that
+// would find the states inside it; short ones recompute fewer cells beside their windows.  Sweeps with 8 / 12 / 16 at most: fp64
+// 3 10^6 cells, 128 steps, every 16th kept 532 / 572 / 486 us; 1.7 10^7, 64, 16th 1426 / 1545 / 1347; 1.2 10^6, 185, 6th 337 / 287 / -;
+// 6 10^6, 64, 8th 439 / - / 507; fp32 3 10^6, 128, 16th 345 / 364 / 306; 10^6, 128, 12th 204 / 139 / -; 8 10^6, 64, 8th 304 / - / 387.
+inline int recompute_steps(long n, int window, long every)
+{
+    int best = 8;
+    double best_cost = 0;
+    for (int most = 8; most <= kRecomputeSteps; most += 4) {
+        double steps, passes, work;
+        auto pass = [&](int m, long kept) {                      // kept: states found in memory, the first one among them
+            const int states = recompute_kernel(m);
+            const double cells = (double)window / (window - 4 * states), waves = states == 8 ? 1 : states == 12 ? 1.03 : 1.05;
+            return (9.0 * (m - kept) + 17.0 * m) * cells * waves;
+        };
+        if (every <= most) {
+            steps = (double)(most / every * every);
+            passes = 1;
+            work = pass((int)steps, most / every);
+        } else {
+            const long parts = ceil_div(every, most), size = ceil_div(every, parts);
+            steps = (double)every;
+            passes = (double)(parts + ceil_div(parts - 1, kForwardSteps / size));
+            work = parts * pass((int)size, 1) + 9.0 * 1.14 * (parts - 1) * size;
+        }
+        const double cost = (passes * (60e6 + 20 * (double)n) + work * (double)n) / steps;
+        if (most == 8 || cost < best_cost) { best = most; best_cost = cost; }
+    }
+    return best;
 }
 
 // nsteps forward steps that store every state (row t at base + t*row, row 0 given).
@@ -124,6 +162,7 @@ template <class Ops> struct BurgersCkptReverse {
     char *work;
     size_t row;
     long every;
+    int most = kRecomputeSteps;         // longest pass
 
     const char *ckpt_row(long j) const { return ckpt + (size_t)j * row; }
 
@@ -163,7 +202,6 @@ template <class Ops> struct BurgersCkptReverse {
         }
         if (int e = ops.reverse_first(u, lam[0], lam[1])) return e;
         if (top == 0) return 0;
-        int most = kRecomputeSteps;
         long passes = count(top, most);
         if (passes == 1 && top % 2 == 0) {                       // one pass would have to write the buffer it reads
             most = (int)(top / 2);
