@@ -24,6 +24,8 @@
 // The outputs must be arrays other than a and b: neighbouring workgroups read the frame of a and
 // the ring of b while this one writes.
 #include "launch.hpp"
+#include "ahead.hpp"
+#include "ahead3d.hpp"
 #include "tile3d.hpp"
 
 #include <type_traits>
@@ -356,10 +358,185 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_kernel(PairArgs a)
     else      pair_march<T, BX, BY, PY, PX, true>(a, tix, tiy, zs, ze, sq1, sq2);
 }
 
-// Tiles of 64 x 32 (fp32: 128 x 32) cells, one workgroup per CU; on small grids, whose chunks the 5 planes that a
-// workgroup marches beyond its own dominate, 64 x 16 cells (fp32: two workgroups per CU), whose march
+// The same on grids that do not fill the chip, where a workgroup marches few planes and the time from a plane's request to the
+// next plane's is what counts.  As in ahead3d.hpp all accesses go through buffer resources, without a condition around any of
+// them, so that D planes are really in flight: a plane that is not wanted has a resource of zero bytes and reads as zero, cells
+// outside I have an offset beyond any plane.  One instantiation serves core and remainder.  The sums are pair_march's, bit for bit.
+// One workgroup per CU and two planes ahead; three planes 2 % slower, two workgroups per CU 5 to 10 % (fp32) or more registers than
+// there are (fp64: 162).  25 steps, the tiles below / this, fp32 96 x 130 x 164 237 / 182 us, 128^3 189 / 153, 300 x 80 x 80 216 / 183, 64^3
+// 97 / 90; fp64 40 x 300 x 96 227 / 191.
+template <class T, int BX, int BY, int PX, int D>
+__global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_ahead_kernel(PairArgs a)
+{
+    using G = PairTile<T, BX, BY, 1, PX>;
+    using V = Vec<T, PX>;
+    static_assert(G::HS == 1, "one frame cell per thread at most");
+    constexpr int LX1 = G::LX1, LX2 = G::LX2;
+    constexpr T W0 = T(3.0 * star_w<1>(0)), W1 = T(star_w<1>(1));
+    __shared__ __attribute__((aligned(16))) T sq1[2 * G::PLANE1];
+    __shared__ __attribute__((aligned(16))) T sq2[2 * G::PLANE2];
+    int tix, tiy, zs, ze;
+    block_to_tile(a.map, blockIdx.x, tix, tiy, zs, ze);
+    const int tid = threadIdx.x, tx = tid % BX, ty = tid / BX;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const unsigned bytes = (unsigned)nx * (unsigned)ny * (unsigned)sizeof(T);
+    const int x0 = tix * G::TX, y0 = tiy * G::TY;
+    const int x = x0 + tx * PX, y = y0 + ty;
+    auto in_I = [&](int xx, int yy) { return xx >= 1 && xx < nx - 1 && yy >= 1 && yy < ny - 1; };
+    auto offset = [&](int xx, int yy) { return ((unsigned)yy * (unsigned)nx + (unsigned)xx) * (unsigned)sizeof(T); };
+    bool in[PX], any_I = false;
+#pragma unroll
+    for (int e = 0; e < PX; ++e) { in[e] = in_I(x + e, y); any_I = any_I || in[e]; }
+    const unsigned ioff = any_I ? offset(x, y) : kNowhere;
+    const unsigned goff = x < nx && y < ny ? offset(x, y) : kNowhere;         // rows are whole vectors
+    // this thread's frame cell, which is a ring cell for the first NRING threads
+    int lx, ly;
+    const bool frame = G::frame_cell(tid, 0, lx, ly), ring = tid < G::NRING;
+    const bool hin = frame && in_I(x0 - 2 + lx, y0 - 2 + ly), rin = ring && hin;
+    const unsigned hoff = hin ? offset(x0 - 2 + lx, y0 - 2 + ly) : kNowhere, roff = ring ? hoff : kNowhere;
+    const int hl = frame ? ly * LX1 + lx : 0;                                 // (0, 0) is a corner nobody reads
+    const int ring1 = ring ? ly * LX1 + lx : LX1 + 1, ring2 = ring ? (ly - 1) * LX2 + (lx - 1) : 0;
+
+    auto plane_of = [&](const void *base, int z, bool wanted) {
+        char *p = static_cast<char *>(const_cast<void *>(base)) + (long long)z * (long long)bytes;
+        return __builtin_amdgcn_make_buffer_rsrc(p, 0, wanted ? bytes : 0u, 0x00020000);
+    };
+    auto plane_in_I = [&](int z) { return z >= 1 && z < nz - 1; };
+    const int zi0 = zs - 2, zi1 = ze + 1;        // q planes that reach the outputs [zs, ze)
+    auto a1_wanted = [&](int z) { return z >= zs - 1 && z <= ze && plane_in_I(z); };
+
+    // in flight: c and a of plane z on tile and frame, b of plane z - 1 on tile and ring
+    V sc[D], sa[D], sb[D];
+    Vec<T, 1> shc[D], sha[D], sbr[D];
+    auto issue = [&](int z, int d) {
+        const bool used = z <= zi1 && plane_in_I(z);
+        const auto rc = plane_of(a.c, z, used), ra = plane_of(a.a, z, used), rb = plane_of(a.b, z - 1, a1_wanted(z - 1));
+        sc[d] = buffer_load<T, PX, kCached>(rc, ioff);
+        sa[d] = buffer_load<T, PX, kCached>(ra, ioff);
+        shc[d] = buffer_load<T, 1, kCached>(rc, hoff);
+        sha[d] = buffer_load<T, 1, kCached>(ra, hoff);
+        sb[d] = buffer_load<T, PX, kCached>(rb, ioff);
+        sbr[d] = buffer_load<T, 1, kCached>(rb, roff);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    // as in pair_march
+    T acc1[PX][3], acc1r[3], acc2[PX][3], c_prev[PX], c_prev_r = T(0), am_prev[PX], q2[PX], q2r = T(0), a1m[PX];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        acc1r[k] = T(0);
+#pragma unroll
+        for (int e = 0; e < PX; ++e) acc1[e][k] = acc2[e][k] = T(0);
+    }
+#pragma unroll
+    for (int e = 0; e < PX; ++e) c_prev[e] = am_prev[e] = q2[e] = a1m[e] = T(0);
+
+    auto step = [&](int z, int d) {
+        T *s1 = sq1 + ((z - zi0) & 1) * G::PLANE1;
+        T *s2 = sq2 + ((z - zi0) & 1) * G::PLANE2;
+        T am[PX], cc[PX], cb[PX];
+        V qo;
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            cc[e] = sc[d].v[e];
+            cb[e] = sb[d].v[e];
+            am[e] = in[e] ? sa[d].v[e] : T(0);
+            qo.v[e] = in[e] ? cc[e] * sa[d].v[e] : T(0);
+        }
+        T amr = sha[d].v[0], ccr = shc[d].v[0], cbr = sbr[d].v[0], qr = ccr * amr;
+        st_vec<T, PX>(s1 + (2 + ty) * LX1 + 2 + tx * PX, qo);
+        s1[hl] = qr;
+#pragma unroll
+        for (int e = 0; e < PX; ++e) s2[(1 + ty) * LX2 + 1 + tx * PX + e] = q2[e];
+        if (ring) s2[ring2] = q2r;
+#pragma unroll
+        for (int e = 0; e < PX; ++e) { computed(cc[e]); computed(cb[e]); computed(am[e]); computed(qo.v[e]); }
+        computed(amr); computed(ccr); computed(cbr); computed(qr);
+        issue(z + D, d);
+        __syncthreads();
+
+        // ---- stage 2: q' of plane z-2 -> a'' sums of planes z-3, z-2, z-1
+        V o;
+        {
+            const T *at = s2 + (1 + ty) * LX2 + 1 + tx * PX;
+#pragma unroll
+            for (int e = 0; e < PX; ++e) {
+                const T left = e > 0 ? q2[e > 0 ? e - 1 : 0] : at[-1], right = e < PX - 1 ? q2[e < PX - 1 ? e + 1 : 0] : at[PX];
+                const T s = W0 * q2[e] + W1 * (left + right) + W1 * (at[e - LX2] + at[e + LX2]);
+                acc2[e][1] += s + T(2) * a1m[e];
+                acc2[e][0] += W1 * q2[e];
+                acc2[e][2] += W1 * q2[e];
+                acc2[e][2] -= am_prev[e];                                     // -a m of plane z-1
+                o.v[e] = acc2[e][0];
+            }
+        }
+        const int zo2 = z - 3, zo1 = z - 1;
+        buffer_store<T, PX, kCached>(plane_of(a.out_a, zo2, zo2 >= zs && zo2 < ze), goff, o);
+
+        // ---- stage 1: q of plane z -> a' sums of planes z-1, z, z+1
+        {
+            const T *at = s1 + (2 + ty) * LX1 + 2 + tx * PX;
+            const V up = ld_vec<T, PX>(at - LX1), down = ld_vec<T, PX>(at + LX1);
+#pragma unroll
+            for (int e = 0; e < PX; ++e) {
+                const T left = e > 0 ? qo.v[e > 0 ? e - 1 : 0] : at[-1], right = e < PX - 1 ? qo.v[e < PX - 1 ? e + 1 : 0] : at[PX];
+                const T s = W0 * qo.v[e] + W1 * (left + right) + W1 * (up.v[e] + down.v[e]);
+                acc1[e][1] += s + T(2) * am[e];
+                acc1[e][0] += W1 * qo.v[e];
+                acc1[e][2] += W1 * qo.v[e];
+            }
+            if (ring) {
+                const T *ar = s1 + ring1;
+                const T s = W0 * qr + W1 * (ar[-1] + ar[1]) + W1 * (ar[-LX1] + ar[LX1]);
+                acc1r[1] += s + T(2) * amr;
+                acc1r[0] += W1 * qr;
+                acc1r[2] += W1 * qr;
+            }
+        }
+        // a' of plane z-1 is complete: form q' and -a' m from it
+        const bool wanted = a1_wanted(zo1);
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            const T a1 = acc1[e][0] + cb[e];
+            a1m[e] = wanted && in[e] ? a1 : T(0);
+            q2[e] = wanted && in[e] ? c_prev[e] * a1 : T(0);
+            o.v[e] = -a1m[e];
+        }
+        q2r = wanted && rin ? c_prev_r * (acc1r[0] + cbr) : T(0);
+        buffer_store<T, PX, kCached>(plane_of(a.out_b, zo1, zo1 >= zs && zo1 < ze), goff, o);
+        acc1r[0] = acc1r[1]; acc1r[1] = acc1r[2]; acc1r[2] = T(0);
+        c_prev_r = ccr;
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            acc1[e][0] = acc1[e][1]; acc1[e][1] = acc1[e][2]; acc1[e][2] = T(0);
+            acc2[e][0] = acc2[e][1]; acc2[e][1] = acc2[e][2]; acc2[e][2] = T(0);
+            c_prev[e] = cc[e];
+            am_prev[e] = am[e];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    const int last = zi1 + 1;
+#pragma unroll
+    for (int d = 0; d < D; ++d) issue(zi0 + d, d);
+    int z = zi0;
+    for (; z + D - 1 <= last; z += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) step(z + d, d);
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) {
+        if (z + d > last) return;
+        step(z + d, d);
+    }
+}
+
+// Beyond the grids of the march above, tiles of 64 x 32 (fp32: 128 x 32) cells, one workgroup per CU; on small grids, whose chunks the
+// 5 planes that a workgroup marches beyond its own dominate, 64 x 16 cells (fp32: two workgroups per CU), whose march
 // step takes 0.72 (fp32: 0.79) of the time.  25 steps, default / small tiles: fp64 24^3 125 / 101 us, 64^3
 // 134 / 110, 128^3 309 / 307; fp32 24^3 146 / 91, 64^3 152 / 96, 96 x 130 x 164 262 / 242, 128^3 191 / 194.
+// The cost prices these two shapes only.  It decides where passes take three steps, which round differently, so that a grid's
+// results stay what they were.
 struct PairPlan {
     TileMap map;
     bool small;
@@ -387,6 +564,18 @@ long adjoint_wave3d_pair_cost(int is_f64, int nx, int ny, int nz)
     return plan_pair(is_f64, nx, ny, nz, LaunchOptions{}).cost;
 }
 
+// Where the march with its requests ahead is taken, by the bytes of the five arrays (340 drawn grids, geometric mean of the time in
+// the shapes above over its time, smallest in brackets).  The arrays of a pass are found in the last-level cache, which this march
+// relies on: fp32 up to 60 MB 1.14 (1.00), 60 .. 130 MB 1.18 (1.05); against the default tiles, which the last passes of a
+// three-step sweep would take, 130 .. 230 MB 1.05 and more, 230 .. 300 MB 0.95 (0.93); fp64 30 .. 60 MB 1.10 (0.98), default tiles up
+// to 230 MB 1.22 (1.12), 230 .. 300 MB 1.09 (0.98).  fp64 in small tiles below 30 MB 0.98 (0.88): a
+// chunk of one to four planes leaves no request to run ahead of.
+static bool pair_runs_ahead(int is_f64, int nx, int ny, int nz, const PairPlan &plan)
+{
+    const double bytes = 5.0 * nx * ny * nz * (is_f64 ? 8 : 4);
+    return bytes <= 230e6 && (!is_f64 || !plan.small || bytes >= 30e6);
+}
+
 template <class T, int PX>
 static hipError_t launch_pair(PairArgs a, const LaunchOptions &opt, hipStream_t stream)
 {
@@ -399,6 +588,11 @@ static hipError_t launch_pair(PairArgs a, const LaunchOptions &opt, hipStream_t 
     if (a.nx % PX != 0) return hipErrorNotSupported;
     const PairPlan plan = plan_pair(sizeof(T) == 8, a.nx, a.ny, a.nz, opt);
     a.map = plan.map;
+    if (pair_runs_ahead(sizeof(T) == 8, a.nx, a.ny, a.nz, plan_pair(sizeof(T) == 8, a.nx, a.ny, a.nz, LaunchOptions{}))) {
+        plan_march(a.map, a.nx, a.ny, a.nz, 64, 16, 2, opt);
+        hipLaunchKernelGGL((adj_wave3d_pair_ahead_kernel<T, BX, BY, 2, 2>), dim3(a.map.total_blocks), dim3(BX * BY), ahead_pad(opt), stream, a);
+        return hipGetLastError();
+    }
     if (plan.small) {
         using S = PairTile<T, BX, BY, 1, 2>;
         const unsigned spad = sizeof(T) == 8 ? one_workgroup_per_cu_pad(sizeof(T) * 2 * (S::PLANE1 + S::PLANE2), opt.lds_pad) : 0;

@@ -74,25 +74,25 @@ def test_passes_of_every_length(sadj, n, dtype):
 
 @pytest.mark.parametrize("fuse", [0, 1])
 def test_single_precision_roundings_do_not_add_up_to_one_side(sadj, fuse):
-    """128 reverse steps over given states against the same in double: a step's roundings, 3.3e-8 of lam, add up with either sign, to at most
-    sqrt(128) of that, 3.7e-7 (bound 6e-7).  1 - 2D rounded by itself is off the same way in every cell and step: 2.9e-6."""
+    """128 reverse steps over states that are given, another one for each step, against the same in double with C and D as fp32 holds
+    them.  A step's roundings are 3.3e-8 of lam; independent from step to step they add up to at most sqrt(128) of that, 3.7e-7
+    (bound 6e-7).  1 - 2D rounded by itself is off the same way in every cell and step, which adds up to 3e-6."""
     n, nsteps = 4001, 128
-    u = inputs.burgers_inputs(n, seed=1, dtype=np.float32)["u"]
+    states = inputs.uniform(1, "u", (nsteps + 1, n), -1, 1).astype(np.float32)
     lam0 = inputs.uniform(n, "r_bar", (n,), -1, 1).astype(np.float32)
+    c, d = float(np.float32(BC)), float(np.float32(BD))
     want = lam0.astype(np.float64)
-    v = u.astype(np.float64)
-    um, u0, up = v[:-2], v[1:-1], v[2:]
-    slope = np.abs(u0) + (u0 >= 0) * (u0 - um) + (u0 <= 0) * (up - u0)
-    for _ in range(nsteps):
-        want[0] = want[-1] = 0
-        rm, r0, rp, want = want[:-2], want[1:-1], want[2:], np.zeros(n)
-        want[:-2][1:] += ((BC * np.maximum(u0, 0) + BD) * r0)[1:]
-        want[2:][:-1] += ((-BC * np.minimum(u0, 0) + BD) * r0)[:-1]
-        want[1:-1] += (1 - 2 * BD - BC * slope) * r0
-    states, lam = to_gpu(np.stack([u] * (nsteps + 1))), [to_gpu(lam0), to_gpu(np.zeros_like(lam0))]
+    for k in range(nsteps - 1, -1, -1):
+        u = states[k].astype(np.float64)
+        um, u0, up = u[:-2], u[1:-1], u[2:]
+        slope = np.abs(u0) + (u0 >= 0) * (u0 - um) + (u0 <= 0) * (up - u0)
+        r, want = want[1:-1], np.zeros(n)
+        want[:-2] += (c * np.maximum(u0, 0) + d) * r
+        want[2:] += (-c * np.minimum(u0, 0) + d) * r
+        want[1:-1] += (1 - 2 * d - c * slope) * r
+    g, lam = to_gpu(states), [to_gpu(lam0), to_gpu(np.zeros_like(lam0))]
     sadj.set_option("burgers1d.fuse", fuse)
-    sadj.sadj_adjoint_burgers1d_steps(BC, BD, nsteps, nsteps, states, *lam)
+    sadj.sadj_adjoint_burgers1d_steps(BC, BD, nsteps, nsteps, g, *lam)
     sadj.set_option("burgers1d.fuse", 0)
     got = to_host(lam[nsteps % 2]).astype(np.float64)
-    inside = slice(1, n - 1)
-    assert np.linalg.norm(got[inside] - want[inside]) < 6e-7 * np.linalg.norm(want[inside])
+    assert np.linalg.norm(got[1:-1] - want[1:-1]) < 6e-7 * np.linalg.norm(want[1:-1])
