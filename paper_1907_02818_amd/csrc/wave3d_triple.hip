@@ -17,6 +17,7 @@
 // q1 and q2 go to LDS as soon as they are formed, c of older planes waits in LDS (all but 320 bytes of the
 // 160 KB are used in fp64), and all LDS planes share one geometry.  Then memory: 512^3 fp64, a pass
 // takes 1.02 ms = 5.2 TB/s on its 40 bytes per cell (a two-step pass 0.95 ms), 0.34 ms per step against 0.48.
+#include "ahead3d.hpp"
 #include "launch.hpp"
 #include "tile3d.hpp"
 
@@ -375,11 +376,216 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_triple_kernel(TripleArgs a)
     else      triple_march<T, BX, BY, PY, PX, true>(a, tix, tiy, zs, ze, sq0, sq1, sq2, cold, coldr);
 }
 
+// The same on grids that do not fill the chip, with D planes in flight, as adj_wave3d_pair_ahead_kernel in wave3d_pair.hip: no
+// condition around any memory access, planes that are not wanted and cells outside I read as zero.  One row of cells per thread
+// and one frame cell at most, so that c of the three planes before stays in registers.  The sums are triple_march's, bit for bit.
+// One workgroup per CU with two planes in flight; three 2 % slower.  25 steps, the wide tiles / this: fp64 128^3 255 / 213 us, 160^3
+// 462 / 352, 300 x 80 x 80 320 / 236; fp32 197 x 68 x 260 383 / 247, 64 x 400 x 400 657 / 453, 200^3 536 / 490.  What bounds it on the
+// smaller ones is the serial chain of a step, 0.9 us: LDS, barrier and three stages, for 8 planes beyond each chunk.
+template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(BX *BY) void adj_wave3d_triple_ahead_kernel(TripleArgs a)
+{
+    using G = TripleTile<T, BX, BY, 1, PX>;
+    using V = Vec<T, PX>;
+    static_assert(G::HS == 1, "one frame cell per thread at most");
+    constexpr int LX = G::LX;
+    constexpr T W0 = T(3.0 * star_w<1>(0)), W1 = T(star_w<1>(1));
+    __shared__ T sq0[2 * G::PLANE];
+    __shared__ T sq1[2 * G::PLANE];
+    __shared__ T sq2[2 * G::PLANE];
+    int tix, tiy, zs, ze;
+    block_to_tile(a.map, blockIdx.x, tix, tiy, zs, ze);
+    const int tid = threadIdx.x, tx = tid % BX, ty = tid / BX;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const unsigned bytes = (unsigned)nx * (unsigned)ny * (unsigned)sizeof(T);
+    const int x0 = tix * G::TX, y0 = tiy * G::TY;
+    const int x = x0 + tx * PX, y = y0 + ty;
+    auto in_I = [&](int xx, int yy) { return xx >= 1 && xx < nx - 1 && yy >= 1 && yy < ny - 1; };
+    auto offset = [&](int xx, int yy) { return ((unsigned)yy * (unsigned)nx + (unsigned)xx) * (unsigned)sizeof(T); };
+    bool in[PX], any_I = false;
+#pragma unroll
+    for (int e = 0; e < PX; ++e) { in[e] = in_I(x + e, y); any_I = any_I || in[e]; }
+    const unsigned ioff = any_I ? offset(x, y) : kNowhere;
+    const unsigned goff = x < nx && y < ny ? offset(x, y) : kNowhere;         // rows are whole vectors
+    int lx, ly;
+    const bool frame = G::frame_cell(tid, 0, lx, ly);
+    const bool ring1 = tid < G::N1 + G::N2, ring2 = tid < G::N1;              // run stage 1, stage 2 as well
+    const bool hin = frame && in_I(x0 - 3 + lx, y0 - 3 + ly);
+    const unsigned hoff = hin ? offset(x0 - 3 + lx, y0 - 3 + ly) : kNowhere, roff = ring1 ? hoff : kNowhere;
+    const int hl = frame ? ly * LX + lx : 0;                                  // (0, 0) is a corner nobody reads
+    const int own = (3 + ty) * LX + 3 + tx * PX;
+
+    auto plane_of = [&](const void *base, int z, bool wanted) {
+        char *p = static_cast<char *>(const_cast<void *>(base)) + (long long)z * (long long)bytes;
+        return __builtin_amdgcn_make_buffer_rsrc(p, 0, wanted ? bytes : 0u, 0x00020000);
+    };
+    auto plane_in_I = [&](int z) { return z >= 1 && z < nz - 1; };
+    const int zi0 = zs - 3, zi1 = ze + 2;        // q0 planes that reach the outputs [zs, ze)
+    auto a1_wanted = [&](int z) { return z >= zs - 2 && z <= ze + 1 && plane_in_I(z); };
+    auto a2_wanted = [&](int z) { return z >= zs - 1 && z <= ze && plane_in_I(z); };
+
+    // in flight: c and a of plane z on tile and frame, b of plane z - 1 on tile, D1 and D2
+    V sc[D], sa[D], sb[D];
+    Vec<T, 1> shc[D], sha[D], sbr[D];
+    auto issue = [&](int z, int d) {
+        const bool used = z <= zi1 && plane_in_I(z);
+        const auto rc = plane_of(a.c, z, used), ra = plane_of(a.a, z, used), rb = plane_of(a.b, z - 1, a1_wanted(z - 1));
+        sc[d] = buffer_load<T, PX, kCached>(rc, ioff);
+        sa[d] = buffer_load<T, PX, kCached>(ra, ioff);
+        shc[d] = buffer_load<T, 1, kCached>(rc, hoff);
+        sha[d] = buffer_load<T, 1, kCached>(ra, hoff);
+        sb[d] = buffer_load<T, PX, kCached>(rb, ioff);
+        sbr[d] = buffer_load<T, 1, kCached>(rb, roff);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto star = [&](const T *sp, T (&acc)[PX][3]) {
+        const T *at = sp + own;
+        T q[PX];
+#pragma unroll
+        for (int e = 0; e < PX; ++e) q[e] = at[e];
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            const T left = e > 0 ? q[e > 0 ? e - 1 : 0] : at[-1], right = e < PX - 1 ? q[e < PX - 1 ? e + 1 : 0] : at[PX];
+            acc[e][1] += W0 * q[e] + W1 * (left + right) + W1 * (at[e - LX] + at[e + LX]);
+            acc[e][0] += W1 * q[e];
+            acc[e][2] += W1 * q[e];
+        }
+    };
+    auto star_ring = [&](const T *at, T (&acc)[3]) {
+        const T q = at[0];
+        acc[1] += W0 * q + W1 * (at[-1] + at[1]) + W1 * (at[-LX] + at[LX]);
+        acc[0] += W1 * q;
+        acc[2] += W1 * q;
+    };
+
+    // as in triple_march; c1, c2, c3: c of the three planes before
+    T acc1[PX][3], acc2[PX][3], acc3[PX][3], acc1r[3], acc2r[3], a1m[PX], c1[PX], c2[PX], c3[PX], c1r = T(0), c2r = T(0), c3r = T(0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        acc1r[k] = acc2r[k] = T(0);
+#pragma unroll
+        for (int e = 0; e < PX; ++e) acc1[e][k] = acc2[e][k] = acc3[e][k] = T(0);
+    }
+#pragma unroll
+    for (int e = 0; e < PX; ++e) a1m[e] = c1[e] = c2[e] = c3[e] = T(0);
+    bool q1_valid = false, q2_valid = false;     // the planes of q1 and q2 that this step reads were staged by the last one
+
+    auto step = [&](int z, int d) {
+        const int buf = (z - zi0) & 1;
+        T *s0 = sq0 + buf * G::PLANE;
+        const T *s1 = sq1 + buf * G::PLANE, *s2 = sq2 + buf * G::PLANE;
+        T *n1 = sq1 + (buf ^ 1) * G::PLANE, *n2 = sq2 + (buf ^ 1) * G::PLANE;
+        T am[PX], cc[PX], cb[PX];
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            cc[e] = sc[d].v[e];
+            cb[e] = sb[d].v[e];
+            am[e] = in[e] ? sa[d].v[e] : T(0);
+            s0[own + e] = in[e] ? cc[e] * sa[d].v[e] : T(0);
+        }
+        T amr = sha[d].v[0], ccr = shc[d].v[0], cbr = sbr[d].v[0];
+        s0[hl] = ccr * amr;
+#pragma unroll
+        for (int e = 0; e < PX; ++e) { computed(cc[e]); computed(cb[e]); computed(am[e]); }
+        computed(amr); computed(ccr); computed(cbr);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(z + D, d);
+        __syncthreads();
+
+        // ---- stage 3: q2 of plane z-4; a3 of plane z-5 is complete
+        if (q2_valid) star(s2, acc3);
+        V o;
+#pragma unroll
+        for (int e = 0; e < PX; ++e) o.v[e] = acc3[e][0];
+        const int zo3 = z - 5, zo2 = z - 3;
+        buffer_store<T, PX, kCached>(plane_of(a.out_a, zo3, zo3 >= zs && zo3 < ze), goff, o);
+
+        // ---- stage 2: q1 of plane z-2; a2 of plane z-3 is complete
+        if (q1_valid) {
+            star(s1, acc2);
+            if (ring2) star_ring(s1 + hl, acc2r);
+        }
+        q2_valid = a2_wanted(zo2);
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            const T a2m = q2_valid && in[e] ? acc2[e][0] : T(0);
+            n2[own + e] = in[e] ? c3[e] * a2m : T(0);
+            acc3[e][0] = acc3[e][1];
+            acc3[e][1] = acc3[e][2] + T(2) * a2m;
+            acc3[e][2] = -a1m[e];                                             // of plane z-2
+            acc2[e][0] = acc2[e][1];
+            acc2[e][1] = acc2[e][2];
+            acc2[e][2] = -am[e];                                              // of plane z
+            o.v[e] = -a2m;
+        }
+        if (ring2) n2[hl] = hin ? c3r * acc2r[0] : T(0);
+        acc2r[0] = acc2r[1]; acc2r[1] = acc2r[2]; acc2r[2] = -amr;
+        buffer_store<T, PX, kCached>(plane_of(a.out_b, zo2, zo2 >= zs && zo2 < ze), goff, o);
+
+        // ---- stage 1: q0 of plane z; a1 of plane z-1 is complete
+        star(s0, acc1);
+        if (ring1) star_ring(s0 + hl, acc1r);
+        q1_valid = a1_wanted(z - 1);
+#pragma unroll
+        for (int e = 0; e < PX; ++e) {
+            const T v = acc1[e][0] + cb[e];
+            a1m[e] = q1_valid && in[e] ? v : T(0);
+            n1[own + e] = in[e] ? c1[e] * v : T(0);
+            acc2[e][1] += T(2) * a1m[e];
+            acc1[e][0] = acc1[e][1] + T(2) * am[e];
+            acc1[e][1] = acc1[e][2];
+            acc1[e][2] = T(0);
+            c3[e] = c2[e]; c2[e] = c1[e]; c1[e] = cc[e];
+        }
+        const T vr = acc1r[0] + cbr;
+        const T a1r = q1_valid && hin ? vr : T(0);
+        if (ring1) n1[hl] = hin ? c1r * vr : T(0);
+        acc2r[1] += T(2) * a1r;
+        acc1r[0] = acc1r[1] + T(2) * amr;
+        acc1r[1] = acc1r[2];
+        acc1r[2] = T(0);
+        c3r = c2r; c2r = c1r; c1r = ccr;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    const int last = ze + 4;
+#pragma unroll
+    for (int d = 0; d < D; ++d) issue(zi0 + d, d);
+    int z = zi0;
+    for (; z + D - 1 <= last; z += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) step(z + d, d);
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) {
+        if (z + d > last) return;
+        step(z + d, d);
+    }
+}
+
+// Where the march with its requests ahead is taken: by the planes it marches against those of the wide tiles below (its step takes
+// 0.54, fp32 0.34, of theirs, whose cells are two and four times as many) and by the bytes of the five arrays, which it relies on
+// finding in the last-level cache.  318 drawn grids, time in the wide tiles over time of this march, geometric mean (smallest): with
+// this rule fp64 1.22 (0.99), fp32 1.31 (1.00) where it is taken; 300 .. 420 MB fp64 1.02 (0.90), 260 .. 420 MB fp32 1.01 (0.86);
+// 8 x 1000 x 1024, where short chunks march 2.2 and 4.1 times the planes, 0.77 and 0.87.  The grid alone decides.
+static bool triple_runs_ahead(int is_f64, int nx, int ny, int nz)
+{
+    if (5.0 * nx * ny * nz * (is_f64 ? 8 : 4) > (is_f64 ? 300e6 : 260e6)) return false;
+    TileMap wide, ahead;
+    plan_march(wide, nx, ny, nz, is_f64 ? 64 : 128, 32, 4, LaunchOptions{});
+    plan_march(ahead, nx, ny, nz, 64, 16, 4, LaunchOptions{});
+    return (is_f64 ? 54 : 34) * march_planes(ahead, 8) < 100 * march_planes(wide, 8);
+}
+
 template <class T, int PX>
 static hipError_t launch_triple(TripleArgs a, const LaunchOptions &opt, hipStream_t stream)
 {
     constexpr int BX = 32, BY = 16, PY = 2;
     using G = TripleTile<T, BX, BY, PY, PX>;
+    if (triple_runs_ahead(sizeof(T) == 8, a.nx, a.ny, a.nz)) {
+        plan_march(a.map, a.nx, a.ny, a.nz, 64, 16, 4, opt);
+        hipLaunchKernelGGL((adj_wave3d_triple_ahead_kernel<T, BX, BY, 2, 2>), dim3(a.map.total_blocks), dim3(BX * BY), ahead_pad(opt), stream, a);
+        return hipGetLastError();
+    }
     // each chunk marches 8 planes beyond its own: plan as a march of radius 4
     plan_march(a.map, a.nx, a.ny, a.nz, G::TX, G::TY, 4, opt);
     hipLaunchKernelGGL((adj_wave3d_triple_kernel<T, BX, BY, PY, PX>), dim3(a.map.total_blocks), dim3(G::NT), 0, stream, a);
