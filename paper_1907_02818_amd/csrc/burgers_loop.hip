@@ -13,7 +13,7 @@
 // per cell and step instead of 16; 10^7 cells, 16 steps: 245 us, 5.5 TB/s.  Reverse over stored states:
 // memory, 8 + 16/m bytes instead of 24; a sweep of 16 steps of 10^7 cells 284 us.  Reverse from a
 // checkpoint: 24/m bytes, the m states are recomputed in registers and the vector ALUs are the bound; so is the forward sweep
-// that stores checkpoints only.  Per four fp64 cells a forward step takes 38 instructions and a reverse one 78 (43 and 103 before
+// that stores checkpoints only.  Per four fp64 cells a forward step takes 38 instructions and a reverse one about 75 (43 and 103 before
 // both were written with g_- and g_+, see burgers.hpp): 3 10^6 cells, 128 steps, every 16th kept, forward 164 -> 155 us, reverse
 // 616 -> 532, and -> 486 with passes of 16 steps.
 #include "burgers.hpp"
