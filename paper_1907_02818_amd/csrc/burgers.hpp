@@ -21,25 +21,46 @@ __device__ __forceinline__ float neg_part(float v) { float r; asm("v_min_f32 %0,
 template <class T> __device__ __forceinline__ T burgers_to_left(T u, T C, T D) { return fma_t(C, pos_part(u), D); }
 template <class T> __device__ __forceinline__ T burgers_to_right(T u, T C, T D) { return fma_t(-C, neg_part(u), D); }
 
-// r_i from (um, u0, up) = u[i-1], u[i], u[i+1].
-template <class T> __device__ __forceinline__ T burgers_primal_cell(T um, T u0, T up, T C, T D)
+// Values that are not finite.  The formula multiplies the difference it does not use by 0, which gives NaN where that difference
+// is not finite; the short forms below leave it out, and a NaN or an infinity beside a cell would get lost.  So:
+//   - Where the short form of r_i is not finite the formula as it stands is evaluated.  The short form is finite only if u_{i-1}, u_i,
+//     u_{i+1} all are: g_- d_l and g_+ d_r are not finite (0 times infinity included) as soon as one of them is not.
+//   - The slope adds 0 times the value that it leaves out, and 0 u_i.  (Not the difference: of finite values it may overflow.)
+// Neither changes a bit of a finite result.  The loops ask once per pass or step and wave whether this is needed.
+template <class T> __device__ __forceinline__ T burgers_primal_formula(T um, T u0, T up, T C, T D)
 {
 #pragma clang fp contract(off)
-    return u0 + fma_t(burgers_to_right(u0, C, D), up - u0, -(burgers_to_left(u0, C, D) * (u0 - um)));
+    const T conv = fma_t(pos_part(u0), u0 - um, neg_part(u0) * (up - u0));
+    return fma_t(D, fma_t(T(-2), u0, um) + up, fma_t(-C, conv, u0));
 }
 
-// The upwind slope without the second term that u = 0 has: |u| + (u >= 0 ? d_l : d_r).  max(u,0) - min(u,0) is |u|.
+// r_i from (um, u0, up) = u[i-1], u[i], u[i+1].  CHECKED: for values that may not be finite.
+template <bool CHECKED, class T> __device__ __forceinline__ T burgers_primal_cell(T um, T u0, T up, T C, T D)
+{
+#pragma clang fp contract(off)
+    const T r = u0 + fma_t(burgers_to_right(u0, C, D), up - u0, -(burgers_to_left(u0, C, D) * (u0 - um)));
+    if (CHECKED && !__builtin_isfinite(r)) return burgers_primal_formula(um, u0, up, C, D);
+    return r;
+}
+
+// The upwind slope of values that are finite and not 0: |u| + (u >= 0 ? d_l : d_r).  max(u,0) - min(u,0) is |u|.
 template <class T> __device__ __forceinline__ T burgers_slope(T um, T u0, T up)
 {
 #pragma clang fp contract(off)
     const T dl = u0 - um, dr = up - u0;
     return __builtin_elementwise_abs(u0) + (u0 >= T(0) ? dl : dr);
 }
-// Both one-sided differences count where u = 0 (of either sign).
-template <class T> __device__ __forceinline__ T burgers_slope_at_zero(T slope, T u0, T up)
+// u is 0 or not finite: one class test, which costs what a comparison costs.
+__device__ __forceinline__ bool burgers_zero_or_not_finite(double u) { return __builtin_amdgcn_class(u, 0x267); }
+__device__ __forceinline__ bool burgers_zero_or_not_finite(float u) { return __builtin_amdgcn_classf(u, 0x267); }
+// The slope of any values, from burgers_slope's: both differences count where u = 0 (of either sign), and values that are not
+// finite where they are not used.
+template <class T> __device__ __forceinline__ T burgers_slope_in_full(T slope, T um, T u0, T up)
 {
 #pragma clang fp contract(off)
-    return u0 == T(0) ? slope + (up - u0) : slope;
+    const T unused = u0 > T(0) ? up : u0 < T(0) ? um : T(0);
+    const T all = fma_t(T(0), u0, fma_t(T(0), unused, slope));
+    return u0 == T(0) ? all + (up - u0) : all;
 }
 
 // g_0 = 1 - 2D - C slope.  1 - 2D is the same for all cells, and what its rounding loses adds up over the steps of a loop.  fp64 rounds it
@@ -67,7 +88,7 @@ template <class T> __device__ __forceinline__ T burgers_adjoint_cell(T slope, T 
 // The same from the values at j-1, j, j+1.
 template <class T> __device__ __forceinline__ T burgers_adjoint_terms(T um, T u0, T up, T rm, T r0, T rp, T C, T D, bool in0)
 {
-    const T slope = burgers_slope_at_zero(burgers_slope(um, u0, up), u0, up);
+    const T slope = burgers_slope_in_full(burgers_slope(um, u0, up), um, u0, up);
     return burgers_adjoint_cell(slope, up, mul_rounded(burgers_to_right(um, C, D), rm), r0, rp, C, D, in0);
 }
 

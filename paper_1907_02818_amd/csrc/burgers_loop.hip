@@ -165,34 +165,43 @@ template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
         before(v, left);
         after(v, right);
     }
-    __device__ __forceinline__ void primal_step(T (&u)[PXL], T C, T D) const
+    template <bool CHECKED> __device__ __forceinline__ void primal_step(T (&u)[PXL], T C, T D) const
     {
         T ul[RUNS], ur[RUNS], next[PXL];
         beside(u, ul, ur);
 #pragma unroll
         for (int e = 0; e < PXL; ++e) {
-            const T val = burgers_primal_cell(e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1], C, D);
+            const T val = burgers_primal_cell<CHECKED>(e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1], C, D);
             next[e] = in[e] ? val : u[e];
         }
 #pragma unroll
         for (int e = 0; e < PXL; ++e) u[e] = next[e];
     }
+    // Whether a value of the window (any lane's) is not finite.
+    __device__ __forceinline__ bool not_finite(const T (&u)[PXL]) const
+    {
+        bool any = false;
+#pragma unroll
+        for (int e = 0; e < PXL; ++e) any = any || !__builtin_isfinite(u[e]);
+        return __any(any);
+    }
     __device__ __forceinline__ void reverse_step(const T (&u)[PXL], T (&lam)[PXL], T C, T D) const
     {
         T ul[RUNS], ur[RUNS], lr[RUNS], left[RUNS], slope[PXL], give[PXL], next[PXL];
-        bool zero = false;
+        bool rare = false;
         beside(u, ul, ur);
 #pragma unroll
         for (int e = 0; e < PXL; ++e) {
             lam[e] = in[e] ? lam[e] : T(0);                                // lam outside I is never used
             slope[e] = burgers_slope(e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1]);
             give[e] = mul_rounded(burgers_to_right(u[e], C, D), lam[e]);
-            zero = zero || u[e] == T(0);
+            rare = rare || burgers_zero_or_not_finite(u[e]);
         }
         // u = 0 exactly is rare but in fields that are zero over a stretch: one test per wave instead of two selections per cell
-        if (__any(zero)) {
+        if (__any(rare)) {
 #pragma unroll
-            for (int e = 0; e < PXL; ++e) slope[e] = burgers_slope_at_zero(slope[e], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1]);
+            for (int e = 0; e < PXL; ++e)
+                slope[e] = burgers_slope_in_full(slope[e], e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1]);
         }
         before(give, left);
         after(lam, lr);
@@ -214,12 +223,11 @@ __device__ __forceinline__ double lane_value(double v, int from)
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), from), __builtin_amdgcn_readlane(__double2loint(v), from));
 }
 
-template <class T, int PXL, bool GUARD, bool SPREAD>
-__device__ __forceinline__ void burgers_forward_window(const BurgersForwardArgs &a, long w, int lane)
+// A pass over one window; u: its cells after the last step.
+template <bool CHECKED, class T, int PXL, bool GUARD, bool SPREAD>
+__device__ __forceinline__ void burgers_forward_pass(const BurgersForwardArgs &a, const Lane<T, PXL, GUARD, SPREAD> &L, T (&u)[PXL])
 {
-    const Lane<T, PXL, GUARD, SPREAD> L(w, lane, a.n, kLoopH);
     const T C = (T)a.C, D = (T)a.D;
-    T u[PXL];
     L.load(static_cast<const T *>(a.src), u);
     T *row = static_cast<T *>(a.rows);
     long next = a.first;
@@ -227,16 +235,16 @@ __device__ __forceinline__ void burgers_forward_window(const BurgersForwardArgs 
     // loop.  Fetched where they are needed, each step of an end window would wait for memory
     // (16 stored steps of 10^6 fp32 cells: 29 us instead of 13).
     T ends = T(0);
-    if (GUARD && !a.hold && lane < 32) ends = row[(long)min(lane & 15, a.m - 1) * a.n + (lane < 16 ? 0 : a.n - 1)];
+    if (GUARD && !a.hold && L.lane < 32) ends = row[(long)min(L.lane & 15, a.m - 1) * a.n + (L.lane < 16 ? 0 : a.n - 1)];
     static_assert(kForwardSteps <= 16, "a lane per given end cell");
     for (int s = 0; s < a.m;) {
         const int stop = next < a.m ? (int)next : a.m;
         for (; s + 2 <= stop; s += 2) {           // by twos: the cells need no moves between registers
-            L.primal_step(u, C, D);
-            L.primal_step(u, C, D);
+            L.template primal_step<CHECKED>(u, C, D);
+            L.template primal_step<CHECKED>(u, C, D);
         }
         if (s < stop) {
-            L.primal_step(u, C, D);
+            L.template primal_step<CHECKED>(u, C, D);
             ++s;
         }
         if (s != next) continue;
@@ -252,6 +260,17 @@ __device__ __forceinline__ void burgers_forward_window(const BurgersForwardArgs 
         next += a.every;
     }
     if (a.last) L.store(static_cast<T *>(a.last), u, true);
+}
+
+// A cell that is not finite stays so and makes its neighbours' next values so, in either form of the step: if the last state
+// is finite all were, else the pass is done again in the checked form (the pass never writes what it reads).
+template <class T, int PXL, bool GUARD, bool SPREAD>
+__device__ __forceinline__ void burgers_forward_window(const BurgersForwardArgs &a, long w, int lane)
+{
+    const Lane<T, PXL, GUARD, SPREAD> L(w, lane, a.n, kLoopH);
+    T u[PXL];
+    burgers_forward_pass<false>(a, L, u);
+    if (L.not_finite(u)) burgers_forward_pass<true>(a, L, u);
 }
 
 template <class T, int PXL, bool SPREAD> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_forward_kernel(BurgersForwardArgs a)
@@ -285,18 +304,15 @@ __device__ __forceinline__ void burgers_reverse_stored(const BurgersReverseArgs 
     L.store(static_cast<T *>(a.lam_out), lam, true);
 }
 
-// Reverse steps from a checkpoint: the states are recomputed forward from state t into registers, except
-// where a further checkpoint is met.
-template <class T, int PXL, bool GUARD, int M>
-__device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseArgs &a, long w, int lane)
+// States t .. t+m-1, recomputed forward from state t in u[0] except where a further checkpoint is met.  Returns whether the checked
+// form is needed (see burgers_forward_window; a row that is read starts a new chain of states).
+template <bool CHECKED, class T, int PXL, bool GUARD, int M>
+__device__ __forceinline__ bool burgers_recompute(const BurgersReverseArgs &a, const Lane<T, PXL, GUARD, false> &L, T (&u)[M][PXL])
 {
-    const Lane<T, PXL, GUARD, false> L(w, lane, a.n, 2 * M);
     const T C = (T)a.C, D = (T)a.D;
-    T lam[PXL], u[M][PXL];
-    L.load(static_cast<const T *>(a.src), u[0]);
-    L.load(static_cast<const T *>(a.lam_in), lam);
     const T *row = static_cast<const T *>(a.rows);
     int next = a.first;
+    bool again = false;
 #pragma unroll
     for (int s = 1; s < M; ++s) {
         if (s >= a.m) continue;
@@ -307,9 +323,23 @@ __device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseAr
         } else {
 #pragma unroll
             for (int e = 0; e < PXL; ++e) u[s][e] = u[s - 1][e];
-            L.primal_step(u[s], C, D);
+            L.template primal_step<CHECKED>(u[s], C, D);
+            if (!CHECKED && (s + 1 == a.m || s + 1 == next)) again = again || L.not_finite(u[s]);
         }
     }
+    return again;
+}
+
+// Reverse steps from a checkpoint.
+template <class T, int PXL, bool GUARD, int M>
+__device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseArgs &a, long w, int lane)
+{
+    const Lane<T, PXL, GUARD, false> L(w, lane, a.n, 2 * M);
+    const T C = (T)a.C, D = (T)a.D;
+    T lam[PXL], u[M][PXL];
+    L.load(static_cast<const T *>(a.src), u[0]);
+    L.load(static_cast<const T *>(a.lam_in), lam);
+    if (burgers_recompute<false>(a, L, u)) burgers_recompute<true>(a, L, u);
 #pragma unroll
     for (int s = M - 1; s >= 0; --s)
         if (s < a.m) L.reverse_step(u[s], lam, C, D);

@@ -228,7 +228,7 @@ __device__ __forceinline__ void pri_burgers_segment(const Args1d &a, long xs, in
         const T u0 = uv[e];
         const bool in = GUARD ? (x + e >= 1 && x + e <= n - 2) : true;
         ok[e] = (GUARD && KEEP_ENDS) ? (x + e < n) : in;
-        const T val = burgers_primal_cell(um, u0, up, C, D);
+        const T val = burgers_primal_cell<true>(um, u0, up, C, D);
         out[e] = (GUARD && KEEP_ENDS) ? (in ? val : u0) : val;
     }
     store_cells<T, PX, GUARD>(rg, x, n, out, ok);
