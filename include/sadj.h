@@ -336,7 +336,7 @@ sadj_status sadj_describe_wave3d_plan(sadj_dtype dtype, int radius, long nx, lon
  * Process-wide integer options that select among equivalent launch strategies; they
  * never change what is computed, only how the regions are mapped to kernels.  Every
  * setting is deterministic (same inputs, same bits).  Settings that select another
- * kernel shape or instruction sequence ("*.variant", "wave2d.ychunk", "wave3d.order",
+ * kernel shape or instruction sequence ("*.variant", "wave2d.ychunk", "wave3d.order", "wave3d.ahead",
  * "stencil1d.functor", "star3d.functor") may round differently from each other within the usual
  * floating-point tolerance; "wave3d.zchunk", "wave3d.split", "wave3d.xcdmap",
  * "wave3d.band" and "wave3d.ldspad" only move work between workgroups and leave every
@@ -368,6 +368,10 @@ sadj_status sadj_describe_wave3d_plan(sadj_dtype dtype, int radius, long nx, lon
  *                    which limits how many workgroups share a CU: 0 (default) as much as
  *                    keeps it at one workgroup per CU (none for the 32 x 16 and fp32 64 x 16 tiles that
  *                    small grids take, which two share), -1 none, n > 0 exactly n (<= 65536).
+ *   "wave3d.ahead"   0 (default): 3-D wave and star calls on grids that do not fill the chip take kernels
+ *                    whose memory requests run ahead of the arithmetic; 1: the kernels and tiles of
+ *                    larger grids on every grid (slower there; they can be run on small arrays this
+ *                    way).  Bits of the wave adjoint and its time loops are the same under both.
  *   "wave3d.remainder" treatment of the boundary / remainder regions (Section 3.3.4) by
  *                    sadj_adjoint_wave3d:  0 (default) one dispatch, tiles that touch the
  *                    remainder run guarded statements, core tiles unguarded ones;

@@ -47,7 +47,7 @@ static inline AheadPlan plan_ahead(bool is_f64, int radius, int nx, int ny, int 
 {
     AheadPlan p;
     const double bytes = (double)nx * ny * nz * rule.words * (is_f64 ? 8 : 4);
-    if (opt.variant != 0 || opt.remainder != 0 || bytes > rule.limit) return p;
+    if (opt.variant != 0 || opt.remainder != 0 || opt.ahead != 0 || bytes > rule.limit) return p;
     const bool whole = nx % (is_f64 ? 2 : 4) == 0;
     const bool long_rows = rule.long_rows_stay && wide_tile_for_unaligned_rows(nx, is_f64 ? 8 : 4, radius, !is_f64) != 0;
     if (long_rows && whole) return p;

@@ -11,7 +11,7 @@
 
 namespace {
 
-std::atomic<long> g_zchunk{0}, g_variant{0}, g_ychunk2d{0}, g_variant2d{0}, g_remainder{0}, g_order{0}, g_functor1d{0}, g_functor_star{0}, g_burgers_fuse{0}, g_wave_fuse{0}, g_xcdmap{0}, g_band{0}, g_ldspad{0}, g_split{0};
+std::atomic<long> g_zchunk{0}, g_variant{0}, g_ychunk2d{0}, g_variant2d{0}, g_remainder{0}, g_order{0}, g_functor1d{0}, g_functor_star{0}, g_burgers_fuse{0}, g_wave_fuse{0}, g_xcdmap{0}, g_band{0}, g_ldspad{0}, g_split{0}, g_ahead{0};
 
 // Options are set one at a time; a call takes one consistent snapshot of all of them under
 // the same lock the setters hold, so it never sees a combination that was not in force at
@@ -31,6 +31,7 @@ sadj::LaunchOptions current_options()
     o.xcd_map = g_xcdmap.load();
     o.band = g_band.load();
     o.lds_pad = g_ldspad.load();
+    o.ahead = g_ahead.load();
     return o;
 }
 
@@ -280,6 +281,11 @@ sadj_status sadj_set_option(const char *name, long value)
         g_split = value;
         return SADJ_OK;
     }
+    if (!std::strcmp(name, "wave3d.ahead")) {
+        if (value < 0 || value > 1) return SADJ_ERR_UNSUPPORTED;
+        g_ahead = value;
+        return SADJ_OK;
+    }
     if (!std::strcmp(name, "wave3d.remainder")) {
         if (value < 0 || value > 2) return SADJ_ERR_UNSUPPORTED;
         g_remainder = value;
@@ -338,6 +344,7 @@ sadj_status sadj_get_option(const char *name, long *value)
     if (!std::strcmp(name, "wave2d.variant")) { *value = g_variant2d; return SADJ_OK; }
     if (!std::strcmp(name, "wave3d.remainder")) { *value = g_remainder; return SADJ_OK; }
     if (!std::strcmp(name, "wave3d.split")) { *value = g_split; return SADJ_OK; }
+    if (!std::strcmp(name, "wave3d.ahead")) { *value = g_ahead; return SADJ_OK; }
     if (!std::strcmp(name, "check.pointers")) { *value = g_check_pointers; return SADJ_OK; }
     if (!std::strcmp(name, "wave3d.order")) { *value = g_order; return SADJ_OK; }
     if (!std::strcmp(name, "wave3d.xcdmap")) { *value = g_xcdmap; return SADJ_OK; }

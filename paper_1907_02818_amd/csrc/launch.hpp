@@ -13,6 +13,7 @@ struct LaunchOptions {
     long band = 0;       // wave3d: tile rows per band of the tile numbering (0 = rows of tiles)
     long lds_pad = 0;    // 3-D marches: dynamic LDS bytes requested to limit workgroups per CU (0 = automatic, -1 = none)
     long split = 0;      // 3-D marches: 0 = left-over tiles may be cut finer than the rest, 1 = all tiles cut alike
+    long ahead = 0;      // 3-D marches: 1 = grids that do not fill the chip take the tiles of larger grids as well
     long remainder = 0;  // wave3d adjoint: remainder strategy (0 guarded where needed, 1 guarded everywhere, 2 split dispatches)
 };
 

@@ -588,7 +588,7 @@ static hipError_t launch_pair(PairArgs a, const LaunchOptions &opt, hipStream_t 
     if (a.nx % PX != 0) return hipErrorNotSupported;
     const PairPlan plan = plan_pair(sizeof(T) == 8, a.nx, a.ny, a.nz, opt);
     a.map = plan.map;
-    if (pair_runs_ahead(sizeof(T) == 8, a.nx, a.ny, a.nz, plan_pair(sizeof(T) == 8, a.nx, a.ny, a.nz, LaunchOptions{}))) {
+    if (opt.ahead == 0 && pair_runs_ahead(sizeof(T) == 8, a.nx, a.ny, a.nz, plan_pair(sizeof(T) == 8, a.nx, a.ny, a.nz, LaunchOptions{}))) {
         plan_march(a.map, a.nx, a.ny, a.nz, 64, 16, 2, opt);
         hipLaunchKernelGGL((adj_wave3d_pair_ahead_kernel<T, BX, BY, 2, 2>), dim3(a.map.total_blocks), dim3(BX * BY), ahead_pad(opt), stream, a);
         return hipGetLastError();

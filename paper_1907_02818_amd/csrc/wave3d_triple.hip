@@ -581,7 +581,7 @@ static hipError_t launch_triple(TripleArgs a, const LaunchOptions &opt, hipStrea
 {
     constexpr int BX = 32, BY = 16, PY = 2;
     using G = TripleTile<T, BX, BY, PY, PX>;
-    if (triple_runs_ahead(sizeof(T) == 8, a.nx, a.ny, a.nz)) {
+    if (opt.ahead == 0 && triple_runs_ahead(sizeof(T) == 8, a.nx, a.ny, a.nz)) {
         plan_march(a.map, a.nx, a.ny, a.nz, 64, 16, 4, opt);
         hipLaunchKernelGGL((adj_wave3d_triple_ahead_kernel<T, BX, BY, 2, 2>), dim3(a.map.total_blocks), dim3(BX * BY), ahead_pad(opt), stream, a);
         return hipGetLastError();

@@ -175,6 +175,19 @@ def test_every_option_the_library_knows_is_documented_in_the_header():
         assert isinstance(sadj.get_option(name), int)
 
 
+def test_the_tiles_of_larger_grids_can_be_asked_for():
+    small = lambda: sadj.sadj_describe_wave3d_plan(1, 4, 112, 96, 80, with_tiles=False)[0]   # noqa: E731
+    assert (small()["tile_w"], small()["tile_h"]) == (32, 16)
+    sadj.set_option("wave3d.ahead", 1)
+    try:
+        assert sadj.get_option("wave3d.ahead") == 1
+        assert (small()["tile_w"], small()["tile_h"]) == (64, 32)
+    finally:
+        sadj.set_option("wave3d.ahead", 0)
+    with pytest.raises(sadj.SadjError):
+        sadj.set_option("wave3d.ahead", 2)
+
+
 @pytest.mark.parametrize("xcdmap,band,zchunk,split", [(0, 0, 0, 0), (1, 0, 7, 0), (2, 0, 0, 0), (3, 0, 16, 1), (1, 3, 0, 0),
                                                       (2, 8, 5, 0), (1, 2, 33, 0), (0, 0, 0, 1), (3, 4, 0, 0)])
 @pytest.mark.parametrize("dtype_code,radius,shape", [(1, 4, (512, 512, 512)), (1, 4, (300, 500, 700)), (0, 4, (512, 512, 512)),

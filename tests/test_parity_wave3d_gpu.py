@@ -57,6 +57,7 @@ def sadj():
     lib.set_option("wave3d.remainder", 0)
     lib.set_option("wave3d.order", 0)
     lib.set_option("wave3d.split", 0)
+    lib.set_option("wave3d.ahead", 0)
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
@@ -394,12 +395,50 @@ TWO_GROUP = [(np.float64, 4, (64, 580, 520)), (np.float64, 1, (24, 400, 610)), (
              (np.float64, 3, (24, 610, 832)), (np.float32, 1, (24, 400, 1216))]
 
 
+def _tiles_left_over(sadj, dtype, radius, shape):
+    nz, ny, nx = shape
+    return sadj.sadj_describe_wave3d_plan(1 if dtype == np.float64 else 0, radius, nx, ny, nz, with_tiles=False)[0]["tiles_a"] > 0
+
+
 @pytest.mark.parametrize("dtype,radius,shape", TWO_GROUP)
 def test_shapes_whose_left_over_tiles_are_cut_finer(sadj, dtype, radius, shape):
+    """In the tiles that the grid takes by default, or, where those leave nothing over, in the tiles of larger grids."""
+    sadj.set_option("wave3d.ahead", 0 if _tiles_left_over(sadj, dtype, radius, shape) else 1)
+    try:
+        _check_left_over_tiles(sadj, dtype, radius, shape)
+    finally:
+        sadj.set_option("wave3d.ahead", 0)
+
+
+# the same in every tile shape and radius: of the march that grids which do not fill the chip take (0), of larger grids (1)
+LEFT_OVER = [(0, np.float32, 1, (16, 134, 1686)), (0, np.float32, 1, (16, 419, 616)), (0, np.float32, 2, (16, 744, 667)),
+             (0, np.float32, 2, (16, 840, 524)), (0, np.float32, 3, (24, 425, 1155)), (0, np.float32, 3, (24, 820, 524)),
+             (0, np.float32, 4, (40, 292, 1638)), (0, np.float32, 4, (40, 674, 672)), (0, np.float64, 1, (16, 431, 291)),
+             (0, np.float64, 1, (16, 304, 440)), (0, np.float64, 1, (40, 552, 136)), (0, np.float64, 2, (16, 179, 1379)),
+             (0, np.float64, 3, (24, 350, 784)), (0, np.float64, 4, (64, 698, 197)), (0, np.float64, 4, (64, 720, 196)),
+             (1, np.float32, 1, (16, 675, 345)), (1, np.float32, 1, (16, 376, 1320)), (1, np.float32, 2, (16, 840, 1184)),
+             (1, np.float32, 3, (24, 613, 837)), (1, np.float32, 4, (40, 200, 2438)), (1, np.float64, 1, (16, 314, 1656)),
+             (1, np.float64, 2, (16, 693, 752)), (1, np.float64, 2, (16, 290, 1720)), (1, np.float64, 3, (24, 499, 1028)),
+             (1, np.float64, 4, (64, 580, 520)), (1, np.float64, 4, (40, 209, 2316))]
+
+
+@pytest.mark.parametrize("off,dtype,radius,shape", LEFT_OVER)
+def test_left_over_tiles_of_both_marches(sadj, off, dtype, radius, shape):
+    sadj.set_option("wave3d.ahead", off)
+    try:
+        _check_left_over_tiles(sadj, dtype, radius, shape)
+    finally:
+        sadj.set_option("wave3d.ahead", 0)
+
+
+def _check_left_over_tiles(sadj, dtype, radius, shape):
+    import torch
     nz, ny, nx = shape
     info, tiles = sadj.sadj_describe_wave3d_plan(1 if dtype == np.float64 else 0, radius, nx, ny, nz)
-    if info["tiles_a"] == 0:
-        pytest.skip("this device's compute-unit count does not leave tiles over at this shape")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if info["tiles_a"] == 0 and cus != 256:
+        pytest.skip("%d compute units leave no tiles over at this shape" % cus)
+    assert info["tiles_a"] > 0, "no tiles left over: the shape does not test what it is here for"
     assert len({ze - zs for _, _, zs, ze in tiles}) >= 2
     d = inputs.wave_inputs(shape, 0.01, 0.1, seed=sum(shape), dtype=dtype, c_mode="iid")
     _check_adjoint(sadj, d, radius, dtype, with_prev=True, what="two groups R=%d %s" % (radius, shape))
