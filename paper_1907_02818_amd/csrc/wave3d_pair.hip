@@ -531,15 +531,14 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_ahead_kernel(PairArgs 
     }
 }
 
-// Beyond the grids of the march above, tiles of 64 x 32 (fp32: 128 x 32) cells, one workgroup per CU; on small grids, whose chunks the
-// 5 planes that a workgroup marches beyond its own dominate, 64 x 16 cells (fp32: two workgroups per CU), whose march
-// step takes 0.72 (fp32: 0.79) of the time.  25 steps, default / small tiles: fp64 24^3 125 / 101 us, 64^3
-// 134 / 110, 128^3 309 / 307; fp32 24^3 146 / 91, 64^3 152 / 96, 96 x 130 x 164 262 / 242, 128^3 191 / 194.
-// The cost prices these two shapes only.  It decides where passes take three steps, which round differently, so that a grid's
-// results stay what they were.
+// Beyond the grids of the march above, tiles of 64 x 32 (fp32: 128 x 32) cells, one workgroup per CU; on the smallest fp64 grids, whose
+// chunks the 5 planes that a workgroup marches beyond its own dominate, 64 x 16 cells, whose march step takes 0.72 of the
+// time.  25 steps, default / small tiles: fp64 24^3 125 / 101 us, 64^3 134 / 110, 128^3 309 / 307.  (fp32 grids like these take the march above.)
+// The cost decides where passes take three steps, which round differently.  It stays what it was when the default and the small
+// tiles (fp32: 0.79 of the step, two workgroups per CU) were all there was, so that a grid's results do as well.
 struct PairPlan {
     TileMap map;
-    bool small;
+    bool small;            // the 64 x 16 tiles cost less
     long cost;             // planes marched in default tiles, times 100
 };
 
@@ -554,7 +553,7 @@ static PairPlan plan_pair(int is_f64, int nx, int ny, int nz, const LaunchOption
         TileMap m;
         plan_march(m, nx, ny, nz, 64, 16, 2, opt, per_cu);
         const long cost = (is_f64 ? 72 : 79) * march_planes(m, 5, per_cu);
-        if (cost < p.cost) p = {m, true, cost};
+        if (cost < p.cost) p = {is_f64 ? m : p.map, true, cost};
     }
     return p;
 }
@@ -569,11 +568,13 @@ long adjoint_wave3d_pair_cost(int is_f64, int nx, int ny, int nz)
 // relies on: fp32 up to 60 MB 1.14 (1.00), 60 .. 130 MB 1.18 (1.05); against the default tiles, which the last passes of a
 // three-step sweep would take, 130 .. 230 MB 1.05 and more, 230 .. 300 MB 0.95 (0.93); fp64 30 .. 60 MB 1.10 (0.98), default tiles up
 // to 230 MB 1.22 (1.12), 230 .. 300 MB 1.09 (0.98).  fp64 in small tiles below 30 MB 0.98 (0.88): a
-// chunk of one to four planes leaves no request to run ahead of.
+// chunk of one to four planes leaves no request to run ahead of.  fp32 grids of more bytes that would cost less in 64 x 16 tiles
+// (few rows of 10^5 cells, whose default tiles are half empty) take it too: 6 x 16 x 200000, 9 steps, without / with requests ahead 466 / 452 us.
 static bool pair_runs_ahead(int is_f64, int nx, int ny, int nz, const PairPlan &plan)
 {
     const double bytes = 5.0 * nx * ny * nz * (is_f64 ? 8 : 4);
-    return bytes <= 230e6 && (!is_f64 || !plan.small || bytes >= 30e6);
+    if (!is_f64) return bytes <= 230e6 || plan.small;
+    return bytes <= 230e6 && (!plan.small || bytes >= 30e6);
 }
 
 template <class T, int PX>
@@ -593,11 +594,13 @@ static hipError_t launch_pair(PairArgs a, const LaunchOptions &opt, hipStream_t 
         hipLaunchKernelGGL((adj_wave3d_pair_ahead_kernel<T, BX, BY, 2, 2>), dim3(a.map.total_blocks), dim3(BX * BY), ahead_pad(opt), stream, a);
         return hipGetLastError();
     }
-    if (plan.small) {
-        using S = PairTile<T, BX, BY, 1, 2>;
-        const unsigned spad = sizeof(T) == 8 ? one_workgroup_per_cu_pad(sizeof(T) * 2 * (S::PLANE1 + S::PLANE2), opt.lds_pad) : 0;
-        hipLaunchKernelGGL((adj_wave3d_pair_kernel<T, BX, BY, 1, 2>), dim3(a.map.total_blocks), dim3(S::NT), spad, stream, a);
-        return hipGetLastError();
+    if constexpr (sizeof(T) == 8) {
+        if (plan.small) {
+            using S = PairTile<T, BX, BY, 1, 2>;
+            const unsigned spad = one_workgroup_per_cu_pad(sizeof(T) * 2 * (S::PLANE1 + S::PLANE2), opt.lds_pad);
+            hipLaunchKernelGGL((adj_wave3d_pair_kernel<T, BX, BY, 1, 2>), dim3(a.map.total_blocks), dim3(S::NT), spad, stream, a);
+            return hipGetLastError();
+        }
     }
     const size_t lds = sizeof(T) * 2 * (G::PLANE1 + G::PLANE2);
     const unsigned pad = one_workgroup_per_cu_pad(lds, opt.lds_pad);

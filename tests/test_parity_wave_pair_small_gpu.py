@@ -1,5 +1,5 @@
-"""GPU parity of the two-step passes in 64 x 16 tiles, which small grids take: exact on dyadic data at the edges
-of those tiles, one and several planes per chunk, NaN where values must not be read."""
+"""GPU parity of the two-step passes in 64 x 16 tiles, which small grids take (fp64; fp32 grids take tiles of the same size whose
+requests run ahead): exact on dyadic data at the edges of those tiles, one and several planes per chunk, NaN where values must not be read."""
 import numpy as np
 import pytest
 
