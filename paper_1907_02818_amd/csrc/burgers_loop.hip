@@ -474,9 +474,9 @@ hipError_t launch_burgers_ckpt_reverse(int is_f64, long n, long nsteps, long eve
     if (every == 1) return launch_burgers_history_reverse(is_f64, n, nsteps, C, D, ckpt, lam, stream);
     LoopOps ops{is_f64, n, C, D, stream};
     char *const l[2] = {static_cast<char *>(lam[0]), static_cast<char *>(lam[1])};
-    BurgersCkptReverse<LoopOps> plan{ops, static_cast<const char *>(ckpt), static_cast<char *>(work), (size_t)n * (is_f64 ? 8 : 4), every};
     const bool wide = is_f64 ? wide_windows<double>(n) : wide_windows<float>(n);
-    plan.most = recompute_steps(n, wide ? (is_f64 ? 256 : 512) : 128, every);
+    BurgersCkptReverse<LoopOps> plan{ops, static_cast<const char *>(ckpt), static_cast<char *>(work), (size_t)n * (is_f64 ? 8 : 4), every,
+                                     recompute_steps(n, wide ? (is_f64 ? 256 : 512) : 128, every)};
     return (hipError_t)plan.run(nsteps, l);
 }
 

@@ -162,7 +162,7 @@ template <class Ops> struct BurgersCkptReverse {
     char *work;
     size_t row;
     long every;
-    int most = kRecomputeSteps;         // longest pass
+    int most;                           // longest pass, see recompute_steps
 
     const char *ckpt_row(long j) const { return ckpt + (size_t)j * row; }
 

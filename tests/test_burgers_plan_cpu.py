@@ -13,6 +13,7 @@ DRIVER = r"""
 #include "burgers_plan.hpp"
 #include <cstdio>
 #include <cstdlib>
+#include <initializer_list>
 #include <vector>
 
 // One "row" is one byte of a flat buffer; val[i] says what row i holds: state t = t, adjoint of
@@ -20,7 +21,7 @@ DRIVER = r"""
 static std::vector<int> val;
 static std::vector<char> given;            // rows no launch may write
 static char arena[4096];
-static int checkpoint_every, failures;
+static int checkpoint_every, failures, most = sadj::kRecomputeSteps;
 static long top;
 #define NEED(c) do { if (!(c)) { if (failures++ < 5) std::printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
 
@@ -46,7 +47,7 @@ struct Ops {
     int reverse(const char *src, const char *rows, int first, int every, int m, const char *in, char *out)
     {
         ++launches;
-        NEED(m >= 1 && m <= (every == 1 ? sadj::kReverseSteps : sadj::kRecomputeSteps));
+        NEED(m >= 1 && m <= (every == 1 ? sadj::kReverseSteps : most));
         NEED(in != out && out != src);
         long i = at(src);
         NEED(i >= 0 && i < top && val[i] >= 0 && val[i] < 1000000);
@@ -100,24 +101,45 @@ static int ckpt(long nsteps, long every, bool want_final)
     for (long j = 0; j < need; ++j) { val[j] = (int)(j * every); given[j] = 1; }
     char *const lam[2] = {arena + need + every - 1, arena + need + every};
     val[at(lam[0])] = 1000000 + nsteps;
-    sadj::BurgersCkptReverse<Ops> plan{ops, arena, arena + need, 1, every};
+    sadj::BurgersCkptReverse<Ops> plan{ops, arena, arena + need, 1, every, most};
     if (plan.run(nsteps, lam)) return 1;
     NEED(val[at(lam[nsteps % 2])] == 1000000);
     return 0;
 }
 
+// The longest pass of a checkpointed sweep is 8, 12 or 16 steps, whichever costs least (window: 256 or 512 cells in long arrays, 128 else).
+static int longest_pass()
+{
+    for (long n = 3; n < (1L << 30); n = n * 3 / 2 + 1)
+        for (int window : {128, 256, 512})
+            for (long every = 2; every <= 100; ++every) {
+                const int m = sadj::recompute_steps(n, window, every);
+                NEED(m == 8 || m == 12 || m == 16);
+                NEED(sadj::recompute_kernel(m) == m);
+            }
+    NEED(sadj::recompute_steps(3000001, 256, 16) == 16 && sadj::recompute_steps(17000000, 256, 16) == 16);
+    NEED(sadj::recompute_steps(6000000, 256, 8) == 8 && sadj::recompute_steps(1200000, 256, 6) == 12);
+    NEED(sadj::recompute_steps(3000000, 512, 16) == 16 && sadj::recompute_steps(1000000, 512, 12) == 12);
+    NEED(sadj::recompute_steps(8000000, 512, 8) == 8 && sadj::recompute_steps(100000, 128, 16) == 16);
+    return 0;
+}
+
 int main()
 {
-    for (long n = 0; n <= 150; ++n) {
-        if (history(n)) std::printf("history %ld\n", n);
-        for (long every = 1; every <= 70; ++every)
-            for (int f = 0; f < 2; ++f)
-                if (ckpt(n, every, f)) std::printf("ckpt nsteps %ld every %ld\n", n, every);
-    }
-    for (long n : {1000L, 1001L, 2047L, 2048L}) {
-        if (history(n)) std::printf("history %ld\n", n);
-        for (long every : {1L, 2L, 7L, 8L, 9L, 16L, 17L, 33L, 100L, 1500L})
-            if (ckpt(n, every, true)) std::printf("ckpt nsteps %ld every %ld\n", n, every);
+    if (longest_pass()) std::printf("longest pass\n");
+    for (int steps : {8, 12, 16}) {
+        most = steps;
+        for (long n = 0; n <= 150; ++n) {
+            if (steps == 16 && history(n)) std::printf("history %ld\n", n);
+            for (long every = 1; every <= 70; ++every)
+                for (int f = 0; f < 2; ++f)
+                    if (ckpt(n, every, f)) std::printf("ckpt nsteps %ld every %ld most %d\n", n, every, most);
+        }
+        for (long n : {1000L, 1001L, 2047L, 2048L}) {
+            if (steps == 16 && history(n)) std::printf("history %ld\n", n);
+            for (long every : {1L, 2L, 7L, 8L, 9L, 16L, 17L, 33L, 100L, 1500L})
+                if (ckpt(n, every, true)) std::printf("ckpt nsteps %ld every %ld most %d\n", n, every, most);
+        }
     }
     std::printf("failures %d\n", failures);
     return failures != 0;
