@@ -26,7 +26,7 @@ template <class T> __device__ __forceinline__ T burgers_to_right(T u, T C, T D) 
 //   - Where the short form of r_i is not finite the formula as it stands is evaluated.  The short form is finite only if u_{i-1}, u_i,
 //     u_{i+1} all are: g_- d_l and g_+ d_r are not finite (0 times infinity included) as soon as one of them is not.
 //   - The slope adds 0 times the value that it leaves out, and 0 u_i.  (Not the difference: of finite values it may overflow.)
-// Neither changes a bit of a finite result.  The loops ask once per pass or step and wave whether this is needed.
+// Neither changes a bit of a finite result.  The loops ask once per pass and wave whether this is needed.
 template <class T> __device__ __forceinline__ T burgers_primal_formula(T um, T u0, T up, T C, T D)
 {
 #pragma clang fp contract(off)
@@ -50,17 +50,18 @@ template <class T> __device__ __forceinline__ T burgers_slope(T um, T u0, T up)
     const T dl = u0 - um, dr = up - u0;
     return __builtin_elementwise_abs(u0) + (u0 >= T(0) ? dl : dr);
 }
-// u is 0 or not finite: one class test, which costs what a comparison costs.
-__device__ __forceinline__ bool burgers_zero_or_not_finite(double u) { return __builtin_amdgcn_class(u, 0x267); }
-__device__ __forceinline__ bool burgers_zero_or_not_finite(float u) { return __builtin_amdgcn_classf(u, 0x267); }
-// The slope of any values, from burgers_slope's: both differences count where u = 0 (of either sign), and values that are not
-// finite where they are not used.
+// Of finite values, from that: both one-sided differences count where u = 0 (of either sign).
+template <class T> __device__ __forceinline__ T burgers_slope_at_zero(T slope, T u0, T up)
+{
+#pragma clang fp contract(off)
+    return u0 == T(0) ? slope + (up - u0) : slope;
+}
+// Of any values: values that are not finite count where they are not used, too.
 template <class T> __device__ __forceinline__ T burgers_slope_in_full(T slope, T um, T u0, T up)
 {
 #pragma clang fp contract(off)
     const T unused = u0 > T(0) ? up : u0 < T(0) ? um : T(0);
-    const T all = fma_t(T(0), u0, fma_t(T(0), unused, slope));
-    return u0 == T(0) ? all + (up - u0) : all;
+    return burgers_slope_at_zero(fma_t(T(0), u0, fma_t(T(0), unused, slope)), u0, up);
 }
 
 // g_0 = 1 - 2D - C slope.  1 - 2D is the same for all cells, and what its rounding loses adds up over the steps of a loop.  fp64 rounds it

@@ -4,7 +4,8 @@
 // A wave holds a window of 64*PXL consecutive cells in registers, PXL per lane, and applies m steps to
 // it.  A cell's value after k steps depends on k cells to either side, so `halo` cells at either end of
 // the window are recomputed by the neighbouring windows and only the 64*PXL - 2 halo between
-// them are stored: halo 16, or 8 in passes of up to 8 steps over stored states.  No LDS, no barrier: neighbours travel by whole-wave lane shifts (DPP).
+// them are stored: halo 16, 8 in passes of up to 8 steps over stored states, and 16, 24 or 32 in passes that recompute up to 8, 12 or 16
+// states.  No LDS, no barrier: neighbours travel by whole-wave lane shifts (DPP).
 //
 // Windows that lie in I = [1, n-2] run without guards; the others clamp their loads into the array
 // and mask with selects.  A window belongs to one wave, so the branch between the two is uniform.
@@ -185,23 +186,26 @@ template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
         for (int e = 0; e < PXL; ++e) any = any || !__builtin_isfinite(u[e]);
         return __any(any);
     }
-    __device__ __forceinline__ void reverse_step(const T (&u)[PXL], T (&lam)[PXL], T C, T D) const
+    // CHECKED: for states that may not be finite.
+    template <bool CHECKED> __device__ __forceinline__ void reverse_step(const T (&u)[PXL], T (&lam)[PXL], T C, T D) const
     {
         T ul[RUNS], ur[RUNS], lr[RUNS], left[RUNS], slope[PXL], give[PXL], next[PXL];
-        bool rare = false;
+        bool zero = CHECKED;
         beside(u, ul, ur);
 #pragma unroll
         for (int e = 0; e < PXL; ++e) {
             lam[e] = in[e] ? lam[e] : T(0);                                // lam outside I is never used
             slope[e] = burgers_slope(e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1]);
             give[e] = mul_rounded(burgers_to_right(u[e], C, D), lam[e]);
-            rare = rare || burgers_zero_or_not_finite(u[e]);
+            zero = zero || u[e] == T(0);
         }
         // u = 0 exactly is rare but in fields that are zero over a stretch: one test per wave instead of two selections per cell
-        if (__any(rare)) {
+        if (__any(zero)) {
 #pragma unroll
-            for (int e = 0; e < PXL; ++e)
-                slope[e] = burgers_slope_in_full(slope[e], e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1]);
+            for (int e = 0; e < PXL; ++e) {
+                const T um = e % RUN == 0 ? ul[e / RUN] : u[e - 1], up = e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1];
+                slope[e] = CHECKED ? burgers_slope_in_full(slope[e], um, u[e], up) : burgers_slope_at_zero(slope[e], u[e], up);
+            }
         }
         before(give, left);
         after(lam, lr);
@@ -216,6 +220,9 @@ template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
     }
 };
 
+// What follows is computed from `lane` anew: in code that is rarely reached, addresses kept from before would cost that code registers.
+__device__ __forceinline__ void computed_here(int &lane) { asm volatile("" : "+v"(lane)); }
+
 // The value that lane `from` (uniform) holds, in all lanes.
 __device__ __forceinline__ float lane_value(float v, int from) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), from)); }
 __device__ __forceinline__ double lane_value(double v, int from)
@@ -223,11 +230,15 @@ __device__ __forceinline__ double lane_value(double v, int from)
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), from), __builtin_amdgcn_readlane(__double2loint(v), from));
 }
 
-// A pass over one window; u: its cells after the last step.
+// A pass over one window.  Returns whether the checked form is needed: a cell that is not finite stays so and makes its neighbours'
+// next values so, in either form of the step, so if the last state is finite all were.
 template <bool CHECKED, class T, int PXL, bool GUARD, bool SPREAD>
-__device__ __forceinline__ void burgers_forward_pass(const BurgersForwardArgs &a, const Lane<T, PXL, GUARD, SPREAD> &L, T (&u)[PXL])
+__device__ __forceinline__ bool burgers_forward_window(const BurgersForwardArgs &a, long w, int lane)
 {
+    if (CHECKED) computed_here(lane);
+    const Lane<T, PXL, GUARD, SPREAD> L(w, lane, a.n, kLoopH);
     const T C = (T)a.C, D = (T)a.D;
+    T u[PXL];
     L.load(static_cast<const T *>(a.src), u);
     T *row = static_cast<T *>(a.rows);
     long next = a.first;
@@ -235,18 +246,17 @@ __device__ __forceinline__ void burgers_forward_pass(const BurgersForwardArgs &a
     // loop.  Fetched where they are needed, each step of an end window would wait for memory
     // (16 stored steps of 10^6 fp32 cells: 29 us instead of 13).
     T ends = T(0);
-    if (GUARD && !a.hold && L.lane < 32) ends = row[(long)min(L.lane & 15, a.m - 1) * a.n + (L.lane < 16 ? 0 : a.n - 1)];
+    if (GUARD && !a.hold && lane < 32) ends = row[(long)min(lane & 15, a.m - 1) * a.n + (lane < 16 ? 0 : a.n - 1)];
     static_assert(kForwardSteps <= 16, "a lane per given end cell");
     for (int s = 0; s < a.m;) {
         const int stop = next < a.m ? (int)next : a.m;
-        for (; s + 2 <= stop; s += 2) {           // by twos: the cells need no moves between registers
-            L.template primal_step<CHECKED>(u, C, D);
-            L.template primal_step<CHECKED>(u, C, D);
+        if (!CHECKED) {
+            for (; s + 2 <= stop; s += 2) {       // by twos: the cells need no moves between registers
+                L.template primal_step<false>(u, C, D);
+                L.template primal_step<false>(u, C, D);
+            }
         }
-        if (s < stop) {
-            L.template primal_step<CHECKED>(u, C, D);
-            ++s;
-        }
+        for (; s < stop; ++s) L.template primal_step<CHECKED>(u, C, D);
         if (s != next) continue;
         if (GUARD && !a.hold) {
 #pragma unroll
@@ -260,17 +270,7 @@ __device__ __forceinline__ void burgers_forward_pass(const BurgersForwardArgs &a
         next += a.every;
     }
     if (a.last) L.store(static_cast<T *>(a.last), u, true);
-}
-
-// A cell that is not finite stays so and makes its neighbours' next values so, in either form of the step: if the last state
-// is finite all were, else the pass is done again in the checked form (the pass never writes what it reads).
-template <class T, int PXL, bool GUARD, bool SPREAD>
-__device__ __forceinline__ void burgers_forward_window(const BurgersForwardArgs &a, long w, int lane)
-{
-    const Lane<T, PXL, GUARD, SPREAD> L(w, lane, a.n, kLoopH);
-    T u[PXL];
-    burgers_forward_pass<false>(a, L, u);
-    if (L.not_finite(u)) burgers_forward_pass<true>(a, L, u);
+    return !CHECKED && L.not_finite(u);
 }
 
 template <class T, int PXL, bool SPREAD> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_forward_kernel(BurgersForwardArgs a)
@@ -279,40 +279,61 @@ template <class T, int PXL, bool SPREAD> __global__ __launch_bounds__(64 * kLoop
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * V - kLoopH;
     if (w * V >= a.n) return;
-    if (x0 >= 1 && x0 + W - 1 <= a.n - 2) burgers_forward_window<T, PXL, false, SPREAD>(a, w, lane);
-    else burgers_forward_window<T, PXL, true, SPREAD>(a, w, lane);
+    const bool inside = x0 >= 1 && x0 + W - 1 <= a.n - 2;
+    const bool again = inside ? burgers_forward_window<false, T, PXL, false, SPREAD>(a, w, lane) : burgers_forward_window<false, T, PXL, true, SPREAD>(a, w, lane);
+    // rare: the pass is done again from its source, which it never writes
+    if (__builtin_expect(again, 0)) burgers_forward_window<true, T, PXL, true, SPREAD>(a, w, lane);
+}
+
+// The end cells of all rows that a pass reads: cell 0 in lanes 0 .. 15, cell n-1 in lanes 16 .. 31 (src where there is no such row).
+template <class T> __device__ __forceinline__ T end_cells(const BurgersReverseArgs &a, int lane)
+{
+    static_assert(kRecomputeSteps <= 16 && kReverseSteps <= 16, "a lane per end cell");
+    const int row = lane & 15;
+    const bool read = row > 0 && a.first + (row - 1) * a.every < a.m;
+    const T *p = read ? static_cast<const T *>(a.rows) + (row - 1) * a.n : static_cast<const T *>(a.src);
+    return p[(lane & 16) == 0 ? 0 : a.n - 1];
 }
 
 // Reverse steps over m states that are all in memory (rows follows src, first = every = 1), m % kAhead == REM.
 // The requests follow the length of the pass: an earlier form issued those of 15 steps always, re-reading the
 // last state for the missing ones, and a sweep of 5 steps over 4 10^6 fp32 cells took 60 us instead of 38, of 3 steps
 // over 10^6 fp64 cells 29 instead of 17.
+// Returns false, as burgers_reverse_recompute does, if a state may not have been finite: a cell of I whose u is not finite has a
+// slope that is not, so its lam is not finite after that step and stays so.  The end cells have no lam of their own;
+// windows that hold one look at them in the rows that the pass reads (recomputed states keep them).
 template <class T, int PXL, bool GUARD, int REM>
-__device__ __forceinline__ void burgers_reverse_stored(const BurgersReverseArgs &a, long w, int lane)
+__device__ __forceinline__ bool burgers_reverse_stored(const BurgersReverseArgs &a, long w, int lane)
 {
     const Lane<T, PXL, GUARD, true> L(w, lane, a.n, a.halo);
     const T C = (T)a.C, D = (T)a.D;
     const T *src = static_cast<const T *>(a.src);
     T lam[PXL], u[kAhead][PXL];
     L.load(static_cast<const T *>(a.lam_in), lam);
+    const T ends = GUARD ? end_cells<T>(a, lane) : T(0);
     stored_reverse_schedule<kAhead, REM>(
         a.m, [&](int t, int slot) { L.template load<true>(src + (long)t * a.n, u[slot]); },
         [&](int slot) {
-            L.reverse_step(u[slot], lam, C, D);
+            L.template reverse_step<false>(u[slot], lam, C, D);
             __builtin_amdgcn_sched_barrier(0);       // steps interleaved with each other need half as many registers again
         });
     L.store(static_cast<T *>(a.lam_out), lam, true);
+    return !(L.not_finite(lam) || (GUARD && __any(!__builtin_isfinite(ends))));
 }
 
-// States t .. t+m-1, recomputed forward from state t in u[0] except where a further checkpoint is met.  Returns whether the checked
-// form is needed (see burgers_forward_window; a row that is read starts a new chain of states).
-template <bool CHECKED, class T, int PXL, bool GUARD, int M>
-__device__ __forceinline__ bool burgers_recompute(const BurgersReverseArgs &a, const Lane<T, PXL, GUARD, false> &L, T (&u)[M][PXL])
+// Reverse steps from a checkpoint: the states are recomputed forward from state t into registers, except
+// where a further checkpoint is met.
+template <class T, int PXL, bool GUARD, int M>
+__device__ __forceinline__ bool burgers_reverse_recompute(const BurgersReverseArgs &a, long w, int lane)
 {
+    const Lane<T, PXL, GUARD, false> L(w, lane, a.n, 2 * M);
     const T C = (T)a.C, D = (T)a.D;
+    T lam[PXL], u[M][PXL];
+    L.load(static_cast<const T *>(a.src), u[0]);
+    L.load(static_cast<const T *>(a.lam_in), lam);
+    const T ends = GUARD ? end_cells<T>(a, lane) : T(0);
     const T *row = static_cast<const T *>(a.rows);
     int next = a.first;
-    bool again = false;
 #pragma unroll
     for (int s = 1; s < M; ++s) {
         if (s >= a.m) continue;
@@ -323,26 +344,36 @@ __device__ __forceinline__ bool burgers_recompute(const BurgersReverseArgs &a, c
         } else {
 #pragma unroll
             for (int e = 0; e < PXL; ++e) u[s][e] = u[s - 1][e];
-            L.template primal_step<CHECKED>(u[s], C, D);
-            if (!CHECKED && (s + 1 == a.m || s + 1 == next)) again = again || L.not_finite(u[s]);
+            L.template primal_step<false>(u[s], C, D);
         }
     }
-    return again;
-}
-
-// Reverse steps from a checkpoint.
-template <class T, int PXL, bool GUARD, int M>
-__device__ __forceinline__ void burgers_reverse_recompute(const BurgersReverseArgs &a, long w, int lane)
-{
-    const Lane<T, PXL, GUARD, false> L(w, lane, a.n, 2 * M);
-    const T C = (T)a.C, D = (T)a.D;
-    T lam[PXL], u[M][PXL];
-    L.load(static_cast<const T *>(a.src), u[0]);
-    L.load(static_cast<const T *>(a.lam_in), lam);
-    if (burgers_recompute<false>(a, L, u)) burgers_recompute<true>(a, L, u);
 #pragma unroll
     for (int s = M - 1; s >= 0; --s)
-        if (s < a.m) L.reverse_step(u[s], lam, C, D);
+        if (s < a.m) L.template reverse_step<false>(u[s], lam, C, D);
+    L.store(static_cast<T *>(a.lam_out), lam, true);
+    return !(L.not_finite(lam) || (GUARD && __any(!__builtin_isfinite(ends))));
+}
+
+// A pass of either kind over states that may not be finite: for each reverse step its state anew from the row before it, in the
+// checked forms, and the lanes store the cells that they stored before.  Loops instead of a pass in registers: small beside the
+// code above, which runs 4 to 6 % slower with tests between its steps or a second copy of itself (3 10^6 cells, fp64 and fp32).  As it
+// is the tests cost fp64 nothing measurable and an fp32 sweep from checkpoints 1.6 %.
+template <class T, int PXL, bool SPREAD>
+__device__ __forceinline__ void burgers_reverse_not_finite(const BurgersReverseArgs &a, long w, int lane, int halo)
+{
+    computed_here(lane);
+    const Lane<T, PXL, true, SPREAD> L(w, lane, a.n, halo);
+    const T C = (T)a.C, D = (T)a.D;
+    T lam[PXL], u[PXL];
+    L.load(static_cast<const T *>(a.lam_in), lam);
+#pragma unroll 1
+    for (int s = a.m - 1; s >= 0; --s) {
+        const int rows = s < a.first ? 0 : (s - a.first) / a.every + 1;       // that hold states up to s, src not counted
+        L.load(rows == 0 ? static_cast<const T *>(a.src) : static_cast<const T *>(a.rows) + (rows - 1) * a.n, u);
+#pragma unroll 1
+        for (int t = rows == 0 ? 0 : a.first + (rows - 1) * a.every; t < s; ++t) L.template primal_step<true>(u, C, D);
+        L.template reverse_step<true>(u, lam, C, D);
+    }
     L.store(static_cast<T *>(a.lam_out), lam, true);
 }
 
@@ -353,19 +384,24 @@ template <class T, int PXL, int REM> __global__ __launch_bounds__(64 * kLoopWave
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long w = (long)blockIdx.x * kLoopWaves + wave, x0 = w * V - halo;
     if (w * V >= a.n) return;
-    if (x0 >= 1 && x0 + W - 1 <= a.n - 2) {
-        if constexpr (REM >= 0) burgers_reverse_stored<T, PXL, false, REM>(a, w, lane);
-        else burgers_reverse_recompute<T, PXL, false, -REM>(a, w, lane);
+    const bool inside = x0 >= 1 && x0 + W - 1 <= a.n - 2;
+    bool done;
+    if (__builtin_expect(inside, 1)) {
+        if constexpr (REM >= 0) done = burgers_reverse_stored<T, PXL, false, REM>(a, w, lane);
+        else done = burgers_reverse_recompute<T, PXL, false, -REM>(a, w, lane);
     } else {
-        if constexpr (REM >= 0) burgers_reverse_stored<T, PXL, true, REM>(a, w, lane);
-        else burgers_reverse_recompute<T, PXL, true, -REM>(a, w, lane);
+        if constexpr (REM >= 0) done = burgers_reverse_stored<T, PXL, true, REM>(a, w, lane);
+        else done = burgers_reverse_recompute<T, PXL, true, -REM>(a, w, lane);
     }
+    if (__builtin_expect(!done, 0)) burgers_reverse_not_finite<T, PXL, (REM >= 0)>(a, w, lane, halo);
 }
 
-// Cells per lane: wide windows (224 own cells of 256 in fp64, 480 of 512 in fp32) recompute the least and
-// are taken where every SIMD of the chip gets one; shorter arrays are spread over more SIMDs in narrow
-// windows (96 of 128): 400 000 cells, 16 stored forward steps, fp64: narrow 11.8, wide 10.0 us; a checkpointed
-// reverse pass of 10^6 cells 38 and 35 us, in fp32 30 and 29 us, of 4 10^6 cells in fp32 79 and 61 us.
+// Cells per lane: wide windows recompute the least (own cells of 256 in fp64: 224, in a reverse pass of 16 recomputed states 192; of 512
+// in fp32: 480 and 448) and are taken where every SIMD of the chip gets one; shorter arrays are spread over more SIMDs in narrow
+// windows (96 and 64 of 128).  Narrow / wide, us, 16 stored forward steps and a reverse sweep of 64 steps from every 16th state:
+// fp64 10^5 cells 11.8 / 14.0 and 40.5 / 43.5, 2.3 10^5 12.0 / 12.5 and 54.4 / 53.2, 5 10^5 22.4 / 21.4 and 84.9 / 75.2, 10^6 40.9 / 36.8 and
+// 147 / 124; fp32 10^5 11.1 / 14.5 and 36.8 / 55.0, 3 10^5 11.7 / 14.7 and 52.0 / 57.6, 5 10^5 12.6 / 15.2 and 64.0 / 63.2, 7 10^5 18.1 / 17.5 and
+// 90.3 / 66.6, 2 10^6 47.0 / 39.9 and 168 / 139.
 template <class T> static bool wide_windows(long n)
 {
     return n >= 1024L * own_cells(32 / (int)sizeof(T), kLoopH);

@@ -57,7 +57,10 @@ def test_one_step_and_its_adjoint_propagate_as_the_formula(sadj, n, dtype):
 def _loops(sadj, u0, nsteps, every):
     n = u0.size
     lam0, lam1 = (inputs.uniform(n, k, (n,), -1, 1).astype(u0.dtype) for k in ("r_bar", "u_bar"))
-    states = to_gpu(np.stack([u0] + [np.zeros_like(u0)] * nsteps))
+    states = np.stack([u0] + [np.zeros_like(u0)] * nsteps)
+    if not np.isfinite(u0[[0, -1]]).all():             # end cells are given in every row
+        states[3::4, 0], states[1::5, -1] = -np.inf, np.nan
+    states = to_gpu(states)
     g = [to_gpu(lam0), to_gpu(lam1)]
     sadj.sadj_primal_burgers1d_steps(BC, BD, nsteps, states)
     sadj.sadj_adjoint_burgers1d_steps(BC, BD, nsteps, nsteps, states, *g)
@@ -75,13 +78,15 @@ def test_loops_propagate_as_one_launch_per_step(sadj, n, dtype):
     blown_up = inputs.uniform(n, "u", (n,), -1, 1).astype(dtype) * dtype(1e100 if dtype == np.float64 else 1e12)
     blown_up[n // 2:] = few[n // 2:]                   # some windows overflow, others meet what is not finite, or neither
     few[n // 2:] = inputs.uniform(n, "u", (n,), -1, 1).astype(dtype)[n // 2:]
-    for u0 in (few, blown_up):
+    ends = inputs.uniform(n, "u", (n,), -1, 1).astype(dtype)
+    ends[0], ends[-1] = np.inf, -np.inf
+    for u0 in (few, blown_up, ends):
         for nsteps, every in ((1, 2), (5, 3), (17, 16), (34, 16), (13, 12), (18, 17), (9, 2)):
             out = []
             for fuse in (1, 0):
                 sadj.set_option("burgers1d.fuse", fuse)
                 out.append(_loops(sadj, u0, nsteps, every))
             sadj.set_option("burgers1d.fuse", 0)
-            assert np.isnan(out[0][0]).any() and np.isfinite(out[0][0][-1]).any()
+            assert not np.isfinite(out[0][0]).all() and np.isfinite(out[0][0][-1]).any()
             for k, (x, y) in enumerate(zip(*out)):
                 assert np.array_equal(x, y, equal_nan=True), (nsteps, every, k)
