@@ -366,8 +366,8 @@ sadj_status sadj_describe_wave3d_plan(sadj_dtype dtype, int radius, long nx, lon
  *                    and the plane at least 8 tile rows.
  *   "wave3d.ldspad"  dynamic LDS bytes requested per workgroup of the 3-D marching kernels,
  *                    which limits how many workgroups share a CU: 0 (default) as much as
- *                    keeps it at one workgroup per CU (none for the 32 x 16 and fp32 64 x 16 tiles that
- *                    small grids take, which two share), -1 none, n > 0 exactly n (<= 65536).
+ *                    keeps it at one workgroup per CU (none in the kernels of grids that do not
+ *                    fill the chip, see "wave3d.ahead"), -1 none, n > 0 exactly n (<= 65536).
  *   "wave3d.ahead"   0 (default): 3-D wave and star calls on grids that do not fill the chip take kernels
  *                    whose memory requests run ahead of the arithmetic; 1: the kernels and tiles of
  *                    larger grids on every grid (slower there; they can be run on small arrays this

@@ -69,7 +69,8 @@ static inline AheadPlan plan_ahead(bool is_f64, int radius, int nx, int ny, int 
 }
 
 // The wave adjoint; accumulates: u_prev_bar is read and written, writes_prev: written (or the array it replaces is), loop: a step
-// of a time loop after its first.  Below 120 MB 1.42 to 1.45 (fp64) and 1.40 (fp32) times as fast as in the tiles of
+// of a time loop that starts from the r_bar of the step before (launch_adjoint_wave3d_middle).  The first two steps of a loop and the
+// single steps between fused passes count as lone calls.  Below 120 MB 1.42 to 1.45 (fp64) and 1.40 (fp32) times as fast as in the tiles of
 // wave3d_adjoint.hip, 1 % behind the better of the two shapes.  40^3 fp64 radius 4, Small / Wide: 4.3 / 5.3 us; 80 x 96 x 112 with
 // u_prev_bar 11.7 / 10.2.
 static inline AheadPlan plan_adjoint_ahead(bool is_f64, int radius, int nx, int ny, int nz, bool accumulates, bool writes_prev, bool loop,

@@ -8,6 +8,7 @@
 //     not wanted has a resource of zero bytes (loads return zero, stores are dropped by the hardware's bounds check), and cells
 //     outside the grid or outside I have an offset beyond any plane.  The wait counters therefore know exactly what is
 //     outstanding, and D planes are really in flight; with a branch around a load or store the compiler waits for everything.
+//     (The adjoints' waits never reach the newest plane; the fp64 primals of radius 3 and some of radius 4 wait for it once every two planes.)
 //     (All slots of the ring of requests are filled and emptied in one order, hence the scheduling barriers.)
 //   - The R planes before and after a chunk add to the chunk's sums by their own cell only (a star has no corners): they
 //     are read without halo, are not staged in LDS and need no barrier, and the R planes before the chunk are requested together.

@@ -360,8 +360,10 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_kernel(PairArgs a)
 
 // The same on grids that do not fill the chip, where a workgroup marches few planes and the time from a plane's request to the
 // next plane's is what counts.  As in ahead3d.hpp all accesses go through buffer resources, without a condition around any of
-// them, so that D planes are really in flight: a plane that is not wanted has a resource of zero bytes and reads as zero, cells
-// outside I have an offset beyond any plane.  One instantiation serves core and remainder.  The sums are pair_march's, bit for bit.
+// them: a plane that is not wanted has a resource of zero bytes and reads as zero, cells outside I have an offset beyond any plane.
+// The waits inside a step therefore leave the other requests in flight (vmcnt 6 to 11, of 6 loads a plane); at the loop's end, every
+// second plane, the compiler moves the newest requests' registers and waits for them (vmcnt 3 and 2), so the march is not yet what D = 2
+// promises.  One instantiation serves core and remainder.  The sums are pair_march's, bit for bit.
 // One workgroup per CU and two planes ahead; three planes 2 % slower, two workgroups per CU 5 to 10 % (fp32) or more registers than
 // there are (fp64: 162).  25 steps, the tiles below / this, fp32 96 x 130 x 164 237 / 182 us, 128^3 189 / 153, 300 x 80 x 80 216 / 183, 64^3
 // 97 / 90; fp64 40 x 300 x 96 227 / 191.

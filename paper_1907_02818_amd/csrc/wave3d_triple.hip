@@ -376,8 +376,8 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_triple_kernel(TripleArgs a)
     else      triple_march<T, BX, BY, PY, PX, true>(a, tix, tiy, zs, ze, sq0, sq1, sq2, cold, coldr);
 }
 
-// The same on grids that do not fill the chip, with D planes in flight, as adj_wave3d_pair_ahead_kernel in wave3d_pair.hip: no
-// condition around any memory access, planes that are not wanted and cells outside I read as zero.  One row of cells per thread
+// The same on grids that do not fill the chip, with requests ahead as in adj_wave3d_pair_ahead_kernel in wave3d_pair.hip (and
+// its wait at the loop's end): no condition around any memory access, planes that are not wanted and cells outside I read as zero.  One row of cells per thread
 // and one frame cell at most, so that c of the three planes before stays in registers.  The sums are triple_march's, bit for bit.
 // One workgroup per CU with two planes in flight; three 2 % slower.  25 steps, the wide tiles / this: fp64 128^3 255 / 213 us, 160^3
 // 462 / 352, 300 x 80 x 80 320 / 236; fp32 197 x 68 x 260 383 / 247, 64 x 400 x 400 657 / 453, 200^3 536 / 490.  What bounds it on the
@@ -594,9 +594,9 @@ static hipError_t launch_triple(TripleArgs a, const LaunchOptions &opt, hipStrea
 
 // A chunk marches 5 planes beyond its own for two steps and 8 for three, and a plane of the three-step march
 // takes about 1.1 (fp64) or 1.2 (fp32) times as long.  Short marches on small grids therefore take two
-// steps per pass: 25 steps, two (in 64 x 32 tiles, fp32 128 x 32) / three per pass, fp64 33 x 40 x 72 71 / 83 us,
-// 128^3 309 / 265, 512^3 12.9 / 9.4 ms; fp32 128^3 192 / 221 us, 96 x 130 x 164 262 / 279, 160 x 180 x 200 451 / 406,
-// 512^3 6.6 / 5.0 ms.  Two and three steps group the sums differently, so grid and type alone decide: options that
+// steps per pass.  Priced and measured in the tiles without requests ahead: 25 steps, two (in 64 x 32 tiles, fp32
+// 128 x 32) / three per pass, fp64 33 x 40 x 72 71 / 83 us, 128^3 309 / 265, 512^3 12.9 / 9.4 ms; fp32 128^3 192 / 221 us,
+// 96 x 130 x 164 262 / 279, 160 x 180 x 200 451 / 406, 512^3 6.6 / 5.0 ms.  Two and three steps group the sums differently, so grid and type alone decide: options that
 // cut the march another way must not change a bit.
 int adjoint_wave3d_steps_per_pass(int is_f64, int nx, int ny, int nz)
 {

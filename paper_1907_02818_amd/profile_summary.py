@@ -14,7 +14,9 @@ DIR holds what three rocprofv3 runs of the same workload wrote (csv output, `-o 
 
 and, optionally, DIR/sq/ from a run with SQ_* counters.  With `--all DIR` instead of a workload
 it writes profiles/all_workloads_stats.txt from DIR/stats/ and DIR/stats.json of a
-`bench.py --all --remainder-study` run under rocprofv3 --kernel-trace --stats.  Writes profiles/WORKLOAD_stats.txt
+`bench.py --all --remainder-study` run under rocprofv3 --kernel-trace --stats, with `--cases DIR` profiles/small_grids_stats.txt
+and profiles/small_grids_pmc.txt from DIR/stats/, fetch/, write/ and sq/ of runs of cases of perf/cases.py (`--cases-command` prints
+the program to profile).  Writes profiles/WORKLOAD_stats.txt
 and profiles/WORKLOAD_pmc.txt.  The counters are calibrated on the run's last dispatch, the
 plain device copy of one 1 GiB array that `--copy-probe` appends (2^30 bytes read, 2^30
 written).  The pmc summary records a hash of the kernel sources, so that bench.py reports its
@@ -61,7 +63,13 @@ def _rows(pattern):
 
 
 def _short(name):
-    return name.split("(")[0].replace("void ", "")
+    """Without the return type and the arguments; template arguments may hold parentheses of their own."""
+    name, depth = name.replace("void ", ""), 0
+    for i, ch in enumerate(name):
+        depth += (ch == "<") - (ch == ">")
+        if ch == "(" and depth == 0:
+            return name[:i]
+    return name
 
 
 def _is_ours(name):
@@ -222,10 +230,65 @@ def summarise_all(d):
     return "\n".join(lines) + "\n"
 
 
+# calls on grids that do not fill the chip, and the gradient from checkpoints; the copy at the end calibrates FETCH_SIZE and WRITE_SIZE
+CASES = ("from perf import cases as p; n = 'wave3d_r4_adjoint_small star3d_r2_adjoint_ragged wave3d_r4_sweep_256 wave3d_r1_sweep_fused_small "
+         "burgers_gradient_ckpt'.split(); c = [x for x in p.listed() if x['name'] in n] + [dict(op='sweep_fused', dtype='f64', radius=1, nz=160, "
+         "ny=160, nx=160, nsteps=25)]; [p.run(s) for x in c for s in [p.prepare(x, 1)] for _ in range(10)]; "
+         "t = p.torch.zeros(1 << 27, dtype=p.torch.float64, device='cuda'); t.clone(); p.torch.cuda.synchronize()")
+SQ = ("SQ_ACTIVE_INST_LDS SQ_ACTIVE_INST_VALU SQ_BUSY_CYCLES SQ_INSTS_LDS SQ_INSTS_VALU SQ_LDS_BANK_CONFLICT SQ_WAIT_INST_ANY "
+      "SQ_WAVE_CYCLES")
+
+
+def summarise_cases(d):
+    """(stats, pmc) of rocprofv3 runs of the CASES program: DIR/stats/, DIR/fetch/, DIR/write/, DIR/sq/."""
+    what = "calls on grids that do not fill the chip, and of the Burgers gradient from checkpoints, one MI355X"
+    prog = ["  python3 -c \"%s\"" % CASES, "(python -m paper_1907_02818_amd.profile_summary --cases-command prints the part in quotes)", ""]
+    per = {}
+    for r in _rows(os.path.join(d, "stats", "**", "*kernel_trace.csv")):
+        if _is_ours(r["Kernel_Name"]):
+            per.setdefault(r["Kernel_Name"], []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"]), r))
+    order = sorted(per, key=lambda k: -sum(t for t, _ in per[k]))
+    stats = ["rocprofv3 kernel-trace summary of " + what, "command: rocprofv3 --kernel-trace --stats -d DIR/stats -o p --output-format csv --"] + prog
+    stats.append("%-100s %6s %9s %9s  %s" % ("kernel", "calls", "avg_us", "min_us", "workgroups x threads, LDS, VGPRs (first launch)"))
+    for k in order:
+        ts, r = [t for t, _ in per[k]], per[k][0][1]
+        threads = int(r["Workgroup_Size_X"])
+        stats.append("%-100s %6d %9.2f %9.2f  %d x %d, %s B, %s" % (_short(k)[:100], len(ts), statistics.mean(ts) / 1e3, min(ts) / 1e3,
+                     int(r["Grid_Size_X"]) // threads, threads, r["LDS_Block_Size"], r.get("VGPR_Count", "?")))
+    acc, copy = {}, {}
+    for sub in ("fetch", "write", "sq"):
+        for r in _rows(os.path.join(d, sub, "**", "*counter_collection.csv")):
+            acc.setdefault(r["Kernel_Name"], {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
+            if "copyBuffer" in r["Kernel_Name"]:
+                copy[r["Counter_Name"]] = float(r["Counter_Value"])
+    pmc = ["rocprofv3 --pmc summary of " + what, "commands, one run each: rocprofv3 --pmc COUNTERS --kernel-trace -d DIR/SUB -o p --output-format csv --",
+           "with COUNTERS = FETCH_SIZE, WRITE_SIZE and " + SQ + ", SUB = fetch, write, sq"] + prog
+    pmc += ["means per launch; MB as calibrated on the copy of 1 GiB at the end; wait: share of the wave-cycles spent waiting for an",
+            "instruction to complete; valu: vector ALU issue (4 cycles an instruction, 1024 SIMDs, 2.4 GHz); conflict: LDS bank-conflict",
+            "cycles per active LDS cycle", "",
+            "%-100s %9s %9s %6s %9s %9s" % ("kernel", "MB read", "written", "wait", "valu_us", "conflict")]
+    for k in order:
+        m = {c: statistics.mean(v) for c, v in acc[k].items()}
+        mb = [m[c] * (GIB / copy[c]) / 1e6 for c in ("FETCH_SIZE", "WRITE_SIZE")]
+        lds = m["SQ_ACTIVE_INST_LDS"]
+        pmc.append("%-100s %9.2f %9.2f %5.0f%% %9.2f %9s" % (_short(k)[:100], mb[0], mb[1], 100 * m["SQ_WAIT_INST_ANY"] / m["SQ_WAVE_CYCLES"],
+                   m["SQ_INSTS_VALU"] * 4 / 1024 / 2400, "%.2f" % (m["SQ_LDS_BANK_CONFLICT"] / lds) if lds else "-"))
+    return "\n".join(stats) + "\n", "\n".join(pmc) + "\n"
+
+
 HEADLINE = "wave3d_r4_f64_adjoint"
 
 
 def main(argv):
+    if argv[1:] == ["--cases-command"]:
+        print(CASES)
+        return 0
+    if len(argv) == 3 and argv[1] == "--cases":
+        for name, txt in zip(("stats", "pmc"), summarise_cases(argv[2])):
+            with open(os.path.join(ROOT, "profiles", "small_grids_%s.txt" % name), "w") as fh:
+                fh.write(txt)
+            sys.stdout.write(txt)
+        return 0
     if len(argv) == 3 and argv[1] == "--all":
         txt = summarise_all(argv[2])
         with open(os.path.join(ROOT, "profiles", "all_workloads_stats.txt"), "w") as fh:

@@ -59,8 +59,7 @@ def test_which_grids_take_small_tiles(dtype_code, radius, shape, small):
 @pytest.mark.parametrize("radius,shape,small", [(1, (73, 174, 61), False), (1, (44, 28, 71), False), (2, (117, 161, 49), False),
                                                 (3, (46, 39, 83), True), (4, (37, 178, 39), True), (4, (37, 178, 40), True)])
 def test_small_tiles_are_priced_against_the_shape_that_would_run(radius, shape, small):
-    """fp32 rows that are not whole vectors run in 64 x 32 tiles with one cell per lane, which small tiles beat only
-    at larger radii."""
+    """fp32 rows that are not whole vectors otherwise run in 64 x 32 tiles, which small tiles beat only at larger radii."""
     torch = pytest.importorskip("torch")
     if torch.cuda.is_available():
         pytest.skip("plans depend on the device's compute units; this test counts on the default")

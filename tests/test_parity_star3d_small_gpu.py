@@ -1,5 +1,5 @@
-"""GPU parity of the radius-4 star in 32 x 16 tiles, which small grids take: exact on dyadic data at the
-edges of those tiles, NaN where values must not be read."""
+"""GPU parity of the radius-4 star on small grids, which take 32 x 16 tiles or wider ones of 16 rows (the march with its requests
+ahead): exact on dyadic data at the edges of those tiles, NaN where values must not be read."""
 import numpy as np
 import pytest
 

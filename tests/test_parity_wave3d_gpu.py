@@ -358,6 +358,8 @@ def test_primal_small(sadj, radius, shape, dtype):
 # rows that are not a multiple of the 128-byte cache line: the launcher takes tiles of 16 rows
 # with long rows when they cover nx well (radius 1: 256 cells, fp32 adjoint 512; larger radii:
 # 1 KB); 1002 is not a multiple of four, so the fp32 calls fall back to the one-cell shape there
+# (the adjoint; the primal of these grids takes the march with its requests ahead, and its wide tiles run in
+# test_parity_large_grid_kernels_gpu.py)
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("radius,shape", [(1, (20, 37, 250)), (1, (9, 40, 500)), (1, (6, 20, 1000)), (1, (5, 17, 1002)),
                                           (1, (19, 33, 750)), (1, (40, 16, 1500)),
