@@ -265,7 +265,7 @@ def summarise_cases(d):
            "with COUNTERS = FETCH_SIZE, WRITE_SIZE and " + SQ + ", SUB = fetch, write, sq"] + prog
     pmc += ["means per launch; MB as calibrated on the copy of 1 GiB at the end; wait: share of the wave-cycles spent waiting for an",
             "instruction to complete; valu: vector ALU issue (4 cycles an instruction, 1024 SIMDs, 2.4 GHz); conflict: LDS bank-conflict",
-            "cycles per active LDS cycle", "",
+            "cycles per active LDS cycle", "library_sources_sha256: %s" % library_sources_sha256(), "",
             "%-100s %9s %9s %6s %9s %9s" % ("kernel", "MB read", "written", "wait", "valu_us", "conflict")]
     for k in order:
         m = {c: statistics.mean(v) for c, v in acc[k].items()}
