@@ -43,25 +43,40 @@ template <bool CHECKED, class T> __device__ __forceinline__ T burgers_primal_cel
     return r;
 }
 
-// The upwind slope of values that are finite and not 0: |u| + (u >= 0 ? d_l : d_r).  max(u,0) - min(u,0) is |u|.
+// Sign bit of v set ? b : a, with a shift and a bit field insert per word (the shift written out: the compiler would make a comparison
+// and selections of it).  Measured with two waves per SIMD: 11 cycles for a double, 13 to 21 with v_cmp and v_cndmask, the most where the
+// selection reads VCC in its short form.
+__device__ __forceinline__ unsigned sign_mask(int high) { unsigned m; asm("v_ashrrev_i32 %0, 31, %1" : "=v"(m) : "v"(high)); return m; }
+__device__ __forceinline__ int by_mask(unsigned m, int a, int b) { return (int)((m & (unsigned)b) | (~m & (unsigned)a)); }
+__device__ __forceinline__ double by_sign(double v, double a, double b)
+{
+    const unsigned m = sign_mask(__double2hiint(v));
+    return __hiloint2double(by_mask(m, __double2hiint(a), __double2hiint(b)), by_mask(m, __double2loint(a), __double2loint(b)));
+}
+__device__ __forceinline__ float by_sign(float v, float a, float b)
+{
+    return __int_as_float(by_mask(sign_mask(__float_as_int(v)), __float_as_int(a), __float_as_int(b)));
+}
+
+// The upwind slope of values that are finite and not 0: |u| + (u > 0 ? d_l : d_r).  max(u,0) - min(u,0) is |u|.
 template <class T> __device__ __forceinline__ T burgers_slope(T um, T u0, T up)
 {
 #pragma clang fp contract(off)
     const T dl = u0 - um, dr = up - u0;
-    return __builtin_elementwise_abs(u0) + (u0 >= T(0) ? dl : dr);
+    return __builtin_elementwise_abs(u0) + by_sign(u0, dl, dr);
 }
 // Of finite values, from that: both one-sided differences count where u = 0 (of either sign).
-template <class T> __device__ __forceinline__ T burgers_slope_at_zero(T slope, T u0, T up)
+template <class T> __device__ __forceinline__ T burgers_slope_at_zero(T slope, T um, T u0, T up)
 {
 #pragma clang fp contract(off)
-    return u0 == T(0) ? slope + (up - u0) : slope;
+    return u0 == T(0) ? (u0 - um) + (up - u0) : slope;
 }
 // Of any values: values that are not finite count where they are not used, too.
 template <class T> __device__ __forceinline__ T burgers_slope_in_full(T slope, T um, T u0, T up)
 {
 #pragma clang fp contract(off)
     const T unused = u0 > T(0) ? up : u0 < T(0) ? um : T(0);
-    return burgers_slope_at_zero(fma_t(T(0), u0, fma_t(T(0), unused, slope)), u0, up);
+    return burgers_slope_at_zero(fma_t(T(0), u0, fma_t(T(0), unused, slope)), um, u0, up);
 }
 
 // g_0 = 1 - 2D - C slope.  1 - 2D is the same for all cells, and what its rounding loses adds up over the steps of a loop.  fp64 rounds it

@@ -14,9 +14,12 @@
 // per cell and step instead of 16; 10^7 cells, 16 steps: 245 us, 5.5 TB/s.  Reverse over stored states:
 // memory, 8 + 16/m bytes instead of 24; a sweep of 16 steps of 10^7 cells 284 us.  Reverse from a
 // checkpoint: 24/m bytes, the m states are recomputed in registers and the vector ALUs are the bound; so is the forward sweep
-// that stores checkpoints only.  Per four fp64 cells a forward step takes 38 instructions and a reverse one about 75 (43 and 103 before
+// that stores checkpoints only.  Per four fp64 cells a forward step takes 38 instructions and a reverse one 64 (43 and 103 before
 // both were written with g_- and g_+, see burgers.hpp): 3 10^6 cells, 128 steps, every 16th kept, forward 164 -> 155 us, reverse
-// 616 -> 532, and -> 486 with passes of 16 steps.
+// 616 -> 532, and -> 486 with passes of 16 steps.  75 -> 64 with the upwind difference taken by the sign bit, one question for zeros a pass
+// and full passes without a condition per step: gradient 620 -> 589 us (fp32 420 -> 386); the vector ALUs are issuing 94 % of the time at
+// the clock that this load leaves, 2.1 GHz.  Windows that refresh their ends from their neighbours through LDS, every 4 or 8 steps,
+// compute 16 and 11 % fewer cells and measured 0 and 2 % faster (fp32 8 % slower): the waits at the barriers take what the cells save.
 #include "burgers.hpp"
 #include "burgers_plan.hpp"
 #include "launch.hpp"
@@ -79,6 +82,20 @@ template <bool RIGHT> __device__ __forceinline__ double lane_rotate(double v)
 {
     return __hiloint2double(lane_rotate<RIGHT>(__double2hiint(v)), lane_rotate<RIGHT>(__double2loint(v)));
 }
+
+// min(|a|, |b|, least), NaN if one of them is.  Of doubles the upper words, taken as floats, which keeps their order; one below 2^-1015
+// is no normal float, one of 2^1017 or more may be NaN.
+__device__ __forceinline__ float least_magnitude(float a, float b, float least)
+{
+    float r;
+    asm("v_minimum3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(a), "v"(b), "v"(least));
+    return r;
+}
+__device__ __forceinline__ float least_magnitude(double a, double b, float least)
+{
+    return least_magnitude(__int_as_float(__double2hiint(a)), __int_as_float(__double2hiint(b)), least);
+}
+constexpr float kLeastNormal = 0x1p-126f;
 
 // A lane's PXL cells of one row, in runs of RUN consecutive cells.  SPREAD: a run is one 16-byte access
 // and the lanes' runs lie side by side, so that every access of a wave is one piece of memory; else the
@@ -191,25 +208,31 @@ template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
             for (int e = 0; e < k; ++e) sum[e] = add_rounded(sum[e], sum[e + k]);
         return __any(!__builtin_isfinite(sum[0]));
     }
-    // CHECKED: for states that may not be finite.
-    template <bool CHECKED> __device__ __forceinline__ void reverse_step(const T (&u)[PXL], T (&lam)[PXL], T C, T D) const
+    // Of the cells of several states, one state after the other: whether one (any lane's) may be zero is then asked once.
+    __device__ __forceinline__ float least_of(const T (&u)[PXL], float least) const
+    {
+#pragma unroll
+        for (int e = 0; e < PXL; e += 2) least = least_magnitude(u[e], u[e + 1], least);
+        return least;
+    }
+    static __device__ __forceinline__ bool maybe_zero(float least) { return __any(!(least >= kLeastNormal)); }
+    // CHECKED: for states that may not be finite.  zero (the same in all lanes): cells of u may be zero.
+    template <bool CHECKED> __device__ __forceinline__ void reverse_step(const T (&u)[PXL], T (&lam)[PXL], T C, T D, bool zero) const
     {
         T ul[RUNS], ur[RUNS], lr[RUNS], left[RUNS], slope[PXL], give[PXL], next[PXL];
-        bool zero = CHECKED;
         beside(u, ul, ur);
 #pragma unroll
         for (int e = 0; e < PXL; ++e) {
             lam[e] = in[e] ? lam[e] : T(0);                                // lam outside I is never used
             slope[e] = burgers_slope(e % RUN == 0 ? ul[e / RUN] : u[e - 1], u[e], e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1]);
             give[e] = mul_rounded(burgers_to_right(u[e], C, D), lam[e]);
-            zero = zero || u[e] == T(0);
         }
-        // u = 0 exactly is rare but in fields that are zero over a stretch: one test per wave instead of two selections per cell
-        if (__any(zero)) {
+        // u = 0 exactly is rare but in fields that are zero over a stretch
+        if (CHECKED || zero) {
 #pragma unroll
             for (int e = 0; e < PXL; ++e) {
                 const T um = e % RUN == 0 ? ul[e / RUN] : u[e - 1], up = e % RUN == RUN - 1 ? ur[e / RUN] : u[e + 1];
-                slope[e] = CHECKED ? burgers_slope_in_full(slope[e], um, u[e], up) : burgers_slope_at_zero(slope[e], u[e], up);
+                slope[e] = CHECKED ? burgers_slope_in_full(slope[e], um, u[e], up) : burgers_slope_at_zero(slope[e], um, u[e], up);
             }
         }
         before(give, left);
@@ -226,7 +249,7 @@ template <class T, int PXL, bool GUARD, bool SPREAD> struct Lane {
 };
 
 // What follows is computed from `lane` anew: in code that is rarely reached, addresses kept from before would cost that code registers.
-__device__ __forceinline__ void computed_here(int &lane) { asm volatile("" : "+v"(lane)); }
+template <class T> __device__ __forceinline__ void computed_here(T &v) { asm volatile("" : "+v"(v)); }
 
 // The value that lane `from` (uniform) holds, in all lanes.
 __device__ __forceinline__ float lane_value(float v, int from) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), from)); }
@@ -319,7 +342,7 @@ __device__ __forceinline__ bool burgers_reverse_stored(const BurgersReverseArgs 
     stored_reverse_schedule<kAhead, REM>(
         a.m, [&](int t, int slot) { L.template load<true>(src + (long)t * a.n, u[slot]); },
         [&](int slot) {
-            L.template reverse_step<false>(u[slot], lam, C, D);
+            L.template reverse_step<false>(u[slot], lam, C, D, L.maybe_zero(L.least_of(u[slot], __builtin_inff())));
             __builtin_amdgcn_sched_barrier(0);       // steps interleaved with each other need half as many registers again
         });
     L.store(static_cast<T *>(a.lam_out), lam, true);
@@ -328,7 +351,9 @@ __device__ __forceinline__ bool burgers_reverse_stored(const BurgersReverseArgs 
 
 // Reverse steps from a checkpoint: the states are recomputed forward from state t into registers, except
 // where a further checkpoint is met.
-template <class T, int PXL, bool GUARD, int M>
+// FULL: all M steps.  Forward and reverse steps of a state share values that would occupy registers in between: computed_here
+// keeps them apart.
+template <class T, int PXL, bool GUARD, int M, bool FULL>
 __device__ __forceinline__ bool burgers_reverse_recompute(const BurgersReverseArgs &a, long w, int lane)
 {
     const Lane<T, PXL, GUARD, false> L(w, lane, a.n, 2 * M);
@@ -339,9 +364,10 @@ __device__ __forceinline__ bool burgers_reverse_recompute(const BurgersReverseAr
     const T ends = GUARD ? end_cells<T>(a, lane) : T(0);
     const T *row = static_cast<const T *>(a.rows);
     int next = a.first;
+    float least = L.least_of(u[0], __builtin_inff());
 #pragma unroll
     for (int s = 1; s < M; ++s) {
-        if (s >= a.m) continue;
+        if (!FULL && s >= a.m) continue;
         if (s == next) {
             L.load(row, u[s]);
             row += a.n;
@@ -351,10 +377,18 @@ __device__ __forceinline__ bool burgers_reverse_recompute(const BurgersReverseAr
             for (int e = 0; e < PXL; ++e) u[s][e] = u[s - 1][e];
             L.template primal_step<false>(u[s], C, D);
         }
+        least = L.least_of(u[s], least);
     }
+    const bool zero = L.maybe_zero(least);
 #pragma unroll
-    for (int s = M - 1; s >= 0; --s)
-        if (s < a.m) L.template reverse_step<false>(u[s], lam, C, D);
+    for (int s = M - 1; s >= 0; --s) {
+        if (FULL) {
+#pragma unroll
+            for (int e = 0; e < PXL; ++e) computed_here(u[s][e]);
+        }
+        if (FULL || s < a.m) L.template reverse_step<false>(u[s], lam, C, D, zero);
+        __builtin_amdgcn_sched_barrier(0);           // nor are steps to be interleaved
+    }
     L.store(static_cast<T *>(a.lam_out), lam, true);
     return !(L.not_finite(lam) || (GUARD && __any(!__builtin_isfinite(ends))));
 }
@@ -377,13 +411,17 @@ __device__ __forceinline__ void burgers_reverse_not_finite(const BurgersReverseA
         L.load(rows == 0 ? static_cast<const T *>(a.src) : static_cast<const T *>(a.rows) + (rows - 1) * a.n, u);
 #pragma unroll 1
         for (int t = rows == 0 ? 0 : a.first + (rows - 1) * a.every; t < s; ++t) L.template primal_step<true>(u, C, D);
-        L.template reverse_step<true>(u, lam, C, D);
+        L.template reverse_step<true>(u, lam, C, D, true);
     }
     L.store(static_cast<T *>(a.lam_out), lam, true);
 }
 
-// REM: number of steps modulo kAhead of a pass over stored states; -M: up to M states are recomputed
-template <class T, int PXL, int REM> __global__ __launch_bounds__(64 * kLoopWaves) void burgers_reverse_kernel(BurgersReverseArgs a)
+// REM: number of steps modulo kAhead of a pass over stored states; -M: up to M states are recomputed.  FULL: M steps, known at compile
+// time, so that lam needs no moves where the steps' branches would join: 4 instructions of 68 a step.  The waves per SIMD are those
+// that fit without it, but for fp64 passes of 8 steps (134 registers, 3 waves; held to 128 they spill: 433 / 468 us for 97 steps of 3 10^6
+// cells); fp32 passes of 8 steps take the form with conditions (295 us; FULL 311, held to 128 registers 330).
+template <class T, int PXL, int REM, bool FULL>
+__global__ __launch_bounds__(64 * kLoopWaves, REM == -12 ? 3 : REM == -16 ? 2 : 1) void burgers_reverse_kernel(BurgersReverseArgs a)
 {
     const int halo = REM >= 0 ? a.halo : -2 * REM, W = 64 * PXL, V = own_cells(PXL, halo);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -393,10 +431,10 @@ template <class T, int PXL, int REM> __global__ __launch_bounds__(64 * kLoopWave
     bool done;
     if (__builtin_expect(inside, 1)) {
         if constexpr (REM >= 0) done = burgers_reverse_stored<T, PXL, false, REM>(a, w, lane);
-        else done = burgers_reverse_recompute<T, PXL, false, -REM>(a, w, lane);
+        else done = burgers_reverse_recompute<T, PXL, false, -REM, FULL>(a, w, lane);
     } else {
         if constexpr (REM >= 0) done = burgers_reverse_stored<T, PXL, true, REM>(a, w, lane);
-        else done = burgers_reverse_recompute<T, PXL, true, -REM>(a, w, lane);
+        else done = burgers_reverse_recompute<T, PXL, true, -REM, false>(a, w, lane);
     }
     if (__builtin_expect(!done, 0)) burgers_reverse_not_finite<T, PXL, (REM >= 0)>(a, w, lane, halo);
 }
@@ -427,14 +465,14 @@ template <class T, bool SPREAD> static hipError_t forward_T(const BurgersForward
     return hipGetLastError();
 }
 
-template <class T, int REM> static hipError_t reverse_T(const BurgersReverseArgs &a, hipStream_t stream)
+template <class T, int REM, bool FULL = false> static hipError_t reverse_T(const BurgersReverseArgs &a, hipStream_t stream)
 {
     constexpr int WIDE = 32 / (int)sizeof(T), NARROW = 2;
     const dim3 block(64 * kLoopWaves);
     if (wide_windows<T>(a.n))
-        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, REM>), loop_grid(WIDE, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, REM, FULL>), loop_grid(WIDE, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
     else
-        hipLaunchKernelGGL((burgers_reverse_kernel<T, NARROW, REM>), loop_grid(NARROW, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, NARROW, REM, FULL>), loop_grid(NARROW, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
     return hipGetLastError();
 }
 
@@ -452,9 +490,9 @@ template <class T> static hipError_t reverse_stored_T(const BurgersReverseArgs &
 template <class T> static hipError_t reverse_recompute_T(const BurgersReverseArgs &a, hipStream_t stream)
 {
     switch (recompute_kernel(a.m)) {
-    case 8: return reverse_T<T, -8>(a, stream);
-    case 12: return reverse_T<T, -12>(a, stream);
-    default: return reverse_T<T, -16>(a, stream);
+    case 8: return sizeof(T) == 8 && a.m == 8 ? reverse_T<T, -8, sizeof(T) == 8>(a, stream) : reverse_T<T, -8>(a, stream);
+    case 12: return a.m == 12 ? reverse_T<T, -12, true>(a, stream) : reverse_T<T, -12>(a, stream);
+    default: return a.m == 16 ? reverse_T<T, -16, true>(a, stream) : reverse_T<T, -16>(a, stream);
     }
 }
 
