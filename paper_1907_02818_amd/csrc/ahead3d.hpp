@@ -39,6 +39,27 @@ template <class T, int R> __device__ __forceinline__ T wave_in_plane(T s, const 
 // request was issued, and copy the slot to keep both).
 template <class T> __device__ __forceinline__ void computed(T &v) { asm volatile("" : "+v"(v)); }
 
+// The same in registers other than those of `v`: of a request's slot a value is taken before the slot's next request, where the
+// compiler would otherwise keep it in the slot's registers, request into others, and at the loop's end move (and so wait for) the newest.
+__device__ __forceinline__ float taken(float v) { float r; asm volatile("v_mov_b32 %0, %1" : "=&v"(r) : "v"(v)); return r; }
+__device__ __forceinline__ double taken(double v)
+{
+    return __hiloint2double(__float_as_int(taken(__int_as_float(__double2hiint(v)))), __float_as_int(taken(__int_as_float(__double2loint(v)))));
+}
+
+// The value of the lane before (AFTER: behind) this one, `edge` where at_edge: the neighbour in x without a way through LDS.
+template <bool AFTER> __device__ __forceinline__ float beside(float v, float edge, bool at_edge)
+{
+    const float r = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), AFTER ? 0x130 : 0x138, 0xf, 0xf, true));
+    return at_edge ? edge : r;
+}
+template <bool AFTER> __device__ __forceinline__ double beside(double v, double edge, bool at_edge)
+{
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), AFTER ? 0x130 : 0x138, 0xf, 0xf, true);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), AFTER ? 0x130 : 0x138, 0xf, 0xf, true);
+    return __hiloint2double(at_edge ? __double2hiint(edge) : hi, at_edge ? __double2loint(edge) : lo);
+}
+
 // ---- buffer access
 typedef unsigned Dwords2 __attribute__((ext_vector_type(2)));
 typedef unsigned Dwords4 __attribute__((ext_vector_type(4)));
@@ -60,6 +81,23 @@ template <class T, int N, int POLICY> __device__ __forceinline__ void buffer_sto
     else if constexpr (sizeof(v) == 8) { Dwords2 t; __builtin_memcpy(&t, &v, 8); __builtin_amdgcn_raw_buffer_store_b64(t, r, off, 0, POLICY); }
     else { Dwords4 t; __builtin_memcpy(&t, &v, 16); __builtin_amdgcn_raw_buffer_store_b128(t, r, off, 0, POLICY); }
 }
+
+// An array along a march: the byte offset of a cell in the plane that step k touches is its offset in a plane plus k planes, counted from
+// the plane that step 0 touches (outside the array perhaps, where it is not wanted).  Steps from `first` on touch wanted planes, `count`
+// of them from step 0 on; the others get a resource of zero bytes or offsets beyond it.  Two scalar instructions an access, where a
+// resource for each plane takes ten.  An array and 16 planes more stay below 2^31 bytes, so that kNowhere stays beyond.
+struct MarchedArray {
+    char *base;
+    int first;
+    unsigned size;
+    __device__ __forceinline__ MarchedArray(const void *array, int z0, int lo, int hi, unsigned bytes)
+        : base(static_cast<char *>(const_cast<void *>(array)) + (long long)z0 * (long long)bytes), first(lo - z0),
+          size(hi >= z0 ? (unsigned)(hi + 1 - z0) * bytes : 0u) {}
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t at(int k) const
+    {
+        return __builtin_amdgcn_make_buffer_rsrc(base, 0, k >= first ? size : 0u, 0x00020000);
+    }
+};
 
 enum class StarOp { WaveAdjoint, WavePrimal, StarAdjoint, StarPrimal };
 

@@ -361,22 +361,23 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_kernel(PairArgs a)
 // The same on grids that do not fill the chip, where a workgroup marches few planes and the time from a plane's request to the
 // next plane's is what counts.  As in ahead3d.hpp all accesses go through buffer resources, without a condition around any of
 // them: a plane that is not wanted has a resource of zero bytes and reads as zero, cells outside I have an offset beyond any plane.
-// The waits inside a step therefore leave the other requests in flight (vmcnt 6 to 11, of 6 loads a plane); at the loop's end, every
-// second plane, the compiler moves the newest requests' registers and waits for them (vmcnt 3 and 2), so the march is not yet what D = 2
-// promises.  One instantiation serves core and remainder.  The sums are pair_march's, bit for bit.
-// One workgroup per CU and two planes ahead; three planes 2 % slower, two workgroups per CU 5 to 10 % (fp32) or more registers than
-// there are (fp64: 162).  25 steps, the tiles below / this, fp32 96 x 130 x 164 237 / 182 us, 128^3 189 / 153, 300 x 80 x 80 216 / 183, 64^3
-// 97 / 90; fp64 40 x 300 x 96 227 / 191.
+// The waits (vmcnt 10 to 13, of 6 loads and 2 stores a plane) leave a plane's requests in flight for two steps; one instantiation
+// serves core and remainder.  The sums are pair_march's, bit for bit.
+// What bounds it is what its waves issue: 120 instructions a step, 0.5 us with two waves per SIMD (half of it vector ALU; half the cells per thread in
+// twice the waves: the same; reading LDS while the next plane arrives: 0 to 7 % slower), then 3 us of start and first latency a launch.  Hence
+// one resource per array and march, neighbours in x from the lanes beside, all LDS reads of a step together, and waves without ring cells
+// that leave the ring out.  25 steps, with a resource per plane and access and all neighbours from LDS / now: fp32 96 x 130 x 164 186 / 163 us, 128^3 155 /
+// 140, 300 x 80 x 80 184 / 160, 64^3 90 / 84; fp64 40 x 300 x 96 191 / 169.  Three planes in flight 8 % slower.
 template <class T, int BX, int BY, int PX, int D>
 __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_ahead_kernel(PairArgs a)
 {
     using G = PairTile<T, BX, BY, 1, PX>;
     using V = Vec<T, PX>;
     static_assert(G::HS == 1, "one frame cell per thread at most");
-    constexpr int LX1 = G::LX1, LX2 = G::LX2;
+    constexpr int LX = G::LX1;                   // both planes have the wider one's geometry, where a thread's cells are whole vectors
     constexpr T W0 = T(3.0 * star_w<1>(0)), W1 = T(star_w<1>(1));
     __shared__ __attribute__((aligned(16))) T sq1[2 * G::PLANE1];
-    __shared__ __attribute__((aligned(16))) T sq2[2 * G::PLANE2];
+    __shared__ __attribute__((aligned(16))) T sq2[2 * G::PLANE1];
     int tix, tiy, zs, ze;
     block_to_tile(a.map, blockIdx.x, tix, tiy, zs, ze);
     const int tid = threadIdx.x, tx = tid % BX, ty = tid / BX;
@@ -396,34 +397,38 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_ahead_kernel(PairArgs 
     const bool frame = G::frame_cell(tid, 0, lx, ly), ring = tid < G::NRING;
     const bool hin = frame && in_I(x0 - 2 + lx, y0 - 2 + ly), rin = ring && hin;
     const unsigned hoff = hin ? offset(x0 - 2 + lx, y0 - 2 + ly) : kNowhere, roff = ring ? hoff : kNowhere;
-    const int hl = frame ? ly * LX1 + lx : 0;                                 // (0, 0) is a corner nobody reads
-    const int ring1 = ring ? ly * LX1 + lx : LX1 + 1, ring2 = ring ? (ly - 1) * LX2 + (lx - 1) : 0;
+    const bool ring_wave = __builtin_amdgcn_readfirstlane(tid) < G::NRING;    // waves without a ring cell skip what is theirs
+    const int hl = frame ? ly * LX + lx : 0;                                  // (0, 0) is a corner nobody reads
+    const int ring1 = ring ? hl : LX + 1;
+    const int own = (2 + ty) * LX + 2 + tx * PX;
+    const bool left_end = tx == 0, right_end = tx == BX - 1;                  // whose neighbour in x is a frame cell
+    const int end = left_end ? own - 1 : right_end ? own + PX : own;
 
-    auto plane_of = [&](const void *base, int z, bool wanted) {
-        char *p = static_cast<char *>(const_cast<void *>(base)) + (long long)z * (long long)bytes;
-        return __builtin_amdgcn_make_buffer_rsrc(p, 0, wanted ? bytes : 0u, 0x00020000);
-    };
-    auto plane_in_I = [&](int z) { return z >= 1 && z < nz - 1; };
     const int zi0 = zs - 2, zi1 = ze + 1;        // q planes that reach the outputs [zs, ze)
-    auto a1_wanted = [&](int z) { return z >= zs - 1 && z <= ze && plane_in_I(z); };
+    const int a1_lo = max(zs - 1, 1), a1_hi = min(ze, nz - 2);      // planes of a' that do and lie in I
+    // step k: c and a of plane zi0 + k, b and out_b of the one before, out_a of two more before
+    const MarchedArray mc(a.c, zi0, max(zi0, 1), min(zi1, nz - 2), bytes), ma(a.a, zi0, max(zi0, 1), min(zi1, nz - 2), bytes);
+    const MarchedArray mb(a.b, zi0 - 1, a1_lo, a1_hi, bytes);
+    const MarchedArray oa(a.out_a, zi0 - 3, zs, ze - 1, bytes), ob(a.out_b, zi0 - 1, zs, ze - 1, bytes);
 
     // in flight: c and a of plane z on tile and frame, b of plane z - 1 on tile and ring
     V sc[D], sa[D], sb[D];
     Vec<T, 1> shc[D], sha[D], sbr[D];
-    auto issue = [&](int z, int d) {
-        const bool used = z <= zi1 && plane_in_I(z);
-        const auto rc = plane_of(a.c, z, used), ra = plane_of(a.a, z, used), rb = plane_of(a.b, z - 1, a1_wanted(z - 1));
-        sc[d] = buffer_load<T, PX, kCached>(rc, ioff);
-        sa[d] = buffer_load<T, PX, kCached>(ra, ioff);
-        shc[d] = buffer_load<T, 1, kCached>(rc, hoff);
-        sha[d] = buffer_load<T, 1, kCached>(ra, hoff);
-        sb[d] = buffer_load<T, PX, kCached>(rb, ioff);
-        sbr[d] = buffer_load<T, 1, kCached>(rb, roff);
+    auto issue = [&](int k, int d) {
+        const unsigned zoff = (unsigned)k * bytes;
+        const auto rc = mc.at(k), ra = ma.at(k), rb = mb.at(k);
+        sc[d] = buffer_load<T, PX, kCached>(rc, ioff + zoff);
+        sa[d] = buffer_load<T, PX, kCached>(ra, ioff + zoff);
+        shc[d] = buffer_load<T, 1, kCached>(rc, hoff + zoff);
+        sha[d] = buffer_load<T, 1, kCached>(ra, hoff + zoff);
+        sb[d] = buffer_load<T, PX, kCached>(rb, ioff + zoff);
+        sbr[d] = buffer_load<T, 1, kCached>(rb, roff + zoff);
         __builtin_amdgcn_sched_barrier(0);
     };
 
     // as in pair_march
-    T acc1[PX][3], acc1r[3], acc2[PX][3], c_prev[PX], c_prev_r = T(0), am_prev[PX], q2[PX], q2r = T(0), a1m[PX];
+    T acc1[PX][3], acc1r[3], acc2[PX][3], c_prev[PX], c_prev_r = T(0), am_prev[PX], q2r = T(0);
+    V q2, neg_a1m;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         acc1r[k] = T(0);
@@ -431,105 +436,116 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_ahead_kernel(PairArgs 
         for (int e = 0; e < PX; ++e) acc1[e][k] = acc2[e][k] = T(0);
     }
 #pragma unroll
-    for (int e = 0; e < PX; ++e) c_prev[e] = am_prev[e] = q2[e] = a1m[e] = T(0);
+    for (int e = 0; e < PX; ++e) c_prev[e] = am_prev[e] = q2.v[e] = neg_a1m.v[e] = T(0);
 
-    auto step = [&](int z, int d) {
-        T *s1 = sq1 + ((z - zi0) & 1) * G::PLANE1;
-        T *s2 = sq2 + ((z - zi0) & 1) * G::PLANE2;
+    auto step = [&](int k, int d) {
+        const unsigned zoff = (unsigned)k * bytes;
+        T *s1 = sq1 + (k & 1) * G::PLANE1;
+        T *s2 = sq2 + (k & 1) * G::PLANE1;
         T am[PX], cc[PX], cb[PX];
         V qo;
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
             cc[e] = sc[d].v[e];
-            cb[e] = sb[d].v[e];
             am[e] = in[e] ? sa[d].v[e] : T(0);
             qo.v[e] = in[e] ? cc[e] * sa[d].v[e] : T(0);
         }
-        T amr = sha[d].v[0], ccr = shc[d].v[0], cbr = sbr[d].v[0], qr = ccr * amr;
-        st_vec<T, PX>(s1 + (2 + ty) * LX1 + 2 + tx * PX, qo);
+        T qr = shc[d].v[0] * sha[d].v[0];
+        st_vec<T, PX>(s1 + own, qo);
         s1[hl] = qr;
+        st_vec<T, PX>(s2 + own, q2);
+        if (ring_wave) s2[hl] = q2r;
 #pragma unroll
-        for (int e = 0; e < PX; ++e) s2[(1 + ty) * LX2 + 1 + tx * PX + e] = q2[e];
-        if (ring) s2[ring2] = q2r;
-#pragma unroll
-        for (int e = 0; e < PX; ++e) { computed(cc[e]); computed(cb[e]); computed(am[e]); computed(qo.v[e]); }
-        computed(amr); computed(ccr); computed(cbr); computed(qr);
-        issue(z + D, d);
+        for (int e = 0; e < PX; ++e) { cc[e] = taken(cc[e]); cb[e] = taken(sb[d].v[e]); computed(am[e]); computed(qo.v[e]); }
+        const T amr = taken(sha[d].v[0]), ccr = taken(shc[d].v[0]), cbr = taken(sbr[d].v[0]);
+        computed(qr);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(k + D, d);
         __syncthreads();
 
+        // the star of plane z without its z neighbours' terms
+        auto in_plane = [&](const V &q, const V &up, const V &down, T frame_cell, int e) {
+            const T left = e > 0 ? q.v[e > 0 ? e - 1 : 0] : beside<false>(q.v[PX - 1], frame_cell, left_end);
+            const T right = e < PX - 1 ? q.v[e < PX - 1 ? e + 1 : 0] : beside<true>(q.v[0], frame_cell, right_end);
+            return W0 * q.v[e] + W1 * (left + right) + W1 * (up.v[e] + down.v[e]);
+        };
+        // all of a step's reads are requested before the first is waited for
+        const V up2 = ld_vec<T, PX>(s2 + own - LX), down2 = ld_vec<T, PX>(s2 + own + LX);
+        const T end2 = s2[end];
+        const V up1 = ld_vec<T, PX>(s1 + own - LX), down1 = ld_vec<T, PX>(s1 + own + LX);
+        const T end1 = s1[end], ring_x = s1[ring1 - 1], ring_X = s1[ring1 + 1], ring_y = s1[ring1 - LX], ring_Y = s1[ring1 + LX];
+        __builtin_amdgcn_sched_barrier(0);
         // ---- stage 2: q' of plane z-2 -> a'' sums of planes z-3, z-2, z-1
         V o;
         {
-            const T *at = s2 + (1 + ty) * LX2 + 1 + tx * PX;
 #pragma unroll
             for (int e = 0; e < PX; ++e) {
-                const T left = e > 0 ? q2[e > 0 ? e - 1 : 0] : at[-1], right = e < PX - 1 ? q2[e < PX - 1 ? e + 1 : 0] : at[PX];
-                const T s = W0 * q2[e] + W1 * (left + right) + W1 * (at[e - LX2] + at[e + LX2]);
-                acc2[e][1] += s + T(2) * a1m[e];
-                acc2[e][0] += W1 * q2[e];
-                acc2[e][2] += W1 * q2[e];
-                acc2[e][2] -= am_prev[e];                                     // -a m of plane z-1
+                acc2[e][1] += in_plane(q2, up2, down2, end2, e) - T(2) * neg_a1m.v[e];
+                acc2[e][0] += W1 * q2.v[e];
+                acc2[e][2] = W1 * q2.v[e] - am_prev[e];                       // -a m of plane z-1
                 o.v[e] = acc2[e][0];
             }
         }
-        const int zo2 = z - 3, zo1 = z - 1;
-        buffer_store<T, PX, kCached>(plane_of(a.out_a, zo2, zo2 >= zs && zo2 < ze), goff, o);
+        buffer_store<T, PX, kCached>(oa.at(k), goff + zoff, o);
 
         // ---- stage 1: q of plane z -> a' sums of planes z-1, z, z+1
         {
-            const T *at = s1 + (2 + ty) * LX1 + 2 + tx * PX;
-            const V up = ld_vec<T, PX>(at - LX1), down = ld_vec<T, PX>(at + LX1);
 #pragma unroll
             for (int e = 0; e < PX; ++e) {
-                const T left = e > 0 ? qo.v[e > 0 ? e - 1 : 0] : at[-1], right = e < PX - 1 ? qo.v[e < PX - 1 ? e + 1 : 0] : at[PX];
-                const T s = W0 * qo.v[e] + W1 * (left + right) + W1 * (up.v[e] + down.v[e]);
-                acc1[e][1] += s + T(2) * am[e];
+                acc1[e][1] += in_plane(qo, up1, down1, end1, e) + T(2) * am[e];
                 acc1[e][0] += W1 * qo.v[e];
-                acc1[e][2] += W1 * qo.v[e];
-            }
-            if (ring) {
-                const T *ar = s1 + ring1;
-                const T s = W0 * qr + W1 * (ar[-1] + ar[1]) + W1 * (ar[-LX1] + ar[LX1]);
-                acc1r[1] += s + T(2) * amr;
-                acc1r[0] += W1 * qr;
-                acc1r[2] += W1 * qr;
+                acc1[e][2] = W1 * qo.v[e];
             }
         }
         // a' of plane z-1 is complete: form q' and -a' m from it
-        const bool wanted = a1_wanted(zo1);
+        const bool wanted = (unsigned)(zi0 + k - 1 - a1_lo) < (unsigned)max(a1_hi + 1 - a1_lo, 0);
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
-            const T a1 = acc1[e][0] + cb[e];
-            a1m[e] = wanted && in[e] ? a1 : T(0);
-            q2[e] = wanted && in[e] ? c_prev[e] * a1 : T(0);
-            o.v[e] = -a1m[e];
+            T neg_a1 = -acc1[e][0] - cb[e], q = c_prev[e] * -neg_a1;
+            computed(neg_a1); computed(q);
+            neg_a1m.v[e] = wanted & in[e] ? neg_a1 : T(0);
+            q2.v[e] = wanted & in[e] ? q : T(0);
         }
-        q2r = wanted && rin ? c_prev_r * (acc1r[0] + cbr) : T(0);
-        buffer_store<T, PX, kCached>(plane_of(a.out_b, zo1, zo1 >= zs && zo1 < ze), goff, o);
-        acc1r[0] = acc1r[1]; acc1r[1] = acc1r[2]; acc1r[2] = T(0);
+        if (ring_wave) {
+            const T s = W0 * qr + W1 * (ring_x + ring_X) + W1 * (ring_y + ring_Y);
+            acc1r[1] += s + T(2) * amr;
+            acc1r[0] += W1 * qr;
+            acc1r[2] = W1 * qr;
+            T q = c_prev_r * (acc1r[0] + cbr);
+            computed(q);
+            q2r = wanted & rin ? q : T(0);
+            acc1r[0] = acc1r[1]; acc1r[1] = acc1r[2];
+        }
+        buffer_store<T, PX, kCached>(ob.at(k), goff + zoff, neg_a1m);
         c_prev_r = ccr;
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
-            acc1[e][0] = acc1[e][1]; acc1[e][1] = acc1[e][2]; acc1[e][2] = T(0);
-            acc2[e][0] = acc2[e][1]; acc2[e][1] = acc2[e][2]; acc2[e][2] = T(0);
+            acc1[e][0] = acc1[e][1]; acc1[e][1] = acc1[e][2];
+            acc2[e][0] = acc2[e][1]; acc2[e][1] = acc2[e][2];
             c_prev[e] = cc[e];
             am_prev[e] = am[e];
         }
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    const int last = zi1 + 1;
+    // each request is followed by two stores, as in the loop (here to nowhere), or the loop's waits would have to suit both counts
 #pragma unroll
-    for (int d = 0; d < D; ++d) issue(zi0 + d, d);
-    int z = zi0;
-    for (; z + D - 1 <= last; z += D) {
+    for (int d = 0; d < D; ++d) {
+        issue(d, d);
+        buffer_store<T, PX, kCached>(oa.at(-1), kNowhere, V{});
+        buffer_store<T, PX, kCached>(ob.at(-1), kNowhere, V{});
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const int steps = zi1 + 2 - zi0;
+    int k = 0;
+    for (; k + D <= steps; k += D) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) step(z + d, d);
+        for (int d = 0; d < D; ++d) step(k + d, d);
     }
 #pragma unroll
     for (int d = 0; d < D - 1; ++d) {
-        if (z + d > last) return;
-        step(z + d, d);
+        if (k + d >= steps) return;
+        step(k + d, d);
     }
 }
 
@@ -565,16 +581,16 @@ long adjoint_wave3d_pair_cost(int is_f64, int nx, int ny, int nz)
     return plan_pair(is_f64, nx, ny, nz, LaunchOptions{}).cost;
 }
 
-// Where the march with its requests ahead is taken, by the bytes of the five arrays (340 drawn grids, geometric mean of the time in
-// the shapes above over its time, smallest in brackets).  The arrays of a pass are found in the last-level cache, which this march
-// relies on: fp32 up to 60 MB 1.14 (1.00), 60 .. 130 MB 1.18 (1.05); against the default tiles, which the last passes of a
-// three-step sweep would take, 130 .. 230 MB 1.05 and more, 230 .. 300 MB 0.95 (0.93); fp64 30 .. 60 MB 1.10 (0.98), default tiles up
-// to 230 MB 1.22 (1.12), 230 .. 300 MB 1.09 (0.98).  fp64 in small tiles below 30 MB 0.98 (0.88): a
-// chunk of one to four planes leaves no request to run ahead of.  fp32 grids of more bytes that would cost less in 64 x 16 tiles
+// Where the march with its requests ahead is taken, by the bytes of the five arrays, which it relies on finding in the last-level cache
+// (drawn grids, time in the shapes above over its time): fp32 up to 130 MB 1.15 to 1.35; against the default tiles, which the
+// last passes of a three-step sweep would take, 130 .. 230 MB 1.05 and more, 230 .. 300 MB 0.95 (0.93); fp64 30 .. 60 MB 1.24, default tiles up
+// to 230 MB 1.22 (1.12), 230 .. 300 MB 1.09 (0.98); fp64 in small tiles below 30 MB 1.00 to 1.17 from 16 planes on, 0.89 to 1.1 with fewer: a
+// chunk of one or two planes leaves no request to run ahead of.  fp32 grids of more bytes that would cost less in 64 x 16 tiles
 // (few rows of 10^5 cells, whose default tiles are half empty) take it too: 6 x 16 x 200000, 9 steps, without / with requests ahead 466 / 452 us.
 static bool pair_runs_ahead(int is_f64, int nx, int ny, int nz, const PairPlan &plan)
 {
-    const double bytes = 5.0 * nx * ny * nz * (is_f64 ? 8 : 4);
+    const double plane = (double)nx * ny * (is_f64 ? 8 : 4), bytes = 5 * plane * nz;
+    if ((nz + 16) * plane >= 0x1p31) return false;                  // see MarchedArray
     if (!is_f64) return bytes <= 230e6 || plan.small;
     return bytes <= 230e6 && (!plan.small || bytes >= 30e6);
 }

@@ -376,22 +376,24 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_triple_kernel(TripleArgs a)
     else      triple_march<T, BX, BY, PY, PX, true>(a, tix, tiy, zs, ze, sq0, sq1, sq2, cold, coldr);
 }
 
-// The same on grids that do not fill the chip, with requests ahead as in adj_wave3d_pair_ahead_kernel in wave3d_pair.hip (and
-// its wait at the loop's end): no condition around any memory access, planes that are not wanted and cells outside I read as zero.  One row of cells per thread
-// and one frame cell at most, so that c of the three planes before stays in registers.  The sums are triple_march's, bit for bit.
-// One workgroup per CU with two planes in flight; three 2 % slower.  25 steps, the wide tiles / this: fp64 128^3 255 / 213 us, 160^3
-// 462 / 352, 300 x 80 x 80 320 / 236; fp32 197 x 68 x 260 383 / 247, 64 x 400 x 400 657 / 453, 200^3 536 / 490.  What bounds it on the
-// smaller ones is the serial chain of a step, 0.9 us: LDS, barrier and three stages, for 8 planes beyond each chunk.
-template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(BX *BY) void adj_wave3d_triple_ahead_kernel(TripleArgs a)
+// The same on grids that do not fill the chip, with requests ahead as in adj_wave3d_pair_ahead_kernel in wave3d_pair.hip: no condition
+// around any memory access, planes that are not wanted and cells outside I read as zero.  One row of cells per thread
+// and one frame cell at most, so that c of the three planes before and the cells' own q stay in registers.  The sums are triple_march's, bit for bit.
+// Two planes in flight; three 3 % (fp32) to 70 % (fp64, registers) slower.  What bounds it on the smaller grids is what its waves issue per
+// step, about 0.8 us, for 8 planes beyond each chunk: neighbours in x come from the lanes beside, resources last for the march,
+// waves without frame cells leave the frame out (fp32 197 x 68 x 260 247 -> 208 us, 200^3 491 -> 412; fp64 128^3 213 -> 195, 160^3 351 -> 326,
+// 300 x 80 x 80 235 -> 208).  Requests after the barrier and the reads: 8 % slower.  fp32 keeps to 128 registers, so that
+// two workgroups share a CU where there are more of them than CUs (64 x 400 x 400: 472 us with 140 registers, 447).
+template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(BX *BY, sizeof(T) == 4 ? 4 : 2) void adj_wave3d_triple_ahead_kernel(TripleArgs a)
 {
     using G = TripleTile<T, BX, BY, 1, PX>;
     using V = Vec<T, PX>;
     static_assert(G::HS == 1, "one frame cell per thread at most");
-    constexpr int LX = G::LX;
+    constexpr int LX = G::TX + 8, PLANE = LX * (G::TY + 6);      // origin (x0-4, y0-3): a thread's cells are a whole vector
     constexpr T W0 = T(3.0 * star_w<1>(0)), W1 = T(star_w<1>(1));
-    __shared__ T sq0[2 * G::PLANE];
-    __shared__ T sq1[2 * G::PLANE];
-    __shared__ T sq2[2 * G::PLANE];
+    __shared__ __attribute__((aligned(16))) T sq0[2 * PLANE];
+    __shared__ __attribute__((aligned(16))) T sq1[2 * PLANE];
+    __shared__ __attribute__((aligned(16))) T sq2[2 * PLANE];
     int tix, tiy, zs, ze;
     block_to_tile(a.map, blockIdx.x, tix, tiy, zs, ze);
     const int tid = threadIdx.x, tx = tid % BX, ty = tid / BX;
@@ -408,51 +410,56 @@ template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(B
     const unsigned goff = x < nx && y < ny ? offset(x, y) : kNowhere;         // rows are whole vectors
     int lx, ly;
     const bool frame = G::frame_cell(tid, 0, lx, ly);
-    const bool ring1 = tid < G::N1 + G::N2, ring2 = tid < G::N1;              // run stage 1, stage 2 as well
+    // frame cells that run stage 1, and waves that hold some, and some that run stage 2 as well; others leave their part out
+    const bool ring1 = tid < G::N1 + G::N2;
+    const bool ring1_wave = __builtin_amdgcn_readfirstlane(tid) < G::N1 + G::N2, ring2_wave = __builtin_amdgcn_readfirstlane(tid) < G::N1;
     const bool hin = frame && in_I(x0 - 3 + lx, y0 - 3 + ly);
     const unsigned hoff = hin ? offset(x0 - 3 + lx, y0 - 3 + ly) : kNowhere, roff = ring1 ? hoff : kNowhere;
-    const int hl = frame ? ly * LX + lx : 0;                                  // (0, 0) is a corner nobody reads
-    const int own = (3 + ty) * LX + 3 + tx * PX;
+    const int hl = frame ? ly * LX + lx + 1 : 0;                              // (0, 0) is a cell nobody reads
+    const int at = ring1 ? hl : LX + 1;                                       // the cell whose neighbours are read
+    const int own = (3 + ty) * LX + 4 + tx * PX;
+    const bool left_end = tx == 0, right_end = tx == BX - 1;                  // whose neighbour in x is a frame cell
+    const int end = left_end ? own - 1 : right_end ? own + PX : own;
 
-    auto plane_of = [&](const void *base, int z, bool wanted) {
-        char *p = static_cast<char *>(const_cast<void *>(base)) + (long long)z * (long long)bytes;
-        return __builtin_amdgcn_make_buffer_rsrc(p, 0, wanted ? bytes : 0u, 0x00020000);
-    };
-    auto plane_in_I = [&](int z) { return z >= 1 && z < nz - 1; };
     const int zi0 = zs - 3, zi1 = ze + 2;        // q0 planes that reach the outputs [zs, ze)
-    auto a1_wanted = [&](int z) { return z >= zs - 2 && z <= ze + 1 && plane_in_I(z); };
-    auto a2_wanted = [&](int z) { return z >= zs - 1 && z <= ze && plane_in_I(z); };
+    const int a1_lo = max(zs - 2, 1), a1_hi = min(ze + 1, nz - 2);            // planes of a1 and a2 that do and lie in I
+    const int a2_lo = max(zs - 1, 1), a2_hi = min(ze, nz - 2);
+    // step k: c and a of plane zi0 + k, b of the one before, out_b of two more before, out_a of another two
+    const MarchedArray mc(a.c, zi0, max(zi0, 1), min(zi1, nz - 2), bytes), ma(a.a, zi0, max(zi0, 1), min(zi1, nz - 2), bytes);
+    const MarchedArray mb(a.b, zi0 - 1, a1_lo, a1_hi, bytes);
+    const MarchedArray oa(a.out_a, zi0 - 5, zs, ze - 1, bytes), ob(a.out_b, zi0 - 3, zs, ze - 1, bytes);
 
     // in flight: c and a of plane z on tile and frame, b of plane z - 1 on tile, D1 and D2
     V sc[D], sa[D], sb[D];
     Vec<T, 1> shc[D], sha[D], sbr[D];
-    auto issue = [&](int z, int d) {
-        const bool used = z <= zi1 && plane_in_I(z);
-        const auto rc = plane_of(a.c, z, used), ra = plane_of(a.a, z, used), rb = plane_of(a.b, z - 1, a1_wanted(z - 1));
-        sc[d] = buffer_load<T, PX, kCached>(rc, ioff);
-        sa[d] = buffer_load<T, PX, kCached>(ra, ioff);
-        shc[d] = buffer_load<T, 1, kCached>(rc, hoff);
-        sha[d] = buffer_load<T, 1, kCached>(ra, hoff);
-        sb[d] = buffer_load<T, PX, kCached>(rb, ioff);
-        sbr[d] = buffer_load<T, 1, kCached>(rb, roff);
+    auto issue = [&](int k, int d) {
+        const unsigned zoff = (unsigned)k * bytes;
+        const auto rc = mc.at(k), ra = ma.at(k), rb = mb.at(k);
+        sc[d] = buffer_load<T, PX, kCached>(rc, ioff + zoff);
+        sa[d] = buffer_load<T, PX, kCached>(ra, ioff + zoff);
+        shc[d] = buffer_load<T, 1, kCached>(rc, hoff + zoff);
+        sha[d] = buffer_load<T, 1, kCached>(ra, hoff + zoff);
+        sb[d] = buffer_load<T, PX, kCached>(rb, ioff + zoff);
+        sbr[d] = buffer_load<T, 1, kCached>(rb, roff + zoff);
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto star = [&](const T *sp, T (&acc)[PX][3]) {
-        const T *at = sp + own;
-        T q[PX];
-#pragma unroll
-        for (int e = 0; e < PX; ++e) q[e] = at[e];
+    // what a plane's cells and a step's neighbours in y and, at a row's ends, in x add
+    struct Beside { V up, down; T end; };
+    auto read_beside = [&](const T *sp) { return Beside{ld_vec<T, PX>(sp + own - LX), ld_vec<T, PX>(sp + own + LX), sp[end]}; };
+    auto star = [&](const V &q, const Beside &n, T (&acc)[PX][3]) {
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
-            const T left = e > 0 ? q[e > 0 ? e - 1 : 0] : at[-1], right = e < PX - 1 ? q[e < PX - 1 ? e + 1 : 0] : at[PX];
-            acc[e][1] += W0 * q[e] + W1 * (left + right) + W1 * (at[e - LX] + at[e + LX]);
-            acc[e][0] += W1 * q[e];
-            acc[e][2] += W1 * q[e];
+            const T left = e > 0 ? q.v[e > 0 ? e - 1 : 0] : beside<false>(q.v[PX - 1], n.end, left_end);
+            const T right = e < PX - 1 ? q.v[e < PX - 1 ? e + 1 : 0] : beside<true>(q.v[0], n.end, right_end);
+            acc[e][1] += W0 * q.v[e] + W1 * (left + right) + W1 * (n.up.v[e] + n.down.v[e]);
+            acc[e][0] += W1 * q.v[e];
+            acc[e][2] += W1 * q.v[e];
         }
     };
-    auto star_ring = [&](const T *at, T (&acc)[3]) {
-        const T q = at[0];
-        acc[1] += W0 * q + W1 * (at[-1] + at[1]) + W1 * (at[-LX] + at[LX]);
+    struct BesideRing { T x, X, y, Y; };
+    auto read_ring = [&](const T *at) { return BesideRing{at[-1], at[1], at[-LX], at[LX]}; };
+    auto star_ring = [&](T q, const BesideRing &n, T (&acc)[3]) {
+        acc[1] += W0 * q + W1 * (n.x + n.X) + W1 * (n.y + n.Y);
         acc[0] += W1 * q;
         acc[2] += W1 * q;
     };
@@ -467,98 +474,128 @@ template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(B
     }
 #pragma unroll
     for (int e = 0; e < PX; ++e) a1m[e] = c1[e] = c2[e] = c3[e] = T(0);
-    bool q1_valid = false, q2_valid = false;     // the planes of q1 and q2 that this step reads were staged by the last one
+    V q1{}, q2{};                                // of the planes that this step reads from LDS
+    T q1r = T(0);
 
-    auto step = [&](int z, int d) {
-        const int buf = (z - zi0) & 1;
-        T *s0 = sq0 + buf * G::PLANE;
-        const T *s1 = sq1 + buf * G::PLANE, *s2 = sq2 + buf * G::PLANE;
-        T *n1 = sq1 + (buf ^ 1) * G::PLANE, *n2 = sq2 + (buf ^ 1) * G::PLANE;
+    auto step = [&](int k, int d) {
+        const unsigned zoff = (unsigned)k * bytes;
+        const int buf = k & 1;
+        T *s0 = sq0 + buf * PLANE;
+        const T *s1 = sq1 + buf * PLANE, *s2 = sq2 + buf * PLANE;
+        T *n1 = sq1 + (buf ^ 1) * PLANE, *n2 = sq2 + (buf ^ 1) * PLANE;
         T am[PX], cc[PX], cb[PX];
+        V q0;
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
             cc[e] = sc[d].v[e];
-            cb[e] = sb[d].v[e];
             am[e] = in[e] ? sa[d].v[e] : T(0);
-            s0[own + e] = in[e] ? cc[e] * sa[d].v[e] : T(0);
+            q0.v[e] = in[e] ? cc[e] * sa[d].v[e] : T(0);
         }
-        T amr = sha[d].v[0], ccr = shc[d].v[0], cbr = sbr[d].v[0];
-        s0[hl] = ccr * amr;
+        T q0r = shc[d].v[0] * sha[d].v[0];
+        st_vec<T, PX>(s0 + own, q0);
+        s0[hl] = q0r;
 #pragma unroll
-        for (int e = 0; e < PX; ++e) { computed(cc[e]); computed(cb[e]); computed(am[e]); }
-        computed(amr); computed(ccr); computed(cbr);
+        for (int e = 0; e < PX; ++e) { cc[e] = taken(cc[e]); cb[e] = taken(sb[d].v[e]); computed(am[e]); computed(q0.v[e]); }
+        const T amr = taken(sha[d].v[0]), ccr = taken(shc[d].v[0]), cbr = taken(sbr[d].v[0]);
+        computed(q0r);
         __builtin_amdgcn_sched_barrier(0);
-        issue(z + D, d);
+        issue(k + D, d);
         __syncthreads();
+        // all of a step's reads are requested before the first is waited for
+        const Beside b2 = read_beside(s2), b1 = read_beside(s1);
+        const BesideRing r1 = read_ring(s1 + at);
+        const Beside b0 = read_beside(s0);
+        const BesideRing r0 = read_ring(s0 + at);
+        __builtin_amdgcn_sched_barrier(0);
 
         // ---- stage 3: q2 of plane z-4; a3 of plane z-5 is complete
-        if (q2_valid) star(s2, acc3);
+        star(q2, b2, acc3);
         V o;
 #pragma unroll
         for (int e = 0; e < PX; ++e) o.v[e] = acc3[e][0];
-        const int zo3 = z - 5, zo2 = z - 3;
-        buffer_store<T, PX, kCached>(plane_of(a.out_a, zo3, zo3 >= zs && zo3 < ze), goff, o);
+        buffer_store<T, PX, kCached>(oa.at(k), goff + zoff, o);
 
         // ---- stage 2: q1 of plane z-2; a2 of plane z-3 is complete
-        if (q1_valid) {
-            star(s1, acc2);
-            if (ring2) star_ring(s1 + hl, acc2r);
-        }
-        q2_valid = a2_wanted(zo2);
+        star(q1, b1, acc2);
+        const bool a2_wanted = (unsigned)(zi0 + k - 3 - a2_lo) < (unsigned)max(a2_hi + 1 - a2_lo, 0);
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
-            const T a2m = q2_valid && in[e] ? acc2[e][0] : T(0);
-            n2[own + e] = in[e] ? c3[e] * a2m : T(0);
+            T neg = -acc2[e][0], q = c3[e] * acc2[e][0];
+            computed(neg); computed(q);
+            o.v[e] = a2_wanted & in[e] ? neg : T(0);                          // -a2 m
+            q2.v[e] = a2_wanted & in[e] ? q : T(0);
             acc3[e][0] = acc3[e][1];
-            acc3[e][1] = acc3[e][2] + T(2) * a2m;
+            acc3[e][1] = acc3[e][2] - T(2) * o.v[e];
             acc3[e][2] = -a1m[e];                                             // of plane z-2
             acc2[e][0] = acc2[e][1];
             acc2[e][1] = acc2[e][2];
             acc2[e][2] = -am[e];                                              // of plane z
-            o.v[e] = -a2m;
         }
-        if (ring2) n2[hl] = hin ? c3r * acc2r[0] : T(0);
-        acc2r[0] = acc2r[1]; acc2r[1] = acc2r[2]; acc2r[2] = -amr;
-        buffer_store<T, PX, kCached>(plane_of(a.out_b, zo2, zo2 >= zs && zo2 < ze), goff, o);
+        st_vec<T, PX>(n2 + own, q2);
+        if (ring2_wave) {
+            star_ring(q1r, r1, acc2r);
+            T q = c3r * acc2r[0];
+            computed(q);
+            n2[hl] = a2_wanted & hin ? q : T(0);
+            acc2r[0] = acc2r[1]; acc2r[1] = acc2r[2]; acc2r[2] = -amr;
+        }
+        buffer_store<T, PX, kCached>(ob.at(k), goff + zoff, o);
 
         // ---- stage 1: q0 of plane z; a1 of plane z-1 is complete
-        star(s0, acc1);
-        if (ring1) star_ring(s0 + hl, acc1r);
-        q1_valid = a1_wanted(z - 1);
+        star(q0, b0, acc1);
+        const bool a1_wanted = (unsigned)(zi0 + k - 1 - a1_lo) < (unsigned)max(a1_hi + 1 - a1_lo, 0);
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
-            const T v = acc1[e][0] + cb[e];
-            a1m[e] = q1_valid && in[e] ? v : T(0);
-            n1[own + e] = in[e] ? c1[e] * v : T(0);
+            T v = acc1[e][0] + cb[e], q = c1[e] * v;
+            computed(v); computed(q);
+            a1m[e] = a1_wanted & in[e] ? v : T(0);
+            q1.v[e] = a1_wanted & in[e] ? q : T(0);
             acc2[e][1] += T(2) * a1m[e];
             acc1[e][0] = acc1[e][1] + T(2) * am[e];
             acc1[e][1] = acc1[e][2];
             acc1[e][2] = T(0);
             c3[e] = c2[e]; c2[e] = c1[e]; c1[e] = cc[e];
         }
-        const T vr = acc1r[0] + cbr;
-        const T a1r = q1_valid && hin ? vr : T(0);
-        if (ring1) n1[hl] = hin ? c1r * vr : T(0);
-        acc2r[1] += T(2) * a1r;
-        acc1r[0] = acc1r[1] + T(2) * amr;
-        acc1r[1] = acc1r[2];
-        acc1r[2] = T(0);
+        st_vec<T, PX>(n1 + own, q1);
+        if (ring1_wave) {
+            star_ring(q0r, r0, acc1r);
+            T v = acc1r[0] + cbr, q = c1r * v;
+            computed(v); computed(q);
+            const T a1r = a1_wanted & hin ? v : T(0);
+            q1r = a1_wanted & hin ? q : T(0);
+            n1[hl] = q1r;
+            acc2r[1] += T(2) * a1r;
+            acc1r[0] = acc1r[1] + T(2) * amr;
+            acc1r[1] = acc1r[2];
+            acc1r[2] = T(0);
+        }
         c3r = c2r; c2r = c1r; c1r = ccr;
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    const int last = ze + 4;
+    // each request is followed by two stores, as in the loop (here to nowhere), or the loop's waits would have to suit both counts
 #pragma unroll
-    for (int d = 0; d < D; ++d) issue(zi0 + d, d);
-    int z = zi0;
-    for (; z + D - 1 <= last; z += D) {
+    for (int d = 0; d < D; ++d) {
+        issue(d, d);
+        buffer_store<T, PX, kCached>(oa.at(-1), kNowhere, V{});
+        buffer_store<T, PX, kCached>(ob.at(-1), kNowhere, V{});
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // the first step reads planes of q1 and q2 that none has written
+    st_vec<T, PX>(sq1 + own, q1);
+    st_vec<T, PX>(sq2 + own, q2);
+    sq1[hl] = T(0);
+    sq2[hl] = T(0);
+    const int steps = ze + 5 - zi0;
+    int k = 0;
+    for (; k + D <= steps; k += D) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) step(z + d, d);
+        for (int d = 0; d < D; ++d) step(k + d, d);
     }
 #pragma unroll
     for (int d = 0; d < D - 1; ++d) {
-        if (z + d > last) return;
-        step(z + d, d);
+        if (k + d >= steps) return;
+        step(k + d, d);
     }
 }
 
