@@ -551,7 +551,8 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_ahead_kernel(PairArgs 
 
 // Beyond the grids of the march above, tiles of 64 x 32 (fp32: 128 x 32) cells, one workgroup per CU; on the smallest fp64 grids, whose
 // chunks the 5 planes that a workgroup marches beyond its own dominate, 64 x 16 cells, whose march step takes 0.72 of the
-// time.  25 steps, default / small tiles: fp64 24^3 125 / 101 us, 64^3 134 / 110, 128^3 309 / 307.  (fp32 grids like these take the march above.)
+// time.  25 steps, default / small tiles: fp64 24^3 125 / 101 us, 64^3 134 / 110, 128^3 309 / 307.  (fp32 grids like these, and fp64 ones of 16 planes
+// or more, take the march above.)
 // The cost decides where passes take three steps, which round differently.  It stays what it was when the default and the small
 // tiles (fp32: 0.79 of the step, two workgroups per CU) were all there was, so that a grid's results do as well.
 struct PairPlan {
@@ -592,7 +593,7 @@ static bool pair_runs_ahead(int is_f64, int nx, int ny, int nz, const PairPlan &
     const double plane = (double)nx * ny * (is_f64 ? 8 : 4), bytes = 5 * plane * nz;
     if ((nz + 16) * plane >= 0x1p31) return false;                  // see MarchedArray
     if (!is_f64) return bytes <= 230e6 || plan.small;
-    return bytes <= 230e6 && (!plan.small || bytes >= 30e6);
+    return bytes <= 230e6 && (!plan.small || bytes >= 30e6 || nz >= 16);
 }
 
 template <class T, int PX>

@@ -599,18 +599,22 @@ template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(B
     }
 }
 
-// Where the march with its requests ahead is taken: by the planes it marches against those of the wide tiles below (its step takes
-// 0.54, fp32 0.34, of theirs, whose cells are two and four times as many) and by the bytes of the five arrays, which it relies on
-// finding in the last-level cache.  318 drawn grids, time in the wide tiles over time of this march, geometric mean (smallest): with
-// this rule fp64 1.22 (0.99), fp32 1.31 (1.00) where it is taken; 300 .. 420 MB fp64 1.02 (0.90), 260 .. 420 MB fp32 1.01 (0.86);
-// 8 x 1000 x 1024, where short chunks march 2.2 and 4.1 times the planes, 0.77 and 0.87.  The grid alone decides.
+// Where the march with its requests ahead is taken: by the planes it marches against those of the wide tiles above, whose cells per workgroup are
+// two (fp32: four) times as many, and by the bytes of the five arrays.  25 steps on 130 drawn grids, time in the wide tiles over time of this march, by
+// the quotient of the planes: fp64 up to 300 MB, quotient to 2 1.00 to 1.29; 300 .. 1200 MB below 1.7 1.02 to 1.24, 1.7 .. 2 0.93 to 1.05;
+// fp32 up to 260 MB, to 3.57 1.08 to 1.42; 260 .. 600 MB below 3.13 1.04 to 1.68, above 0.88 to 1.12.  Grids of few planes, whose chunks are short,
+// gain less (6 x 676 x 588, quotient 2, 0.80) and keep the quotients 1.85 and 2.94.  The grid alone decides.
 static bool triple_runs_ahead(int is_f64, int nx, int ny, int nz)
 {
-    if (5.0 * nx * ny * nz * (is_f64 ? 8 : 4) > (is_f64 ? 300e6 : 260e6)) return false;
+    const double plane = (double)nx * ny * (is_f64 ? 8 : 4), bytes = 5 * plane * nz;
+    const bool cached = bytes <= (is_f64 ? 300e6 : 260e6);
+    if (bytes > (is_f64 ? 1200e6 : 600e6) || (nz + 16) * plane >= 0x1p31) return false;       // the latter: see MarchedArray
+    if (!cached && nz < 16) return false;
     TileMap wide, ahead;
     plan_march(wide, nx, ny, nz, is_f64 ? 64 : 128, 32, 4, LaunchOptions{});
     plan_march(ahead, nx, ny, nz, 64, 16, 4, LaunchOptions{});
-    return (is_f64 ? 54 : 34) * march_planes(ahead, 8) < 100 * march_planes(wide, 8);
+    const int percent = nz < 16 ? (is_f64 ? 54 : 34) : cached ? (is_f64 ? 49 : 28) : is_f64 ? 59 : 32;
+    return percent * march_planes(ahead, 8) < 100 * march_planes(wide, 8);
 }
 
 template <class T, int PX>
