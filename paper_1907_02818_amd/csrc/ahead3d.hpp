@@ -5,11 +5,11 @@
 // and waits for each of them; what counts there is the time from a plane's request to the next plane's.  This march differs in
 // three things:
 //   - No condition on the plane index around any memory access: arrays are addressed through buffer resources, a plane that is
-//     not wanted has a resource of zero bytes (loads return zero, stores are dropped by the hardware's bounds check), and cells
-//     outside the grid or outside I have an offset beyond any plane.  The wait counters therefore know exactly what is
+//     not wanted has a resource of zero bytes or lies beyond it (loads return zero, stores are dropped by the hardware's bounds check), and
+//     cells outside the grid or outside I have an offset beyond any plane.  The wait counters therefore know exactly what is
 //     outstanding, and D planes are really in flight; with a branch around a load or store the compiler waits for everything.
-//     (The adjoints' waits never reach the newest plane; the fp64 primals of radius 3 and some of radius 4 wait for it once every two planes.)
-//     (All slots of the ring of requests are filled and emptied in one order, hence the scheduling barriers.)
+//     (All slots of the ring of requests are filled and emptied in one order, hence the scheduling barriers; the requests before the loop
+//     are followed by as many stores, to nowhere, as those in it.)
 //   - The R planes before and after a chunk add to the chunk's sums by their own cell only (a star has no corners): they
 //     are read without halo, are not staged in LDS and need no barrier, and the R planes before the chunk are requested together.
 //     A chunk of n planes costs n full steps and R cheap ones where the other kernels take n + 2R.
@@ -19,6 +19,9 @@
 // 128^3 15.4 / 9.1, 256^3 53.2 / 43.6; fp64 radius 1 128^3 14.8 / 12.1, 200^3 54.1 / 40.4.  128^3 fp64 radius 4: star adjoint 26.6 /
 // 16.3, star primal 22.8 / 12.4, wave primal 22.3 / 14.3 (the first of each in the kernels' shapes of larger grids).
 // Two planes in flight: one measured 0 to 10 % slower; four, in fp64, up to six times as long.
+// A step's own instructions: one resource per array and march instead of one per plane and access takes 40 scalar instructions in two steps
+// instead of 115 to 175, next to 80 (radius 1) to 160 vector ones (fp64, 80 x 96 x 112 radius 4 with u_prev_bar 10.8 -> 10.5 us; fp32 star
+// primal radius 4 536 x 36 x 176 13.2 -> 11.2; 140 drawn grids 1.01 times as fast, most of them bound by the launch or by memory).
 #pragma once
 #include "ahead.hpp"
 
@@ -197,58 +200,50 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
     auto z_weight_up = [&](int k) { return WAVE ? T(star_w<R>(k)) : wz[R - k]; };
     auto z_weight_down = [&](int k) { return WAVE ? T(star_w<R>(k)) : wz[R + k - 1]; };
 
-    // source planes that exist: of I (adjoint: q is zero elsewhere), of the grid (primal)
-    auto plane_used = [&](int z) { return ADJ ? z >= R && z < nz - R : true; };
-    auto plane_of = [&](const void *base, int z, bool wanted) {
-        char *p = static_cast<char *>(const_cast<void *>(base)) + (long long)z * (long long)bytes;
-        return __builtin_amdgcn_make_buffer_rsrc(p, 0, wanted ? bytes : 0u, 0x00020000);
-    };
-    const void *startg = OP == StarOp::WaveAdjoint && UPREV >= 3 ? a.in2 : a.out0;
+    // The arrays along the march: step k has plane z = zs - R + k arrive and completes plane zo = z - R.  Source planes that exist: of I
+    // (adjoint: q is zero elsewhere), of the grid (primal); halo cells of the chunk's planes only.
+    const int z0 = zs - R, zlast = ze - 1 + R;
+    const int src_lo = ADJ ? R : 0, src_hi = ADJ ? nz - R - 1 : nz - 1;
+    const MarchedArray in0(a.in0, z0, src_lo, min(zlast, src_hi), bytes), in0h(a.in0, z0, src_lo, min(ze - 1, src_hi), bytes);
+    const MarchedArray in1(a.in1, z0, src_lo, min(zlast, src_hi), bytes), in1h(a.in1, z0, src_lo, min(ze - 1, src_hi), bytes);
+    const MarchedArray out0(a.out0, z0 - R, zs, ze - 1, bytes);
+    // what the completing output plane is combined with: start value (wave adjoint), u_bar (star adjoint), c (primals); r_bar (UPREV 4), u_prev (wave primal)
+    const MarchedArray with0(OP == StarOp::WaveAdjoint ? (UPREV >= 3 ? a.in2 : a.out0) : OP == StarOp::StarAdjoint ? a.out0 : UPRIMAL ? a.in2 : a.in1,
+                             z0 - R, zs, ze - 1, bytes);
+    const MarchedArray with1(a.in1, z0 - R, zs, ze - 1, bytes);
+    // u_prev_bar of the arriving plane: where it is accumulated (UPREV 1) of I only; of the completing plane (UPREV 4)
+    const MarchedArray prev(a.out1, z0, max(zs, UPREV == 1 ? R : 0), UPREV == 1 ? min(ze - 1, nz - R - 1) : ze - 1, bytes), prev4(a.out1, z0 - R, zs, ze - 1, bytes);
 
     // values in flight; s0 (, s1): the source field's factors; o0 (, o1): what the completing output plane is combined with
     // (wave adjoint: start value, UPREV 4: r_bar; star adjoint: u_bar; wave primal: c, u_prev; star primal: c);
     // pv: u_prev_bar of the arriving plane (UPREV 1)
     V s0[D], s1[D], o0[D], o1[D], pv[D], h0[D][HS], h1[D][HS];
-    const int zlast = ze - 1 + R;
-    auto issue = [&](int z, int d) {
-        const bool used = z <= zlast && plane_used(z);
-        const auto r0 = plane_of(a.in0, z, used);
-        s0[d] = buffer_load<T, PX, kCached>(r0, soff);
-        const auto q0 = plane_of(a.in0, z, used && z < ze);
+    auto issue = [&](int k, int d) {
+        const unsigned zoff = (unsigned)k * bytes;
+        s0[d] = buffer_load<T, PX, kCached>(in0.at(k), soff + zoff);
         if (ADJ) {
-            s1[d] = buffer_load<T, PX, kCached>(plane_of(a.in1, z, used), soff);
-            if (UPREV == 1) pv[d] = buffer_load<T, PX, POLICY>(plane_of(a.out1, z, used && z < ze), goff);
-            const auto q1 = plane_of(a.in1, z, used && z < ze);
+            s1[d] = buffer_load<T, PX, kCached>(in1.at(k), soff + zoff);
+            if (UPREV == 1) pv[d] = buffer_load<T, PX, POLICY>(prev.at(k), goff + zoff);
 #pragma unroll
             for (int s = 0; s < HS; ++s) {
-                h0[d][s] = buffer_load<T, PX, kCached>(q0, hoff[s]);
-                h1[d][s] = buffer_load<T, PX, kCached>(q1, hoff[s]);
+                h0[d][s] = buffer_load<T, PX, kCached>(in0h.at(k), hoff[s] + zoff);
+                h1[d][s] = buffer_load<T, PX, kCached>(in1h.at(k), hoff[s] + zoff);
             }
         } else {
 #pragma unroll
-            for (int s = 0; s < HS; ++s) h0[d][s] = buffer_load<T, PX, kCached>(q0, hoff[s]);
+            for (int s = 0; s < HS; ++s) h0[d][s] = buffer_load<T, PX, kCached>(in0h.at(k), hoff[s] + zoff);
         }
     };
-    auto issue_out = [&](int z, int d) {
-        const int zo = z - R;
-        const bool wanted = zo >= zs && zo < ze;
-        if (OP == StarOp::WaveAdjoint) {
-            o0[d] = buffer_load<T, PX, POLICY>(plane_of(startg, zo, wanted), goff);
-            if (UPREV == 4) o1[d] = buffer_load<T, PX, POLICY>(plane_of(a.in1, zo, wanted), goff);
-        } else if (OP == StarOp::StarAdjoint) {
-            o0[d] = buffer_load<T, PX, POLICY>(plane_of(a.out0, zo, wanted), goff);
-        } else if (OP == StarOp::WavePrimal) {
-            o0[d] = buffer_load<T, PX, POLICY>(plane_of(a.in2, zo, wanted), ioff);
-            o1[d] = buffer_load<T, PX, POLICY>(plane_of(a.in1, zo, wanted), ioff);
-        } else {
-            o0[d] = buffer_load<T, PX, POLICY>(plane_of(a.in1, zo, wanted), ioff);
-        }
+    auto issue_out = [&](int k, int d) {
+        const unsigned off = (ADJ ? goff : ioff) + (unsigned)k * bytes;
+        o0[d] = buffer_load<T, PX, POLICY>(with0.at(k), off);
+        if (UPRIMAL || (OP == StarOp::WaveAdjoint && UPREV == 4)) o1[d] = buffer_load<T, PX, POLICY>(with1.at(k), off);
     };
-    auto store_out = [&](__amdgpu_buffer_rsrc_t r, const V &o) {
-        buffer_store<T, PX, POLICY>(r, woff, o);
+    auto store_out = [&](__amdgpu_buffer_rsrc_t r, unsigned zoff, const V &o) {
+        buffer_store<T, PX, POLICY>(r, woff + zoff, o);
         if (PARTIAL && parts) {
 #pragma unroll
-            for (int e = 0; e < PX; ++e) buffer_store<T, 1, POLICY>(r, poff[e], Vec<T, 1>{{o.v[e]}});
+            for (int e = 0; e < PX; ++e) buffer_store<T, 1, POLICY>(r, poff[e] + zoff, Vec<T, 1>{{o.v[e]}});
         }
     };
     auto source = [&](T f0, T f1, bool inside) {
@@ -268,9 +263,10 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
         for (int k = 0; k < R; ++k) hist[e][k] = T(0);
     }
 
-    auto step = [&](int z, int d) {
-        const int zo = z - R;
-        T *sb = sq + ((z - zs) & 1) * G::PLANE;
+    auto step = [&](int k, int d) {
+        const int z = z0 + k, zo = z - R;
+        const unsigned zoff = (unsigned)k * bytes;
+        T *sb = sq + (k & 1) * G::PLANE;
         T own[PX], rr[PX], r2[PX];
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
@@ -296,14 +292,14 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
             V o;
 #pragma unroll
             for (int e = 0; e < PX; ++e) o.v[e] = (UPREV == 1 ? pv[d].v[e] : T(0)) - rr[e];
-            store_out(plane_of(a.out1, z, z < ze && (UPREV == 2 || plane_used(z))), o);
+            store_out(prev.at(k), zoff, o);
         }
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
             computed(own[e]);
             if (OP == StarOp::WaveAdjoint) computed(r2[e]);
         }
-        issue(z + D, d);
+        issue(k + D, d);
         if (z < ze) {
             __syncthreads();
             T row[PX + 2 * HX];
@@ -311,10 +307,13 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
             const T *at = sb + (R + ty) * LX + tx * PX;
 #pragma unroll
             for (int i = 0; i < PX + 2 * HX; i += PX) {
+                if (i == HX) continue;
                 const V t = ld_vec<T, PX>(at + i);
 #pragma unroll
                 for (int e = 0; e < PX; ++e) row[i + e] = t.v[e];
             }
+#pragma unroll
+            for (int e = 0; e < PX; ++e) row[HX + e] = own[e];
 #pragma unroll
             for (int k = -R; k <= R; ++k)
                 if (k != 0) col[R + k] = ld_vec<T, PX>(at + HX + k * LX);
@@ -345,7 +344,6 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
         for (int e = 0; e < PX; ++e)
 #pragma unroll
             for (int k = 1; k <= R; ++k) acc[e][R - k] = fma_t(z_weight_down(k), own[e], acc[e][R - k]);
-        const auto ro = plane_of(a.out0, zo, zo >= zs);
         const bool zin = zo >= R && zo < nz - R;
         V o;
 #pragma unroll
@@ -361,13 +359,13 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
                 o.v[e] = mul_rounded(o0[d].v[e], acc[e][0]);
             }
         }
-        store_out(ro, o);
+        store_out(out0.at(k), zoff, o);
         if (OP == StarOp::WaveAdjoint && UPREV == 4) {
 #pragma unroll
             for (int e = 0; e < PX; ++e) o.v[e] = zin && in[e] ? T(0) - o1[d].v[e] : T(0);
-            store_out(plane_of(a.out1, zo, zo >= zs), o);
+            store_out(prev4.at(k), zoff, o);
         }
-        issue_out(z + D, d);
+        issue_out(k + D, d);
 #pragma unroll
         for (int e = 0; e < PX; ++e) {
 #pragma unroll
@@ -386,15 +384,18 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
     V f0[R], f1[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const int z = zs - R + j;
-        f0[j] = buffer_load<T, PX, kCached>(plane_of(a.in0, z, plane_used(z)), soff);
-        if (ADJ) f1[j] = buffer_load<T, PX, kCached>(plane_of(a.in1, z, plane_used(z)), soff);
+        f0[j] = buffer_load<T, PX, kCached>(in0.at(j), soff + (unsigned)j * bytes);
+        if (ADJ) f1[j] = buffer_load<T, PX, kCached>(in1.at(j), soff + (unsigned)j * bytes);
     }
     __builtin_amdgcn_sched_barrier(0);
+    // as many stores as in a step (here to nowhere), or the loop's waits would have to suit both counts
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        issue(zs + d, d);
-        issue_out(zs + d, d);
+        if (OP == StarOp::WaveAdjoint && (UPREV == 1 || UPREV == 2)) buffer_store<T, PX, POLICY>(prev.at(-1), kNowhere, V{});
+        issue(R + d, d);
+        buffer_store<T, PX, POLICY>(out0.at(-1), kNowhere, V{});
+        if (OP == StarOp::WaveAdjoint && UPREV == 4) buffer_store<T, PX, POLICY>(prev4.at(-1), kNowhere, V{});
+        issue_out(R + d, d);
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -407,15 +408,16 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
             for (int i = 0; i <= j; ++i) acc[e][R + i] = fma_t(z_weight_up(R - j + i), q, acc[e][R + i]);
             if (UPRIMAL) hist[e][R - 1 - j] = q;
         }
-    int z = zs;
-    for (; z + D - 1 <= zlast; z += D) {
+    const int end = zlast - z0;
+    int k = R;
+    for (; k + D - 1 <= end; k += D) {
 #pragma unroll
-        for (int d = 0; d < D; ++d) step(z + d, d);
+        for (int d = 0; d < D; ++d) step(k + d, d);
     }
 #pragma unroll
     for (int d = 0; d < D - 1; ++d) {
-        if (z + d > zlast) return;
-        step(z + d, d);
+        if (k + d > end) return;
+        step(k + d, d);
     }
 }
 
