@@ -5,20 +5,31 @@
 
 namespace sadj {
 
-// Small: 32 x 16 cells, 256 threads with two cells each, two workgroups per CU.  Wide: 16 bytes per lane, 512 threads: 64 x 16
+// Rows, RowsStream: see plan_rows.  Small: 32 x 16 cells, 256 threads with two cells each, two workgroups per CU.  Wide: 16 bytes per lane, 512 threads: 64 x 16
 // cells in fp64, 128 x 16 in fp32 (64 x 32 where rows are not whole vectors: one partial vector per row of 16 lanes), one
-// workgroup per CU.  WideStream: Wide with streaming accesses to the arrays without reuse.
-enum class AheadShape { None, Small, Wide, WideStream };
+// workgroup per CU.  WideStream, RowsStream: with streaming accesses to the arrays without reuse.
+enum class AheadShape { None, Small, Wide, WideStream, Rows, RowsStream };
+
+// A tile of whole rows: bx vectors of 16 bytes by `by` rows, one per thread; h / bx is (h * reciprocal) >> 20 for h < 1024.  (Radii 3
+// and 4 need more registers than 1024 threads have.)
+constexpr int rows_threads(int radius) { return radius > 2 ? 512 : 1024; }
+constexpr int rows_max_x(int radius) { return radius > 2 ? 128 : radius == 2 ? 256 : 512; }
+constexpr int kRowsMaxY = 32;
+struct RowsTile {
+    int bx = 0, by = 0, reciprocal = 0;
+};
 
 struct AheadPlan {
     AheadShape shape = AheadShape::None;
     int TX = 0, TY = 0;
+    RowsTile rows;
     TileMap map{};
 };
 
 struct AheadArgs {
     March3dArgs m;              // arrays, extents and map, as the operation's other kernel takes them
     double w0, w[3][8];         // free-weight star: gather table (see StarArgs in star3d.hip)
+    RowsTile rows;              // of Rows and RowsStream
 };
 
 // When this march is taken, by the bytes a call moves (what it moves per cell, times the cells).  All figures: 1300 drawn grids
@@ -41,13 +52,51 @@ struct AheadRule {
 constexpr double kAheadLoopStream = 380e6, kAheadCallStream = 125e6;
 constexpr int kPercentStream = 150;     // streaming, Wide against Small, which has no streaming form (12 of 455 such grids take Small)
 
+// Tiles of whole rows, for rows that are no multiples of a cache line or fill the wide tiles badly: the rows of a tile are then one piece of memory, whose
+// inner lines are used in full whatever the rows' alignment, and no thread lies beside the grid.  (Tiles of a fixed width start and end within lines
+// on both sides, and the last one is in part outside the grid.)  A tile has as many rows as its threads allow.  Time in the tiles below and in those of
+// the larger grids over time in these, 340 drawn grids of 50 MB to 2.5 GB that a call moves, and the bounds:
+//   radius 1, 2   rows to 256 vectors, 125 MB: 1.02 to 1.65 (three of 130 grids 0.95 to 0.98); 50 .. 125 MB 0.86 to 1.23; radius 1, 257 to
+//                 512 vectors, 250 MB: 0.99 to 1.39; below 0.91 to 1.22
+//   radius 3, 4   rows to 128 vectors (four rows a tile; with fewer every plane is read three times over, 0.63 to 1.15), 250 MB: 0.99
+//                 to 1.68; 80 .. 250 MB 0.86 to 1.32; radius 4, whole vectors, fewer than six rows 0.95 to 1.15
+//   rows of whole lines, radius 1, 2, that fill less than 0.9 of the wide tiles: 1.00 to 1.25 (one of 24 0.93; loops in the last-level cache
+//                 0.97 to 1.10); the others 0.85 to 1.19, 512^3 fp32 0.92
+//   fewer than 20 R planes: 0.95 to 1.17; they stay in the other tiles.
+// fp32 500^3 radius 1 primal 389 -> 344 us; 300 x 350 x 404 radius 2 star adjoint 164 -> 122; 1000 x 300 x 404 primal 460 -> 368.
+static inline bool plan_rows(AheadPlan &p, bool is_f64, int radius, int nx, int ny, int nz, double bytes, const AheadRule &rule, LaunchOptions opt)
+{
+    const int size = is_f64 ? 8 : 4, px = 16 / size, bx = cdiv_i(nx, px), threads = rows_threads(radius);
+    if (bx < threads / kRowsMaxY || bx > rows_max_x(radius) || nz < 20 * radius) return false;
+    if (bytes <= (radius > 2 || bx > 256 ? 250e6 : kAheadCallStream)) return false;
+    if (radius == 4 && nx % px == 0 && threads / bx < 6) return false;
+    if ((long)nx * size % 128 == 0) {
+        const int tile = 32 * px;
+        if (radius > 2 || bx > 256 || bytes <= rule.stream || 10L * nx >= 9L * cdiv_i(nx, tile) * tile) return false;
+    }
+    p.rows = {bx, cdiv_i(ny, cdiv_i(ny, threads / bx)), (1 << 20) / bx + 1};
+    p.TX = bx * px;
+    p.TY = p.rows.by;
+    p.shape = bytes > rule.stream ? AheadShape::RowsStream : AheadShape::Rows;
+    const double most = 0x1p31 / ((double)nx * ny * size) - 16;                // planes of a chunk, see MarchedArray
+    if (most < 32) return false;
+    plan_march(p.map, nx, ny, nz, p.TX, p.TY, radius, opt);
+    if (p.map.zchunk > most || p.map.zchunk_a > most) {
+        opt.zchunk = cdiv_i(nz, cdiv_i(nz, (int)most));
+        plan_march(p.map, nx, ny, nz, p.TX, p.TY, radius, opt);
+    }
+    return true;
+}
+
 // Small or Wide: the planes marched, times the relative cost of a step.  The cheap planes of a chunk count as 2R full ones, which
 // is also what the z cut is planned with (other weights moved no grid's time by more than 3 %).
 static inline AheadPlan plan_ahead(bool is_f64, int radius, int nx, int ny, int nz, const AheadRule &rule, const LaunchOptions &opt)
 {
     AheadPlan p;
     const double bytes = (double)nx * ny * nz * rule.words * (is_f64 ? 8 : 4);
-    if (opt.variant != 0 || opt.remainder != 0 || opt.ahead != 0 || bytes > rule.limit) return p;
+    if (opt.variant != 0 || opt.remainder != 0 || opt.ahead != 0) return p;
+    if (plan_rows(p, is_f64, radius, nx, ny, nz, bytes, rule, opt)) return p;
+    if (bytes > rule.limit) return p;
     const bool whole = nx % (is_f64 ? 2 : 4) == 0;
     const bool long_rows = rule.long_rows_stay && wide_tile_for_unaligned_rows(nx, is_f64 ? 8 : 4, radius, !is_f64) != 0;
     if (long_rows && whole) return p;

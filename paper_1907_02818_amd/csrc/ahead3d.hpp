@@ -1,4 +1,5 @@
-// Star stencils on grids that do not fill the chip: a z-march whose requests run ahead of the arithmetic.
+// Star stencils on grids that do not fill the chip, and on larger ones whose rows are no whole cache lines (plan_rows in ahead.hpp): a z-march
+// whose requests run ahead of the arithmetic.
 //
 // The kernels of wave3d_adjoint.hip, wave3d_primal.hip and star3d.hip are built for grids of several 10^8 bytes, where memory
 // is the bound and one plane in flight per workgroup keeps it busy.  On smaller grids a workgroup marches a few planes only
@@ -88,7 +89,7 @@ template <class T, int N, int POLICY> __device__ __forceinline__ void buffer_sto
 // An array along a march: the byte offset of a cell in the plane that step k touches is its offset in a plane plus k planes, counted from
 // the plane that step 0 touches (outside the array perhaps, where it is not wanted).  Steps from `first` on touch wanted planes, `count`
 // of them from step 0 on; the others get a resource of zero bytes or offsets beyond it.  Two scalar instructions an access, where a
-// resource for each plane takes ten.  An array and 16 planes more stay below 2^31 bytes, so that kNowhere stays beyond.
+// resource for each plane takes ten.  A chunk (of a grid's z cut) and 16 planes more stay below 2^31 bytes, so that kNowhere stays beyond.
 struct MarchedArray {
     char *base;
     int first;
@@ -104,25 +105,34 @@ struct MarchedArray {
 
 enum class StarOp { WaveAdjoint, WavePrimal, StarAdjoint, StarPrimal };
 
+// BX x BY: threads of a tile.  BX = 0: tiles of whole rows, of size.bx vectors, whose halo columns lie outside the grid.
 template <class T, int R, int BX, int BY, int PX> struct AheadTile {
-    static constexpr int TX = BX * PX, TY = BY, NT = BX * BY;
+    static constexpr bool ROWS = BX == 0;
+    static constexpr int NT = ROWS ? rows_threads(R) : BX * BY;
     static constexpr int HV = (R + PX - 1) / PX, HX = HV * PX;           // halo columns on a side, in vectors and in cells
-    static constexpr int LX = TX + 2 * HX, LY = TY + 2 * R, PLANE = LX * LY;
-    static constexpr int NH = 2 * R * BX + 2 * HV * TY, HS = (NH + NT - 1) / NT;     // halo vectors; slots per thread
+    static constexpr int PLANE = ROWS ? NT * PX + 2 * HX * kRowsMaxY + 2 * R * (rows_max_x(R) * PX + 2 * HX) : (BX * PX + 2 * HX) * (BY + 2 * R);
+    // halo vectors at most; slots per thread
+    static constexpr int NH = ROWS ? 2 * R * rows_max_x(R) : 2 * R * BX + 2 * HV * BY, HS = (NH + NT - 1) / NT;
+    static_assert(!ROWS || HS * NT <= 1024, "quotients by the reciprocal");
+    RowsTile size;
+    __device__ __forceinline__ int bx() const { return ROWS ? size.bx : BX; }
+    __device__ __forceinline__ int by() const { return ROWS ? size.by : BY; }
+    __device__ __forceinline__ int lx() const { return bx() * PX + 2 * HX; }
+    __device__ __forceinline__ int rows(int h) const { return ROWS ? (h * size.reciprocal) >> 20 : h / BX; }
     // LDS coordinates of the first cell of halo vector tid + s * NT: rows above and below the tile, then columns beside it
-    __device__ static __forceinline__ bool halo_vector(int tid, int s, int &lx, int &ly)
+    __device__ __forceinline__ bool halo_vector(int tid, int s, int &lx, int &ly) const
     {
         const int h = tid + s * NT;
-        if (h < 2 * R * BX) {
-            const int row = h / BX;
-            lx = HX + h % BX * PX;
-            ly = row < R ? row : row + TY;
+        if (ROWS || h < 2 * R * bx()) {
+            const int row = rows(h);
+            lx = HX + (h - row * bx()) * PX;
+            ly = row < R ? row : row + by();
         } else {
-            const int h2 = h - 2 * R * BX, k = h2 % (2 * HV);
-            lx = (k < HV ? k : k + BX) * PX;
+            const int h2 = h - 2 * R * bx(), k = h2 % (2 * HV);
+            lx = (k < HV ? k : k + bx()) * PX;
             ly = R + h2 / (2 * HV);
         }
-        return h < NH;
+        return h < 2 * R * bx() + (ROWS ? 0 : 2 * HV * by());
     }
 };
 
@@ -130,11 +140,13 @@ template <class T, int R, int BX, int BY, int PX> struct AheadTile {
 // into the next row: its cells there are masked on loading and it is stored cell by cell.
 // UPREV (wave adjoint): see wave3d_adjoint.hip.  D: planes in flight.  POLICY: of the arrays without reuse.
 template <StarOp OP, class T, int R, int BX, int BY, int PX, int D, int UPREV, int POLICY, bool RAGGED>
-__global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
+__global__ __launch_bounds__((AheadTile<T, R, BX, BY, PX>::NT), 2) void star_ahead_kernel(AheadArgs args)
 {
     using G = AheadTile<T, R, BX, BY, PX>;
+    const G tile{args.rows};
     using V = Vec<T, PX>;
-    constexpr int LX = G::LX, HS = G::HS, HX = G::HX;
+    constexpr int HS = G::HS, HX = G::HX;
+    const int LX = tile.lx();
     constexpr bool ADJ = OP == StarOp::WaveAdjoint || OP == StarOp::StarAdjoint;
     constexpr bool WAVE = OP == StarOp::WaveAdjoint || OP == StarOp::WavePrimal;
     constexpr bool UPRIMAL = OP == StarOp::WavePrimal;
@@ -150,10 +162,12 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
         ze = min(ze, nz - R);
         if (zs >= ze) return;
     }
-    const int tid = threadIdx.x, tx = tid % BX, ty = tid / BX;
+    const int tid = threadIdx.x, ty = tile.rows(tid), tx = tid - ty * tile.bx();
     const unsigned bytes = (unsigned)nx * (unsigned)ny * (unsigned)sizeof(T);
-    const int x0 = tix * G::TX, y0 = tiy * G::TY;
-    const int x = x0 + tx * PX, y = y0 + ty;
+    const int x0 = tix * tile.bx() * PX, y0 = tiy * tile.by();
+    const bool idle = G::ROWS && ty >= tile.by();   // threads that whole rows leave over: cells outside the grid
+    const int x = x0 + tx * PX, y = idle ? ny : y0 + ty;
+    const int row_at = idle ? R * LX : (R + ty) * LX + tx * PX, own_at = idle ? 0 : row_at + HX;             // (0, 0) is a corner nobody reads
     auto in_I = [&](int xx, int yy) { return xx >= R && xx < nx - R && yy >= R && yy < ny - R; };
     auto in_grid = [&](int xx, int yy) { return xx >= 0 && xx < nx && yy >= 0 && yy < ny; };
     auto offset = [&](int xx, int yy) { return ((unsigned)yy * (unsigned)nx + (unsigned)xx) * (unsigned)sizeof(T); };
@@ -181,7 +195,7 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
 #pragma unroll
     for (int s = 0; s < HS; ++s) {
         int lx, ly;
-        const bool slot = G::halo_vector(tid, s, lx, ly);
+        const bool slot = tile.halo_vector(tid, s, lx, ly);
         const int hx = x0 - HX + lx, hy = y0 - R + ly;
         bool any = false;
 #pragma unroll
@@ -190,7 +204,7 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
             any = any || hin[s][e];
         }
         hoff[s] = any ? offset(hx, hy) : kNowhere;
-        hl[s] = slot ? ly * LX + lx : 0;            // (0, 0) is a corner nobody reads
+        hl[s] = slot ? ly * LX + lx : 0;
     }
     const T w0 = (T)args.w0;
     T wx[2 * R], wy[2 * R], wz[2 * R];
@@ -280,7 +294,7 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
             V v;
 #pragma unroll
             for (int e = 0; e < PX; ++e) v.v[e] = own[e];
-            st_vec<T, PX>(sb + (R + ty) * LX + HX + tx * PX, v);
+            st_vec<T, PX>(sb + own_at, v);
 #pragma unroll
             for (int s = 0; s < HS; ++s) {
 #pragma unroll
@@ -304,7 +318,7 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
             __syncthreads();
             T row[PX + 2 * HX];
             V col[2 * R + 1];
-            const T *at = sb + (R + ty) * LX + tx * PX;
+            const T *at = sb + row_at;
 #pragma unroll
             for (int i = 0; i < PX + 2 * HX; i += PX) {
                 if (i == HX) continue;
@@ -408,6 +422,13 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
             for (int i = 0; i <= j; ++i) acc[e][R + i] = fma_t(z_weight_up(R - j + i), q, acc[e][R + i]);
             if (UPRIMAL) hist[e][R - 1 - j] = q;
         }
+    if (G::ROWS) {                                   // halo columns, of both planes in LDS
+        for (int i = tid; i < 2 * HX * tile.by(); i += G::NT) {
+            const int row = i / (2 * HX), col = i % (2 * HX);
+            T *at = sq + (R + row) * LX + (col < HX ? col : col + tile.bx() * PX);
+            at[0] = at[G::PLANE] = T(0);
+        }
+    }
     const int end = zlast - z0;
     int k = R;
     for (; k + D - 1 <= end; k += D) {
@@ -424,7 +445,8 @@ __global__ __launch_bounds__(BX *BY, 2) void star_ahead_kernel(AheadArgs args)
 template <StarOp OP, class T, int R, int UPREV, int BX, int BY, int PX, int POLICY, bool RAGGED>
 static hipError_t launch_ahead_kernel(const AheadArgs &a, unsigned pad, hipStream_t stream)
 {
-    hipLaunchKernelGGL((star_ahead_kernel<OP, T, R, BX, BY, PX, 2, UPREV, POLICY, RAGGED>), dim3(a.m.map.total_blocks), dim3(BX * BY), pad, stream, a);
+    hipLaunchKernelGGL((star_ahead_kernel<OP, T, R, BX, BY, PX, 2, UPREV, POLICY, RAGGED>), dim3(a.m.map.total_blocks),
+                       dim3(AheadTile<T, R, BX, BY, PX>::NT), pad, stream, a);
     return hipGetLastError();
 }
 
@@ -444,6 +466,14 @@ template <StarOp OP, class T, int R, int UPREV> static hipError_t launch_ahead(A
     case AheadShape::WideStream:
         return whole ? launch_ahead_kernel<OP, T, R, UPREV, 32, 16, PXV, kStreaming, false>(a, pad, stream)
                      : launch_ahead_kernel<OP, T, R, UPREV, RX, RY, PXV, kStreaming, true>(a, pad, stream);
+    case AheadShape::Rows:                           // loops only, see plan_rows
+        if constexpr (OP == StarOp::WaveAdjoint && UPREV >= 3)
+            return whole ? launch_ahead_kernel<OP, T, R, UPREV, 0, 0, PXV, kCached, false>(a, pad, stream)
+                         : launch_ahead_kernel<OP, T, R, UPREV, 0, 0, PXV, kCached, true>(a, pad, stream);
+        else return hipErrorNotSupported;
+    case AheadShape::RowsStream:
+        return whole ? launch_ahead_kernel<OP, T, R, UPREV, 0, 0, PXV, kStreaming, false>(a, pad, stream)
+                     : launch_ahead_kernel<OP, T, R, UPREV, 0, 0, PXV, kStreaming, true>(a, pad, stream);
     default: return hipErrorNotSupported;
     }
 }

@@ -231,6 +231,7 @@ static hipError_t launch_star_TR(const StarArgs &a, const LaunchOptions &opt, hi
         h.m.in0 = a.in0; h.m.in1 = a.in1; h.m.out0 = a.out;
         h.m.nx = a.nx; h.m.ny = a.ny; h.m.nz = a.nz;
         h.m.map = ahead.map;
+        h.rows = ahead.rows;
         h.w0 = a.w0;
         for (int d = 0; d < 3; ++d)
             for (int i = 0; i < 8; ++i) h.w[d][i] = a.w[d][i];

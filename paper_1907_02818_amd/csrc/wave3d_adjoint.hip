@@ -453,6 +453,7 @@ static hipError_t launch_T(const March3dArgs &a, const LaunchOptions &opt, hipSt
         AheadArgs h{};
         h.m = a;
         h.m.map = ahead.map;
+        h.rows = ahead.rows;
         return launch_adjoint_wave3d_ahead(sizeof(T) == 8, R, h, ahead.shape, ahead_pad(opt), stream);
     }
     const long v = choose_adjoint_shape(sizeof(T) == 8, R, a.nx, a.out1 && !a.out1_assign, opt);

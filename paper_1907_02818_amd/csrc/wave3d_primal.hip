@@ -210,6 +210,7 @@ static hipError_t launch_primal_T(const March3dArgs &a, const LaunchOptions &opt
         AheadArgs h{};
         h.m = a;
         h.m.map = ahead.map;
+        h.rows = ahead.rows;
         return launch_primal_wave3d_ahead(sizeof(T) == 8, R, h, ahead.shape, ahead_pad(opt), stream);
     }
     long v = opt.variant;

@@ -1,0 +1,108 @@
+"""GPU test of the 3-D march in tiles of whole rows (rows that are no multiples of a cache line or fill
+other tiles badly, calls of 125 or 250 MB and more): the wave adjoint
+in every form has the bits of the one-cell tiles, NaN outside I is not read; the free-weight star and the wave primal agree with
+the one-cell tiles to the rounding of their sums.  Rows of the fewest and the most vectors, whole vectors and not, tiles of one
+row short and full, a grid whose chunks are cut for their bytes."""
+import numpy as np
+import pytest
+
+from test_parity_ahead3d_gpu import _calls
+
+pytestmark = pytest.mark.gpu
+
+F64, F32 = np.float64, np.float32
+GRIDS = [(F64, 1, (260, 250, 63)), (F64, 1, (63, 193, 330)), (F64, 1, (40, 203, 511)), (F64, 1, (60, 257, 514)), (F64, 1, (33, 240, 1022)),
+         (F64, 2, (260, 250, 63)), (F64, 2, (60, 130, 510)), (F64, 3, (510, 501, 31)), (F64, 4, (90, 350, 255)), (F64, 4, (170, 300, 170)), (F64, 2, (140, 300, 96)),
+         (F32, 1, (250, 251, 126)), (F32, 1, (40, 193, 1021)), (F32, 1, (31, 251, 2046)), (F32, 2, (63, 260, 484)), (F32, 2, (41, 193, 1021)),
+         (F32, 1, (100, 351, 224)), (F32, 3, (500, 500, 63)), (F32, 4, (160, 310, 340)), (F32, 4, (101, 310, 507))]
+
+
+@pytest.fixture
+def sadj():
+    import paper_1907_02818_amd as lib
+    lib.load()
+    yield lib
+    lib.set_option("wave3d.variant", 0)
+    lib.set_option("wave3d.zchunk", 0)
+
+
+def _fields(torch, dtype, shape, n):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(sum(shape))
+    t = torch.float64 if dtype == F64 else torch.float32
+    return [torch.rand(shape, generator=gen, dtype=t, device="cuda").mul_(2).sub_(1) for _ in range(n)]
+
+
+def _nan_outside(torch, x, radius):
+    y = torch.full_like(x, float("nan"))
+    inside = tuple(slice(radius, n - radius) for n in x.shape)
+    y[inside] = x[inside]
+    return y
+
+
+def _both(lib, call):
+    got = call()
+    lib.set_option("wave3d.variant", 3)
+    want = call()
+    lib.set_option("wave3d.variant", 0)
+    return got, want
+
+
+@pytest.mark.parametrize("dtype,radius,shape", GRIDS)
+def test_wave_adjoint_has_the_bits_of_the_one_cell_tiles(sadj, dtype, radius, shape):
+    import torch
+    c, a, b, p = _fields(torch, dtype, shape, 4)
+    c, a = _nan_outside(torch, c, radius), _nan_outside(torch, a, radius)
+    nx = shape[2]
+    px = 2 if dtype == F64 else 4
+    width = sadj.sadj_describe_wave3d_plan(1 if dtype == F64 else 0, radius, nx, shape[1], shape[0], False)[0]["tile_w"]
+    assert width == -(-nx // px) * px                                     # the tiles under test
+    got, want = _both(sadj, lambda: _calls(sadj, torch, radius, c, a, b, p, nx % 2))
+    for i, (x, y) in enumerate(zip(got, want)):
+        assert torch.equal(torch.nan_to_num(x, nan=7.0), torch.nan_to_num(y, nan=7.0)), i
+        if i in (0, 1, 2):
+            assert torch.isfinite(x).all()
+
+
+@pytest.mark.parametrize("dtype,radius,shape", GRIDS)
+def test_star_and_primal_agree_with_the_one_cell_tiles(sadj, dtype, radius, shape):
+    import torch
+    shape = (shape[0] * 7 // 5,) + shape[1:]                              # the star primal moves three arrays
+    c, a, b, p = _fields(torch, dtype, shape, 4)
+    w = [((7 * i) % 11 - 5) / 8.0 for i in range(1 + 6 * radius)]
+    # values up to 1: a sum of n terms of at most `largest` together is rounded n times in either kernel
+    largest, n = max(3 + sum(abs(x) for x in w), 3 + 4 * 16 / 3), 1 + 6 * radius + 4
+    bound = 2 * n * largest * float(np.finfo(dtype).eps)
+
+    def star(adjoint):
+        out = b.clone()
+        sadj.sadj_adjoint_star3d(radius, w, c, a, out) if adjoint else sadj.sadj_primal_star3d(radius, w, a, c, out)
+        return out
+
+    def wave():
+        out = b.clone()
+        sadj.sadj_primal_wave3d(radius, a, p, c, out)
+        return out
+
+    edge = torch.ones_like(b, dtype=torch.bool)
+    edge[tuple(slice(radius, m - radius) for m in shape)] = False
+    for primal, call in ((False, lambda: star(True)), (True, lambda: star(False)), (True, wave)):
+        got, want = _both(sadj, call)
+        assert float((got - want).abs().max()) <= bound
+        assert not primal or torch.equal(got[edge], b[edge])               # r outside I stays untouched
+
+
+@pytest.mark.parametrize("dtype,shape", [(F32, (280, 1000, 2002)), (F64, (300, 999, 999))])
+def test_chunks_of_arrays_beyond_two_gigabytes(sadj, dtype, shape):
+    import torch
+    c, a, b = _fields(torch, dtype, shape, 3)
+
+    def call():
+        out = b.clone()
+        sadj.sadj_adjoint_wave3d(1, c, a, out)
+        return out
+
+    for zchunk in (0, 1000):
+        sadj.set_option("wave3d.zchunk", zchunk)
+        got, want = _both(sadj, call)
+        assert torch.equal(got, want)
