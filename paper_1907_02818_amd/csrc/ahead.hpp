@@ -57,17 +57,19 @@ constexpr int kPercentStream = 150;     // streaming, Wide against Small, which 
 // on both sides, and the last one is in part outside the grid.)  A tile has as many rows as its threads allow.  Time in the tiles below and in those of
 // the larger grids over time in these, 340 drawn grids of 50 MB to 2.5 GB that a call moves, and the bounds:
 //   radius 1, 2   rows to 256 vectors, 125 MB: 1.02 to 1.65 (three of 130 grids 0.95 to 0.98); 50 .. 125 MB 0.86 to 1.23; radius 1, 257 to
-//                 512 vectors, 250 MB: 0.99 to 1.39; below 0.91 to 1.22
+//                 512 vectors, 250 MB, where wide_tile_for_unaligned_rows finds no tile: 1.05 to 1.39 (where it does 0.99 to 1.15); below
+//                 250 MB 0.91 to 1.22
 //   radius 3, 4   rows to 128 vectors (four rows a tile; with fewer every plane is read three times over, 0.63 to 1.15), 250 MB: 0.99
 //                 to 1.68; 80 .. 250 MB 0.86 to 1.32; radius 4, whole vectors, fewer than six rows 0.95 to 1.15
 //   rows of whole lines, radius 1, 2, that fill less than 0.9 of the wide tiles: 1.00 to 1.25 (one of 24 0.93; loops in the last-level cache
 //                 0.97 to 1.10); the others 0.85 to 1.19, 512^3 fp32 0.92
-//   fewer than 20 R planes: 0.95 to 1.17; they stay in the other tiles.
+//   fewer than 20 R planes: 0.95 to 1.17; they stay in the other tiles, as do fewer than 32 rows (not measured).
 // fp32 500^3 radius 1 primal 389 -> 344 us; 300 x 350 x 404 radius 2 star adjoint 164 -> 122; 1000 x 300 x 404 primal 460 -> 368.
 static inline bool plan_rows(AheadPlan &p, bool is_f64, int radius, int nx, int ny, int nz, double bytes, const AheadRule &rule, LaunchOptions opt)
 {
     const int size = is_f64 ? 8 : 4, px = 16 / size, bx = cdiv_i(nx, px), threads = rows_threads(radius);
-    if (bx < threads / kRowsMaxY || bx > rows_max_x(radius) || nz < 20 * radius) return false;
+    if (bx < threads / kRowsMaxY || bx > rows_max_x(radius) || ny < 32 || nz < 20 * radius) return false;
+    if (bx > 256 && wide_tile_for_unaligned_rows(nx, size, radius, !is_f64) != 0) return false;
     if (bytes <= (radius > 2 || bx > 256 ? 250e6 : kAheadCallStream)) return false;
     if (radius == 4 && nx % px == 0 && threads / bx < 6) return false;
     if ((long)nx * size % 128 == 0) {

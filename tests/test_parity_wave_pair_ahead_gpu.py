@@ -1,5 +1,6 @@
 """GPU parity of the two- and three-step passes that request their planes ahead (64 x 16 cells; two steps: fp32 up to 230 MB in five
-arrays, fp64 where the grid takes no small tiles or from 30 MB; three steps up to 260 and 300 MB): exact on dyadic data for chunks of one plane to the whole depth, at the edges of tiles and of
+arrays, fp64 where the grid takes no small tiles or from 30 MB; three steps up to 260 and 300 MB; more grids in
+test_parity_wave_ahead_rule_gpu): exact on dyadic data for chunks of one plane to the whole depth, at the edges of tiles and of
 the range, NaN where values must not be read."""
 import numpy as np
 import pytest
