@@ -76,12 +76,12 @@ static inline bool plan_rows(AheadPlan &p, bool is_f64, int radius, int nx, int 
         const int tile = 32 * px;
         if (radius > 2 || bx > 256 || bytes <= rule.stream || 10L * nx >= 9L * cdiv_i(nx, tile) * tile) return false;
     }
+    const double most = 0x1p31 / ((double)nx * ny * size) - 16;                // planes of a chunk, see MarchedArray
+    if (most < 32) return false;                                               // planes of more than 44.7 MB
     p.rows = {bx, cdiv_i(ny, cdiv_i(ny, threads / bx)), (1 << 20) / bx + 1};
     p.TX = bx * px;
     p.TY = p.rows.by;
     p.shape = bytes > rule.stream ? AheadShape::RowsStream : AheadShape::Rows;
-    const double most = 0x1p31 / ((double)nx * ny * size) - 16;                // planes of a chunk, see MarchedArray
-    if (most < 32) return false;
     plan_march(p.map, nx, ny, nz, p.TX, p.TY, radius, opt);
     if (p.map.zchunk > most || p.map.zchunk_a > most) {
         opt.zchunk = cdiv_i(nz, cdiv_i(nz, (int)most));

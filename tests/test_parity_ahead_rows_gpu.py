@@ -106,3 +106,16 @@ def test_chunks_of_arrays_beyond_two_gigabytes(sadj, dtype, shape):
         sadj.set_option("wave3d.zchunk", zchunk)
         got, want = _both(sadj, call)
         assert torch.equal(got, want)
+
+
+def test_planes_too_large_for_tiles_of_whole_rows(sadj):
+    """Planes of 48 MB, whose chunks would be too short: every operation runs in the tiles of larger grids."""
+    import torch
+    shape = (20, 12000, 500)
+    info, _ = sadj.sadj_describe_wave3d_plan(1, 1, *shape[::-1], False)
+    assert info["tile_w"] == 256
+    c, a, b, p = _fields(torch, F64, shape, 4)
+    got, want = _both(sadj, lambda: _calls(sadj, torch, 1, c, a, b, p, 0))
+    for i, (x, y) in enumerate(zip(got, want)):
+        assert torch.equal(x, y), i
+    test_star_and_primal_agree_with_the_one_cell_tiles(sadj, F64, 1, shape)
