@@ -19,6 +19,12 @@ struct RowsTile {
     int bx = 0, by = 0, reciprocal = 0;
 };
 
+// Wide and WideStream, `whole`: rows of whole vectors.
+struct WideTile {
+    int x, y;
+};
+static inline WideTile wide_tile(bool is_f64, bool whole) { return {is_f64 || !whole ? 64 : 128, is_f64 || whole ? 16 : 32}; }
+
 struct AheadPlan {
     AheadShape shape = AheadShape::None;
     int TX = 0, TY = 0;
@@ -55,38 +61,52 @@ constexpr int kPercentStream = 150;     // streaming, Wide against Small, which 
 // Tiles of whole rows, for rows that are no multiples of a cache line or fill the wide tiles badly: the rows of a tile are then one piece of memory, whose
 // inner lines are used in full whatever the rows' alignment, and no thread lies beside the grid.  (Tiles of a fixed width start and end within lines
 // on both sides, and the last one is in part outside the grid.)  A tile has as many rows as its threads allow.  Time in the tiles below and in those of
-// the larger grids over time in these, 340 drawn grids of 50 MB to 2.5 GB that a call moves, and the bounds:
-//   radius 1, 2   rows to 256 vectors, 125 MB: 1.02 to 1.65 (three of 130 grids 0.95 to 0.98); 50 .. 125 MB 0.86 to 1.23; radius 1, 257 to
-//                 512 vectors, 250 MB, where wide_tile_for_unaligned_rows finds no tile: 1.05 to 1.39 (where it does 0.99 to 1.15); below
-//                 250 MB 0.91 to 1.22
-//   radius 3, 4   rows to 128 vectors (four rows a tile; with fewer every plane is read three times over, 0.63 to 1.15), 250 MB: 0.99
-//                 to 1.68; 80 .. 250 MB 0.86 to 1.32; radius 4, whole vectors, fewer than six rows 0.95 to 1.15
-//   rows of whole lines, radius 1, 2, that fill less than 0.9 of the wide tiles: 1.00 to 1.25 (one of 24 0.93; loops in the last-level cache
-//                 0.97 to 1.10); the others 0.85 to 1.19, 512^3 fp32 0.92
+// the larger grids over time in these; 1286 drawn grids up to 1.5 GB that a call moves and this rule takes, 5 % of them below the second figure:
+//   radius 1, 2, rows that are no whole vectors 0.98, 1.04 .. 1.74, other rows that are no whole lines 0.89, 1.01 .. 1.56, whole lines 0.89,
+//   1.01 .. 1.89; radius 3, 4 1.01, 1.05 .. 1.92.  Below 0.97 are 13 of them, most of fewer than 60 rows or few planes, whose neighbours in
+//   size are faster (fp64 573 x 60 x 360 0.93, 600 x 60 x 360 1.07).
+// The bounds, with the same quotient beyond them:
+//   bytes of a call, 125 MB (50 .. 125 MB: 0.86 to 1.23); radius 1, 257 to 512 vectors, where wide_tile_for_unaligned_rows finds no tile, and
+//     radius 3 and 4: 250 MB (0.91 to 1.22 and 0.86 to 1.32)
+//   vectors in a row: 256, radius 1 512 (where wide_tile_for_unaligned_rows finds a tile 0.99 to 1.15), radius 3 and 4 128, or four
+//     rows a tile; with fewer every plane is read three times over (0.63 to 1.15); radius 4, whole vectors, six rows (0.95 to 1.15)
+//   radius 3, 4: rows that fit Wide are whole there already (0.84 to 1.27, half of 77 grids slower)
+//   radius 1, 2, whole vectors, where the other choice is Wide: at most 1.1 times the vectors that Wide's march computes, which shallow grids and grids
+//     of few rows pass; of rows of whole lines, which gain nothing from their alignment, 0.95 times (beyond both 0.79 to 1.22, a quarter
+//     of 107 grids slower), and the wide tiles filled to less than 0.9 (else 0.85 to 1.19, 512^3 fp32 0.92; loops in the last-level cache 0.97 to 1.10)
 //   fewer than 20 R planes: 0.95 to 1.17; they stay in the other tiles, as do fewer than 32 rows (not measured).
 // fp32 500^3 radius 1 primal 389 -> 344 us; 300 x 350 x 404 radius 2 star adjoint 164 -> 122; 1000 x 300 x 404 primal 460 -> 368.
 static inline bool plan_rows(AheadPlan &p, bool is_f64, int radius, int nx, int ny, int nz, double bytes, const AheadRule &rule, LaunchOptions opt)
 {
     const int size = is_f64 ? 8 : 4, px = 16 / size, bx = cdiv_i(nx, px), threads = rows_threads(radius);
+    const bool whole = nx % px == 0, lines = (long)nx * size % 128 == 0;
+    const WideTile wide = wide_tile(is_f64, whole);
     if (bx < threads / kRowsMaxY || bx > rows_max_x(radius) || ny < 32 || nz < 20 * radius) return false;
     if (bx > 256 && wide_tile_for_unaligned_rows(nx, size, radius, !is_f64) != 0) return false;
     if (bytes <= (radius > 2 || bx > 256 ? 250e6 : kAheadCallStream)) return false;
-    if (radius == 4 && nx % px == 0 && threads / bx < 6) return false;
-    if ((long)nx * size % 128 == 0) {
-        const int tile = 32 * px;
-        if (radius > 2 || bx > 256 || bytes <= rule.stream || 10L * nx >= 9L * cdiv_i(nx, tile) * tile) return false;
-    }
+    if (radius == 4 && whole && threads / bx < 6) return false;
+    if (radius > 2 && nx <= wide.x && bytes <= rule.limit) return false;
+    if (lines && (radius > 2 || bx > 256 || bytes <= rule.stream || 10L * nx >= 9L * cdiv_i(nx, wide.x) * wide.x)) return false;
     const double most = 0x1p31 / ((double)nx * ny * size) - 16;                // planes of a chunk, see MarchedArray
     if (most < 32) return false;                                               // planes of more than 44.7 MB
-    p.rows = {bx, cdiv_i(ny, cdiv_i(ny, threads / bx)), (1 << 20) / bx + 1};
-    p.TX = bx * px;
-    p.TY = p.rows.by;
-    p.shape = bytes > rule.stream ? AheadShape::RowsStream : AheadShape::Rows;
-    plan_march(p.map, nx, ny, nz, p.TX, p.TY, radius, opt);
-    if (p.map.zchunk > most || p.map.zchunk_a > most) {
-        opt.zchunk = cdiv_i(nz, cdiv_i(nz, (int)most));
-        plan_march(p.map, nx, ny, nz, p.TX, p.TY, radius, opt);
+    const RowsTile rows = {bx, cdiv_i(ny, cdiv_i(ny, threads / bx)), (1 << 20) / bx + 1};
+    TileMap map;
+    plan_march(map, nx, ny, nz, bx * px, rows.by, radius, LaunchOptions{});    // grid and type alone decide, as in plan_ahead
+    if (radius < 3 && whole && bytes <= rule.limit) {       // a step of these tiles has 1024 vectors, one of Wide 512
+        TileMap other;
+        plan_march(other, nx, ny, nz, wide.x, wide.y, radius, LaunchOptions{});
+        if (200 * march_planes(map, 2 * radius) > (lines ? 95 : 110) * march_planes(other, 2 * radius)) return false;
     }
+    if (opt.zchunk != 0 || opt.split != 0 || opt.xcd_map != 0 || opt.band != 0) plan_march(map, nx, ny, nz, bx * px, rows.by, radius, opt);
+    if (map.zchunk > most || map.zchunk_a > most) {
+        opt.zchunk = cdiv_i(nz, cdiv_i(nz, (int)most));
+        plan_march(map, nx, ny, nz, bx * px, rows.by, radius, opt);
+    }
+    p.shape = bytes > rule.stream ? AheadShape::RowsStream : AheadShape::Rows;
+    p.TX = bx * px;
+    p.TY = rows.by;
+    p.rows = rows;
+    p.map = map;
     return true;
 }
 
@@ -102,17 +122,17 @@ static inline AheadPlan plan_ahead(bool is_f64, int radius, int nx, int ny, int 
     const bool whole = nx % (is_f64 ? 2 : 4) == 0;
     const bool long_rows = rule.long_rows_stay && wide_tile_for_unaligned_rows(nx, is_f64 ? 8 : 4, radius, !is_f64) != 0;
     if (long_rows && whole) return p;
-    const int wide_x = is_f64 ? 64 : whole ? 128 : 64, wide_y = !is_f64 && !whole ? 32 : 16;
+    const WideTile wide_shape = wide_tile(is_f64, whole);
     // grid and type alone decide, so that options that move work between workgroups change nothing else
     TileMap small, wide;
     plan_march(small, nx, ny, nz, 32, 16, radius, LaunchOptions{}, 2);
-    plan_march(wide, nx, ny, nz, wide_x, wide_y, radius, LaunchOptions{});
+    plan_march(wide, nx, ny, nz, wide_shape.x, wide_shape.y, radius, LaunchOptions{});
     const bool stream = bytes > rule.stream;
     const int percent = small.tiles_a == 0 && small.zchunk <= 2 * radius ? rule.percent_short : stream ? kPercentStream : rule.percent;
     const bool is_small = !long_rows && percent * march_planes(small, 2 * radius, 2) < 100 * march_planes(wide, 2 * radius);
     p.shape = is_small ? AheadShape::Small : stream ? AheadShape::WideStream : AheadShape::Wide;
-    p.TX = is_small ? 32 : wide_x;
-    p.TY = is_small ? 16 : wide_y;
+    p.TX = is_small ? 32 : wide_shape.x;
+    p.TY = is_small ? 16 : wide_shape.y;
     p.map = is_small ? small : wide;
     if (opt.zchunk != 0 || opt.split != 0 || opt.xcd_map != 0 || opt.band != 0)
         plan_march(p.map, nx, ny, nz, p.TX, p.TY, radius, opt, is_small ? 2 : 1);
