@@ -503,8 +503,8 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_ahead_kernel(PairArgs 
         for (int e = 0; e < PX; ++e) {
             T neg_a1 = -acc1[e][0] - cb[e], q = c_prev[e] * -neg_a1;
             computed(neg_a1); computed(q);
-            neg_a1m.v[e] = wanted & in[e] ? neg_a1 : T(0);
-            q2.v[e] = wanted & in[e] ? q : T(0);
+            neg_a1m.v[e] = (wanted & in[e]) ? neg_a1 : T(0);
+            q2.v[e] = (wanted & in[e]) ? q : T(0);
         }
         if (ring_wave) {
             const T s = W0 * qr + W1 * (ring_x + ring_X) + W1 * (ring_y + ring_Y);
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_pair_ahead_kernel(PairArgs 
             acc1r[2] = W1 * qr;
             T q = c_prev_r * (acc1r[0] + cbr);
             computed(q);
-            q2r = wanted & rin ? q : T(0);
+            q2r = (wanted & rin) ? q : T(0);
             acc1r[0] = acc1r[1]; acc1r[1] = acc1r[2];
         }
         buffer_store<T, PX, kCached>(ob.at(k), goff + zoff, neg_a1m);

@@ -522,8 +522,8 @@ template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(B
         for (int e = 0; e < PX; ++e) {
             T neg = -acc2[e][0], q = c3[e] * acc2[e][0];
             computed(neg); computed(q);
-            o.v[e] = a2_wanted & in[e] ? neg : T(0);                          // -a2 m
-            q2.v[e] = a2_wanted & in[e] ? q : T(0);
+            o.v[e] = (a2_wanted & in[e]) ? neg : T(0);                          // -a2 m
+            q2.v[e] = (a2_wanted & in[e]) ? q : T(0);
             acc3[e][0] = acc3[e][1];
             acc3[e][1] = acc3[e][2] - T(2) * o.v[e];
             acc3[e][2] = -a1m[e];                                             // of plane z-2
@@ -536,7 +536,7 @@ template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(B
             star_ring(q1r, r1, acc2r);
             T q = c3r * acc2r[0];
             computed(q);
-            n2[hl] = a2_wanted & hin ? q : T(0);
+            n2[hl] = (a2_wanted & hin) ? q : T(0);
             acc2r[0] = acc2r[1]; acc2r[1] = acc2r[2]; acc2r[2] = -amr;
         }
         buffer_store<T, PX, kCached>(ob.at(k), goff + zoff, o);
@@ -548,8 +548,8 @@ template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(B
         for (int e = 0; e < PX; ++e) {
             T v = acc1[e][0] + cb[e], q = c1[e] * v;
             computed(v); computed(q);
-            a1m[e] = a1_wanted & in[e] ? v : T(0);
-            q1.v[e] = a1_wanted & in[e] ? q : T(0);
+            a1m[e] = (a1_wanted & in[e]) ? v : T(0);
+            q1.v[e] = (a1_wanted & in[e]) ? q : T(0);
             acc2[e][1] += T(2) * a1m[e];
             acc1[e][0] = acc1[e][1] + T(2) * am[e];
             acc1[e][1] = acc1[e][2];
@@ -561,8 +561,8 @@ template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(B
             star_ring(q0r, r0, acc1r);
             T v = acc1r[0] + cbr, q = c1r * v;
             computed(v); computed(q);
-            const T a1r = a1_wanted & hin ? v : T(0);
-            q1r = a1_wanted & hin ? q : T(0);
+            const T a1r = (a1_wanted & hin) ? v : T(0);
+            q1r = (a1_wanted & hin) ? q : T(0);
             n1[hl] = q1r;
             acc2r[1] += T(2) * a1r;
             acc1r[0] = acc1r[1] + T(2) * amr;
