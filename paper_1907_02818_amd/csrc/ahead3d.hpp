@@ -353,6 +353,13 @@ __global__ __launch_bounds__((AheadTile<T, R, BX, BY, PX>::NT), 2) void star_ahe
                     }
                     const T t = UPRIMAL ? wave_in_plane_small_first<T, R>(own[e], xs, ys) : wave_in_plane<T, R>(own[e], xs, ys);
                     acc[e][R] = add_rounded(acc[e][R], OP == StarOp::WaveAdjoint ? add_rounded(r2[e], t) : t);
+                } else if (R == 1) {
+                    // one sum, from the planes before to the centre: seven roundings, where axes summed by themselves have nine and an in-plane sum,
+                    // centre first, eight of larger values (fp32 primal, error against 64 bits, in-plane sum / each axis by itself / this: random
+                    // weights 5.81e-8 / 5.82e-8 / 5.70e-8, one-sided ones 4.98e-8 / 5.21e-8 / 4.67e-8, 7-point Laplacian 7.07e-8 / 5.71e-8 / 4.68e-8;
+                    // star3d.hip 5.89e-8, 5.41e-8, 6.28e-8)
+                    const T t = fma_t(wx[1], row[HX + e + 1], fma_t(wx[0], row[HX + e - 1], acc[e][1]));
+                    acc[e][1] = fma_t(w0, own[e], fma_t(wy[1], col[2].v[e], fma_t(wy[0], col[0].v[e], t)));
                 } else {
                     // each axis summed by itself: partial sums and with them their roundings are smaller (fp32 primal, error against 64
                     // bits, one sum / this: radius 2 2.50e-8 / 2.39e-8, radius 4 2.27e-8 / 2.07e-8; star3d.hip 2.43e-8, 2.12e-8)
