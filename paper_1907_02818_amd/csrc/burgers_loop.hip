@@ -419,7 +419,8 @@ __device__ __forceinline__ void burgers_reverse_not_finite(const BurgersReverseA
 // REM: number of steps modulo kAhead of a pass over stored states; -M: up to M states are recomputed.  FULL: M steps, known at compile
 // time, so that lam needs no moves where the steps' branches would join: 4 instructions of 68 a step.  The waves per SIMD are those
 // that fit without it, but for fp64 passes of 8 steps (134 registers, 3 waves; held to 128 they spill: 433 / 468 us for 97 steps of 3 10^6
-// cells); fp32 passes of 8 steps take the form with conditions (295 us; FULL 311, held to 128 registers 330).
+// cells).  In wide windows of floats passes of 8 steps take the form with conditions (295 us; FULL 311, held to 128 registers 330), and so do
+// those of 12, which FULL spills three registers of (153 without; 6 10^5 cells, 120 steps, every 12th kept 103 / 107 us, 2 10^6, 96, 24th 203 / 208).
 template <class T, int PXL, int REM, bool FULL>
 __global__ __launch_bounds__(64 * kLoopWaves, REM == -12 ? 3 : REM == -16 ? 2 : 1) void burgers_reverse_kernel(BurgersReverseArgs a)
 {
@@ -468,9 +469,10 @@ template <class T, bool SPREAD> static hipError_t forward_T(const BurgersForward
 template <class T, int REM, bool FULL = false> static hipError_t reverse_T(const BurgersReverseArgs &a, hipStream_t stream)
 {
     constexpr int WIDE = 32 / (int)sizeof(T), NARROW = 2;
+    constexpr bool WIDE_FULL = FULL && !(sizeof(T) == 4 && REM == -12);     // see burgers_reverse_kernel
     const dim3 block(64 * kLoopWaves);
     if (wide_windows<T>(a.n))
-        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, REM, FULL>), loop_grid(WIDE, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
+        hipLaunchKernelGGL((burgers_reverse_kernel<T, WIDE, REM, WIDE_FULL>), loop_grid(WIDE, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
     else
         hipLaunchKernelGGL((burgers_reverse_kernel<T, NARROW, REM, FULL>), loop_grid(NARROW, REM >= 0 ? a.halo : -2 * REM, a.n), block, 0, stream, a);
     return hipGetLastError();
