@@ -14,7 +14,7 @@ DRIVER = r"""
 #include <vector>
 using namespace sadj;
 
-static int failures, taken, rows, refused;
+static int failures, taken, rows, cut, refused, zchunk;
 static void check(const AheadPlan &p, const char *op, bool f64, int R, int nx, int ny, int nz)
 {
     const char *what = nullptr;
@@ -24,6 +24,7 @@ static void check(const AheadPlan &p, const char *op, bool f64, int R, int nx, i
     const TileMap &m = p.map;
     const bool whole_rows = p.shape == AheadShape::Rows || p.shape == AheadShape::RowsStream;
     rows += whole_rows;
+    cut += whole_rows && zchunk >= nz && (nz + 16) * plane > 0x1p31;           // one chunk was asked for and is too long
     if (m.total_blocks < 1) what = "no workgroups";
     else if ((long)m.ntx * p.TX < nx || (long)m.nty * p.TY < ny) what = "cells without a tile";
     else if (whole_rows && (m.ntx != 1 || p.rows.bx * p.rows.by > rows_threads(R) || p.rows.by > kRowsMaxY)) what = "tile of whole rows";
@@ -46,6 +47,7 @@ static void check(const AheadPlan &p, const char *op, bool f64, int R, int nx, i
 
 static void all(int nx, int ny, int nz, const LaunchOptions &opt)
 {
+    zchunk = opt.zchunk;
     for (int f64 = 0; f64 < 2; ++f64)
         for (int R = 1; R <= 4; ++R) {
             if (nx < 2 * R + 1 || ny < 2 * R + 1 || nz < 2 * R + 1) continue;
@@ -95,8 +97,8 @@ int main()
         const int nz = extent(3, std::fmin(std::fmax(3, 4e9 / ((double)nx * ny)), 4e4));
         all(nx, ny, nz, i % 3 == 0 ? chunk : i % 3 == 1 ? split : opt);
     }
-    std::printf("taken %d, whole rows %d, large planes left to the other tiles %d\n", taken, rows, refused);
-    return failures != 0 || taken < 10000 || rows < 1000 || refused < 1000;
+    std::printf("taken %d, whole rows %d, chunks cut %d, large planes left to the other tiles %d\n", taken, rows, cut, refused);
+    return failures != 0 || taken < 10000 || rows < 1000 || cut < 100 || refused < 1000;
 }
 """
 

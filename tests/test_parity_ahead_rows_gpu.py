@@ -102,8 +102,13 @@ def test_chunks_of_arrays_beyond_two_gigabytes(sadj, dtype, shape):
         sadj.sadj_adjoint_wave3d(1, c, a, out)
         return out
 
+    px = 2 if dtype == F64 else 4
     for zchunk in (0, 1000):
         sadj.set_option("wave3d.zchunk", zchunk)
+        info, tiles = sadj.sadj_describe_wave3d_plan(1 if dtype == F64 else 0, 1, *shape[::-1])
+        longest = max(end - first for _, _, first, end in tiles)
+        assert info["tile_w"] == -(-shape[2] // px) * px and longest < shape[0]          # whole rows, in chunks although one was asked for
+        assert (longest + 16) * shape[1] * shape[2] * (16 // px) <= 2 ** 31
         got, want = _both(sadj, call)
         assert torch.equal(got, want)
 
