@@ -61,19 +61,21 @@ constexpr int kPercentStream = 150;     // streaming, Wide against Small, which 
 // Tiles of whole rows, for rows that are no multiples of a cache line or fill the wide tiles badly: the rows of a tile are then one piece of memory, whose
 // inner lines are used in full whatever the rows' alignment, and no thread lies beside the grid.  (Tiles of a fixed width start and end within lines
 // on both sides, and the last one is in part outside the grid.)  A tile has as many rows as its threads allow.  Time in the tiles below and in those of
-// the larger grids over time in these; 1286 drawn grids up to 1.5 GB that a call moves and this rule takes, 5 % of them below the second figure:
-//   radius 1, 2, rows that are no whole vectors 0.98, 1.04 .. 1.74, other rows that are no whole lines 0.89, 1.01 .. 1.56, whole lines 0.89,
-//   1.01 .. 1.89; radius 3, 4 1.01, 1.05 .. 1.92.  Below 0.97 are 13 of them, most of fewer than 60 rows or few planes, whose neighbours in
-//   size are faster (fp64 573 x 60 x 360 0.93, 600 x 60 x 360 1.07).
+// the larger grids over time in these, 2876 drawn grids up to 3 GB that a call moves and this rule takes (geometric mean 1.18), 5 % of them below the
+// second figure and 5 % above the third:
+//   radius 1, 2, rows that are no whole vectors 0.91, 1.02, 1.61; other rows that are no whole lines 0.85, 0.99, 1.38; whole lines 0.90, 0.98, 1.26
+//   radius 3, 4, the first and second of these 0.79, 1.01, 1.63 and 0.94, 1.00, 1.49
+// Below 0.97 are 55 of them, half in calls of less than 170 MB, many of 32 rows; grids next to them in size are faster (fp64 573 x 60 x 360 0.93, 600 x 60 x 360 1.07).
 // The bounds, with the same quotient beyond them:
 //   bytes of a call, 125 MB (50 .. 125 MB: 0.86 to 1.23); radius 1, 257 to 512 vectors, where wide_tile_for_unaligned_rows finds no tile, and
 //     radius 3 and 4: 250 MB (0.91 to 1.22 and 0.86 to 1.32)
 //   vectors in a row: 256, radius 1 512 (where wide_tile_for_unaligned_rows finds a tile 0.99 to 1.15), radius 3 and 4 128, or four
 //     rows a tile; with fewer every plane is read three times over (0.63 to 1.15); radius 4, whole vectors, six rows (0.95 to 1.15)
-//   radius 3, 4: rows that fit Wide are whole there already (0.84 to 1.27, half of 77 grids slower)
-//   radius 1, 2, whole vectors, where the other choice is Wide: at most 1.1 times the vectors that Wide's march computes, which shallow grids and grids
-//     of few rows pass; of rows of whole lines, which gain nothing from their alignment, 0.95 times (beyond both 0.79 to 1.22, a quarter
-//     of 107 grids slower), and the wide tiles filled to less than 0.9 (else 0.85 to 1.19, 512^3 fp32 0.92; loops in the last-level cache 0.97 to 1.10)
+//   where the other choice is the march of small grids, vectors that this march computes over those of its Wide tiles, which shallow grids and grids of few
+//     rows exceed: 0.7 for rows that fit a wide tile, which are whole there already (0.83 to 1.10, geometric mean of 67 grids 0.95); radius 1, 2, whole
+//     vectors 1.3 (0.88 to 1.15, 0.96), in loops in the last-level cache 1.2 (0.93 to 1.04, 0.99), rows of whole lines, which gain
+//     nothing from their alignment, 1.1 (0.91 to 1.07, 0.99)
+//   rows of whole lines: wide tiles filled to less than 0.9 (else 0.85 to 1.19, 512^3 fp32 0.92; loops in the last-level cache 0.97 to 1.10)
 //   fewer than 20 R planes: 0.95 to 1.17; they stay in the other tiles, as do fewer than 32 rows (not measured).
 // fp32 500^3 radius 1 primal 389 -> 344 us; 300 x 350 x 404 radius 2 star adjoint 164 -> 122; 1000 x 300 x 404 primal 460 -> 368.
 static inline bool plan_rows(AheadPlan &p, bool is_f64, int radius, int nx, int ny, int nz, double bytes, const AheadRule &rule, LaunchOptions opt)
@@ -85,17 +87,17 @@ static inline bool plan_rows(AheadPlan &p, bool is_f64, int radius, int nx, int 
     if (bx > 256 && wide_tile_for_unaligned_rows(nx, size, radius, !is_f64) != 0) return false;
     if (bytes <= (radius > 2 || bx > 256 ? 250e6 : kAheadCallStream)) return false;
     if (radius == 4 && whole && threads / bx < 6) return false;
-    if (radius > 2 && nx <= wide.x && bytes <= rule.limit) return false;
     if (lines && (radius > 2 || bx > 256 || bytes <= rule.stream || 10L * nx >= 9L * cdiv_i(nx, wide.x) * wide.x)) return false;
     const double most = 0x1p31 / ((double)nx * ny * size) - 16;                // planes of a chunk, see MarchedArray
     if (most < 32) return false;                                               // planes of more than 44.7 MB
     const RowsTile rows = {bx, cdiv_i(ny, cdiv_i(ny, threads / bx)), (1 << 20) / bx + 1};
     TileMap map;
     plan_march(map, nx, ny, nz, bx * px, rows.by, radius, LaunchOptions{});    // grid and type alone decide, as in plan_ahead
-    if (radius < 3 && whole && bytes <= rule.limit) {       // a step of these tiles has 1024 vectors, one of Wide 512
+    const int percent = nx <= wide.x ? 70 : radius > 2 || !whole ? 0 : lines ? 110 : bytes > rule.stream ? 130 : 120;
+    if (percent != 0 && bytes <= rule.limit) {                                 // a step of Wide has 512 vectors
         TileMap other;
         plan_march(other, nx, ny, nz, wide.x, wide.y, radius, LaunchOptions{});
-        if (200 * march_planes(map, 2 * radius) > (lines ? 95 : 110) * march_planes(other, 2 * radius)) return false;
+        if (100L * threads * march_planes(map, 2 * radius) > 512L * percent * march_planes(other, 2 * radius)) return false;
     }
     if (opt.zchunk != 0 || opt.split != 0 || opt.xcd_map != 0 || opt.band != 0) plan_march(map, nx, ny, nz, bx * px, rows.by, radius, opt);
     if (map.zchunk > most || map.zchunk_a > most) {
