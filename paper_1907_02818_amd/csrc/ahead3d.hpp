@@ -23,6 +23,8 @@
 // A step's own instructions: one resource per array and march instead of one per plane and access takes 40 scalar instructions in two steps
 // instead of 115 to 175, next to 80 (radius 1) to 160 vector ones (fp64, 80 x 96 x 112 radius 4 with u_prev_bar 10.8 -> 10.5 us; fp32 star
 // primal radius 4 536 x 36 x 176 13.2 -> 11.2; 140 drawn grids 1.01 times as fast, most of them bound by the launch or by memory).
+// Registers: the tiles of whole rows leave 128 at radius 1 and 2.  One form spills five of them, the fp32 adjoint of radius 2 that accumulates u_prev_bar in
+// rows that are no whole vectors; 300 x 350 x 405 292 -> 192 us all the same, against the tiles of larger grids.
 #pragma once
 #include "ahead.hpp"
 
@@ -357,7 +359,7 @@ __global__ __launch_bounds__((AheadTile<T, R, BX, BY, PX>::NT), 2) void star_ahe
                     // one sum, from the planes before to the centre: seven roundings, where axes summed by themselves have nine and an in-plane sum,
                     // centre first, eight of larger values (fp32 primal, error against 64 bits, in-plane sum / each axis by itself / this: random
                     // weights 5.81e-8 / 5.82e-8 / 5.70e-8, one-sided ones 4.98e-8 / 5.21e-8 / 4.67e-8, 7-point Laplacian 7.07e-8 / 5.71e-8 / 4.68e-8;
-                    // star3d.hip 5.89e-8, 5.41e-8, 6.28e-8)
+                    // star3d.hip 5.89e-8, 5.41e-8, 6.28e-8; from one set of weights to another 0.77 to 1.19 times the in-plane sum's)
                     const T t = fma_t(wx[1], row[HX + e + 1], fma_t(wx[0], row[HX + e - 1], acc[e][1]));
                     acc[e][1] = fma_t(w0, own[e], fma_t(wy[1], col[2].v[e], fma_t(wy[0], col[0].v[e], t)));
                 } else {

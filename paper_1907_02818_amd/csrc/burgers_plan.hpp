@@ -56,17 +56,19 @@ __attribute__((always_inline)) constexpr void stored_reverse_schedule(int m, con
     for (int j = 0; j < AHEAD; ++j) step((REM + j) % AHEAD);
 }
 
-// The kernel that takes a pass of m recomputed steps: it holds 8, 12 or 16 states in registers (109, 141, 173 of them in fp64: 4, 3
-// and 2 waves per SIMD) and recomputes two cells per state and side.
+// The kernel that takes a pass of m recomputed steps: it holds 8, 12 or 16 states in registers (fp64: 116, 148 and 180 of them, 4, 3 and 2
+// waves per SIMD; in passes of exactly 8, 12 or 16 steps 134, 166 and 198, 3, 3 and 2 waves) and recomputes two cells per state and side.
 inline int recompute_kernel(int m) { return m <= 8 ? 8 : m <= 12 ? 12 : 16; }
 
 // Longest pass of a checkpointed reverse sweep (8, 12 or 16 steps) on n cells in windows of `window`: the one whose passes cost
 // least per step.  A pass costs its launch, about 60 instructions in each of 10^6 cells, and per cell 20 instructions' time for
 // its loads and stores, 9 instructions for each state that it recomputes and 17 for each reverse step, times window / own cells;
-// fewer waves per SIMD cost 3 and 5 %.  Long passes spare launches and, where they cover a checkpoint interval, the launches that
-// would find the states inside it; short ones recompute fewer cells beside their windows.  Sweeps with 8 / 12 / 16 at most: fp64
-// 3 10^6 cells, 128 steps, every 16th kept 532 / 572 / 486 us; 1.7 10^7, 64, 16th 1426 / 1545 / 1347; 1.2 10^6, 185, 6th 337 / 287 / -;
-// 6 10^6, 64, 8th 439 / - / 507; fp32 3 10^6, 128, 16th 345 / 364 / 306; 10^6, 128, 12th 204 / 139 / -; 8 10^6, 64, 8th 304 / - / 387.
+// fewer waves per SIMD cost 3 and 5 %.  (A reverse step takes 16 by now, and passes of exactly 8 steps have three waves; with these weights one choice in twenty
+// would be another, between lengths that the model puts within 3 % of each other.  The choices below are still the fastest, or within 2 % of it.)
+// Long passes spare launches and, where they cover a checkpoint interval, the launches that
+// would find the states inside it; short ones recompute fewer cells beside their windows.  Reverse sweeps with 8 / 12 / 16 at most: fp64
+// 3 10^6 cells, 128 steps, every 16th kept 520 / 533 / 451 us; 1.7 10^7, 64, 16th 1399 / 1399 / 1345; 1.2 10^6, 185, 6th 342 / 292 / 288;
+// 6 10^6, 64, 8th 427 / 425 / 521; fp32 3 10^6, 128, 16th 385 / 384 / 307; 10^6, 128, 12th 217 / 147 / 146; 8 10^6, 64, 8th 344 / 344 / 352.
 inline int recompute_steps(long n, int window, long every)
 {
     int best = 8;

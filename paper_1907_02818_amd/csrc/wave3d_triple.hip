@@ -382,7 +382,8 @@ __global__ __launch_bounds__(BX *BY) void adj_wave3d_triple_kernel(TripleArgs a)
 // Two planes in flight; three 3 % (fp32) to 70 % (fp64, registers) slower.  What bounds it on the smaller grids is what its waves issue per
 // step, about 0.8 us, for 8 planes beyond each chunk: neighbours in x come from the lanes beside, resources last for the march,
 // waves without frame cells leave the frame out (fp32 197 x 68 x 260 247 -> 208 us, 200^3 491 -> 412; fp64 128^3 213 -> 195, 160^3 351 -> 326,
-// 300 x 80 x 80 235 -> 208).  Requests after the barrier and the reads: 8 % slower.  fp32 keeps to 128 registers, so that
+// 300 x 80 x 80 235 -> 208).  The stages' stars also run on the planes at a chunk's ends whose q is zero (12 of 57 stage runs of a chunk of 11
+// planes): left out by a uniform condition the same time within 2 % on 15 grids, fp32 slower.  Requests after the barrier and the reads: 8 % slower.  fp32 keeps to 128 registers, so that
 // two workgroups share a CU where there are more of them than CUs (64 x 400 x 400: 472 us with 140 registers, 447).
 template <class T, int BX, int BY, int PX, int D> __global__ __launch_bounds__(BX *BY, sizeof(T) == 4 ? 4 : 2) void adj_wave3d_triple_ahead_kernel(TripleArgs a)
 {
