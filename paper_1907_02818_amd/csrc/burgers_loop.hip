@@ -19,7 +19,7 @@
 // 616 -> 532, and -> 486 with passes of 16 steps.  75 -> 64 with the upwind difference taken by the sign bit, one question for zeros a pass
 // and full passes without a condition per step: gradient 662 -> 623 us, fp32 420 -> 386 (up to 5 % more or less from box to box, with the shader clock).
 // The vector ALUs issue for 41 us at 2.4 GHz in a pass of 3 10^6 cells of 56 to 61 us, whose last round of windows is partly filled, for 230 in one of 2^24 cells
-// of 270 to 285; this load leaves a clock of about 2.1 GHz.  Windows that refresh their ends from their neighbours through LDS, every 4 or 8 steps,
+// of 270 to 300; this load leaves a clock of about 2.1 GHz.  Windows that refresh their ends from their neighbours through LDS, every 4 or 8 steps,
 // compute 16 and 11 % fewer cells and measured 0 and 2 % faster (fp32 8 % slower): the waits at the barriers take what the cells save.
 #include "burgers.hpp"
 #include "burgers_plan.hpp"
